@@ -54,13 +54,8 @@ int cu_count(int dev) {
   return n;
 }
 
-bool vec_path(int dtype, int64_t V) {
-  const int64_t eb = dtype == SPC_BF16 ? 2 : 4;
-  return (V * eb) % 16 == 0;  // every row starts on a 16-byte boundary
-}
-
-int64_t stat_tiles(int dtype, bool vec, int64_t V) {
-  const int64_t n = spc::stat_tile_elems(dtype, vec);
+int64_t stat_tiles(int dtype, int64_t V) {
+  const int64_t n = spc::stat_tile_elems(dtype);
   return (V + n - 1) / n;
 }
 
@@ -75,12 +70,12 @@ int64_t seqs_per_launch(int64_t B, int64_t gamma) {
 
 namespace spc {
 
-WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype, bool vec) {
+WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype) {
   // The zero region (job counter lines, per-row lines) has the same size
   // and offset for every shape, so one zeroed workspace serves calls of any
   // shape it is large enough for; launches leave it as found.
   const int64_t R = B * (gamma + 1);
-  const int64_t nt = stat_tiles(dtype, vec, V);
+  const int64_t nt = stat_tiles(dtype, V);
   WsLayout L;
   size_t o = 0;
   L.hdr = o;
@@ -96,7 +91,7 @@ WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype, bool vec) {
   L.tvpart = o; o = align_up(o + sizeof(double) * R * nt * kSlices, 256);
   // residual sub-chunk masses per sequence, or (small path) two sets per row
   L.submass = o;
-  o = align_up(o + sizeof(double) * std::max<int64_t>(B * nt * tile_subchunks(dtype, vec),
+  o = align_up(o + sizeof(double) * std::max<int64_t>(B * nt * tile_subchunks(dtype),
                                                        R * 2 * kSmallSub), 256);
   L.moms = o; o = align_up(o + sizeof(TileMom) * R * nt, 256);
   L.rowstat = o; o = align_up(o + sizeof(RowStat) * R, 256);
@@ -133,7 +128,7 @@ spc_status check_shape(int32_t B, int32_t gamma, int32_t V) {
 
 // The layout of one launch of a verify call of this shape.
 spc::WsLayout launch_layout(int32_t B, int32_t gamma, int32_t V, int dtype) {
-  return spc::ws_layout(seqs_per_launch(B, gamma), gamma, V, dtype, vec_path(dtype, V));
+  return spc::ws_layout(seqs_per_launch(B, gamma), gamma, V, dtype);
 }
 
 bool capturing(hipStream_t stream) {
@@ -195,13 +190,13 @@ std::map<int, NoAllocDev> g_na;
 
 // Sequences per launch that the static scratch holds for this row shape
 // (0: not even one).
-int64_t noalloc_seqs(int64_t gamma, int64_t V, int dtype, bool vec) {
-  const size_t one = spc::ws_layout(1, gamma, V, dtype, vec).total;
+int64_t noalloc_seqs(int64_t gamma, int64_t V, int dtype) {
+  const size_t one = spc::ws_layout(1, gamma, V, dtype).total;
   if (one > kNoAllocBytes) return 0;
   int64_t lo = 1, hi = spc::kMaxRows;  // largest b with layout(b) <= the scratch
   while (lo < hi) {
     const int64_t mid = (lo + hi + 1) / 2;
-    if (spc::ws_layout(mid, gamma, V, dtype, vec).total <= kNoAllocBytes) lo = mid;
+    if (spc::ws_layout(mid, gamma, V, dtype).total <= kNoAllocBytes) lo = mid;
     else hi = mid - 1;
   }
   return lo;
@@ -260,7 +255,6 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
   if (((uintptr_t)q | (uintptr_t)p) % 16 != 0)
     return fail(SPC_E_ALIGN, "logit base pointers must be 16-byte aligned");
 
-  const bool vec = vec_path(dtype, V);
   const int64_t g1 = (int64_t)gamma + 1;
   int64_t b_launch = seqs_per_launch(B, gamma);
   if (no_alloc) {
@@ -268,14 +262,14 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
       return fail(SPC_E_WORKSPACE, "spc_verify_noalloc takes no caller workspace");
     // as many sequences per launch as the static scratch holds (the layout
     // grows with the sequences of a launch)
-    b_launch = std::min<int64_t>(b_launch, noalloc_seqs(gamma, V, dtype, vec));
+    b_launch = std::min<int64_t>(b_launch, noalloc_seqs(gamma, V, dtype));
     if (b_launch < 1)
       return fail(SPC_E_WORKSPACE,
                   "one sequence of gamma=%d V=%d needs %zu bytes of workspace, more than the "
                   "%zu-byte static scratch of spc_verify_noalloc",
-                  gamma, V, spc::ws_layout(1, gamma, V, dtype, vec).total, kNoAllocBytes);
+                  gamma, V, spc::ws_layout(1, gamma, V, dtype).total, kNoAllocBytes);
   }
-  const spc::WsLayout L = spc::ws_layout(b_launch, gamma, V, dtype, vec);
+  const spc::WsLayout L = spc::ws_layout(b_launch, gamma, V, dtype);
   // argument checks end here: no HIP call precedes them
   if (ex && ex->workspace &&
       (ex->workspace_bytes < L.total || ((uintptr_t)ex->workspace % 256) != 0))
@@ -327,9 +321,9 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
   const bool tv_rows = may_sample && (rules & kTv);
   // Small problems (rows that fit one workgroup's registers, at most two
   // rows per compute unit, no first moments) take the single-launch path.
-  const bool small = !need_mom && V <= spc::small_row_elems(dtype, vec) &&
+  const bool small = !need_mom && V <= spc::small_row_elems(dtype) &&
                      b_launch * g1 <= 2 * (int64_t)cus;
-  const int64_t nt = stat_tiles(dtype, vec, V);
+  const int64_t nt = stat_tiles(dtype, V);
   const int64_t eb = dtype == SPC_BF16 ? 2 : 4;
 
   for (int64_t b0 = 0; b0 < B; b0 += b_launch) {
@@ -381,7 +375,7 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     // jobs: argmax halves, TV tiles whose wait timed out or TV slices, the
     // slices of the tiles a token row lists for eta (a row has one kind)
     P.single_slots = 2 * R + bl + R * nt * spc::kSlices;
-    P.nsub = (int32_t)(nt * spc::tile_subchunks(dtype, vec));
+    P.nsub = (int32_t)(nt * spc::tile_subchunks(dtype));
     // workgroups of the job pass: a wavefront per item of its largest
     // expected list (eta slices of every tile, argmax halves), at most two
     // workgroups per compute unit
@@ -409,9 +403,9 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     if (small) {
       // one launch: a workgroup per row holding the row in registers
       P.nsub = spc::kSmallSub;
-      e = spc::launch_small(P, dtype, vec, ev0, ev1, stream);
+      e = spc::launch_small(P, dtype, ev0, ev1, stream);
     } else {
-      e = spc::launch_step(P, dtype, vec, draw_pass, tv_pass, job_pass, job_groups, ev0, ev1,
+      e = spc::launch_step(P, dtype, draw_pass, tv_pass, job_pass, job_groups, ev0, ev1,
                            stream);
     }
     if (e != hipSuccess) return fail(SPC_E_HIP, "kernel launch: %s", hipGetErrorString(e));
@@ -433,10 +427,9 @@ spc_status draft_impl(const void* logits, int32_t dtype, int32_t B, int32_t V, f
   if (dtype != SPC_F32 && dtype != SPC_BF16) return fail(SPC_E_PARAM, "unknown dtype %d", dtype);
   if ((uintptr_t)logits % 16 != 0)
     return fail(SPC_E_ALIGN, "logit base pointer must be 16-byte aligned");
-  const bool vec = vec_path(dtype, V);
   // rows per launch, as a verify step of gamma = 1 with as many sequences
   const int64_t b_launch = seqs_per_launch(B, 1);
-  const spc::WsLayout L = spc::ws_layout(b_launch, 1, V, dtype, vec);
+  const spc::WsLayout L = spc::ws_layout(b_launch, 1, V, dtype);
   // argument checks end here: no HIP call precedes them
   if (workspace && (workspace_bytes < L.total || ((uintptr_t)workspace % 256) != 0))
     return fail(SPC_E_WORKSPACE, "workspace of %zu bytes (need %zu, 256-byte aligned)",
@@ -460,19 +453,20 @@ spc_status draft_impl(const void* logits, int32_t dtype, int32_t B, int32_t V, f
     // least 4 workgroups per CU; small batches take the statistics tile
     // length, for twice the workgroups (either way no more partials per row
     // than the workspace holds for this shape).
-    const int64_t long_n = spc::draft_tile_elems(dtype, vec, true);
+    const int64_t long_n = spc::draft_tile_elems(dtype, true);
     const bool long_tiles = bl * ((V + long_n - 1) / long_n) >= 1024;
-    const int64_t tile_n = long_tiles ? long_n : spc::draft_tile_elems(dtype, vec, false);
+    const int64_t tile_n = long_tiles ? long_n : spc::draft_tile_elems(dtype, false);
     P.nt = (int32_t)((V + tile_n - 1) / tile_n);
     P.rule = SPC_RULE_NEVER;
     P.temp = greedy ? 0.0f : temperature;
     P.force_greedy = greedy ? 1 : 0;
     P.temp_ps = offset(temp_per_seq, b0);
     P.out_token = out_token + b0;
+    P.hdr = reinterpret_cast<uint32_t*>(ws + L.hdr);
     P.samp_cnt = reinterpret_cast<uint32_t*>(ws + L.rowline) + spc::kDraftArrive;
     P.tiles = reinterpret_cast<spc::TilePart*>(ws + L.tiles);
     const hipError_t e =
-        spc::launch_draft(P, dtype, vec, greedy || temp_per_seq, long_tiles, stream);
+        spc::launch_draft(P, dtype, greedy || temp_per_seq, long_tiles, stream);
     if (e != hipSuccess) return fail(SPC_E_HIP, "kernel launch: %s", hipGetErrorString(e));
   }
   return SPC_OK;
@@ -556,7 +550,7 @@ size_t spc_workspace_zero_bytes(int32_t B, int32_t gamma, int32_t V, int32_t dty
 
 size_t spc_draft_workspace_bytes(int32_t B, int32_t V, int32_t dtype) {
   if (B < 1 || V < 2 || (dtype != SPC_F32 && dtype != SPC_BF16)) return 0;
-  return spc::ws_layout(seqs_per_launch(B, 1), 1, V, dtype, vec_path(dtype, V)).total;
+  return spc::ws_layout(seqs_per_launch(B, 1), 1, V, dtype).total;
 }
 
 const char* spc_last_error(void) { return g_err.c_str(); }

@@ -94,11 +94,11 @@ struct Params {
   int32_t* etacnt;         // [R] tiles listed in etalist
 };
 
-// Entries per statistics tile and per drafter tile for a dtype and load path.
-int stat_tile_elems(int dtype, bool vec);
+// Entries per statistics tile and per drafter tile for a dtype.
+int stat_tile_elems(int dtype);
 // Sub-chunks (lane-load rows of a wavefront) per statistics tile.
-int tile_subchunks(int dtype, bool vec);
-int draft_tile_elems(int dtype, bool vec, bool long_tiles);
+int tile_subchunks(int dtype);
+int draft_tile_elems(int dtype, bool long_tiles);
 
 // Counters live on 128-byte lines of 32-bit words: arrivals on a shared line
 // serialise.
@@ -138,21 +138,21 @@ struct WsLayout {
   size_t jobs, tiles, tvpart, submass, moms, rowstat, rowdec, etalist, argres, etacnt,
       total;
 };
-WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype, bool vec);
+WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype);
 
 // Enqueue the drafter sampling kernel (Params: q = the logits [B][V], nt,
 // uniforms [B], temp_ps or temp, out_token, samp_cnt with kDraftCntStride,
 // tiles).  argmax: some row may be at temperature 0.
 // long_tiles: tiles of twice the statistics tile's lane loads (large
 // batches) rather than the statistics tile's (small ones).
-hipError_t launch_draft(const Params& P, int dtype, bool vec, bool argmax, bool long_tiles,
+hipError_t launch_draft(const Params& P, int dtype, bool argmax, bool long_tiles,
                         hipStream_t stream);
 
 // The small-problem path (k_small): a workgroup per row holding the row in
 // registers; rows of at most small_row_elems entries, kSmallSub sub-chunks.
 constexpr int kSmallSub = 64;
-int small_row_elems(int dtype, bool vec);
-hipError_t launch_small(const Params& P, int dtype, bool vec, hipEvent_t ev_begin,
+int small_row_elems(int dtype);
+hipError_t launch_small(const Params& P, int dtype, hipEvent_t ev_begin,
                         hipEvent_t ev_end, hipStream_t stream);
 
 // Enqueue one verify launch: the statistics tiles (k_tiles; with P.tv_self
@@ -160,7 +160,7 @@ hipError_t launch_small(const Params& P, int dtype, bool vec, hipEvent_t ev_begi
 // `tv_pass`, the job pass (k_jobs, of `job_groups` workgroups) when
 // `job_pass`, and last the draw pass (k_res) when `draw_pass`.
 // ev_begin / ev_end (may be null): recorded right before and after k_tiles.
-hipError_t launch_step(const Params& P, int dtype, bool vec, bool draw_pass, bool tv_pass,
+hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass,
                        bool job_pass, int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end,
                        hipStream_t stream);
 

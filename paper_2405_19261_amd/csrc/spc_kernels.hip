@@ -59,89 +59,156 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kWaves = kThreads / 64;
 
 // ------------------------------------------------------------------ geometry
-// A lane load is one 16-byte vector (8 bf16 or 4 f32 entries) on the vector
-// path, one entry on the scalar path (rows not 16-byte aligned).  A tile is U
-// lane loads per thread, U * kThreads * VW entries.
-template <int DT, bool VEC, int U_>
+// A lane load is one 16-byte vector (8 bf16 or 4 f32 entries) at any entry
+// boundary: rows of a vocabulary that is no multiple of a vector start at
+// whatever address the row before them ends at.  A tile is U lane loads per
+// thread, U * kThreads * VW entries.
+template <int DT, int U_>
 struct Tile {
   static constexpr int EB = (DT == 1) ? 2 : 4;  // element bytes (1 = bf16, 0 = f32)
-  static constexpr int VW = VEC ? 16 / EB : 1;  // entries per lane load
-  static constexpr int NW = VEC ? 4 : 1;        // 32-bit words per lane load
+  static constexpr int VW = 16 / EB;            // entries per lane load
+  static constexpr int NW = 4;                  // 32-bit words per lane load
   static constexpr int U = U_;                  // lane loads per thread
   static constexpr int N = kThreads * U * VW;   // entries per tile
 };
 // statistics / TV tiles: small, so that many workgroups are resident
-template <int DT, bool VEC>
-using StatTile = Tile<DT, VEC, VEC ? 4 : 8>;
+template <int DT>
+using StatTile = Tile<DT, 4>;
 
 // drafter tiles: one tensor, M times the lane loads of a statistics tile
 // (M = 2: the same bytes per workgroup, for large batches; M = 1: twice the
 // workgroups, for small ones)
-template <int DT, bool VEC, int M>
-using DraftTile = Tile<DT, VEC, M * StatTile<DT, VEC>::U>;
+template <int DT, int M>
+using DraftTile = Tile<DT, M * StatTile<DT>::U>;
 
 // bfloat16 -> float32 is exact: the bf16 bits are the top half of the float.
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ float elem(const uint32_t* w, int e) {
   if constexpr (DT == 1) {
-    if constexpr (VEC) {
-      const uint32_t x = w[e >> 1];
-      return (e & 1) ? __uint_as_float(x & 0xffff0000u) : __uint_as_float(x << 16);
-    } else {
-      return __uint_as_float(w[0] << 16);
+    const uint32_t x = w[e >> 1];
+    return (e & 1) ? __uint_as_float(x & 0xffff0000u) : __uint_as_float(x << 16);
+  } else {
+    return __uint_as_float(w[e]);
+  }
+}
+
+// A lane load at any entry address (unaligned 16-byte loads are one
+// instruction here; a wavefront's 1 KiB then touches nine 128-byte lines
+// instead of eight).
+template <int DT>
+struct LaneVec {  // float32
+  typedef u32x4 type __attribute__((aligned(4)));
+};
+template <>
+struct LaneVec<1> {  // bfloat16
+  typedef u32x4 type __attribute__((aligned(2)));
+};
+
+// The first `n` < VW entries of a lane load at `a`, the others -inf: the lane
+// load that holds a row's last entries where the vocabulary is no multiple
+// of VW.  Read entry by entry, so nothing past the row is touched.
+template <int DT>
+__device__ __forceinline__ void load_partial(const char* a, int n, uint32_t (&x)[4]) {
+  if constexpr (DT == 1) {
+    const uint16_t* s = reinterpret_cast<const uint16_t*>(a);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t lo = 2 * j < n ? (uint32_t)s[2 * j] : 0xff80u;
+      const uint32_t hi = 2 * j + 1 < n ? (uint32_t)s[2 * j + 1] : 0xff80u;
+      x[j] = lo | (hi << 16);
     }
   } else {
-    return __uint_as_float(w[VEC ? e : 0]);
+    const uint32_t* s = reinterpret_cast<const uint32_t*>(a);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = j < n ? s[j] : 0xff800000u;
   }
 }
 
 // Lane loads of one tile of one row into w[U][NW] by the GT threads of a
 // group, tid the thread's index in it.  Thread t's lane load i covers entries
 // e = t0 + (i*GT + t) * VW .. + VW - 1 (interleaved, so each load
-// instruction of a wavefront reads one contiguous 1 KiB).
-// Entries at or past `end` read as -inf; a lane past the end re-reads the
-// tile's first entry and discards the value, so the loads are branch-free.
-// With MASK false the caller guarantees a whole tile before `end`.  Addresses
-// are a uniform tile base plus a 32-bit lane offset.
-template <int DT, bool VEC, int U, bool NT, int GT = kThreads, bool MASK = true>
+// instruction of a wavefront reads one contiguous 1 KiB).  Addresses are a
+// uniform base plus a 32-bit lane offset.  Only issues the loads: a lane
+// whose lane load is not wholly before `end` reads other entries (the tile's
+// first ones; the row's first ones where the tile holds no whole lane load;
+// `safe`, any 16 readable bytes, where the row holds none), which mask_tile
+// replaces.  The two are apart so that a caller issues every load of both
+// tensors before anything branches or waits on their values.
+template <int DT, int U, bool NT, int GT = kThreads>
 __device__ __forceinline__ void load_tile(const char* row, int64_t t0, int64_t end,
-                                          uint32_t (&w)[U][Tile<DT, VEC, U>::NW], int tid) {
-  using T = Tile<DT, VEC, U>;
-  constexpr uint32_t kPad = (DT == 1) ? 0xff80ff80u : 0xff800000u;
+                                          uint32_t (&w)[U][Tile<DT, U>::NW], int tid,
+                                          const void* safe) {
+  using T = Tile<DT, U>;
+  using LV = typename LaneVec<DT>::type;
   constexpr int kSpan = GT * U * T::VW;  // entries of a whole tile
-  const char* base = row + t0 * T::EB;
   const int left = (int)(end - t0 < (int64_t)kSpan ? end - t0 : (int64_t)kSpan);
-  const bool full = !MASK || left == kSpan;
+  const char* base = left >= T::VW ? row + t0 * T::EB
+                     : end >= T::VW ? row : static_cast<const char*>(safe);
 #pragma unroll
   for (int i = 0; i < U; ++i) {
     const int e = (i * GT + tid) * T::VW;
-    const bool ok = full || e < left;
-    const char* a = base + (uint32_t)((ok ? e : 0) * T::EB);
-    if constexpr (VEC) {
-      const u32x4* src = reinterpret_cast<const u32x4*>(a);
-      const u32x4 v = NT ? __builtin_nontemporal_load(src) : *src;
-      w[i][0] = ok ? v.x : kPad;
-      w[i][1] = ok ? v.y : kPad;
-      w[i][2] = ok ? v.z : kPad;
-      w[i][3] = ok ? v.w : kPad;
-    } else if constexpr (DT == 1) {
-      const uint32_t v = *reinterpret_cast<const uint16_t*>(a);
-      w[i][0] = ok ? v : kPad;
-    } else {
-      const uint32_t v = *reinterpret_cast<const uint32_t*>(a);
-      w[i][0] = ok ? v : kPad;
+    const LV* src =
+        reinterpret_cast<const LV*>(base + (uint32_t)((e + T::VW <= left ? e : 0) * T::EB));
+    const u32x4 v = NT ? __builtin_nontemporal_load(src) : *src;
+    w[i][0] = v.x;
+    w[i][1] = v.y;
+    w[i][2] = v.z;
+    w[i][3] = v.w;
+  }
+}
+
+// After load_tile: entries at or past `end` become -inf.  Whole tiles take
+// one uniform branch.  Where the row ends inside a lane load, that load's
+// lane reads it entry by entry.
+template <int DT, int U, int GT = kThreads>
+__device__ __forceinline__ void mask_tile(const char* row, int64_t t0, int64_t end,
+                                          uint32_t (&w)[U][Tile<DT, U>::NW], int tid) {
+  using T = Tile<DT, U>;
+  constexpr uint32_t kPad = (DT == 1) ? 0xff80ff80u : 0xff800000u;
+  constexpr int kSpan = GT * U * T::VW;
+  if (end - t0 >= (int64_t)kSpan) return;
+  const int left = (int)(end - t0);
+#pragma unroll
+  for (int i = 0; i < U; ++i) {
+    const bool ok = (i * GT + tid) * T::VW + T::VW <= left;
+#pragma unroll
+    for (int j = 0; j < T::NW; ++j) w[i][j] = ok ? w[i][j] : kPad;
+  }
+  if (left % T::VW != 0) {  // uniform
+    const int slot = left / T::VW;
+    if (tid == slot % GT) {
+      uint32_t x[4];
+      load_partial<DT>(row + (t0 + slot * T::VW) * T::EB, left % T::VW, x);
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (i == slot / GT)
+#pragma unroll
+          for (int j = 0; j < T::NW; ++j) w[i][j] = x[j];
     }
   }
+}
+
+// Both tensors' lane loads of the tile at entry t0 of a row, masked.  TQ /
+// TP: which of them to read (the other's words are left alone).
+template <int DT, int U, bool NT, int GT = kThreads, bool TQ = true, bool TP = true>
+__device__ __forceinline__ void load_tiles(const char* qrow, const char* prow, int64_t t0,
+                                           int64_t end, uint32_t (&wq)[U][Tile<DT, U>::NW],
+                                           uint32_t (&wp)[U][Tile<DT, U>::NW], int tid,
+                                           const void* safe) {
+  if (TQ) load_tile<DT, U, NT, GT>(qrow, t0, end, wq, tid, safe);
+  if (TP) load_tile<DT, U, NT, GT>(prow, t0, end, wp, tid, safe);
+  if (TQ) mask_tile<DT, U, GT>(qrow, t0, end, wq, tid);
+  if (TP) mask_tile<DT, U, GT>(prow, t0, end, wp, tid);
 }
 
 // The lowest entry attaining m among a thread's U lane loads w (lane load i
 // holds entries base + i * GT * VW + e, e < VW), given each lane load's
 // maximum g[i]: the first lane load whose maximum is m, then the first entry
 // of it equal to m.  INT_MAX when m = -inf (no finite entry).
-template <int DT, bool VEC, int U, int GT>
-__device__ __forceinline__ int first_max_index(const uint32_t (&w)[U][Tile<DT, VEC, U>::NW],
+template <int DT, int U, int GT>
+__device__ __forceinline__ int first_max_index(const uint32_t (&w)[U][Tile<DT, U>::NW],
                                                const float (&g)[U], float m, int base) {
-  using T = Tile<DT, VEC, U>;
+  using T = Tile<DT, U>;
   int gi = 0;
 #pragma unroll
   for (int i = U - 1; i >= 0; --i)
@@ -156,7 +223,7 @@ __device__ __forceinline__ int first_max_index(const uint32_t (&w)[U][Tile<DT, V
   int ei = 0;
 #pragma unroll
   for (int e = T::VW - 1; e >= 0; --e)
-    if (elem<DT, VEC>(s, e) == m) ei = e;
+    if (elem<DT>(s, e) == m) ei = e;
   return m == kNegInf ? 0x7fffffff : base + gi * GT * T::VW + ei;
 }
 
@@ -905,34 +972,33 @@ __device__ __forceinline__ RowDecision decide_row(const SeqParam& sp, const RowS
 // lane load i covers entries (i * 64 + l) * VW .. + VW - 1 of it.  A
 // statistics tile is a whole number of SubChunks; the residual job and the
 // in-tile draw sum them in the same order.
-template <int DT, bool VEC, int U_>
+template <int DT, int U_>
 struct Chunk {
   static constexpr int U = U_;
-  static constexpr int NW = Tile<DT, VEC, U_>::NW, VW = Tile<DT, VEC, U_>::VW;
+  static constexpr int NW = Tile<DT, U_>::NW, VW = Tile<DT, U_>::VW;
   static constexpr int N = 64 * U * VW;  // entries per chunk
 };
 // A sub-chunk of a TN-entry tile drawn from by NWV wavefronts: one per
 // wavefront, or several of at most 2 lane loads each (few registers: the
 // draw shares its launch with the statistics tiles).
-template <int DT, bool VEC, int NWV, int TN = StatTile<DT, VEC>::N>
-using SubChunk = Chunk<DT, VEC, (TN / (64 * NWV * Tile<DT, VEC, 1>::VW) < 2)
-                                    ? TN / (64 * NWV * Tile<DT, VEC, 1>::VW)
+template <int DT, int NWV, int TN = StatTile<DT>::N>
+using SubChunk = Chunk<DT, (TN / (64 * NWV * Tile<DT, 1>::VW) < 2)
+                                    ? TN / (64 * NWV * Tile<DT, 1>::VW)
                                     : 2>;
 
 template <class C>
 using ChunkRegs = uint32_t[C::U][C::NW];
 
-// Lane loads of the chunk starting at entry c0 of a row (V entries); a chunk
-// past the row reads entry 0 and masks everything.
-template <int DT, bool VEC, class C>
-__device__ __forceinline__ void load_chunk(const char* row, int64_t c0, int V, ChunkRegs<C>& w) {
-  const int lane = threadIdx.x & 63;
-  if (c0 + C::N <= V) {  // a whole chunk (wave-uniform): no masking
-    load_tile<DT, VEC, C::U, false, 64, false>(row, c0, V, w, lane);
-  } else {
-    const bool live = c0 < V;
-    load_tile<DT, VEC, C::U, false, 64>(row, live ? c0 : 0, live ? V : 0, w, lane);
-  }
+// Both tensors' lane loads of the chunk starting at entry c0 of a row (V
+// entries), as the distribution KIND needs them; a chunk past the row is all
+// -inf.
+template <int DT, class C, int KIND>
+__device__ __forceinline__ void load_chunks(const char* qrow, const char* prow, int64_t c0, int V,
+                                            ChunkRegs<C>& wq, ChunkRegs<C>& wp,
+                                            const void* safe) {
+  const bool live = c0 < V;  // wave-uniform
+  load_tiles<DT, C::U, false, 64, KIND != kP, KIND != kQ>(qrow, prow, live ? c0 : 0, live ? V : 0,
+                                                          wq, wp, threadIdx.x & 63, safe);
 }
 
 // Sources of the part masses of the sampled distribution: the statistics
@@ -1038,17 +1104,16 @@ __device__ __forceinline__ double find_part(const Params& P, int64_t row, int b,
 // are scanned in entry order -- lane load i, then lane -- for the first one
 // where the running mass exceeds rem; its lane then walks its VW entries.
 // Rounding that leaves rem unreached takes the last entry with mass.
-template <int DT, bool VEC, class C, int KIND>
+template <int DT, class C, int KIND>
 __device__ __forceinline__ void pick_wave(const Params& P, int b, int64_t row, int64_t c0,
                                           double rem, const ProbScale& ps, int kind = -1) {
-  constexpr int EB = StatTile<DT, VEC>::EB;
+  constexpr int EB = StatTile<DT>::EB;
   const int lane = threadIdx.x & 63;
   const int V = P.V;
   const char* qrow = (const char*)P.q + row * V * EB;
   const char* prow = (const char*)P.p + row * V * EB;
   ChunkRegs<C> cq = {}, cp = {};
-  if (KIND != kP) load_chunk<DT, VEC, C>(qrow, c0, V, cq);
-  if (KIND != kQ) load_chunk<DT, VEC, C>(prow, c0, V, cp);
+  load_chunks<DT, C, KIND>(qrow, prow, c0, V, cq, cp, P.hdr);
   double carry = 0.0, before = 0.0;
   int hlane = -1, last_pos = -1;
   int64_t hbase = 0;
@@ -1059,7 +1124,7 @@ __device__ __forceinline__ void pick_wave(const Params& P, int b, int64_t row, i
     double m = 0.0;
 #pragma unroll
     for (int e = 0; e < C::VW; ++e) {
-      const float w = weight_k<DT, KIND>(elem<DT, VEC>(cq[i], e), elem<DT, VEC>(cp[i], e), ps, kind);
+      const float w = weight_k<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps, kind);
       m += (double)w;
       if (w > 0.0f) last_pos = max(last_pos, (int)(base + e));
       if (e & 1) __builtin_amdgcn_sched_barrier(0);
@@ -1090,7 +1155,7 @@ __device__ __forceinline__ void pick_wave(const Params& P, int b, int64_t row, i
   int hit = -1, lastw = -1;
 #pragma unroll
   for (int e = 0; e < C::VW; ++e) {
-    const float w = weight_k<DT, KIND>(elem<DT, VEC>(sq, e), elem<DT, VEC>(sp_, e), ps, kind);
+    const float w = weight_k<DT, KIND>(elem<DT>(sq, e), elem<DT>(sp_, e), ps, kind);
     run += (double)w;
     if (w > 0.0f) lastw = (int)(hbase + e);
     if (hit < 0 && run > rem && w > 0.0f) hit = (int)(hbase + e);
@@ -1102,29 +1167,28 @@ __device__ __forceinline__ void pick_wave(const Params& P, int b, int64_t row, i
 // Whole block: the masses of the sub-chunks of the TN-entry tile at entry t0
 // of a row under the distribution KIND, in sh.dv[0 .. NS-1] (wave w sums
 // sub-chunks w, w + NWV, ...).  Ends with a block barrier.
-template <int DT, bool VEC, int KIND, int NWV, int TN = StatTile<DT, VEC>::N>
+template <int DT, int KIND, int NWV, int TN = StatTile<DT>::N>
 __device__ __forceinline__ void subchunk_masses(const Params& P, int64_t row, int64_t t0,
                                                 const ProbScale& ps, SharedT<NWV>& sh) {
-  using C = SubChunk<DT, VEC, NWV, TN>;
+  using C = SubChunk<DT, NWV, TN>;
   constexpr int NS = TN / C::N;  // sub-chunks of the tile
   static_assert(NS * C::N == TN && NS % NWV == 0 && NS <= 64,
                 "a tile is a whole number of sub-chunks per wavefront");
-  constexpr int EB = StatTile<DT, VEC>::EB;
+  constexpr int EB = StatTile<DT>::EB;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int V = P.V;
   const char* qrow = (const char*)P.q + row * V * EB;
   const char* prow = (const char*)P.p + row * V * EB;
   for (int sc = wv; sc < NS; sc += NWV) {
     ChunkRegs<C> cq = {}, cp = {};
-    if (KIND != kP) load_chunk<DT, VEC, C>(qrow, t0 + sc * C::N, V, cq);
-    if (KIND != kQ) load_chunk<DT, VEC, C>(prow, t0 + sc * C::N, V, cp);
+    load_chunks<DT, C, KIND>(qrow, prow, t0 + sc * C::N, V, cq, cp, P.hdr);
     double m = 0.0;
 #pragma unroll
     for (int i = 0; i < C::U; ++i) {
       float t = 0.0f;
 #pragma unroll
       for (int e = 0; e < C::VW; ++e) {
-        t += weight_of<DT, KIND>(elem<DT, VEC>(cq[i], e), elem<DT, VEC>(cp[i], e), ps);
+        t += weight_of<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps);
         // two entries at a time keep the weights' temporaries few
         if (e & 1) __builtin_amdgcn_sched_barrier(0);
       }
@@ -1139,21 +1203,21 @@ __device__ __forceinline__ void subchunk_masses(const Params& P, int64_t row, in
 // Wave 0: the total of a tile's sub-chunk masses (after subchunk_masses),
 // summed by the same scan the in-tile draw runs, so a draw whose target falls
 // in this tile by the tile masses finds it among the sub-chunks.
-template <int DT, bool VEC, int NWV, int TN = StatTile<DT, VEC>::N>
+template <int DT, int NWV, int TN = StatTile<DT>::N>
 __device__ __forceinline__ double tile_mass(const SharedT<NWV>& sh) {
-  constexpr int NS = TN / SubChunk<DT, VEC, NWV, TN>::N;
+  constexpr int NS = TN / SubChunk<DT, NWV, TN>::N;
   const int lane = threadIdx.x & 63;
   return lane_f64(wave_incl_scan(lane < NS ? sh.dv[lane] : 0.0), NS - 1);
 }
 
 // Whole block: the draw inside the tile at entry t0.  Wave 0 scans the
 // sub-chunk masses for the sub-chunk where rem is crossed and draws inside it.
-template <int DT, bool VEC, int KIND, int NWV, int TN = StatTile<DT, VEC>::N>
+template <int DT, int KIND, int NWV, int TN = StatTile<DT>::N>
 __device__ __forceinline__ void pick_tile(const Params& P, int b, int64_t row, int64_t t0,
                                           double rem, const ProbScale& ps, SharedT<NWV>& sh) {
-  using C = SubChunk<DT, VEC, NWV, TN>;
+  using C = SubChunk<DT, NWV, TN>;
   constexpr int NS = TN / C::N;
-  subchunk_masses<DT, VEC, KIND, NWV, TN>(P, row, t0, ps, sh);
+  subchunk_masses<DT, KIND, NWV, TN>(P, row, t0, ps, sh);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (wv != 0) return;
   const double ml = lane < NS ? sh.dv[lane] : 0.0;
@@ -1169,7 +1233,7 @@ __device__ __forceinline__ void pick_tile(const Params& P, int b, int64_t row, i
     c = pos ? 63 - __clzll(pos) : 0;
     r = __builtin_huge_val();
   }
-  pick_wave<DT, VEC, C, KIND>(P, b, row, t0 + c * C::N, r, ps);
+  pick_wave<DT, C, KIND>(P, b, row, t0 + c * C::N, r, ps);
 }
 
 // ================================================================ statistics tiles
@@ -1179,19 +1243,19 @@ __device__ __forceinline__ void pick_tile(const Params& P, int b, int64_t row, i
 // x = sum 2^a_q a_p (entries of zero weight contribute nothing, so -inf
 // logits never meet an infinite factor; a finite-weight q entry facing a -inf
 // p logit makes x = -inf).  Moments outside the set stay 0.
-template <int DT, bool VEC, int MOM>
-__device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
-                                          const uint32_t (&wp)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
+template <int DT, int MOM>
+__device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
+                                          const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW],
                                           const SeqParam& sp, float rq, float rp, float& sq,
                                           float& spp, float& hq, float& hp, float& xq) {
-  using T = StatTile<DT, VEC>;
+  using T = StatTile<DT>;
   if constexpr (MOM) {
     // one running sum per quantity: the moments' extra values stay short-lived
 #pragma unroll
     for (int i = 0; i < T::U; ++i)
 #pragma unroll
       for (int e = 0; e < T::VW; ++e) {
-        const float zq = elem<DT, VEC>(wq[i], e), zp = elem<DT, VEC>(wp[i], e);
+        const float zq = elem<DT>(wq[i], e), zp = elem<DT>(wp[i], e);
         const float aq = fmaf(zq, sp.c_lo, fmaf(zq, sp.c_hi, -rq));
         const float ap = fmaf(zp, sp.c_lo, fmaf(zp, sp.c_hi, -rp));
         const float tq = exp2_hw(aq), tp = exp2_hw(ap);
@@ -1210,7 +1274,7 @@ __device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT, VEC>
       float tq[T::VW], tp[T::VW];
 #pragma unroll
       for (int e = 0; e < T::VW; ++e) {
-        const float zq = elem<DT, VEC>(wq[i], e), zp = elem<DT, VEC>(wp[i], e);
+        const float zq = elem<DT>(wq[i], e), zp = elem<DT>(wp[i], e);
         tq[e] = exp2_hw(fmaf(zq, sp.c_lo, fmaf(zq, sp.c_hi, -rq)));
         tp[e] = exp2_hw(fmaf(zp, sp.c_lo, fmaf(zp, sp.c_hi, -rp)));
       }
@@ -1230,12 +1294,12 @@ __device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT, VEC>
 // The partial of statistics tile k of row r from its loaded entries (wq, wp),
 // written by thread 0 through agent-scope stores, for readers in the same
 // launch.
-template <int DT, bool VEC, int MOM>
+template <int DT, int MOM>
 __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, const SeqParam& sp,
-                                             const uint32_t (&wq)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
-                                             const uint32_t (&wp)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
+                                             const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
+                                             const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW],
                                              Shared& sh) {
-  using T = StatTile<DT, VEC>;
+  using T = StatTile<DT>;
   // Thread max, from the maxima of its lane loads.
   float gq[T::U], gp[T::U];
 #pragma unroll
@@ -1243,8 +1307,8 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
     float a = kNegInf, b = kNegInf;
 #pragma unroll
     for (int e = 0; e < T::VW; ++e) {
-      a = fmaxf(a, elem<DT, VEC>(wq[i], e));
-      b = fmaxf(b, elem<DT, VEC>(wp[i], e));
+      a = fmaxf(a, elem<DT>(wq[i], e));
+      b = fmaxf(b, elem<DT>(wp[i], e));
     }
     gq[i] = a;
     gp[i] = b;
@@ -1259,7 +1323,7 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
   const float rp = (mp == kNegInf) ? 0.0f : mp * sp.c_hi;
   float sq = 0.0f, spp = 0.0f, hq = 0.0f, hp = 0.0f, xq = 0.0f;
   constexpr bool mom = MOM;
-  tile_sums<DT, VEC, MOM>(wq, wp, sp, rq, rp, sq, spp, hq, hp, xq);
+  tile_sums<DT, MOM>(wq, wp, sp, rq, rp, sq, spp, hq, hp, xq);
   // the moments are complete here: left free, the compiler sinks their
   // accumulation into the conditional combine below and keeps every
   // exponential of the tile live until then
@@ -1351,18 +1415,18 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
 // The second-pass weight summed over a thread's entries of one statistics
 // tile: for a token rule eta's share (the q mass of the entries the rule
 // marks), else max(0, p - q) (D_TV of Lemma 3) in float32.
-template <int DT, bool VEC, bool TOK>
-__device__ __forceinline__ double pass2_sum(const uint32_t (&wq)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
-                                            const uint32_t (&wp)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
+template <int DT, bool TOK>
+__device__ __forceinline__ double pass2_sum(const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
+                                            const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW],
                                             const ProbScale& ps) {
-  using T = StatTile<DT, VEC>;
+  using T = StatTile<DT>;
   double acc = 0.0;
 #pragma unroll
   for (int i = 0; i < T::U; ++i) {
     float t = 0.0f;
 #pragma unroll
     for (int e = 0; e < T::VW; ++e) {
-      const float zq = elem<DT, VEC>(wq[i], e), zp = elem<DT, VEC>(wp[i], e);
+      const float zq = elem<DT>(wq[i], e), zp = elem<DT>(wp[i], e);
       if constexpr (TOK) {
         t += token_r(ps.tok, zq, zp) ? prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo) : 0.0f;
       } else {
@@ -1412,10 +1476,10 @@ __device__ __forceinline__ bool eta_from_stats(const TokenRule& tr, const TilePa
 // wavefront that takes one slice compute the same partial with the same
 // arithmetic, so a row's result does not depend on which did it.
 static_assert(kSlices == kWaves, "a tile has one slice per wavefront of its workgroup");
-template <int DT, bool VEC>
-using PartC = Chunk<DT, VEC, 2 * StatTile<DT, VEC>::U>;  // half a tile, wave-contiguous
-template <int DT, bool VEC>
-using SubC = Chunk<DT, VEC, 1>;
+template <int DT>
+using PartC = Chunk<DT, 2 * StatTile<DT>::U>;  // half a tile, wave-contiguous
+template <int DT>
+using SubC = Chunk<DT, 1>;
 
 // Wave: "am I the last of n arrivals on cnt?" after this wavefront's item
 // (its results stored by its own lanes), arriving with weight w.  On true
@@ -1435,11 +1499,11 @@ __device__ __forceinline__ bool arrive_last_w(uint32_t* cnt, uint32_t n, uint32_
 
 // Wave: the slice's sub-chunk masses from its loaded entries (lane i < U
 // returns sub-chunk i * 4 + w's).
-template <int DT, bool VEC, int KIND>
-__device__ __forceinline__ double slice_masses_of(const uint32_t (&cq)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
-                                                  const uint32_t (&cp)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
+template <int DT, int KIND>
+__device__ __forceinline__ double slice_masses_of(const uint32_t (&cq)[StatTile<DT>::U][StatTile<DT>::NW],
+                                                  const uint32_t (&cp)[StatTile<DT>::U][StatTile<DT>::NW],
                                                   const ProbScale& ps, int kind) {
-  using T = StatTile<DT, VEC>;
+  using T = StatTile<DT>;
   const int lane = threadIdx.x & 63;
   double mine = 0.0;
 #pragma unroll
@@ -1447,7 +1511,7 @@ __device__ __forceinline__ double slice_masses_of(const uint32_t (&cq)[StatTile<
     float t = 0.0f;
 #pragma unroll
     for (int e = 0; e < T::VW; ++e) {
-      t += weight_k<DT, KIND>(elem<DT, VEC>(cq[i], e), elem<DT, VEC>(cp[i], e), ps, kind);
+      t += weight_k<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps, kind);
       if (e & 1) __builtin_amdgcn_sched_barrier(0);
     }
     const double s = wave_sum((double)t);
@@ -1460,27 +1524,26 @@ __device__ __forceinline__ double slice_masses_of(const uint32_t (&cq)[StatTile<
 // Wave: the masses of the sub-chunks of slice w of the tile at entry t0 of
 // a row under the distribution KIND; lane i < U returns sub-chunk i * 4 + w's
 // (float sums per lane load, fp64 across lanes), other lanes 0.
-template <int DT, bool VEC, int KIND>
+template <int DT, int KIND>
 __device__ __forceinline__ double slice_masses_w(const Params& P, int64_t row, int64_t t0, int w,
                                                  const ProbScale& ps, int kind = -1) {
-  using T = StatTile<DT, VEC>;
+  using T = StatTile<DT>;
   const int lane = threadIdx.x & 63, V = P.V;
   uint32_t cq[T::U][T::NW] = {}, cp[T::U][T::NW] = {};
-  if (KIND != kP)
-    load_tile<DT, VEC, T::U, true>((const char*)P.q + row * V * T::EB, t0, V, cq, w * 64 + lane);
-  if (KIND != kQ)
-    load_tile<DT, VEC, T::U, true>((const char*)P.p + row * V * T::EB, t0, V, cp, w * 64 + lane);
-  return slice_masses_of<DT, VEC, KIND>(cq, cp, ps, kind);
+  load_tiles<DT, T::U, true, kThreads, KIND != kP, KIND != kQ>(
+      (const char*)P.q + row * V * T::EB, (const char*)P.p + row * V * T::EB, t0, V, cq, cp,
+      w * 64 + lane, P.hdr);
+  return slice_masses_of<DT, KIND>(cq, cp, ps, kind);
 }
 
 
 // Wave: the second-pass partial of slice w of tile k of row r -- the TV
 // weight max(0, p - q), or eta's share (the q mass of the entries the rule
 // marks) -- into tvpart[r][k * 4 + w].
-template <int DT, bool VEC, bool TOK, bool NT = true>
+template <int DT, bool TOK, bool NT = true>
 __device__ __forceinline__ void pass2_slice_w(const Params& P, int r, int k, int w,
                                               const SeqParam& sp) {
-  using T = StatTile<DT, VEC>;
+  using T = StatTile<DT>;
   const int lane = threadIdx.x & 63, V = P.V;
   const int64_t t0 = (int64_t)k * T::N;
   // the row's statistics and the slice's entries are requested together,
@@ -1501,11 +1564,15 @@ __device__ __forceinline__ void pass2_slice_w(const Params& P, int r, int k, int
   }
   __builtin_amdgcn_sched_barrier(0);
   uint32_t wq[T::U][T::NW], wp[T::U][T::NW];
-  load_tile<DT, VEC, T::U, NT>((const char*)P.q + (int64_t)r * V * T::EB, t0, V, wq, w * 64 + lane);
-  load_tile<DT, VEC, T::U, NT>((const char*)P.p + (int64_t)r * V * T::EB, t0, V, wp, w * 64 + lane);
+  const char* qrow = (const char*)P.q + (int64_t)r * V * T::EB;
+  const char* prow = (const char*)P.p + (int64_t)r * V * T::EB;
+  load_tile<DT, T::U, NT>(qrow, t0, V, wq, w * 64 + lane, P.hdr);
+  load_tile<DT, T::U, NT>(prow, t0, V, wp, w * 64 + lane, P.hdr);
   __builtin_amdgcn_sched_barrier(0);
   const ProbScale ps = prob_scale(sp, rs, TOK);
-  double acc = pass2_sum<DT, VEC, TOK>(wq, wp, ps);
+  mask_tile<DT, T::U>(qrow, t0, V, wq, w * 64 + lane);
+  mask_tile<DT, T::U>(prow, t0, V, wp, w * 64 + lane);
+  double acc = pass2_sum<DT, TOK>(wq, wp, ps);
   acc = wave_sum(acc);
   if (lane == 0) st_dev_f64(P.tvpart + ((int64_t)r * P.nt + k) * kSlices + w, acc);
 }
@@ -1513,13 +1580,13 @@ __device__ __forceinline__ void pass2_slice_w(const Params& P, int r, int k, int
 // Wave: the TV partial of slice w of tile k of row r from the slice's entries
 // already in registers (the statistics tile's own loads), into
 // tvpart[r][k * 4 + w].
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ void tv_slice_regs_w(
     const Params& P, int r, int k, int w, const SeqParam& sp,
-    const uint32_t (&wq)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
-    const uint32_t (&wp)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW]) {
+    const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
+    const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW]) {
   const ProbScale ps = prob_scale(sp, ld_rowstat(P.rowstat + r), false);
-  const double acc = wave_sum(pass2_sum<DT, VEC, false>(wq, wp, ps));
+  const double acc = wave_sum(pass2_sum<DT, false>(wq, wp, ps));
   if ((threadIdx.x & 63) == 0) st_dev_f64(P.tvpart + ((int64_t)r * P.nt + k) * kSlices + w, acc);
 }
 
@@ -1927,18 +1994,18 @@ __device__ __forceinline__ void tv_skip_arrive_w(const Params& P, int rv) {
 // resident at once, so the row's last tile arrives while the others wait).
 // Once the row's merge has set its ready flag each wavefront sums its slice;
 // the last of the row's slices decides the row.
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ void tv_self(
     const Params& P, int r, int k, const SeqParam& sp, Shared& sh,
-    const uint32_t (&wq)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW],
-    const uint32_t (&wp)[StatTile<DT, VEC>::U][StatTile<DT, VEC>::NW]) {
+    const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
+    const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW]) {
   const uint32_t f = tv_wait_ready(P, r, k, sh);  // block-uniform
   if (f == 0u) return;
   if (f == 2u) {
     if (threadIdx.x < 64) tv_skip_arrive_w(P, r);
     return;
   }
-  tv_slice_regs_w<DT, VEC>(P, r, k, threadIdx.x >> 6, sp, wq, wp);
+  tv_slice_regs_w<DT>(P, r, k, threadIdx.x >> 6, sp, wq, wp);
   vmem_drain();
   __syncthreads();  // all four slices are stored
   if (threadIdx.x < 64 &&
@@ -1961,12 +2028,12 @@ enum TvMode : int { kTvNone = 0, kTvSelf = 2 };
 // With first moments the block is held to 96 VGPRs (five workgroups per
 // SIMD); the two-tile form keeps its registers (capped, it spills in the
 // streaming loop).
-template <int DT, bool VEC, int MS, int TVM, bool PAIR = false>
+template <int DT, int MS, int TVM, bool PAIR = false>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
   static_assert(!PAIR || TVM == kTvNone, "a pair of tiles takes no TV pass");
   constexpr bool NT = true;
-  using T = StatTile<DT, VEC>;
+  using T = StatTile<DT>;
   __shared__ Shared shs[PAIR ? 2 : 1];
   Shared& sh = shs[0];
   const int k = PAIR ? 2 * (int)blockIdx.x : (int)blockIdx.x, r = blockIdx.y;
@@ -1980,22 +2047,26 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
   const int64_t t0 = (int64_t)k * T::N;
   const bool two = PAIR && k + 1 < nt;  // block-uniform
   uint32_t wq[T::U][T::NW], wp[T::U][T::NW], vq[T::U][T::NW], vp[T::U][T::NW];
-  load_tile<DT, VEC, T::U, NT>(qrow, t0, V, wq, threadIdx.x);
-  load_tile<DT, VEC, T::U, NT>(prow, t0, V, wp, threadIdx.x);
+  load_tile<DT, T::U, NT>(qrow, t0, V, wq, threadIdx.x, P.hdr);
+  load_tile<DT, T::U, NT>(prow, t0, V, wp, threadIdx.x, P.hdr);
   if (two) {
-    load_tile<DT, VEC, T::U, NT>(qrow, t0 + T::N, V, vq, threadIdx.x);
-    load_tile<DT, VEC, T::U, NT>(prow, t0 + T::N, V, vp, threadIdx.x);
+    load_tile<DT, T::U, NT>(qrow, t0 + T::N, V, vq, threadIdx.x, P.hdr);
+    load_tile<DT, T::U, NT>(prow, t0 + T::N, V, vp, threadIdx.x, P.hdr);
   }
+  mask_tile<DT, T::U>(qrow, t0, V, wq, threadIdx.x);
+  mask_tile<DT, T::U>(prow, t0, V, wp, threadIdx.x);
   if (MS != 0 && needs_mom(sp))
-    tile_partial<DT, VEC, MS>(P, r, k, sp, wq, wp, sh);
+    tile_partial<DT, MS>(P, r, k, sp, wq, wp, sh);
   else
-    tile_partial<DT, VEC, 0>(P, r, k, sp, wq, wp, sh);
+    tile_partial<DT, 0>(P, r, k, sp, wq, wp, sh);
   if constexpr (PAIR) {
     if (two) {
+      mask_tile<DT, T::U>(qrow, t0 + T::N, V, vq, threadIdx.x);
+      mask_tile<DT, T::U>(prow, t0 + T::N, V, vp, threadIdx.x);
       if (MS != 0 && needs_mom(sp))
-        tile_partial<DT, VEC, MS>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
+        tile_partial<DT, MS>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
       else
-        tile_partial<DT, VEC, 0>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
+        tile_partial<DT, 0>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
     }
   }
   const uint32_t n = two ? 2u : 1u;  // tiles this block adds to its row
@@ -2013,7 +2084,7 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
     }
   }
   if constexpr (TVM == kTvSelf) {
-    if (sp.valid && !sp.greedy && has_tv_parts(sp.rule)) tv_self<DT, VEC>(P, r, k, sp, sh, wq, wp);
+    if (sp.valid && !sp.greedy && has_tv_parts(sp.rule)) tv_self<DT>(P, r, k, sp, sh, wq, wp);
   }
 }
 
@@ -2024,14 +2095,14 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
 // is their last read); the last of the row's slices decides the row, and a
 // sequence that decision finishes is drawn by the draw pass that follows.
 // Other rows' workgroups leave at once.
-template <int DT, bool VEC>
+template <int DT>
 __global__ __launch_bounds__(kThreads) void k_tvpass(Params P) {
   const int k = blockIdx.x, r = blockIdx.y;
   const SeqParam sp = seq_param(P, r / (P.gamma + 1));
   if (!(sp.valid && !sp.greedy && has_tv_parts(sp.rule))) return;  // block-uniform
   // rows decided without a TV pass have no ready flag
   if (ld_u32(row_word(P, r, kRowReady)) != 1u) return;  // block-uniform
-  pass2_slice_w<DT, VEC, false>(P, r, k, threadIdx.x >> 6, sp);
+  pass2_slice_w<DT, false>(P, r, k, threadIdx.x >> 6, sp);
   vmem_drain();
   __syncthreads();  // all four slices are stored
   if (threadIdx.x < 64 &&
@@ -2043,22 +2114,22 @@ __global__ __launch_bounds__(kThreads) void k_tvpass(Params P) {
 // Wave: the masses of the NS sub-chunks of the part at entry e0 of a row
 // under the distribution KIND; lane base + i returns sub-chunk i's (float
 // sums per lane load, fp64 across lanes), other lanes 0.
-template <int DT, bool VEC, int KIND>
+template <int DT, int KIND>
 __device__ __forceinline__ double part_masses_w(const Params& P, int64_t row, int64_t e0,
                                                 const ProbScale& ps, int base = 0, int kind = -1) {
-  using C = PartC<DT, VEC>;
-  constexpr int EB = StatTile<DT, VEC>::EB;
+  using C = PartC<DT>;
+  constexpr int EB = StatTile<DT>::EB;
   const int lane = threadIdx.x & 63, V = P.V;
   ChunkRegs<C> cq = {}, cp = {};
-  if (KIND != kP) load_chunk<DT, VEC, C>((const char*)P.q + row * V * EB, e0, V, cq);
-  if (KIND != kQ) load_chunk<DT, VEC, C>((const char*)P.p + row * V * EB, e0, V, cp);
+  load_chunks<DT, C, KIND>((const char*)P.q + row * V * EB, (const char*)P.p + row * V * EB, e0, V,
+                           cq, cp, P.hdr);
   double mine = 0.0;
 #pragma unroll
   for (int i = 0; i < C::U; ++i) {
     float t = 0.0f;
 #pragma unroll
     for (int e = 0; e < C::VW; ++e) {
-      t += weight_k<DT, KIND>(elem<DT, VEC>(cq[i], e), elem<DT, VEC>(cp[i], e), ps, kind);
+      t += weight_k<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps, kind);
       if (e & 1) __builtin_amdgcn_sched_barrier(0);
     }
     const double s = wave_sum((double)t);
@@ -2072,7 +2143,7 @@ __device__ __forceinline__ double part_masses_w(const Params& P, int64_t row, in
 // masses lane i < NSUB holds: the first sub-chunk where the running mass
 // exceeds rem (rounding that leaves rem unreached takes the last sub-chunk
 // with mass), then the entry inside it.
-template <int DT, bool VEC, int KIND>
+template <int DT, int KIND>
 __device__ __forceinline__ void draw_in_subs_w(const Params& P, int b, int64_t row, int64_t e0,
                                                double ml, int nsub, double rem,
                                                const ProbScale& ps, int kind = -1) {
@@ -2090,7 +2161,7 @@ __device__ __forceinline__ void draw_in_subs_w(const Params& P, int b, int64_t r
     c = pos ? 63 - __clzll(pos) : 0;
     r = __builtin_huge_val();
   }
-  pick_wave<DT, VEC, SubC<DT, VEC>, KIND>(P, b, row, e0 + (int64_t)c * SubC<DT, VEC>::N, r, ps,
+  pick_wave<DT, SubC<DT>, KIND>(P, b, row, e0 + (int64_t)c * SubC<DT>::N, r, ps,
                                           kind);
 }
 
@@ -2099,26 +2170,26 @@ __device__ __forceinline__ void draw_in_subs_w(const Params& P, int b, int64_t r
 // partials per tile (then the tile's sub-chunk masses are summed here), or
 // the residual job's sub-chunk masses, searched directly.  An empty residual
 // (possible only through rounding) is replaced by p.
-template <int DT, bool VEC, int KIND>
+template <int DT, int KIND>
 __device__ __forceinline__ void draw_kind_w(const Params& P, int b, int64_t row, int ks,
                                             double rem, const ProbScale& ps) {
   if constexpr (KIND == kResidual || KIND == kTokRes) {
     // the residual job's sub-chunk masses were searched: ks is a sub-chunk
-    pick_wave<DT, VEC, SubC<DT, VEC>, KIND>(P, b, row, (int64_t)ks * SubC<DT, VEC>::N, rem, ps);
+    pick_wave<DT, SubC<DT>, KIND>(P, b, row, (int64_t)ks * SubC<DT>::N, rem, ps);
   } else {
     // a statistics tile: the masses of its sub-chunks (its two
     // wave-contiguous halves, in order), then the sub-chunk's entry
-    const int64_t t0 = (int64_t)ks * StatTile<DT, VEC>::N;
-    constexpr int NS = PartC<DT, VEC>::U;
+    const int64_t t0 = (int64_t)ks * StatTile<DT>::N;
+    constexpr int NS = PartC<DT>::U;
     double m = 0.0;
 #pragma unroll 1
     for (int half = 0; half < 2; ++half)
-      m += part_masses_w<DT, VEC, KIND>(P, row, t0 + half * PartC<DT, VEC>::N, ps, half * NS);
-    draw_in_subs_w<DT, VEC, KIND>(P, b, row, t0, m, 2 * NS, rem, ps);
+      m += part_masses_w<DT, KIND>(P, row, t0 + half * PartC<DT>::N, ps, half * NS);
+    draw_in_subs_w<DT, KIND>(P, b, row, t0, m, 2 * NS, rem, ps);
   }
 }
 
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ void draw_w(const Params& P, int b, int64_t row, int kind, int src,
                                        const SeqParam& sp, const RowStat& rs) {
   const int lane = threadIdx.x & 63;
@@ -2140,16 +2211,16 @@ __device__ __forceinline__ void draw_w(const Params& P, int b, int64_t row, int 
   }
   if (ks < 0) return;  // wave-uniform
   const ProbScale ps = prob_scale(sp, rs, kind == kTokRes || kind == kTokPi);
-  if (kind == kQ) draw_kind_w<DT, VEC, kQ>(P, b, row, ks, rem, ps);
-  else if (kind == kP) draw_kind_w<DT, VEC, kP>(P, b, row, ks, rem, ps);
-  else if (kind == kTokPi) draw_kind_w<DT, VEC, kTokPi>(P, b, row, ks, rem, ps);
-  else if (kind == kTokRes) draw_kind_w<DT, VEC, kTokRes>(P, b, row, ks, rem, ps);
-  else draw_kind_w<DT, VEC, kResidual>(P, b, row, ks, rem, ps);
+  if (kind == kQ) draw_kind_w<DT, kQ>(P, b, row, ks, rem, ps);
+  else if (kind == kP) draw_kind_w<DT, kP>(P, b, row, ks, rem, ps);
+  else if (kind == kTokPi) draw_kind_w<DT, kTokPi>(P, b, row, ks, rem, ps);
+  else if (kind == kTokRes) draw_kind_w<DT, kTokRes>(P, b, row, ks, rem, ps);
+  else draw_kind_w<DT, kResidual>(P, b, row, ks, rem, ps);
 }
 
 // Wave: item c = k * 4 + w of a TV or eta row job of row r: slice w of tile
 // k (for eta, of the k-th listed tile; an item past the list does nothing).
-template <int DT, bool VEC, bool TOK>
+template <int DT, bool TOK>
 __device__ __forceinline__ void pass2_item_w(const Params& P, int r, int c) {
   int k = c / kSlices;
   const int w = c % kSlices;
@@ -2157,7 +2228,7 @@ __device__ __forceinline__ void pass2_item_w(const Params& P, int r, int c) {
     if (k >= ld_i32(P.etacnt + r)) return;  // wave-uniform
     k = ld_i32(P.etalist + (int64_t)r * P.nt + k);
   }
-  pass2_slice_w<DT, VEC, TOK>(P, r, k, w, seq_param(P, r / (P.gamma + 1)));
+  pass2_slice_w<DT, TOK>(P, r, k, w, seq_param(P, r / (P.gamma + 1)));
 }
 
 // Wave: half h of the argmax of greedy row r: the lowest index of the row
@@ -2165,9 +2236,9 @@ __device__ __forceinline__ void pass2_item_w(const Params& P, int r, int c) {
 // in the slices of that tile that attain it (usually one; a slice's lane
 // loads interleave with the other slices', so the minimum is taken over
 // every slice read).
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ void arg_half_w(const Params& P, int r, int h) {
-  using T = StatTile<DT, VEC>;
+  using T = StatTile<DT>;
   const int V = P.V;
   const int lane = threadIdx.x & 63;
   const int packed = ld_i32(P.argres + (int64_t)r * 4 + h);
@@ -2186,13 +2257,14 @@ __device__ __forceinline__ void arg_half_w(const Params& P, int r, int h) {
   for (int w = 0; w < kSlices; ++w) {
     if (!((mask >> w) & 1)) continue;  // wave-uniform
     uint32_t c[T::U][T::NW];
-    load_tile<DT, VEC, T::U, true>(row, t0, V, c, w * 64 + lane);
+    load_tile<DT, T::U, true>(row, t0, V, c, w * 64 + lane, P.hdr);
+    mask_tile<DT, T::U>(row, t0, V, c, w * 64 + lane);
 #pragma unroll
     for (int i = T::U - 1; i >= 0; --i) {
       const int base = (int)t0 + ((i * kSlices + w) * 64 + lane) * T::VW;
 #pragma unroll
       for (int e = T::VW - 1; e >= 0; --e)
-        if (elem<DT, VEC>(c[i], e) == z && base + e < V) idx = min(idx, base + e);
+        if (elem<DT>(c[i], e) == z && base + e < V) idx = min(idx, base + e);
     }
   }
   idx = wave_min(idx);
@@ -2203,11 +2275,11 @@ __device__ __forceinline__ void arg_half_w(const Params& P, int r, int h) {
 // sampling kind KIND: the residual masses of the sub-chunks of slice w of
 // tile k, stored at their place in the row's sub-chunk order, which the draw
 // searches directly.
-template <int DT, bool VEC, int KIND>
+template <int DT, int KIND>
 __device__ __forceinline__ void res_slice_w(const Params& P, int b, int c, int f,
                                             const RowStat& rs) {
-  constexpr int U = StatTile<DT, VEC>::U;
-  using T = StatTile<DT, VEC>;
+  constexpr int U = StatTile<DT>::U;
+  using T = StatTile<DT>;
   const int k = c / kSlices, w = c % kSlices;
   const int lane = threadIdx.x & 63, V = P.V;
   const int64_t row = (int64_t)b * (P.gamma + 1) + f;
@@ -2216,9 +2288,10 @@ __device__ __forceinline__ void res_slice_w(const Params& P, int b, int c, int f
   const ProbScale ps = prob_scale(sp, rs, KIND == kTokRes);
   __builtin_amdgcn_sched_barrier(0);
   uint32_t cq[T::U][T::NW], cp[T::U][T::NW];
-  load_tile<DT, VEC, T::U, true>((const char*)P.q + row * V * T::EB, t0, V, cq, w * 64 + lane);
-  load_tile<DT, VEC, T::U, true>((const char*)P.p + row * V * T::EB, t0, V, cp, w * 64 + lane);
-  const double ml = slice_masses_of<DT, VEC, KIND>(cq, cp, ps, -1);
+  load_tiles<DT, T::U, true>((const char*)P.q + row * V * T::EB,
+                             (const char*)P.p + row * V * T::EB, t0, V, cq, cp, w * 64 + lane,
+                             P.hdr);
+  const double ml = slice_masses_of<DT, KIND>(cq, cp, ps, -1);
   if (lane < U)
     st_dev_f64(P.submass + (int64_t)b * P.nsub + (int64_t)k * (U * kSlices) + lane * kSlices + w,
                ml);
@@ -2237,7 +2310,7 @@ __device__ __forceinline__ void res_slice_w(const Params& P, int b, int c, int f
 // large batches (256 sequences: 8192 workgroups) one workgroup's loads
 // overlap another's residual weights.  What spills is the draw's own code,
 // which only the last arrival of a sequence runs.
-template <int DT, bool VEC>
+template <int DT>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(DT == SPC_BF16 ? 6 : 1))) void k_res(Params P) {
   const int k = blockIdx.x, b = blockIdx.y;
@@ -2255,19 +2328,19 @@ __attribute__((amdgpu_waves_per_eu(DT == SPC_BF16 ? 6 : 1))) void k_res(Params P
   const bool residual = kind == kResidual || kind == kTokRes;
   if (residual) {
     const int w = threadIdx.x >> 6;
-    if (kind == kTokRes) res_slice_w<DT, VEC, kTokRes>(P, b, k * kSlices + w, f, rs);
-    else res_slice_w<DT, VEC, kResidual>(P, b, k * kSlices + w, f, rs);
+    if (kind == kTokRes) res_slice_w<DT, kTokRes>(P, b, k * kSlices + w, f, rs);
+    else res_slice_w<DT, kResidual>(P, b, k * kSlices + w, f, rs);
     vmem_drain();
   }
   __syncthreads();  // every wavefront's masses are stored
   if (threadIdx.x >= 64) return;
   if (!residual && k == 0) {
     const int src = kind == kQ ? kSrcStatsQ : kind == kP ? kSrcStatsP : kSrcTokPi;
-    draw_w<DT, VEC>(P, b, row, kind, src, sp, ld_rowstat(P.rowstat + row));
+    draw_w<DT>(P, b, row, kind, src, sp, ld_rowstat(P.rowstat + row));
     vmem_drain();
   }
   if (arrive_last_w(row_word(P, b, kSeqResArrive), (uint32_t)P.nt)) {
-    if (residual) draw_w<DT, VEC>(P, b, row, kind, kSrcPass, sp, ld_rowstat(P.rowstat + row));
+    if (residual) draw_w<DT>(P, b, row, kind, kSrcPass, sp, ld_rowstat(P.rowstat + row));
     if ((threadIdx.x & 63) == 0) st_u32(row_word(P, b, kSeqInfo), 0u);
   }
 }
@@ -2297,7 +2370,7 @@ __device__ __forceinline__ void exit_tree(const Params& P) {
 // items w, w + W, ...  The item that completes a job decides its row; a
 // sequence that decision finishes is drawn by the draw pass that follows.
 // Held to 128 VGPRs: two workgroups per compute unit.
-template <int DT, bool VEC>
+template <int DT>
 __global__ __launch_bounds__(kJobThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_jobs(
     Params P) {
   __shared__ uint32_t count;
@@ -2340,29 +2413,29 @@ __global__ __launch_bounds__(kJobThreads) __attribute__((amdgpu_waves_per_eu(4))
         const SeqParam spt = seq_param(P, id / g1);
 #pragma unroll 1
         for (int w = 0; w < kSlices; ++w)
-          pass2_slice_w<DT, VEC, false>(P, id, (int)job_extra(e), w, spt);
+          pass2_slice_w<DT, false>(P, id, (int)job_extra(e), w, spt);
         if (arrive_last_w(row_word(P, id, kRowTvArrive), (uint32_t)(kSlices * nt), kSlices))
           tv_row_done<DT>(P, id);
       } else if (kind == kJobTvSlice) {
         // slice x % 4 of tile x / 4 of TV row id
         const int x = (int)job_extra(e);
-        pass2_slice_w<DT, VEC, false>(P, id, x / kSlices, x % kSlices, seq_param(P, id / g1));
+        pass2_slice_w<DT, false>(P, id, x / kSlices, x % kSlices, seq_param(P, id / g1));
         if (arrive_last_w(row_word(P, id, kRowTvArrive), (uint32_t)(kSlices * nt)))
           tv_row_done<DT>(P, id);
       } else if (kind == kJobEta) {
         // slice c % 4 of the (c / 4)-th listed tile of token row id
         const uint32_t n = (uint32_t)ld_i32(P.etacnt + id) * (uint32_t)kSlices;
-        pass2_item_w<DT, VEC, true>(P, id, (int)job_extra(e));
+        pass2_item_w<DT, true>(P, id, (int)job_extra(e));
         if (arrive_last_w(row_word(P, id, kRowTvArrive), n)) row_job_decide<DT>(P, kind, id);
       } else {  // kJobArg
-        arg_half_w<DT, VEC>(P, id, (int)job_extra(e));
+        arg_half_w<DT>(P, id, (int)job_extra(e));
         if (arrive_last_w(row_word(P, id, kRowJobDone), 2u)) row_job_decide<DT>(P, kind, id);
       }
     }
   }
 }
 
-template <int DT, bool VEC>
+template <int DT>
 hipError_t launch_step_t(const Params& P, hipStream_t st, bool draw_pass, bool tv_pass,
                          bool job_pass, int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end) {
   const dim3 grid((unsigned)P.nt, (unsigned)(P.B * (P.gamma + 1))), block(kThreads);
@@ -2373,35 +2446,35 @@ hipError_t launch_step_t(const Params& P, hipStream_t st, bool draw_pass, bool t
   constexpr int kAll = kMomX | kMomHQ | kMomHP;
   if (!P.tv_self && P.pair && P.mom_set == 0) {
     const dim3 grid2((unsigned)((P.nt + 1) / 2), (unsigned)(P.B * (P.gamma + 1)));
-    hipLaunchKernelGGL((k_tiles<DT, VEC, 0, kTvNone, true>), grid2, block, 0, st, P);
+    hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, true>), grid2, block, 0, st, P);
   } else if (!P.tv_self) {
     if (P.mom_set == 0)
-      hipLaunchKernelGGL((k_tiles<DT, VEC, 0, kTvNone>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone>), grid, block, 0, st, P);
     else if (P.mom_set == kMomX)
-      hipLaunchKernelGGL((k_tiles<DT, VEC, kMomX, kTvNone>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, kMomX, kTvNone>), grid, block, 0, st, P);
     else if (P.mom_set == kMomHQ)
-      hipLaunchKernelGGL((k_tiles<DT, VEC, kMomHQ, kTvNone>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, kMomHQ, kTvNone>), grid, block, 0, st, P);
     else
-      hipLaunchKernelGGL((k_tiles<DT, VEC, kAll, kTvNone>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, kAll, kTvNone>), grid, block, 0, st, P);
   } else {
     if (P.mom_set == 0)
-      hipLaunchKernelGGL((k_tiles<DT, VEC, 0, kTvSelf>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvSelf>), grid, block, 0, st, P);
     else
-      hipLaunchKernelGGL((k_tiles<DT, VEC, kAll, kTvSelf>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, kAll, kTvSelf>), grid, block, 0, st, P);
   }
   hipError_t err = hipGetLastError();
   if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, st);
   if (err == hipSuccess && tv_pass) {
-    hipLaunchKernelGGL((k_tvpass<DT, VEC>), grid, block, 0, st, P);
+    hipLaunchKernelGGL((k_tvpass<DT>), grid, block, 0, st, P);
     err = hipGetLastError();
   }
   if (err == hipSuccess && job_pass) {
-    hipLaunchKernelGGL((k_jobs<DT, VEC>), dim3((unsigned)job_groups), dim3(kJobThreads), 0, st,
+    hipLaunchKernelGGL((k_jobs<DT>), dim3((unsigned)job_groups), dim3(kJobThreads), 0, st,
                        P);
     err = hipGetLastError();
   }
   if (err == hipSuccess && draw_pass) {  // every sequence is finished by now
-    hipLaunchKernelGGL((k_res<DT, VEC>), dim3((unsigned)P.nt, (unsigned)P.B), block, 0, st, P);
+    hipLaunchKernelGGL((k_res<DT>), dim3((unsigned)P.nt, (unsigned)P.B), block, 0, st, P);
     err = hipGetLastError();
   }
   return err;
@@ -2422,9 +2495,9 @@ constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kSmallU = 4;
 static_assert(kSmallU * kSmallWaves == kSmallSub, "sub-chunks per row of the small path");
 
-template <int DT, bool VEC>
+template <int DT>
 struct SmallRow {
-  using T = Tile<DT, VEC, kSmallU>;  // element geometry (EB, VW, NW)
+  using T = Tile<DT, kSmallU>;  // element geometry (EB, VW, NW)
   static constexpr int N = kSmallThreads * kSmallU * T::VW;  // entries a workgroup holds
 };
 
@@ -2466,67 +2539,80 @@ __device__ __forceinline__ double small_sum(double v, SmallShared& sh) {
 // tiles and the row merge compute them: per thread against its own maximum,
 // per wavefront against the wavefront's, then (fp64) against the row's; with
 // ARG the lowest index of each row maximum, with MOM the first moments.
-template <int DT, bool VEC>
-using SmallRegs = uint32_t[kSmallU][Tile<DT, VEC, kSmallU>::NW];
+template <int DT>
+using SmallRegs = uint32_t[kSmallU][Tile<DT, kSmallU>::NW];
 
 // Thread t's lane load i of a row (entries (i * 1024 + t) * VW ..), raw: a
-// lane load past the row reads the row's first entries instead, and every
-// pass reads it as -inf through small_elem (a lane load is wholly inside or
-// wholly outside the row).  Keeping the raw words, rather than selecting
-// the padding once, spares the registers of a second copy.
-template <int DT, bool VEC>
-__device__ __forceinline__ void small_load(const char* row, int V, SmallRegs<DT, VEC>& w) {
-  using T = Tile<DT, VEC, kSmallU>;
+// lane load not wholly inside the row reads the row's first entries instead
+// (`safe`, 16 readable bytes, where the row holds no whole lane load).  The
+// passes read a lane load wholly past the row as -inf through small_elem;
+// small_tail fills the one the row ends in.  Keeping the raw words, rather
+// than selecting the padding once, spares the registers of a second copy.
+template <int DT>
+__device__ __forceinline__ void small_load(const char* row, int V, SmallRegs<DT>& w,
+                                           const void* safe) {
+  using T = Tile<DT, kSmallU>;
+  using LV = typename LaneVec<DT>::type;
+  const char* base = V >= T::VW ? row : static_cast<const char*>(safe);
 #pragma unroll
   for (int i = 0; i < kSmallU; ++i) {
     const int e = (i * kSmallThreads + (int)threadIdx.x) * T::VW;
-    const char* a = row + (uint32_t)((e < V ? e : 0) * T::EB);
-    if constexpr (VEC) {
-      const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(a));
-      w[i][0] = v.x;
-      w[i][1] = v.y;
-      w[i][2] = v.z;
-      w[i][3] = v.w;
-    } else if constexpr (DT == 1) {
-      w[i][0] = *reinterpret_cast<const uint16_t*>(a);
-    } else {
-      w[i][0] = *reinterpret_cast<const uint32_t*>(a);
-    }
+    const u32x4 v = __builtin_nontemporal_load(
+        reinterpret_cast<const LV*>(base + (uint32_t)((e + T::VW <= V ? e : 0) * T::EB)));
+    w[i][0] = v.x;
+    w[i][1] = v.y;
+    w[i][2] = v.z;
+    w[i][3] = v.w;
+  }
+}
+template <int DT>
+__device__ __forceinline__ void small_tail(const char* row, int V, SmallRegs<DT>& w) {
+  using T = Tile<DT, kSmallU>;
+  if (V % T::VW == 0) return;  // uniform
+  const int slot = V / T::VW;
+  if ((int)threadIdx.x == slot % kSmallThreads) {
+    uint32_t x[4];
+    load_partial<DT>(row + (uint32_t)(slot * T::VW * T::EB), V % T::VW, x);
+#pragma unroll
+    for (int i = 0; i < kSmallU; ++i)
+      if (i == slot / kSmallThreads)
+#pragma unroll
+        for (int j = 0; j < T::NW; ++j) w[i][j] = x[j];
   }
 }
 
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ bool small_ok(int i, int V) {
-  return (i * kSmallThreads + (int)threadIdx.x) * Tile<DT, VEC, kSmallU>::VW < V;
+  return (i * kSmallThreads + (int)threadIdx.x) * Tile<DT, kSmallU>::VW < V;
 }
 
 // Whether any lane of this wavefront holds entries of lane load i
 // (wavefront-uniform): lane loads wholly past the row are skipped.
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ bool small_live(int i, int V) {
-  return (i * kSmallThreads + (int)(threadIdx.x & ~63)) * Tile<DT, VEC, kSmallU>::VW < V;
+  return (i * kSmallThreads + (int)(threadIdx.x & ~63)) * Tile<DT, kSmallU>::VW < V;
 }
 
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ float small_elem(const uint32_t* w, int e, bool ok) {
-  return ok ? elem<DT, VEC>(w, e) : kNegInf;
+  return ok ? elem<DT>(w, e) : kNegInf;
 }
 
-template <int DT, bool VEC, int MOM, bool ARG>
-__device__ __forceinline__ RowStat small_stats(SmallRegs<DT, VEC>& wq, SmallRegs<DT, VEC>& wp,
+template <int DT, int MOM, bool ARG>
+__device__ __forceinline__ RowStat small_stats(SmallRegs<DT>& wq, SmallRegs<DT>& wp,
                                                int V, const SeqParam& sp, int mrule,
                                                SmallShared& sh) {
-  using T = Tile<DT, VEC, kSmallU>;
+  using T = Tile<DT, kSmallU>;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   float mq = kNegInf, mp = kNegInf;
 #pragma unroll
   for (int i = 0; i < kSmallU; ++i) {
-    if (!small_live<DT, VEC>(i, V)) continue;  // wavefront-uniform
-    const bool ok = small_ok<DT, VEC>(i, V);
+    if (!small_live<DT>(i, V)) continue;  // wavefront-uniform
+    const bool ok = small_ok<DT>(i, V);
 #pragma unroll
     for (int e = 0; e < T::VW; ++e) {
-      mq = fmaxf(mq, small_elem<DT, VEC>(wq[i], e, ok));
-      mp = fmaxf(mp, small_elem<DT, VEC>(wp[i], e, ok));
+      mq = fmaxf(mq, small_elem<DT>(wq[i], e, ok));
+      mp = fmaxf(mp, small_elem<DT>(wp[i], e, ok));
     }
   }
   small_fence(wq, wp);
@@ -2535,13 +2621,13 @@ __device__ __forceinline__ RowStat small_stats(SmallRegs<DT, VEC>& wq, SmallRegs
     // the first entry equal to the thread maximum, entries in index order
 #pragma unroll
     for (int i = kSmallU - 1; i >= 0; --i) {
-      if (!small_live<DT, VEC>(i, V)) continue;  // wavefront-uniform
-      const bool ok = small_ok<DT, VEC>(i, V);
+      if (!small_live<DT>(i, V)) continue;  // wavefront-uniform
+      const bool ok = small_ok<DT>(i, V);
 #pragma unroll
       for (int e = T::VW - 1; e >= 0; --e) {
         const int idx = (i * kSmallThreads + (int)threadIdx.x) * T::VW + e;
-        if (small_elem<DT, VEC>(wq[i], e, ok) == mq) iq = idx;
-        if (small_elem<DT, VEC>(wp[i], e, ok) == mp) ip = idx;
+        if (small_elem<DT>(wq[i], e, ok) == mq) iq = idx;
+        if (small_elem<DT>(wp[i], e, ok) == mp) ip = idx;
       }
     }
     if (mq == kNegInf) iq = 0x7fffffff;
@@ -2553,11 +2639,11 @@ __device__ __forceinline__ RowStat small_stats(SmallRegs<DT, VEC>& wq, SmallRegs
   float sq = 0.0f, spp = 0.0f, hq = 0.0f, hp = 0.0f, xq = 0.0f;
 #pragma unroll
   for (int i = 0; i < kSmallU; ++i) {
-    if (!small_live<DT, VEC>(i, V)) continue;  // wavefront-uniform
-    const bool ok = small_ok<DT, VEC>(i, V);
+    if (!small_live<DT>(i, V)) continue;  // wavefront-uniform
+    const bool ok = small_ok<DT>(i, V);
 #pragma unroll
     for (int e = 0; e < T::VW; ++e) {
-      const float zq = small_elem<DT, VEC>(wq[i], e, ok), zp = small_elem<DT, VEC>(wp[i], e, ok);
+      const float zq = small_elem<DT>(wq[i], e, ok), zp = small_elem<DT>(wp[i], e, ok);
       const float aq = fmaf(zq, sp.c_lo, fmaf(zq, sp.c_hi, -rq));
       const float ap = fmaf(zp, sp.c_lo, fmaf(zp, sp.c_hi, -rp));
       const float tq = exp2_hw(aq), tp = exp2_hw(ap);
@@ -2640,14 +2726,14 @@ __device__ __forceinline__ RowStat small_stats(SmallRegs<DT, VEC>& wq, SmallRegs
 
 // Thread: sum over its entries of the sampled distribution KIND's weights
 // for lane load i (float, entry order).
-template <int DT, bool VEC, int KIND>
-__device__ __forceinline__ float small_weight_row(const uint32_t (&wq)[Tile<DT, VEC, kSmallU>::NW],
-                                                  const uint32_t (&wp)[Tile<DT, VEC, kSmallU>::NW],
+template <int DT, int KIND>
+__device__ __forceinline__ float small_weight_row(const uint32_t (&wq)[Tile<DT, kSmallU>::NW],
+                                                  const uint32_t (&wp)[Tile<DT, kSmallU>::NW],
                                                   bool ok, const ProbScale& ps, int kind) {
   float t = 0.0f;
 #pragma unroll
-  for (int e = 0; e < Tile<DT, VEC, kSmallU>::VW; ++e) {
-    t += weight_k<DT, KIND>(small_elem<DT, VEC>(wq, e, ok), small_elem<DT, VEC>(wp, e, ok), ps, kind);
+  for (int e = 0; e < Tile<DT, kSmallU>::VW; ++e) {
+    t += weight_k<DT, KIND>(small_elem<DT>(wq, e, ok), small_elem<DT>(wp, e, ok), ps, kind);
     if (e & 1) __builtin_amdgcn_sched_barrier(0);
   }
   return t;
@@ -2656,18 +2742,18 @@ __device__ __forceinline__ float small_weight_row(const uint32_t (&wq)[Tile<DT, 
 // Whole block: the masses of the row's sub-chunks under KIND (sub-chunk
 // i * 16 + w is wave w's lane load i), stored as set `set` of the row for
 // the sequence's draw; returns their total.
-template <int DT, bool VEC, int KIND>
+template <int DT, int KIND>
 __device__ __forceinline__ double small_masses(const Params& P, int r, int set, int kind,
-                                               const uint32_t (&wq)[kSmallU][Tile<DT, VEC, kSmallU>::NW],
-                                               const uint32_t (&wp)[kSmallU][Tile<DT, VEC, kSmallU>::NW],
+                                               const uint32_t (&wq)[kSmallU][Tile<DT, kSmallU>::NW],
+                                               const uint32_t (&wp)[kSmallU][Tile<DT, kSmallU>::NW],
                                                const ProbScale& ps, SmallShared& sh) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   double tot = 0.0;
 #pragma unroll
   for (int i = 0; i < kSmallU; ++i) {
     double m = 0.0;
-    if (small_live<DT, VEC>(i, P.V))  // wavefront-uniform
-      m = wave_sum((double)small_weight_row<DT, VEC, KIND>(wq[i], wp[i], small_ok<DT, VEC>(i, P.V),
+    if (small_live<DT>(i, P.V))  // wavefront-uniform
+      m = wave_sum((double)small_weight_row<DT, KIND>(wq[i], wp[i], small_ok<DT>(i, P.V),
                                                            ps, kind));
     if (lane == 0)
       st_dev_f64(P.submass + ((int64_t)r * 2 + set) * kSmallSub + i * kSmallWaves + wv, m);
@@ -2677,22 +2763,22 @@ __device__ __forceinline__ double small_masses(const Params& P, int r, int set, 
   return small_sum(lane == 0 ? tot : 0.0, sh);
 }
 
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ double small_masses_kind(const Params& P, int r, int set, int kind,
-                                                    const uint32_t (&wq)[kSmallU][Tile<DT, VEC, kSmallU>::NW],
-                                                    const uint32_t (&wp)[kSmallU][Tile<DT, VEC, kSmallU>::NW],
+                                                    const uint32_t (&wq)[kSmallU][Tile<DT, kSmallU>::NW],
+                                                    const uint32_t (&wp)[kSmallU][Tile<DT, kSmallU>::NW],
                                                     const ProbScale& ps, SmallShared& sh) {
-  if (kind == kResidual) return small_masses<DT, VEC, kResidual>(P, r, set, kind, wq, wp, ps, sh);
-  if (kind == kTokRes) return small_masses<DT, VEC, kTokRes>(P, r, set, kind, wq, wp, ps, sh);
-  if (kind == kQ) return small_masses<DT, VEC, kQ>(P, r, set, kind, wq, wp, ps, sh);
-  if (kind == kP) return small_masses<DT, VEC, kP>(P, r, set, kind, wq, wp, ps, sh);
-  return small_masses<DT, VEC, kTokPi>(P, r, set, kind, wq, wp, ps, sh);
+  if (kind == kResidual) return small_masses<DT, kResidual>(P, r, set, kind, wq, wp, ps, sh);
+  if (kind == kTokRes) return small_masses<DT, kTokRes>(P, r, set, kind, wq, wp, ps, sh);
+  if (kind == kQ) return small_masses<DT, kQ>(P, r, set, kind, wq, wp, ps, sh);
+  if (kind == kP) return small_masses<DT, kP>(P, r, set, kind, wq, wp, ps, sh);
+  return small_masses<DT, kTokPi>(P, r, set, kind, wq, wp, ps, sh);
 }
 
 // Wave: the draw of sequence b at row j* = f from that row's stored
 // sub-chunk masses under `kind`: the sub-chunk where u W is crossed, then
 // the entry inside it (read again).
-template <int DT, bool VEC>
+template <int DT>
 __device__ __forceinline__ void small_draw_w(const Params& P, int b, int f, int kind, int set,
                                              const SeqParam& sp) {
   const int64_t row = (int64_t)b * (P.gamma + 1) + f;
@@ -2710,17 +2796,17 @@ __device__ __forceinline__ void small_draw_w(const Params& P, int b, int f, int 
   }
   if (ks < 0) return;  // wave-uniform
   const ProbScale ps = prob_scale(sp, rs, kind == kTokRes || kind == kTokPi);
-  const int64_t c0 = (int64_t)ks * SubC<DT, VEC>::N;
-  if (kind == kResidual) pick_wave<DT, VEC, SubC<DT, VEC>, kResidual>(P, b, row, c0, rem, ps);
-  else if (kind == kTokRes) pick_wave<DT, VEC, SubC<DT, VEC>, kTokRes>(P, b, row, c0, rem, ps);
-  else if (kind == kQ) pick_wave<DT, VEC, SubC<DT, VEC>, kQ>(P, b, row, c0, rem, ps);
-  else if (kind == kP) pick_wave<DT, VEC, SubC<DT, VEC>, kP>(P, b, row, c0, rem, ps);
-  else pick_wave<DT, VEC, SubC<DT, VEC>, kTokPi>(P, b, row, c0, rem, ps);
+  const int64_t c0 = (int64_t)ks * SubC<DT>::N;
+  if (kind == kResidual) pick_wave<DT, SubC<DT>, kResidual>(P, b, row, c0, rem, ps);
+  else if (kind == kTokRes) pick_wave<DT, SubC<DT>, kTokRes>(P, b, row, c0, rem, ps);
+  else if (kind == kQ) pick_wave<DT, SubC<DT>, kQ>(P, b, row, c0, rem, ps);
+  else if (kind == kP) pick_wave<DT, SubC<DT>, kP>(P, b, row, c0, rem, ps);
+  else pick_wave<DT, SubC<DT>, kTokPi>(P, b, row, c0, rem, ps);
 }
 
-template <int DT, bool VEC, int MS>
+template <int DT, int MS>
 __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
-  using T = Tile<DT, VEC, kSmallU>;
+  using T = Tile<DT, kSmallU>;
   __shared__ SmallShared sh;
   const int r = blockIdx.x, gamma = P.gamma, g1 = gamma + 1, V = P.V;
   const int b = r / g1, j = r - b * g1;
@@ -2729,16 +2815,20 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
   const int x = (sp.valid && j < gamma) ? P.draft[(int64_t)b * gamma + j] : -1;
   const float u = (sp.valid && !sp.greedy) ? P.uniforms[r] : 0.0f;
   uint32_t wq[kSmallU][T::NW], wp[kSmallU][T::NW];
-  small_load<DT, VEC>((const char*)P.q + (int64_t)r * V * T::EB, V, wq);
-  small_load<DT, VEC>((const char*)P.p + (int64_t)r * V * T::EB, V, wp);
+  const char* qrow = (const char*)P.q + (int64_t)r * V * T::EB;
+  const char* prow = (const char*)P.p + (int64_t)r * V * T::EB;
+  small_load<DT>(qrow, V, wq, P.hdr);
+  small_load<DT>(prow, V, wp, P.hdr);
+  small_tail<DT>(qrow, V, wq);
+  small_tail<DT>(prow, V, wp);
   const int mrule = (MS != 0 && needs_mom(sp)) ? sp.rule : 0;
   RowStat rs;
   if (sp.greedy)  // block-uniform
-    rs = (MS != 0 && mrule) ? small_stats<DT, VEC, 1, true>(wq, wp, V, sp, mrule, sh)
-                            : small_stats<DT, VEC, 0, true>(wq, wp, V, sp, 0, sh);
+    rs = (MS != 0 && mrule) ? small_stats<DT, 1, true>(wq, wp, V, sp, mrule, sh)
+                            : small_stats<DT, 0, true>(wq, wp, V, sp, 0, sh);
   else
-    rs = (MS != 0 && mrule) ? small_stats<DT, VEC, 1, false>(wq, wp, V, sp, mrule, sh)
-                            : small_stats<DT, VEC, 0, false>(wq, wp, V, sp, 0, sh);
+    rs = (MS != 0 && mrule) ? small_stats<DT, 1, false>(wq, wp, V, sp, mrule, sh)
+                            : small_stats<DT, 0, false>(wq, wp, V, sp, 0, sh);
   // the logits the decision reads, from the thread holding them: the draft
   // token's, or (greedy TokenV2/V3, BiLD*) p's at the drafter's argmax
   int xi = x;
@@ -2761,8 +2851,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
 #pragma unroll
           for (int ee = 0; ee < T::VW; ++ee)
             if (ee == e) {
-              zq = elem<DT, VEC>(wq[ii], ee);
-              zp = elem<DT, VEC>(wp[ii], ee);
+              zq = elem<DT>(wq[ii], ee);
+              zp = elem<DT>(wp[ii], ee);
             }
         }
       sh.zx[0] = sp.greedy ? 0.0f : zq;
@@ -2778,12 +2868,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
     double acc = 0.0;
 #pragma unroll
     for (int i = 0; i < kSmallU; ++i) {
-      if (!small_live<DT, VEC>(i, V)) continue;  // wavefront-uniform
-      const bool ok = small_ok<DT, VEC>(i, V);
+      if (!small_live<DT>(i, V)) continue;  // wavefront-uniform
+      const bool ok = small_ok<DT>(i, V);
       float t = 0.0f;
 #pragma unroll
       for (int e = 0; e < T::VW; ++e) {
-        const float zq = small_elem<DT, VEC>(wq[i], e, ok), zp = small_elem<DT, VEC>(wp[i], e, ok);
+        const float zq = small_elem<DT>(wq[i], e, ok), zp = small_elem<DT>(wp[i], e, ok);
         if (eta) {
           t += token_r(ps.tok, zq, zp) ? prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo) : 0.0f;
         } else {
@@ -2817,11 +2907,11 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
   }
   double W0 = 0.0;
   if (kind0 != kNone)  // block-uniform
-    W0 = small_masses_kind<DT, VEC>(P, r, 0, kind0, wq, wp,
+    W0 = small_masses_kind<DT>(P, r, 0, kind0, wq, wp,
                                     prob_scale(sp, rs, kind0 == kTokRes || kind0 == kTokPi), sh);
   small_fence(wq, wp);
   if (kind1 != kNone)
-    (void)small_masses_kind<DT, VEC>(P, r, 1, kind1, wq, wp, prob_scale(sp, rs, false), sh);
+    (void)small_masses_kind<DT>(P, r, 1, kind1, wq, wp, prob_scale(sp, rs, false), sh);
   __syncthreads();  // the logits at the draft token are in shared memory
   // the decision (wave 0)
   if (threadIdx.x < 64) {
@@ -2865,10 +2955,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
     }
     return;
   }
-  small_draw_w<DT, VEC>(P, b, f, (recf >> 4) & 0xf, (recf >> 8) & 1, sp);
+  small_draw_w<DT>(P, b, f, (recf >> 4) & 0xf, (recf >> 8) & 1, sp);
 }
 
-template <int DT, bool VEC>
+template <int DT>
 hipError_t launch_small_t(const Params& P, hipStream_t st, hipEvent_t ev_begin,
                           hipEvent_t ev_end) {
   if (ev_begin) {
@@ -2879,7 +2969,7 @@ hipError_t launch_small_t(const Params& P, hipStream_t st, hipEvent_t ev_begin,
   // fit beside the row)
   if (P.mom_set != 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(P.B * (P.gamma + 1))), block(kSmallThreads);
-  hipLaunchKernelGGL((k_small<DT, VEC, 0>), grid, block, 0, st, P);
+  hipLaunchKernelGGL((k_small<DT, 0>), grid, block, 0, st, P);
   hipError_t err = hipGetLastError();
   if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, st);
   return err;
@@ -2892,9 +2982,9 @@ hipError_t launch_small_t(const Params& P, hipStream_t st, hipEvent_t ev_begin,
 // masses give the tile where u W falls, then the tile's sub-chunks and
 // lanes are scanned in vocabulary order.  A greedy row (temperature 0)
 // takes the lowest index attaining its max instead.
-template <int DT, bool VEC, bool ARGMAX, int TM>
+template <int DT, bool ARGMAX, int TM>
 __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
-  using T = DraftTile<DT, VEC, TM>;
+  using T = DraftTile<DT, TM>;
   __shared__ Shared sh;
   __shared__ RowStat srow;
   __shared__ PickState pks;
@@ -2904,13 +2994,14 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
   const char* row = (const char*)P.q + (int64_t)b * V * T::EB;
   const int64_t t0 = (int64_t)k * T::N;
   uint32_t w[T::U][T::NW];
-  load_tile<DT, VEC, T::U, true>(row, t0, V, w, threadIdx.x);
+  load_tile<DT, T::U, true>(row, t0, V, w, threadIdx.x, P.hdr);
+  mask_tile<DT, T::U>(row, t0, V, w, threadIdx.x);
   float g[T::U];
 #pragma unroll
   for (int i = 0; i < T::U; ++i) {
     float a = kNegInf;
 #pragma unroll
-    for (int e = 0; e < T::VW; ++e) a = fmaxf(a, elem<DT, VEC>(w[i], e));
+    for (int e = 0; e < T::VW; ++e) a = fmaxf(a, elem<DT>(w[i], e));
     g[i] = a;
   }
   float m = g[0];
@@ -2919,7 +3010,7 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
   int im = 0x7fffffff;
   const int base = (int)t0 + (int)threadIdx.x * T::VW;
   if constexpr (ARGMAX) {
-    im = first_max_index<DT, VEC, T::U, kThreads>(w, g, m, base);
+    im = first_max_index<DT, T::U, kThreads>(w, g, m, base);
     // unpack again for the sums rather than hold every entry with the words
 #pragma unroll
     for (int i = 0; i < T::U; ++i)
@@ -2933,7 +3024,7 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
     float t[T::VW];
 #pragma unroll
     for (int e = 0; e < T::VW; ++e) {
-      const float z = elem<DT, VEC>(w[i], e);
+      const float z = elem<DT>(w[i], e);
       t[e] = exp2_hw(fmaf(z, sp.c_lo, fmaf(z, sp.c_hi, -r)));
     }
 #pragma unroll
@@ -3020,55 +3111,41 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
   __syncthreads();
   const PickState pk = pks;
   if (pk.k < 0) return;  // block-uniform
-  pick_tile<DT, VEC, kQ, kWaves, T::N>(P, b, b, (int64_t)pk.k * T::N, pk.rem, prob_scale(sp, rs),
+  pick_tile<DT, kQ, kWaves, T::N>(P, b, b, (int64_t)pk.k * T::N, pk.rem, prob_scale(sp, rs),
                                        sh);
 }
 
-template <int DT, bool VEC, int TM>
+template <int DT, int TM>
 hipError_t launch_draft_t(const Params& P, bool argmax, hipStream_t st) {
   const dim3 grid(P.nt, P.B);
   if (argmax)
-    hipLaunchKernelGGL((k_draft<DT, VEC, true, TM>), grid, dim3(kThreads), 0, st, P);
+    hipLaunchKernelGGL((k_draft<DT, true, TM>), grid, dim3(kThreads), 0, st, P);
   else
-    hipLaunchKernelGGL((k_draft<DT, VEC, false, TM>), grid, dim3(kThreads), 0, st, P);
+    hipLaunchKernelGGL((k_draft<DT, false, TM>), grid, dim3(kThreads), 0, st, P);
   return hipGetLastError();
 }
 
 
 }  // namespace
 
-int stat_tile_elems(int dtype, bool vec) {
-  if (dtype == 1) return vec ? StatTile<1, true>::N : StatTile<1, false>::N;
-  return vec ? StatTile<0, true>::N : StatTile<0, false>::N;
+int stat_tile_elems(int dtype) {
+  return dtype == 1 ? StatTile<1>::N : StatTile<0>::N;
 }
 
-int tile_subchunks(int dtype, bool vec) {
-  if (dtype == 1) return kSlices * (vec ? StatTile<1, true>::U : StatTile<1, false>::U);
-  return kSlices * (vec ? StatTile<0, true>::U : StatTile<0, false>::U);
+int tile_subchunks(int dtype) {
+  return kSlices * (dtype == 1 ? StatTile<1>::U : StatTile<0>::U);
 }
 
-int draft_tile_elems(int dtype, bool vec, bool long_tiles) {
-  if (long_tiles) {
-    if (dtype == 1) return vec ? DraftTile<1, true, 2>::N : DraftTile<1, false, 2>::N;
-    return vec ? DraftTile<0, true, 2>::N : DraftTile<0, false, 2>::N;
-  }
-  if (dtype == 1) return vec ? DraftTile<1, true, 1>::N : DraftTile<1, false, 1>::N;
-  return vec ? DraftTile<0, true, 1>::N : DraftTile<0, false, 1>::N;
+int draft_tile_elems(int dtype, bool long_tiles) {
+  if (long_tiles) return dtype == 1 ? DraftTile<1, 2>::N : DraftTile<0, 2>::N;
+  return dtype == 1 ? DraftTile<1, 1>::N : DraftTile<0, 1>::N;
 }
 
-hipError_t launch_draft(const Params& P, int dtype, bool vec, bool argmax, bool long_tiles,
+hipError_t launch_draft(const Params& P, int dtype, bool argmax, bool long_tiles,
                         hipStream_t st) {
-  if (long_tiles) {
-    if (dtype == 1)
-      return vec ? launch_draft_t<1, true, 2>(P, argmax, st)
-                 : launch_draft_t<1, false, 2>(P, argmax, st);
-    return vec ? launch_draft_t<0, true, 2>(P, argmax, st)
-               : launch_draft_t<0, false, 2>(P, argmax, st);
-  }
-  if (dtype == 1)
-    return vec ? launch_draft_t<1, true, 1>(P, argmax, st)
-               : launch_draft_t<1, false, 1>(P, argmax, st);
-  return vec ? launch_draft_t<0, true, 1>(P, argmax, st) : launch_draft_t<0, false, 1>(P, argmax, st);
+  if (long_tiles)
+    return dtype == 1 ? launch_draft_t<1, 2>(P, argmax, st) : launch_draft_t<0, 2>(P, argmax, st);
+  return dtype == 1 ? launch_draft_t<1, 1>(P, argmax, st) : launch_draft_t<0, 1>(P, argmax, st);
 }
 
 namespace {
@@ -3087,32 +3164,22 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-int small_row_elems(int dtype, bool vec) {
-  if (dtype == 1) return vec ? SmallRow<1, true>::N : SmallRow<1, false>::N;
-  return vec ? SmallRow<0, true>::N : SmallRow<0, false>::N;
+int small_row_elems(int dtype) {
+  return dtype == 1 ? SmallRow<1>::N : SmallRow<0>::N;
 }
 
-hipError_t launch_small(const Params& P, int dtype, bool vec, hipEvent_t ev_begin,
+hipError_t launch_small(const Params& P, int dtype, hipEvent_t ev_begin,
                         hipEvent_t ev_end, hipStream_t st) {
-  if (dtype == 1)
-    return vec ? launch_small_t<1, true>(P, st, ev_begin, ev_end)
-               : launch_small_t<1, false>(P, st, ev_begin, ev_end);
-  return vec ? launch_small_t<0, true>(P, st, ev_begin, ev_end)
-             : launch_small_t<0, false>(P, st, ev_begin, ev_end);
+  return dtype == 1 ? launch_small_t<1>(P, st, ev_begin, ev_end)
+                    : launch_small_t<0>(P, st, ev_begin, ev_end);
 }
 
-hipError_t launch_step(const Params& P, int dtype, bool vec, bool draw_pass, bool tv_pass,
+hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass,
                        bool job_pass, int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end,
                        hipStream_t st) {
   if (dtype == 1)
-    return vec ? launch_step_t<1, true>(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin,
-                                        ev_end)
-               : launch_step_t<1, false>(P, st, draw_pass, tv_pass, job_pass, job_groups,
-                                         ev_begin, ev_end);
-  return vec ? launch_step_t<0, true>(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin,
-                                      ev_end)
-             : launch_step_t<0, false>(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin,
-                                       ev_end);
+    return launch_step_t<1>(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin, ev_end);
+  return launch_step_t<0>(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin, ev_end);
 }
 
 }  // namespace spc

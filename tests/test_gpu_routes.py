@@ -1,0 +1,53 @@
+"""The kernels' routes at the sizes where each can go wrong, against the fp64
+oracle (needs an MI355X)."""
+import pytest
+import torch
+
+import parity
+from paper_2405_19261_amd import spc
+from paper_2405_19261_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    yield
+    torch.cuda.synchronize()
+
+
+# Rows that start inside a 16-byte vector and end inside a lane load: fewer
+# entries than one vector, one entry either side of a vector, of a
+# wavefront's lane load and of a tile (8192 bfloat16 / 4096 float32), on the
+# statistics-tile path (more rows than the one-launch paths take).
+@pytest.mark.parametrize("dtype,V,B,rule", [
+    ("bf16", 2, 300, W.DIFF), ("bf16", 7, 300, W.OPT), ("bf16", 9, 300, W.TOKEN_V2),
+    ("bf16", 511, 300, W.LOSSY), ("bf16", 513, 300, W.OPT), ("bf16", 8191, 280, W.DIFF),
+    ("bf16", 8193, 280, W.TOKEN_V1), ("bf16", 40001, 5, W.OPT), ("bf16", 65543, 70, W.DIFF),
+    ("f32", 3, 300, W.DIFF), ("f32", 5, 300, W.OPT), ("f32", 4095, 280, W.BILD),
+    ("f32", 4097, 280, W.DIFFLOG), ("f32", 33333, 6, W.OPTLOG)])
+@pytest.mark.parametrize("greedy", [False, True])
+def test_rows_at_any_alignment(dtype, V, B, rule, greedy):
+    wl = W.WORKLOADS[3].with_(B=B, gamma=1, V=V, dtype=dtype, rule=rule, alpha=0.1,
+                              temperature=0.0 if greedy else 1.0)
+    parity.parity_workload(wl, 1, step0=31, report_name=f"anyalign.{dtype}.{V}")
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 20003), ("f32", 9999)])
+def test_rows_do_not_depend_on_their_alignment(dtype, V):
+    """The same row at every position of the batch, so at every alignment,
+    gives bitwise the same statistics."""
+    g = torch.Generator(device=DEV).manual_seed(3)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    B, g1 = 16, 3
+    row = torch.randn(2, V, generator=g, device=DEV).to(dt)
+    q, p = (row[i].expand(B, g1, V).contiguous() for i in range(2))
+    draft = torch.zeros(B, g1 - 1, dtype=torch.int32, device=DEV)
+    st = torch.empty(B, g1, 8, device=DEV)
+    u = torch.full((B, g1), 0.5, device=DEV)
+    _, tok, _ = spc.spc_verify_ex(q, p, draft, u, W.OPT, 0.1, 1.0, out_row_stats=st)
+    assert torch.equal(st, st[:1, :1].expand(B, g1, 8))
+    assert torch.equal(tok, tok[:1].expand(B))
