@@ -83,9 +83,9 @@ WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype) {
   L.rowline = o;
   o = align_up(o + 4 * (size_t)(kMaxRows * kLineWords), 256);
   L.zero_end = o;
-  // the job pass's list: at most 2 R argmax halves, R nt TV tiles handed
-  // back by their workgroups or R nt 4 eta slices (a row is one or the
-  // other), and B spare
+  // the job pass's list: at most R nt TV tiles handed back by their
+  // workgroups or R nt 4 TV or eta slices (a row has one kind), and 2 R + B
+  // spare
   L.jobs = o; o = align_up(o + 8 * (size_t)(2 * R + B + R * nt * kSlices), 256);
   L.tiles = o; o = align_up(o + sizeof(TilePart) * R * nt, 256);
   L.tvpart = o; o = align_up(o + sizeof(double) * R * nt * kSlices, 256);
@@ -97,7 +97,6 @@ WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype) {
   L.rowstat = o; o = align_up(o + sizeof(RowStat) * R, 256);
   L.rowdec = o; o = align_up(o + sizeof(int32_t) * R, 256);
   L.etalist = o; o = align_up(o + sizeof(int32_t) * R * nt, 256);
-  L.argres = o; o = align_up(o + sizeof(int32_t) * 4 * R, 256);
   L.etacnt = o; o = align_up(o + sizeof(int32_t) * R, 256);
   L.total = o;
   return L;
@@ -310,14 +309,9 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
                                            : 0);
   // Rows of OPT / OPTLOG at T > 0 are decided after their TV pass, rows of
   // a token rule after their eta pass (the job pass, for the tiles their
-  // statistics leave open), greedy rows after their argmax (the job pass);
-  // every other row by its last statistics tile.
+  // statistics leave open), every other row by its last statistics tile.
   constexpr uint32_t kTok = (1u << SPC_RULE_TOKEN_V1) | (1u << SPC_RULE_TOKEN_V2) |
                             (1u << SPC_RULE_TOKEN_V3);
-  const bool may_greedy = force_greedy || per_temp;
-  // Every sequence with a draw is drawn by the draw pass, the last kernel of
-  // a launch (greedy ones write their token directly).
-  const bool draw_pass = may_sample;
   const bool tv_rows = may_sample && (rules & kTv);
   // Small problems (rows that fit one workgroup's registers, at most two
   // rows per compute unit, no first moments) take the single-launch path.
@@ -367,21 +361,18 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     P.pair = (!P.tv_self && mom_set == 0 && R * nt >= 64 * (int64_t)cus) ? 1 : 0;
     P.tv_jobs = (tv_rows && !P.tv_self && per_rule) ? 1 : 0;
     const bool tv_pass = tv_rows && !P.tv_self && !P.tv_jobs;
-    // the job pass: argmax halves, eta slices, TV slices (tv_jobs), and the
-    // TV tiles whose wait for their row's merge timed out (tv_self)
-    const bool job_pass =
-        may_greedy || (may_sample && (rules & kTok)) || P.tv_self || P.tv_jobs;
+    // the job pass: eta slices, TV slices (tv_jobs), and the TV tiles whose wait for their row's merge timed out (tv_self)
+    const bool job_pass = (may_sample && (rules & kTok)) || P.tv_self || P.tv_jobs;
+    P.may_greedy = (force_greedy || per_temp) ? 1 : 0;
     P.wait_ticks = tv_wait_ticks();
-    // jobs: argmax halves, TV tiles whose wait timed out or TV slices, the
+    // jobs: TV tiles whose wait timed out or TV slices, the
     // slices of the tiles a token row lists for eta (a row has one kind)
     P.single_slots = 2 * R + bl + R * nt * spc::kSlices;
     P.nsub = (int32_t)(nt * spc::tile_subchunks(dtype));
     // workgroups of the job pass: a wavefront per item of its largest
-    // expected list (eta slices of every tile, argmax halves), at most two
-    // workgroups per compute unit
+    // expected list (eta or TV slices of every tile), at most two workgroups per compute unit
     const int64_t np = nt * spc::kSlices;
-    const int64_t items1 =
-        np * (((rules & kTok) || P.tv_jobs) ? R : 0) + (may_greedy ? 2 * R : 0);
+    const int64_t items1 = np * (((rules & kTok) || P.tv_jobs) ? R : 0);
     constexpr int64_t kW = spc::kJobThreads / 64;
     const int job_groups = (int)std::max<int64_t>(
         1, std::min<int64_t>((items1 + kW - 1) / kW, 2 * (int64_t)cus));
@@ -395,7 +386,6 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     P.rowstat = reinterpret_cast<spc::RowStat*>(ws + L.rowstat);
     P.rowdec = reinterpret_cast<int32_t*>(ws + L.rowdec);
     P.etalist = reinterpret_cast<int32_t*>(ws + L.etalist);
-    P.argres = reinterpret_cast<int32_t*>(ws + L.argres);
     P.etacnt = reinterpret_cast<int32_t*>(ws + L.etacnt);
     const bool first = b0 == 0;
     hipEvent_t ev0 = first && ex ? ex->ev_tiles_begin : nullptr;
@@ -405,8 +395,9 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
       P.nsub = spc::kSmallSub;
       e = spc::launch_small(P, dtype, ev0, ev1, stream);
     } else {
-      e = spc::launch_step(P, dtype, draw_pass, tv_pass, job_pass, job_groups, ev0, ev1,
-                           stream);
+      // sequences with a draw are drawn by the draw pass, the last kernel
+      // (greedy ones write their token directly)
+      e = spc::launch_step(P, dtype, may_sample, tv_pass, job_pass, job_groups, ev0, ev1, stream);
     }
     if (e != hipSuccess) return fail(SPC_E_HIP, "kernel launch: %s", hipGetErrorString(e));
   }

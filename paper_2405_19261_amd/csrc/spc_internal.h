@@ -24,8 +24,9 @@ struct TilePart {
   double s_q, s_p;
   float r_q, r_p;
   float zmax_q, zmax_p;   // largest raw logit of the tile
-  int32_t amax_q, amax_p; // statistics tiles: bit w set when slice w attains zmax;
-                          // drafter tiles: lowest row index attaining it, or -1
+  int32_t amax_q, amax_p; // statistics tiles of greedy rows: the first entry of the
+                          // first lane load attaining it; drafter tiles: the lowest
+                          // index attaining it; else -1
 };
 
 // First moments of one (row, stats tile) for the log-loss rules and BiLD*,
@@ -75,7 +76,8 @@ struct Params {
   int32_t tv_self;         // TV rows get their TV pass from their own tiles' registers
   int32_t pair;            // statistics workgroups take two tiles each (large batches)
   int32_t tv_jobs;         // TV rows' slices are job-pass items (else the TV pass kernel)
-  uint32_t wait_ticks;     // bound of a wait for a TV row's merge (100 MHz clock ticks)
+  int32_t may_greedy;      // some sequence may be at temperature 0
+  uint32_t wait_ticks;     // bound of a wait inside a kernel (100 MHz clock ticks)
   // workspace: zero region (counters; every launch leaves it as it found it)
   uint32_t* hdr;           // [kHdrLines][kLineWords] job counters
   uint32_t* rowline;       // [kMaxRows][kLineWords] per-row and per-sequence counters
@@ -89,8 +91,6 @@ struct Params {
   RowStat* rowstat;        // [R] merged row statistics
   int32_t* rowdec;         // [R] bit 0 a_j, bit 1 delta_j
   int32_t* etalist;        // [R][nt] tiles whose eta share needs a second look
-  int32_t* argres;         // [R][4] first tile of the q / p maximum (k * 16 + its slice
-                           // mask), then the lowest index of the maximum
   int32_t* etacnt;         // [R] tiles listed in etalist
 };
 
@@ -120,11 +120,11 @@ constexpr int kHdrLines = kHdrExit + kExitLeaves + 1;
 
 // Words of a row line (counters and flags, zero between calls): the row's
 // tile arrivals, the decided-row mask of the sequence with the same index (64
-// bits), the row's argmax-half arrivals, its "merged, TV pass open" flag and
-// TV slice arrivals, the draw pass's arrivals for the sequence, the drafter
-// kernel's per-row arrivals, and the sequence's outcome for the draw pass.
-constexpr int kRowArrive = 0, kSeqMask = 2, kRowJobDone = 4, kRowReady = 5, kRowTvArrive = 6,
-              kSeqResArrive = 7, kDraftArrive = 8, kSeqInfo = 9;
+// bits), the row's "merged, TV pass open" flag and TV slice arrivals, the
+// draw pass's arrivals for the sequence, the drafter kernel's per-row
+// arrivals, and the sequence's outcome for the draw pass.
+constexpr int kRowArrive = 0, kSeqMask = 2, kRowReady = 5, kRowTvArrive = 6, kSeqResArrive = 7,
+              kDraftArrive = 8, kSeqInfo = 9;
 // A sequence's outcome word (kSeqInfo): kSeqInfoSet | sample kind << 8 | j*.
 constexpr uint32_t kSeqInfoSet = 0x80000000u;
 
@@ -135,8 +135,7 @@ constexpr int kDraftCntStride = kLineWords;
 // region (header lines, row lines) has the same size for every shape.
 struct WsLayout {
   size_t hdr, rowline, zero_end;
-  size_t jobs, tiles, tvpart, submass, moms, rowstat, rowdec, etalist, argres, etacnt,
-      total;
+  size_t jobs, tiles, tvpart, submass, moms, rowstat, rowdec, etalist, etacnt, total;
 };
 WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype);
 
@@ -160,8 +159,7 @@ hipError_t launch_small(const Params& P, int dtype, hipEvent_t ev_begin,
 // `tv_pass`, the job pass (k_jobs, of `job_groups` workgroups) when
 // `job_pass`, and last the draw pass (k_res) when `draw_pass`.
 // ev_begin / ev_end (may be null): recorded right before and after k_tiles.
-hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass,
-                       bool job_pass, int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end,
+hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass, bool job_pass, int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end,
                        hipStream_t stream);
 
 // Enqueue a kernel writing `bytes` zero bytes at `ptr` (a multiple of 4, ptr

@@ -1,8 +1,8 @@
 // spc_kernels.hip -- gfx950 kernels of the speculative-cascade verify step.
 //
 // The step (GenSpecSample, Alg. 4, with the cascade target T_delta of eq. (6)
-// and the deferral rules of Table 1) runs as a statistics launch and one or
-// two job launches; no workgroup ever waits for another.  A row is one
+// and the deferral rules of Table 1) runs as a statistics launch, the second
+// passes some rules need, and a draw launch.  A row is one
 // position (b, j) of the logit pair (q, p); rows are cut into statistics
 // tiles of consecutive vocabulary entries.
 //
@@ -10,30 +10,27 @@
 //                {max z, sum 2^(z c - r)} (c = log2(e) / T); its first
 //                wavefront then arrives on the row's counter, and the last
 //                tile of the row merges the row.  Then, per row:
-//                  OPT / OPTLOG at T > 0   publishes a TV job (D_TV of Lemma 3
-//                                          needs both normalisers: one chunk
-//                                          per tile, the row read again);
+//                  OPT / OPTLOG at T > 0   needs its TV pass (D_TV of Lemma 3
+//                                          needs both normalisers), unless
+//                                          the decision is the same for every
+//                                          D_TV it can have;
 //                  token rules at T > 0    settles eta (Alg. 6) for the tiles
 //                                          wholly below the rule's threshold
 //                                          from their statistics and
-//                                          publishes a job for the others;
-//                  T = 0                   publishes the two halves of its
-//                                          argmax (the lowest index of a row
-//                                          maximum lies in the first tile
-//                                          whose maximum it is);
+//                                          publishes a job per slice of the
+//                                          others;
+//                  T = 0                   takes its argmax from the lane
+//                                          loads its tiles name;
 //                  otherwise               decides the row at once.
 //   row decision delta_j and a_j of the row, then an atomic OR of the row into
 //                its sequence's decided-row mask.  The decision that completes
 //                the prefix 0..j* of decided rows containing the first
-//                rejection j* finishes the sequence: the greedy token, or a
-//                draw published to the next job pass (from the statistics
-//                partials, for an extra token from q, p or a token rule's
-//                target; else a residual job over row j*).
-//   k_jobs       a static walk over the jobs the launches before it
-//                published: every chunk of every row job, then the single
-//                jobs.  The last chunk of a job continues it (the row's
-//                decision, which may publish to the next pass, or the
-//                residual draw).
+//                rejection j* finishes the sequence: the greedy token, or the
+//                outcome the draw pass reads.
+//   k_tvpass     the TV passes, when most rows may need one.
+//   k_jobs       a static walk over the jobs the statistics launch published.
+//                The last slice of a row's job decides the row.
+//   k_res        the draws, the step's last launch.
 //
 // Draws are inverse CDF in vocabulary order.  Merges and sums run in fixed
 // orders, so results do not depend on scheduling.  Counters sit in a zeroed
@@ -788,15 +785,15 @@ __device__ __forceinline__ double log_stat(int rule, double lq2, double lp2, dou
 // rule's statistic from the tiles' first moments: against the row references,
 //   H(q) = ln 2 (log2 S_q - H_q / S_q),  H(p) = ln 2 (log2 S_p - H_p / S_p),
 //   D(q, p) = -sum q log p = ln 2 (log2 S_p - X / S_q),
-// each a sum of two non-negative terms.  kq / kp: the first tile whose
-// largest logit is the row's (it holds the lowest index of the row maximum),
-// as k * 16 + the mask of the tile's slices that attain it.
+// each a sum of two non-negative terms.  arg: a greedy row, whose tiles hold
+// the start of the first lane load that attains their maximum; the row's are
+// the lowest among the tiles that attain the row maximum.
 // tv_low (rows of at most 64 tiles, else 0): half the L1 distance between
 // the tile masses of p and q, a lower bound on D_TV (merging entries into
 // tiles can only shrink the distance).
 // Every lane returns the same RowStat.
-__device__ __forceinline__ RowStat merge_row(const Params& P, int r, int mrule, int* kq_out,
-                                             int* kp_out, bool want_low, double& tv_low) {
+__device__ __forceinline__ RowStat merge_row(const Params& P, int r, int mrule, bool arg,
+                                             bool want_low, double& tv_low) {
   const int lane = threadIdx.x & 63;
   const int nt = P.nt;
   const TilePart* tp = P.tiles + (int64_t)r * nt;
@@ -820,24 +817,24 @@ __device__ __forceinline__ RowStat merge_row(const Params& P, int r, int mrule, 
   rq = wave_max(rq);
   rp = wave_max(rp);
   double sq = 0.0, sp = 0.0, mhq = 0.0, mhp = 0.0, mx = 0.0;
-  int kq = 0x7fffffff, kp = 0x7fffffff;
-  auto add = [&](const TilePart& tk, const TileMom& mk, int k) {
+  int aq = 0x7fffffff, ap = 0x7fffffff;
+  auto add = [&](const TilePart& tk, const TileMom& mk) {
     // r_k - r is exact in fp64; an all -inf tile has s = 0
     const double gq = (double)tk.r_q - (double)rq, gp = (double)tk.r_p - (double)rp;
     const double fq = exp2_acc(gq), fp = exp2_acc(gp);
     sq += tk.s_q * fq;
     sp += tk.s_p * fp;
-    if (tk.zmax_q == zq) kq = min(kq, k);
-    if (tk.zmax_p == zp) kp = min(kp, k);
+    if (arg && tk.zmax_q == zq) aq = min(aq, tk.amax_q);
+    if (arg && tk.zmax_p == zp) ap = min(ap, tk.amax_p);
     if (mrule) {
       mom_add(mhq, mk.hq, tk.s_q, fq, gq);
       mom_add(mhp, mk.hp, tk.s_p, fp, gp);
       mom_add(mx, mk.x, tk.s_q, fq, gp);
     }
   };
-  if (lane < nt) add(t0, m0, lane);
+  if (lane < nt) add(t0, m0);
   for (int k = lane + 64; k < nt; k += 64)
-    add(ld_tile(tp + k), mrule ? ld_mom(mp + k) : TileMom{0.0, 0.0, 0.0}, k);
+    add(ld_tile(tp + k), mrule ? ld_mom(mp + k) : TileMom{0.0, 0.0, 0.0});
   sq = wave_sum(sq);
   sp = wave_sum(sp);
   tv_low = 0.0;
@@ -849,17 +846,6 @@ __device__ __forceinline__ RowStat merge_row(const Params& P, int r, int mrule, 
                t0.s_q * exp2_acc((double)t0.r_q - (double)rq) / sq);
     tv_low = 0.5 * wave_sum(d);
   }
-  kq = wave_min(kq);
-  kp = wave_min(kp);
-  // with the slice masks of those tiles (statistics tiles record them)
-  const auto mask_of = [&](int k, bool pq) {
-    if (k >= nt) return 15;
-    if (k < 64) return lane_i32(pq ? t0.amax_p : t0.amax_q, k) & 15;
-    const TilePart tk = ld_tile(tp + k);
-    return (pq ? tk.amax_p : tk.amax_q) & 15;
-  };
-  *kq_out = kq < nt ? kq * 16 + mask_of(kq, false) : kq;
-  *kp_out = kp < nt ? kp * 16 + mask_of(kp, true) : kp;
   RowStat rs;
   const double lq2 = log2_acc(sq), lp2 = log2_acc(sp);
   rs.lz_q = (double)rq + lq2;
@@ -874,8 +860,8 @@ __device__ __forceinline__ RowStat merge_row(const Params& P, int r, int mrule, 
   }
   rs.zmax_q = zq;
   rs.zmax_p = zp;
-  rs.amax_q = -1;
-  rs.amax_p = -1;
+  rs.amax_q = arg ? wave_min(aq) : -1;
+  rs.amax_p = arg ? wave_min(ap) : -1;
   return rs;
 }
 
@@ -1294,7 +1280,7 @@ __device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT>::U][
 // The partial of statistics tile k of row r from its loaded entries (wq, wp),
 // written by thread 0 through agent-scope stores, for readers in the same
 // launch.
-template <int DT, int MOM>
+template <int DT, int MOM, bool GR>
 __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, const SeqParam& sp,
                                              const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
                                              const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW],
@@ -1318,6 +1304,18 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
   for (int i = 1; i < T::U; ++i) {
     mq = fmaxf(mq, gq[i]);
     mp = fmaxf(mp, gp[i]);
+  }
+  const bool arg = GR && sp.greedy;  // block-uniform
+  int iq = 0, ip = 0;
+  if (arg) {
+    // a greedy row: the thread's first lane load that attains its maximum
+#pragma unroll
+    for (int i = T::U - 1; i >= 0; --i) {
+      if (gq[i] == mq) iq = i * kThreads;
+      if (gp[i] == mp) ip = i * kThreads;
+    }
+    iq += (int)threadIdx.x;
+    ip += (int)threadIdx.x;
   }
   const float rq = (mq == kNegInf) ? 0.0f : mq * sp.c_hi;
   const float rp = (mp == kNegInf) ? 0.0f : mp * sp.c_hi;
@@ -1345,11 +1343,19 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
     mhp = wave_sum(mp == kNegInf ? 0.0 : mom_move(hp, spp, fp, ep));
     mx = wave_sum(mq == kNegInf ? 0.0 : mom_move(xq, sq, fq, ep));
   }
+  if (arg) {
+    iq = wave_min(mq == Wq ? iq : 0x7fffffff);
+    ip = wave_min(mp == Wp ? ip : 0x7fffffff);
+  }
   if (lane == 0) {
     sh.m[wv][0] = Wq;
     sh.m[wv][1] = Wp;
     sh.d[wv][0] = dq;
     sh.d[wv][1] = dp;
+    if (arg) {
+      sh.i[wv][0] = iq;
+      sh.i[wv][1] = ip;
+    }
     if constexpr (mom) {
       sh.h[wv][0] = mhq;
       sh.h[wv][1] = mhp;
@@ -1381,15 +1387,18 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
     t.r_p = (Mp == kNegInf) ? kNegInf : Rp;
     t.zmax_q = Mq;
     t.zmax_p = Mp;
-    // the slices (waves) whose entries attain the tile maximum
-    int mq = 0, mp = 0;
+    t.amax_q = -1;
+    t.amax_p = -1;
+    if (arg) {
+      int aq = 0x7fffffff, ap = 0x7fffffff;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      mq |= (sh.m[w][0] == Mq) ? 1 << w : 0;
-      mp |= (sh.m[w][1] == Mp) ? 1 << w : 0;
+      for (int w = 0; w < kWaves; ++w) {
+        if (sh.m[w][0] == Mq) aq = min(aq, sh.i[w][0]);
+        if (sh.m[w][1] == Mp) ap = min(ap, sh.i[w][1]);
+      }
+      t.amax_q = k * T::N + aq * T::VW;
+      t.amax_p = k * T::N + ap * T::VW;
     }
-    t.amax_q = mq;
-    t.amax_p = mp;
     st_tile(P.tiles + (int64_t)r * P.nt + k, t);
     if constexpr (mom) {
       // the waves' moments against the tile references, in wave order
@@ -1530,7 +1539,7 @@ __device__ __forceinline__ double slice_masses_w(const Params& P, int64_t row, i
   using T = StatTile<DT>;
   const int lane = threadIdx.x & 63, V = P.V;
   uint32_t cq[T::U][T::NW] = {}, cp[T::U][T::NW] = {};
-  load_tiles<DT, T::U, true, kThreads, KIND != kP, KIND != kQ>(
+  load_tiles<DT, T::U, false, kThreads, KIND != kP, KIND != kQ>(
       (const char*)P.q + row * V * T::EB, (const char*)P.p + row * V * T::EB, t0, V, cq, cp,
       w * 64 + lane, P.hdr);
   return slice_masses_of<DT, KIND>(cq, cp, ps, kind);
@@ -1595,7 +1604,7 @@ __device__ __forceinline__ void tv_slice_regs_w(
 // eta second pass over a row and the residual masses of row j* of a sequence
 // are "row jobs" of nt chunks (one per tile); the two halves of a greedy
 // row's argmax and the draws from statistics partials are single chunks.
-enum JobKind : int { kJobTv = 1, kJobEta = 2, kJobArg = 4, kJobTvTile = 6, kJobTvSlice = 7 };
+enum JobKind : int { kJobTv = 1, kJobEta = 2, kJobTvTile = 6, kJobTvSlice = 7 };
 
 // A job entry: kind (bits 60..63), an extra field (bits 32..59: the argmax
 // tensor, or a draw's sample kind and j*) and the row or sequence it belongs
@@ -1663,8 +1672,7 @@ struct StepShared {
 // Wave: sequence b's first rejection is j* = f.  Writes its accept length,
 // then the greedy token; or, for a draw (from the statistics partials, or
 // from the residual of row f), records it in the sequence's outcome word for
-// the draw pass (k_res) that follows the launch finishing the sequence: the
-// statistics kernel's, or the job pass's.
+// the draw pass (k_res), the step's last kernel.
 template <int DT>
 __device__ __forceinline__ void seq_finish_w(const Params& P, int b, int f, const SeqParam& sp,
                                              int rec) {
@@ -1831,33 +1839,41 @@ __device__ __forceinline__ int row_decide_w(const Params& P, int r, int b, int j
   return f >= p_old ? f : -1;
 }
 
+// Wave: the lowest indices of greedy row r's two maxima, from the starts of
+// the lane loads that hold them (rs.amax_q / amax_p), read again entry by
+// entry: lanes 0 .. 31 q's, lanes 32 .. 63 p's, one round trip.
+// (The argmax was a pass of its own over the rows: 11 us of a 123 us step for
+// 640 rows of V = 256 000 bfloat16, nearly all of it launch and latency.)
+template <int DT>
+__device__ __forceinline__ void arg_rows_w(const Params& P, int r, RowStat& rs) {
+  using T = StatTile<DT>;
+  const int lane = threadIdx.x & 63, V = P.V;
+  const bool p = lane >= 32;
+  const int e = (p ? rs.amax_p : rs.amax_q) + (lane & 31);
+  const bool in = (lane & 31) < T::VW && (uint32_t)e < (uint32_t)V;
+  const float z = load_logit<DT>(p ? P.p : P.q, r, V, in ? e : 0);
+  const uint64_t hit = __ballot(in && z == (p ? rs.zmax_p : rs.zmax_q));
+  // (no hit: a row of NaN; its first lane load stands)
+  if ((uint32_t)hit) rs.amax_q += __builtin_ctz((uint32_t)hit);
+  if (hit >> 32) rs.amax_p += __builtin_ctz((uint32_t)(hit >> 32));
+}
+
 // Wave, after the last tile of row r = (b, j) arrived: merge the row, then
 // publish its second pass (TV, or eta for the tiles its statistics leave
 // open) or its argmax to the job pass, or decide it and, when that settles
 // j*, finish the sequence.
-template <int DT, int MS>
+template <int DT, int MS, bool GR>
 __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int j,
                                              const SeqParam& sp, int x) {
   const int lane = threadIdx.x & 63;
   const int nt = P.nt;
   // the decision's draft inputs, requested together with the tile partials
   const DraftIn in = draft_in<DT>(P, r, x, sp);
-  int kq, kp;
   double tv_low;
-  RowStat rs = merge_row(P, r, (MS != 0 && needs_mom(sp)) ? sp.rule : 0, &kq, &kp,
+  RowStat rs = merge_row(P, r, (MS != 0 && needs_mom(sp)) ? sp.rule : 0, GR && sp.greedy,
                          sp.valid && !sp.greedy && has_tv_parts(sp.rule) && !P.out_stats, tv_low);
-  if (sp.valid && sp.greedy) {
-    // the lowest index of each row maximum, from the first tile holding it
-    if (lane == 0) {
-      st_rowstat(P.rowstat + r, rs);
-      st_i32(P.argres + (int64_t)r * 4 + 0, kq);
-      st_i32(P.argres + (int64_t)r * 4 + 1, kp);
-      publish_single(P, kJobArg, 0u, (uint32_t)r);
-      publish_single(P, kJobArg, 1u, (uint32_t)r);
-    }
-    return;
-  }
-  if (sp.valid && has_tv_parts(sp.rule)) {
+  if (GR && sp.valid && sp.greedy) arg_rows_w<DT>(P, r, rs);
+  if (sp.valid && !sp.greedy && has_tv_parts(sp.rule)) {
     // Without row statistics to report, a row whose decision D_TV cannot
     // change is decided now and takes no TV pass: its ready flag says 2 to
     // its own waiting workgroups (tv_self) and stays 0 for the TV pass
@@ -1880,7 +1896,7 @@ __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int 
     if (!free) return;
     rs.tv = 1.0;  // any D_TV in [lo, 1] decides it alike
   }
-  if (sp.valid && is_token(sp.rule)) {
+  if (sp.valid && !sp.greedy && is_token(sp.rule)) {
     // eta's share of every tile wholly below the rule's threshold comes from
     // its statistics; the other tiles are listed for a second look (the job's
     // chunks past the list do nothing).  With none listed, eta is summed
@@ -1927,20 +1943,15 @@ __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int 
 // Wave: the row's decision once its TV, eta or argmax is known; when it
 // settles j*, the sequence's finish publishes to the next job pass.
 template <int DT>
-__device__ __forceinline__ void row_job_decide(const Params& P, int kind, int r) {
+__device__ __forceinline__ void row_job_decide(const Params& P, int r) {
   const int g1 = P.gamma + 1, np = P.nt * kSlices;
   const int b = r / g1, j = r - b * g1;
   RowStat rs = ld_rowstat(P.rowstat + r);
-  if (kind == kJobArg) {
-    rs.amax_q = ld_i32(P.argres + (int64_t)r * 4 + 2);
-    rs.amax_p = ld_i32(P.argres + (int64_t)r * 4 + 3);
-  } else {
-    // the TV or eta partials of every slice, in slice order
-    double s = 0.0;
-    for (int k = threadIdx.x & 63; k < np; k += 64)
-      s += ld_dev_f64(P.tvpart + (int64_t)r * np + k);
-    rs.tv = wave_sum(s);
-  }
+  // the TV or eta partials of every slice, in slice order
+  double s = 0.0;
+  for (int k = threadIdx.x & 63; k < np; k += 64)
+    s += ld_dev_f64(P.tvpart + (int64_t)r * np + k);
+  rs.tv = wave_sum(s);
   const SeqParam sp = seq_param(P, b);
   int rec = 0;
   const int f = row_decide_w<DT>(P, r, b, j, sp, rs, nullptr, &rec);
@@ -1956,7 +1967,7 @@ __device__ __forceinline__ void row_job_decide(const Params& P, int kind, int r)
 // flag is cleared for the next call.
 template <int DT>
 __device__ __forceinline__ void tv_row_done(const Params& P, int rv) {
-  row_job_decide<DT>(P, kJobTv, rv);
+  row_job_decide<DT>(P, rv);
   if ((threadIdx.x & 63) == 0) st_u32(row_word(P, rv, kRowReady), 0u);
 }
 
@@ -2013,6 +2024,115 @@ __device__ __forceinline__ void tv_self(
     tv_row_done<DT>(P, r);
 }
 
+// ---------------------------------------------------------------- draws
+// Wave: slice w of tile k of row f (= j*) of sequence b: the residual masses
+// (KIND) of its sub-chunks, stored at their place in the row's sub-chunk
+// order, which the draw searches directly.
+template <int DT, int KIND>
+__device__ __forceinline__ void res_slice_w(const Params& P, int b, int k, int w, int f,
+                                            const SeqParam& sp) {
+  using T = StatTile<DT>;
+  const int lane = threadIdx.x & 63, V = P.V;
+  const int64_t row = (int64_t)b * (P.gamma + 1) + f;
+  const int64_t t0 = (int64_t)k * T::N;
+  // the row's statistics and the slice's entries in one round trip, as in
+  // pass2_slice_w
+  const uint64_t* rw = reinterpret_cast<const uint64_t*>(P.rowstat + row);
+  RowStat rs{};
+  rs.lz_q = __longlong_as_double((long long)ld_u64(rw));
+  rs.lz_p = __longlong_as_double((long long)ld_u64(rw + 1));
+  if constexpr (KIND == kTokRes) {
+    rs.tv = __longlong_as_double((long long)ld_u64(rw + 2));
+    const uint64_t m = ld_u64(rw + 4);
+    __builtin_memcpy(&rs.zmax_q, &m, sizeof m);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const char* qrow = (const char*)P.q + row * V * T::EB;
+  const char* prow = (const char*)P.p + row * V * T::EB;
+  uint32_t cq[T::U][T::NW], cp[T::U][T::NW];
+  load_tile<DT, T::U, true>(qrow, t0, V, cq, w * 64 + lane, P.hdr);
+  load_tile<DT, T::U, true>(prow, t0, V, cp, w * 64 + lane, P.hdr);
+  __builtin_amdgcn_sched_barrier(0);
+  const ProbScale ps = prob_scale(sp, rs, KIND == kTokRes);
+  mask_tile<DT, T::U>(qrow, t0, V, cq, w * 64 + lane);
+  mask_tile<DT, T::U>(prow, t0, V, cp, w * 64 + lane);
+  const double ml = slice_masses_of<DT, KIND>(cq, cp, ps, -1);
+  if (lane < T::U)
+    st_dev_f64(P.submass + (int64_t)b * P.nsub + (int64_t)k * (T::U * kSlices) +
+                   lane * kSlices + w, ml);
+}
+
+// Wave: the draw inside the NSUB sub-chunks starting at entry e0 whose
+// masses lane i < NSUB holds: the first sub-chunk where the running mass
+// exceeds rem (rounding that leaves rem unreached takes the last sub-chunk
+// with mass), then the entry inside it.
+template <int DT, int KIND>
+__device__ __forceinline__ void draw_in_subs_w(const Params& P, int b, int64_t row, int64_t e0,
+                                               double ml, int nsub, double rem,
+                                               const ProbScale& ps, int kind = -1) {
+  const int lane = threadIdx.x & 63;
+  ml = lane < nsub ? ml : 0.0;
+  const double incl = wave_incl_scan(ml);
+  const unsigned long long hit = __ballot(ml > 0.0 && incl > rem);
+  const unsigned long long pos = __ballot(ml > 0.0);
+  int c;
+  double r;
+  if (hit) {
+    c = __ffsll(hit) - 1;
+    r = rem - (lane_f64(incl, c) - lane_f64(ml, c));
+  } else {
+    c = pos ? 63 - __clzll(pos) : 0;
+    r = __builtin_huge_val();
+  }
+  pick_wave<DT, SubC<DT>, KIND>(P, b, row, e0 + (int64_t)c * SubC<DT>::N, r, ps,
+                                          kind);
+}
+
+// Sub-chunks of a statistics tile.
+constexpr int kDrawSubs = 16;
+static_assert(StatTile<0>::U * kSlices == kDrawSubs && StatTile<1>::U * kSlices == kDrawSubs,
+              "sub-chunks of a tile");
+
+// Whole block: the draw of sequence b inside statistics tile ks of row `row`,
+// rem the target mass left at its start: wavefront w sums the masses of slice
+// w's sub-chunks, wavefront 0 searches them.  dv: kDrawSubs doubles of LDS.
+template <int DT, int KIND>
+__device__ __forceinline__ void draw_tile(const Params& P, int b, int64_t row, int ks, double rem,
+                                          const ProbScale& ps, double* dv) {
+  using T = StatTile<DT>;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t t0 = (int64_t)ks * T::N;
+  const double ml = slice_masses_w<DT, KIND>(P, row, t0, w, ps);
+  if (lane < T::U) dv[lane * kSlices + w] = ml;
+  __syncthreads();
+  if (w != 0) return;
+  draw_in_subs_w<DT, KIND>(P, b, row, t0, lane < kDrawSubs ? dv[lane] : 0.0, kDrawSubs, rem, ps);
+}
+
+// Whole block: the draw of sequence b at row `row` from q, p or a token
+// rule's target, found by the tile masses of the statistics partials (every
+// wavefront makes the same search).
+template <int DT>
+__device__ __forceinline__ void draw_stats(const Params& P, int b, int64_t row, int kind,
+                                           const SeqParam& sp, double* dv) {
+  const RowStat rs = ld_rowstat(P.rowstat + row);
+  const float u = P.uniforms[(int64_t)b * (P.gamma + 1) + P.gamma];
+  int ks;
+  double rem, W;
+  if (kind == kQ) W = find_part<kSrcStatsQ>(P, row, b, P.nt, rs, u, &ks, &rem);
+  else if (kind == kP) W = find_part<kSrcStatsP>(P, row, b, P.nt, rs, u, &ks, &rem);
+  else W = find_part<kSrcTokPi>(P, row, b, P.nt, rs, u, &ks, &rem);
+  if (threadIdx.x == 0) {
+    if (P.out_norm) P.out_norm[b] = (float)W;
+    if (ks < 0) P.out_token[b] = -1;
+  }
+  if (ks < 0) return;  // block-uniform
+  const ProbScale ps = prob_scale(sp, rs, kind == kTokPi);
+  if (kind == kQ) draw_tile<DT, kQ>(P, b, row, ks, rem, ps, dv);
+  else if (kind == kP) draw_tile<DT, kP>(P, b, row, ks, rem, ps, dv);
+  else draw_tile<DT, kTokPi>(P, b, row, ks, rem, ps, dv);
+}
+
 // How the statistics tiles serve the TV pass (OPT / OPTLOG rows at T > 0):
 // not at all (the TV pass kernel takes it, or there is no TV row), or, in a
 // grid resident at once, on their own row from registers (tv_self).
@@ -2025,10 +2145,11 @@ enum TvMode : int { kTvNone = 0, kTvSelf = 2 };
 // row's counter, and the last tile of the row merges and decides it (a TV
 // row: marks it merged).  With kTvSelf the block then takes its share of its
 // own row's TV pass; otherwise waves 1-3 leave after the partials.
+// GR: some row may be at temperature 0 (its tiles track their argmax).
 // With first moments the block is held to 96 VGPRs (five workgroups per
 // SIMD); the two-tile form keeps its registers (capped, it spills in the
 // streaming loop).
-template <int DT, int MS, int TVM, bool PAIR = false>
+template <int DT, int MS, int TVM, bool PAIR = false, bool GR = true>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
   static_assert(!PAIR || TVM == kTvNone, "a pair of tiles takes no TV pass");
@@ -2056,17 +2177,17 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
   mask_tile<DT, T::U>(qrow, t0, V, wq, threadIdx.x);
   mask_tile<DT, T::U>(prow, t0, V, wp, threadIdx.x);
   if (MS != 0 && needs_mom(sp))
-    tile_partial<DT, MS>(P, r, k, sp, wq, wp, sh);
+    tile_partial<DT, MS, GR>(P, r, k, sp, wq, wp, sh);
   else
-    tile_partial<DT, 0>(P, r, k, sp, wq, wp, sh);
+    tile_partial<DT, 0, GR>(P, r, k, sp, wq, wp, sh);
   if constexpr (PAIR) {
     if (two) {
       mask_tile<DT, T::U>(qrow, t0 + T::N, V, vq, threadIdx.x);
       mask_tile<DT, T::U>(prow, t0 + T::N, V, vp, threadIdx.x);
       if (MS != 0 && needs_mom(sp))
-        tile_partial<DT, MS>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
+        tile_partial<DT, MS, GR>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
       else
-        tile_partial<DT, 0>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
+        tile_partial<DT, 0, GR>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
     }
   }
   const uint32_t n = two ? 2u : 1u;  // tiles this block adds to its row
@@ -2080,7 +2201,7 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
     }
     if ((uint32_t)lane_i32((int)prev, 0) + n == (uint32_t)nt) {
       vmem_drain();
-      row_merged_w<DT, MS>(P, r, b, j, sp, x);
+      row_merged_w<DT, MS, GR>(P, r, b, j, sp, x);
     }
   }
   if constexpr (TVM == kTvSelf) {
@@ -2111,113 +2232,6 @@ __global__ __launch_bounds__(kThreads) void k_tvpass(Params P) {
 }
 
 // ---------------------------------------------------------------- job pass
-// Wave: the masses of the NS sub-chunks of the part at entry e0 of a row
-// under the distribution KIND; lane base + i returns sub-chunk i's (float
-// sums per lane load, fp64 across lanes), other lanes 0.
-template <int DT, int KIND>
-__device__ __forceinline__ double part_masses_w(const Params& P, int64_t row, int64_t e0,
-                                                const ProbScale& ps, int base = 0, int kind = -1) {
-  using C = PartC<DT>;
-  constexpr int EB = StatTile<DT>::EB;
-  const int lane = threadIdx.x & 63, V = P.V;
-  ChunkRegs<C> cq = {}, cp = {};
-  load_chunks<DT, C, KIND>((const char*)P.q + row * V * EB, (const char*)P.p + row * V * EB, e0, V,
-                           cq, cp, P.hdr);
-  double mine = 0.0;
-#pragma unroll
-  for (int i = 0; i < C::U; ++i) {
-    float t = 0.0f;
-#pragma unroll
-    for (int e = 0; e < C::VW; ++e) {
-      t += weight_k<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps, kind);
-      if (e & 1) __builtin_amdgcn_sched_barrier(0);
-    }
-    const double s = wave_sum((double)t);
-    if (lane == base + i) mine = s;
-    __builtin_amdgcn_sched_barrier(0);  // one lane load's weights at a time
-  }
-  return mine;
-}
-
-// Wave: the draw inside the NSUB sub-chunks starting at entry e0 whose
-// masses lane i < NSUB holds: the first sub-chunk where the running mass
-// exceeds rem (rounding that leaves rem unreached takes the last sub-chunk
-// with mass), then the entry inside it.
-template <int DT, int KIND>
-__device__ __forceinline__ void draw_in_subs_w(const Params& P, int b, int64_t row, int64_t e0,
-                                               double ml, int nsub, double rem,
-                                               const ProbScale& ps, int kind = -1) {
-  const int lane = threadIdx.x & 63;
-  ml = lane < nsub ? ml : 0.0;
-  const double incl = wave_incl_scan(ml);
-  const unsigned long long hit = __ballot(ml > 0.0 && incl > rem);
-  const unsigned long long pos = __ballot(ml > 0.0);
-  int c;
-  double r;
-  if (hit) {
-    c = __ffsll(hit) - 1;
-    r = rem - (lane_f64(incl, c) - lane_f64(ml, c));
-  } else {
-    c = pos ? 63 - __clzll(pos) : 0;
-    r = __builtin_huge_val();
-  }
-  pick_wave<DT, SubC<DT>, KIND>(P, b, row, e0 + (int64_t)c * SubC<DT>::N, r, ps,
-                                          kind);
-}
-
-// Wave: the inverse-CDF draw of sequence b at row `row` (the row of j*) from
-// the distribution `kind`, its part masses from `src`: the statistics
-// partials per tile (then the tile's sub-chunk masses are summed here), or
-// the residual job's sub-chunk masses, searched directly.  An empty residual
-// (possible only through rounding) is replaced by p.
-template <int DT, int KIND>
-__device__ __forceinline__ void draw_kind_w(const Params& P, int b, int64_t row, int ks,
-                                            double rem, const ProbScale& ps) {
-  if constexpr (KIND == kResidual || KIND == kTokRes) {
-    // the residual job's sub-chunk masses were searched: ks is a sub-chunk
-    pick_wave<DT, SubC<DT>, KIND>(P, b, row, (int64_t)ks * SubC<DT>::N, rem, ps);
-  } else {
-    // a statistics tile: the masses of its sub-chunks (its two
-    // wave-contiguous halves, in order), then the sub-chunk's entry
-    const int64_t t0 = (int64_t)ks * StatTile<DT>::N;
-    constexpr int NS = PartC<DT>::U;
-    double m = 0.0;
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half)
-      m += part_masses_w<DT, KIND>(P, row, t0 + half * PartC<DT>::N, ps, half * NS);
-    draw_in_subs_w<DT, KIND>(P, b, row, t0, m, 2 * NS, rem, ps);
-  }
-}
-
-template <int DT>
-__device__ __forceinline__ void draw_w(const Params& P, int b, int64_t row, int kind, int src,
-                                       const SeqParam& sp, const RowStat& rs) {
-  const int lane = threadIdx.x & 63;
-  const float u = P.uniforms[(int64_t)b * (P.gamma + 1) + P.gamma];
-  int ks;
-  double rem, W;
-  if (src == kSrcStatsQ) W = find_part<kSrcStatsQ>(P, row, b, P.nt, rs, u, &ks, &rem);
-  else if (src == kSrcStatsP) W = find_part<kSrcStatsP>(P, row, b, P.nt, rs, u, &ks, &rem);
-  else if (src == kSrcTokPi) W = find_part<kSrcTokPi>(P, row, b, P.nt, rs, u, &ks, &rem);
-  else W = find_part<kSrcPass, 8>(P, row, b, P.nsub, rs, u, &ks, &rem);
-  if ((kind == kResidual || kind == kTokRes) && !(W > 0.0)) {
-    kind = kP;
-    src = kSrcStatsP;
-    W = find_part<kSrcStatsP>(P, row, b, P.nt, rs, u, &ks, &rem);
-  }
-  if (lane == 0) {
-    if (P.out_norm) P.out_norm[b] = (float)W;
-    if (ks < 0) P.out_token[b] = -1;
-  }
-  if (ks < 0) return;  // wave-uniform
-  const ProbScale ps = prob_scale(sp, rs, kind == kTokRes || kind == kTokPi);
-  if (kind == kQ) draw_kind_w<DT, kQ>(P, b, row, ks, rem, ps);
-  else if (kind == kP) draw_kind_w<DT, kP>(P, b, row, ks, rem, ps);
-  else if (kind == kTokPi) draw_kind_w<DT, kTokPi>(P, b, row, ks, rem, ps);
-  else if (kind == kTokRes) draw_kind_w<DT, kTokRes>(P, b, row, ks, rem, ps);
-  else draw_kind_w<DT, kResidual>(P, b, row, ks, rem, ps);
-}
-
 // Wave: item c = k * 4 + w of a TV or eta row job of row r: slice w of tile
 // k (for eta, of the k-th listed tile; an item past the list does nothing).
 template <int DT, bool TOK>
@@ -2231,73 +2245,6 @@ __device__ __forceinline__ void pass2_item_w(const Params& P, int r, int c) {
   pass2_slice_w<DT, TOK>(P, r, k, w, seq_param(P, r / (P.gamma + 1)));
 }
 
-// Wave: half h of the argmax of greedy row r: the lowest index of the row
-// maximum of q (h = 0) or p (h = 1), in the first tile holding it, read only
-// in the slices of that tile that attain it (usually one; a slice's lane
-// loads interleave with the other slices', so the minimum is taken over
-// every slice read).
-template <int DT>
-__device__ __forceinline__ void arg_half_w(const Params& P, int r, int h) {
-  using T = StatTile<DT>;
-  const int V = P.V;
-  const int lane = threadIdx.x & 63;
-  const int packed = ld_i32(P.argres + (int64_t)r * 4 + h);
-  int k = packed >> 4, mask = packed & 15;
-  if (packed < 0 || k >= P.nt) {  // a broken record: search the whole first tile
-    k = 0;
-    mask = 15;
-  }
-  if (mask == 0) mask = 15;
-  const RowStat rs = ld_rowstat(P.rowstat + r);
-  const float z = h ? rs.zmax_p : rs.zmax_q;
-  const char* row = (const char*)(h ? P.p : P.q) + (int64_t)r * V * T::EB;
-  const int64_t t0 = (int64_t)k * T::N;
-  int idx = 0x7fffffff;
-#pragma unroll 1
-  for (int w = 0; w < kSlices; ++w) {
-    if (!((mask >> w) & 1)) continue;  // wave-uniform
-    uint32_t c[T::U][T::NW];
-    load_tile<DT, T::U, true>(row, t0, V, c, w * 64 + lane, P.hdr);
-    mask_tile<DT, T::U>(row, t0, V, c, w * 64 + lane);
-#pragma unroll
-    for (int i = T::U - 1; i >= 0; --i) {
-      const int base = (int)t0 + ((i * kSlices + w) * 64 + lane) * T::VW;
-#pragma unroll
-      for (int e = T::VW - 1; e >= 0; --e)
-        if (elem<DT>(c[i], e) == z && base + e < V) idx = min(idx, base + e);
-    }
-  }
-  idx = wave_min(idx);
-  if (lane == 0) st_i32(P.argres + (int64_t)r * 4 + 2 + h, idx);
-}
-
-// Wave: item c = k * 4 + w of sequence b's residual job over row f (= j*),
-// sampling kind KIND: the residual masses of the sub-chunks of slice w of
-// tile k, stored at their place in the row's sub-chunk order, which the draw
-// searches directly.
-template <int DT, int KIND>
-__device__ __forceinline__ void res_slice_w(const Params& P, int b, int c, int f,
-                                            const RowStat& rs) {
-  constexpr int U = StatTile<DT>::U;
-  using T = StatTile<DT>;
-  const int k = c / kSlices, w = c % kSlices;
-  const int lane = threadIdx.x & 63, V = P.V;
-  const int64_t row = (int64_t)b * (P.gamma + 1) + f;
-  const int64_t t0 = (int64_t)k * T::N;
-  const SeqParam sp = seq_param(P, b);
-  const ProbScale ps = prob_scale(sp, rs, KIND == kTokRes);
-  __builtin_amdgcn_sched_barrier(0);
-  uint32_t cq[T::U][T::NW], cp[T::U][T::NW];
-  load_tiles<DT, T::U, true>((const char*)P.q + row * V * T::EB,
-                             (const char*)P.p + row * V * T::EB, t0, V, cq, cp, w * 64 + lane,
-                             P.hdr);
-  const double ml = slice_masses_of<DT, KIND>(cq, cp, ps, -1);
-  if (lane < U)
-    st_dev_f64(P.submass + (int64_t)b * P.nsub + (int64_t)k * (U * kSlices) + lane * kSlices + w,
-               ml);
-}
-
-
 // ---------------------------------------------------------------- draw pass
 // k_res: grid (nt, B), the step's last kernel.  For a sequence finished with
 // a residual draw, workgroup (k, b) sums the residual masses of the
@@ -2308,41 +2255,54 @@ __device__ __forceinline__ void res_slice_w(const Params& P, int b, int c, int f
 // (greedy or invalid) have no outcome word and are skipped.
 // bfloat16: held to 80 VGPRs, six resident workgroups per SIMD, so that in
 // large batches (256 sequences: 8192 workgroups) one workgroup's loads
-// overlap another's residual weights.  What spills is the draw's own code,
-// which only the last arrival of a sequence runs.
+// overlap another's residual weights.
 template <int DT>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(DT == SPC_BF16 ? 6 : 1))) void k_res(Params P) {
+  __shared__ double dv[kDrawSubs];
+  __shared__ int empty;
   const int k = blockIdx.x, b = blockIdx.y;
-  const int g1 = P.gamma + 1, lane = threadIdx.x & 63;
-  // the statistics of every row of the sequence (lane j: row j), requested
-  // together with the outcome word that names the row the draw needs
-  RowStat mine{};
-  if (lane < g1) mine = ld_rowstat(P.rowstat + (int64_t)b * g1 + lane);
-  const uint32_t info = ld_u32(row_word(P, b, kSeqInfo));
+  const int g1 = P.gamma + 1, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t info = (uint32_t)lane_i32((int)ld_u32(row_word(P, b, kSeqInfo)), 0);
   if (!(info & kSeqInfoSet)) return;  // block-uniform
   const int f = (int)(info & 0xffu), kind = (int)((info >> 8) & 0xffu);
   const int64_t row = (int64_t)b * g1 + f;
-  const RowStat rs = lane_rowstat(mine, f);
   const SeqParam sp = seq_param(P, b);
-  const bool residual = kind == kResidual || kind == kTokRes;
-  if (residual) {
-    const int w = threadIdx.x >> 6;
-    if (kind == kTokRes) res_slice_w<DT, kTokRes>(P, b, k * kSlices + w, f, rs);
-    else res_slice_w<DT, kResidual>(P, b, k * kSlices + w, f, rs);
-    vmem_drain();
+  uint32_t* cnt = row_word(P, b, kSeqResArrive);
+  if (kind != kResidual && kind != kTokRes) {
+    if (k == 0) draw_stats<DT>(P, b, row, kind, sp, dv);
+    if (w == 0 && arrive_last_w(cnt, (uint32_t)P.nt) && lane == 0)
+      st_u32(row_word(P, b, kSeqInfo), 0u);
+    return;
   }
+  if (kind == kTokRes) res_slice_w<DT, kTokRes>(P, b, k, w, f, sp);
+  else res_slice_w<DT, kResidual>(P, b, k, w, f, sp);
+  vmem_drain();
   __syncthreads();  // every wavefront's masses are stored
-  if (threadIdx.x >= 64) return;
-  if (!residual && k == 0) {
-    const int src = kind == kQ ? kSrcStatsQ : kind == kP ? kSrcStatsP : kSrcTokPi;
-    draw_w<DT>(P, b, row, kind, src, sp, ld_rowstat(P.rowstat + row));
-    vmem_drain();
+  if (w == 0) {
+    const bool last = arrive_last_w(cnt, (uint32_t)P.nt);
+    if (lane == 0) empty = 0;
+    if (last) {
+      if (lane == 0) st_u32(row_word(P, b, kSeqInfo), 0u);
+      const RowStat rs = ld_rowstat(P.rowstat + row);
+      const float u = P.uniforms[(int64_t)b * g1 + P.gamma];
+      int ks;
+      double rem;
+      const double W = find_part<kSrcPass, 8>(P, row, b, P.nsub, rs, u, &ks, &rem);
+      if (W > 0.0) {
+        if (lane == 0 && P.out_norm) P.out_norm[b] = (float)W;
+        const int64_t c0 = (int64_t)ks * SubC<DT>::N;
+        const ProbScale ps = prob_scale(sp, rs, kind == kTokRes);
+        if (kind == kTokRes) pick_wave<DT, SubC<DT>, kTokRes>(P, b, row, c0, rem, ps);
+        else pick_wave<DT, SubC<DT>, kResidual>(P, b, row, c0, rem, ps);
+      } else if (lane == 0) {
+        empty = 1;
+      }
+    }
   }
-  if (arrive_last_w(row_word(P, b, kSeqResArrive), (uint32_t)P.nt)) {
-    if (residual) draw_w<DT>(P, b, row, kind, kSrcPass, sp, ld_rowstat(P.rowstat + row));
-    if ((threadIdx.x & 63) == 0) st_u32(row_word(P, b, kSeqInfo), 0u);
-  }
+  __syncthreads();
+  // an empty residual (possible only through rounding) is replaced by p
+  if (empty) draw_stats<DT>(P, b, row, kP, sp, dv);
 }
 
 // Thread 0 of each workgroup, after reading the pass's job counts: arrive
@@ -2366,7 +2326,7 @@ __device__ __forceinline__ void exit_tree(const Params& P) {
 // The job pass: a static walk over the jobs the statistics kernel of this
 // call published: a slice of a TV row (batches of mixed rules), a slice of
 // a tile a token row listed for eta, a TV tile whose wait timed out, an
-// argmax half.  Wavefront w of the grid takes
+// Wavefront w of the grid takes
 // items w, w + W, ...  The item that completes a job decides its row; a
 // sequence that decision finishes is drawn by the draw pass that follows.
 // Held to 128 VGPRs: two workgroups per compute unit.
@@ -2422,14 +2382,11 @@ __global__ __launch_bounds__(kJobThreads) __attribute__((amdgpu_waves_per_eu(4))
         pass2_slice_w<DT, false>(P, id, x / kSlices, x % kSlices, seq_param(P, id / g1));
         if (arrive_last_w(row_word(P, id, kRowTvArrive), (uint32_t)(kSlices * nt)))
           tv_row_done<DT>(P, id);
-      } else if (kind == kJobEta) {
+      } else {  // kJobEta
         // slice c % 4 of the (c / 4)-th listed tile of token row id
         const uint32_t n = (uint32_t)ld_i32(P.etacnt + id) * (uint32_t)kSlices;
         pass2_item_w<DT, true>(P, id, (int)job_extra(e));
-        if (arrive_last_w(row_word(P, id, kRowTvArrive), n)) row_job_decide<DT>(P, kind, id);
-      } else {  // kJobArg
-        arg_half_w<DT>(P, id, (int)job_extra(e));
-        if (arrive_last_w(row_word(P, id, kRowJobDone), 2u)) row_job_decide<DT>(P, kind, id);
+        if (arrive_last_w(row_word(P, id, kRowTvArrive), n)) row_job_decide<DT>(P, id);
       }
     }
   }
@@ -2446,10 +2403,15 @@ hipError_t launch_step_t(const Params& P, hipStream_t st, bool draw_pass, bool t
   constexpr int kAll = kMomX | kMomHQ | kMomHP;
   if (!P.tv_self && P.pair && P.mom_set == 0) {
     const dim3 grid2((unsigned)((P.nt + 1) / 2), (unsigned)(P.B * (P.gamma + 1)));
-    hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, true>), grid2, block, 0, st, P);
+    if (P.may_greedy)
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, true>), grid2, block, 0, st, P);
+    else
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, true, false>), grid2, block, 0, st, P);
   } else if (!P.tv_self) {
-    if (P.mom_set == 0)
+    if (P.mom_set == 0 && P.may_greedy)
       hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone>), grid, block, 0, st, P);
+    else if (P.mom_set == 0)
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, false, false>), grid, block, 0, st, P);
     else if (P.mom_set == kMomX)
       hipLaunchKernelGGL((k_tiles<DT, kMomX, kTvNone>), grid, block, 0, st, P);
     else if (P.mom_set == kMomHQ)
@@ -3174,8 +3136,8 @@ hipError_t launch_small(const Params& P, int dtype, hipEvent_t ev_begin,
                     : launch_small_t<0>(P, st, ev_begin, ev_end);
 }
 
-hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass,
-                       bool job_pass, int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end,
+hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass, bool job_pass,
+                       int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end,
                        hipStream_t st) {
   if (dtype == 1)
     return launch_step_t<1>(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin, ev_end);
