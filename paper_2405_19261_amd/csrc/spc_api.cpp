@@ -313,9 +313,25 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
   constexpr uint32_t kTok = (1u << SPC_RULE_TOKEN_V1) | (1u << SPC_RULE_TOKEN_V2) |
                             (1u << SPC_RULE_TOKEN_V3);
   const bool tv_rows = may_sample && (rules & kTv);
-  // Small problems (rows that fit one workgroup's registers, at most two
-  // rows per compute unit, no first moments) take the single-launch path.
-  const bool small = !need_mom && V <= spc::small_row_elems(dtype) &&
+  // Batches of short sequences take the one-launch path with a workgroup per
+  // sequence: up to a length that depends on how the rows fill the chip
+  // otherwise.  us per step, that path / the next best, bfloat16 unless said:
+  //   rows within the compute units: Diff V=1000 gamma=4 B=1 f32 9.4 / 10.4,
+  //   V=4000 gamma=1 9.6 / 10.5, V=4000 gamma=4 13.0 / 11.1; OPT f32 V=1000
+  //   gamma=1 9.9 / 10.7, gamma=7 13.5 / 11.3, TokenV2 V=2000 gamma=7 17.5 / 16.1;
+  //   more rows: Diff B=256 gamma=7 V=4000 16.9 / 26.9, B=64 gamma=4 V=8000
+  //   f32 17.4 / 21.9, gamma=7 V=16000 29.4 / 28.1; OPT B=64 gamma=4 V=4000
+  //   f32 19.9 / 21.2, gamma=7 23.9 / 22.2; TokenV2 B=256 gamma=7 V=4000
+  //   27.0 / 68.3; DiffLog B=64 gamma=4 V=4000 f32 19.5 / 20.2; greedy B=256
+  //   gamma=4 V=8000 19.0 / 15.1.
+  const bool tok_rows = may_sample && (rules & kTok);
+  const bool full = b_launch * g1 > (int64_t)cus;
+  const int64_t seq_most = !full ? (tv_rows || tok_rows ? 4096 : 8192)
+                           : tv_rows || need_mom || !may_sample ? 20480 : 40960;
+  const bool seq = V <= spc::seq_row_elems(dtype) && g1 * V <= seq_most && B <= 2 * (int64_t)cus;
+  // Other small problems (rows that fit one workgroup's registers, at most two
+  // rows per compute unit, no first moments): one launch, a workgroup per row.
+  const bool small = !seq && !need_mom && V <= spc::small_row_elems(dtype) &&
                      b_launch * g1 <= 2 * (int64_t)cus;
   const int64_t nt = stat_tiles(dtype, V);
   const int64_t eb = dtype == SPC_BF16 ? 2 : 4;
@@ -390,7 +406,9 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     const bool first = b0 == 0;
     hipEvent_t ev0 = first && ex ? ex->ev_tiles_begin : nullptr;
     hipEvent_t ev1 = first && ex ? ex->ev_tiles_end : nullptr;
-    if (small) {
+    if (seq) {
+      e = spc::launch_seq(P, dtype, ev0, ev1, stream);
+    } else if (small) {
       // one launch: a workgroup per row holding the row in registers
       P.nsub = spc::kSmallSub;
       e = spc::launch_small(P, dtype, ev0, ev1, stream);

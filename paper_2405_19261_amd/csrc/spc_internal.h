@@ -147,6 +147,12 @@ WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype);
 hipError_t launch_draft(const Params& P, int dtype, bool argmax, bool long_tiles,
                         hipStream_t stream);
 
+// The short-sequence path (k_seq): a workgroup per sequence, rows of at most
+// seq_row_elems entries.  It uses no workspace but 16 readable bytes (hdr).
+int seq_row_elems(int dtype);
+hipError_t launch_seq(const Params& P, int dtype, hipEvent_t ev_begin, hipEvent_t ev_end,
+                      hipStream_t stream);
+
 // The small-problem path (k_small): a workgroup per row holding the row in
 // registers; rows of at most small_row_elems entries, kSmallSub sub-chunks.
 constexpr int kSmallSub = 64;

@@ -1086,20 +1086,16 @@ __device__ __forceinline__ double find_part(const Params& P, int64_t row, int b,
   return W;
 }
 
-// Wave 0: the in-chunk draw in the chunk starting at entry c0.  Lane loads
-// are scanned in entry order -- lane load i, then lane -- for the first one
-// where the running mass exceeds rem; its lane then walks its VW entries.
-// Rounding that leaves rem unreached takes the last entry with mass.
+// Wave: the in-chunk draw in the chunk starting at entry c0, from its loaded
+// entries.  Lane loads are scanned in entry order -- lane load i, then lane --
+// for the first one where the running mass exceeds rem; its lane then walks
+// its VW entries.  Rounding that leaves rem unreached takes the last entry
+// with mass.
 template <int DT, class C, int KIND>
-__device__ __forceinline__ void pick_wave(const Params& P, int b, int64_t row, int64_t c0,
-                                          double rem, const ProbScale& ps, int kind = -1) {
-  constexpr int EB = StatTile<DT>::EB;
+__device__ __forceinline__ void pick_from(const Params& P, int b, int64_t c0, double rem,
+                                          const ProbScale& ps, const ChunkRegs<C>& cq,
+                                          const ChunkRegs<C>& cp, int kind = -1) {
   const int lane = threadIdx.x & 63;
-  const int V = P.V;
-  const char* qrow = (const char*)P.q + row * V * EB;
-  const char* prow = (const char*)P.p + row * V * EB;
-  ChunkRegs<C> cq = {}, cp = {};
-  load_chunks<DT, C, KIND>(qrow, prow, c0, V, cq, cp, P.hdr);
   double carry = 0.0, before = 0.0;
   int hlane = -1, last_pos = -1;
   int64_t hbase = 0;
@@ -1148,6 +1144,19 @@ __device__ __forceinline__ void pick_wave(const Params& P, int b, int64_t row, i
     if (e & 1) __builtin_amdgcn_sched_barrier(0);
   }
   P.out_token[b] = hit >= 0 ? hit : lastw;  // rounding inside the lane load
+}
+
+// The same from memory.
+template <int DT, class C, int KIND>
+__device__ __forceinline__ void pick_wave(const Params& P, int b, int64_t row, int64_t c0,
+                                          double rem, const ProbScale& ps, int kind = -1) {
+  constexpr int EB = StatTile<DT>::EB;
+  const int V = P.V;
+  const char* qrow = (const char*)P.q + row * V * EB;
+  const char* prow = (const char*)P.p + row * V * EB;
+  ChunkRegs<C> cq = {}, cp = {};
+  load_chunks<DT, C, KIND>(qrow, prow, c0, V, cq, cp, P.hdr);
+  pick_from<DT, C, KIND>(P, b, c0, rem, ps, cq, cp, kind);
 }
 
 // Whole block: the masses of the sub-chunks of the TN-entry tile at entry t0
@@ -1424,11 +1433,11 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
 // The second-pass weight summed over a thread's entries of one statistics
 // tile: for a token rule eta's share (the q mass of the entries the rule
 // marks), else max(0, p - q) (D_TV of Lemma 3) in float32.
-template <int DT, bool TOK>
-__device__ __forceinline__ double pass2_sum(const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
-                                            const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW],
+template <int DT, int U, bool TOK>
+__device__ __forceinline__ double pass2_sum(const uint32_t (&wq)[U][Tile<DT, U>::NW],
+                                            const uint32_t (&wp)[U][Tile<DT, U>::NW],
                                             const ProbScale& ps) {
-  using T = StatTile<DT>;
+  using T = Tile<DT, U>;
   double acc = 0.0;
 #pragma unroll
   for (int i = 0; i < T::U; ++i) {
@@ -1581,7 +1590,7 @@ __device__ __forceinline__ void pass2_slice_w(const Params& P, int r, int k, int
   const ProbScale ps = prob_scale(sp, rs, TOK);
   mask_tile<DT, T::U>(qrow, t0, V, wq, w * 64 + lane);
   mask_tile<DT, T::U>(prow, t0, V, wp, w * 64 + lane);
-  double acc = pass2_sum<DT, TOK>(wq, wp, ps);
+  double acc = pass2_sum<DT, T::U, TOK>(wq, wp, ps);
   acc = wave_sum(acc);
   if (lane == 0) st_dev_f64(P.tvpart + ((int64_t)r * P.nt + k) * kSlices + w, acc);
 }
@@ -1595,7 +1604,7 @@ __device__ __forceinline__ void tv_slice_regs_w(
     const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
     const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW]) {
   const ProbScale ps = prob_scale(sp, ld_rowstat(P.rowstat + r), false);
-  const double acc = wave_sum(pass2_sum<DT, false>(wq, wp, ps));
+  const double acc = wave_sum(pass2_sum<DT, StatTile<DT>::U, false>(wq, wp, ps));
   if ((threadIdx.x & 63) == 0) st_dev_f64(P.tvpart + ((int64_t)r * P.nt + k) * kSlices + w, acc);
 }
 
@@ -1669,6 +1678,16 @@ struct StepShared {
   int a[4];  // values thread 0 or wave 0 hands to the block
 };
 
+// What a sampled sequence with first rejection f (delta there) draws from.
+__device__ __forceinline__ int sample_kind(const SeqParam& sp, int f, int gamma, int delta) {
+  if (is_token(sp.rule)) return f < gamma ? kTokRes : kTokPi;
+  // lossy: residual max(0, pi - q) = max(0, p - q); extra token from p
+  if (sp.rule == SPC_RULE_LOSSY) return f < gamma ? kResidual : kP;
+  // a rejection with delta = 0 only happens for an out-of-range draft; its
+  // residual max(0, q - q) is empty, so p is sampled instead
+  return f < gamma ? (delta ? kResidual : kP) : (delta ? kP : kQ);
+}
+
 // Wave: sequence b's first rejection is j* = f.  Writes its accept length,
 // then the greedy token; or, for a draw (from the statistics partials, or
 // from the residual of row f), records it in the sequence's outcome word for
@@ -1693,25 +1712,14 @@ __device__ __forceinline__ void seq_finish_w(const Params& P, int b, int f, cons
     if (P.out_norm) P.out_norm[b] = 1.0f;
     return;
   }
-  int kind;
-  if (is_token(sp.rule)) {
-    kind = (f < gamma) ? kTokRes : kTokPi;
-  } else if (sp.rule == SPC_RULE_LOSSY) {
-    // residual max(0, pi - q) = max(0, p - q); extra token from p
-    kind = (f < gamma) ? kResidual : kP;
-  } else {
-    // a rejection with delta = 0 only happens for an out-of-range draft; its
-    // residual max(0, q - q) is empty, so p is sampled instead
-    kind = (f < gamma) ? (dstar ? kResidual : kP) : (dstar ? kP : kQ);
-  }
+  const int kind = sample_kind(sp, f, gamma, dstar);
   st_u32(row_word(P, b, kSeqInfo), kSeqInfoSet | ((uint32_t)kind << 8) | (uint32_t)f);
 }
 
-// Lane 0: write the outputs and the record of decided row r (d from
-// decide_row; an invalid sequence's rows record "reject, no deferral"),
-// with `extra` in the record's bits 4 and up.
-__device__ __forceinline__ void row_record(const Params& P, int r, const SeqParam& sp,
-                                           const RowDecision& d, int extra) {
+// One lane: the outputs of decided row r (d from decide_row; an invalid
+// sequence's rows report no deferral).
+__device__ __forceinline__ void row_outputs(const Params& P, int r, const SeqParam& sp,
+                                            const RowDecision& d) {
   P.out_defer[r] = sp.valid ? (uint8_t)d.delta : (uint8_t)0;
   if (sp.valid && P.out_stats) {
     const double T = sp.greedy ? 1.0 : kLog2e / sp.c;
@@ -1729,6 +1737,14 @@ __device__ __forceinline__ void row_record(const Params& P, int r, const SeqPara
     P.out_argmax[(int64_t)r * 2 + 0] = d.rs.amax_q;
     P.out_argmax[(int64_t)r * 2 + 1] = d.rs.amax_p;
   }
+}
+
+// Lane 0: write the outputs and the record of decided row r (an invalid
+// sequence's rows record "reject, no deferral"), with `extra` in the
+// record's bits 4 and up.
+__device__ __forceinline__ void row_record(const Params& P, int r, const SeqParam& sp,
+                                           const RowDecision& d, int extra) {
+  row_outputs(P, r, sp, d);
   if (sp.valid) st_rowstat(P.rowstat + r, d.rs);
   st_i32(P.rowdec + r, (sp.valid ? d.keep | (d.delta << 1) : 0) | (extra << 4));
 }
@@ -2442,6 +2458,411 @@ hipError_t launch_step_t(const Params& P, hipStream_t st, bool draw_pass, bool t
   return err;
 }
 
+// ================================================================ short sequences
+// k_seq: one workgroup of 16 wavefronts per sequence, for sequences whose
+// gamma + 1 rows together are short.  Everything a step resolves between
+// workgroups elsewhere (a row on its tiles, a sequence on its rows, a draw on
+// its sub-chunks) is resolved here through LDS, so the step is one launch
+// and its chain of memory round trips is: the logits, row j*'s logits again
+// (from L2).  A row is read by `wpr` wavefronts in chunks of U lane loads,
+// and its first wavefront merges and decides it, all rows side by side.
+// Bound by issue: 16 wavefronts on one compute unit, so a row takes only as
+// many of them as it has chunks.
+constexpr int kSeqThreads = 1024;
+constexpr int kSeqWaves = kSeqThreads / 64;
+constexpr int kSeqSubs = 256;  // sub-chunks (64 lane loads) a row may have
+
+struct SeqPart {  // one wavefront's share of a row
+  double sq, sp, hq, hp, x;
+  float mq, mp;
+  int kq, kp;  // first entry of the first lane load attaining mq / mp
+};
+struct SeqShared {
+  SeqPart part[64];    // [row * wpr + part], at most 64
+  double tv[64];       // second-pass partials
+  RowStat rs[64];
+  double mass[kSeqSubs];
+  uint8_t pass2[64];   // the row needs its second pass
+  uint8_t dec[64];     // bit 0 a_j, bit 1 delta_j
+};
+
+// The packed words stay live across the passes over them; each pass unpacks
+// them again (otherwise every unpacked entry is kept, twice the registers).
+template <class C>
+__device__ __forceinline__ void seq_fence(ChunkRegs<C>& q, ChunkRegs<C>& p) {
+#pragma unroll
+  for (int i = 0; i < C::U; ++i)
+#pragma unroll
+    for (int k = 0; k < C::NW; ++k) asm volatile("" : "+v"(q[i][k]), "+v"(p[i][k]));
+}
+
+// Lane sums of one chunk against the lane's running maxima.  Contraction is
+// off so that identical q and p rows take identical operations.
+struct SeqAcc {
+  float mq = kNegInf, mp = kNegInf;
+  int kq = 0, kp = 0;  // first entry of the first lane load attaining mq / mp
+  double sq = 0.0, sp = 0.0, hq = 0.0, hp = 0.0, x = 0.0;
+};
+template <int DT, class C, bool MOM>
+__device__ __forceinline__ void seq_sum(ChunkRegs<C>& wq, ChunkRegs<C>& wp, int c0,
+                                        const SeqParam& sp, SeqAcc& a) {
+#pragma clang fp contract(off)
+  float nq = a.mq, np = a.mp;
+#pragma unroll
+  for (int i = 0; i < C::U; ++i) {
+    float g = elem<DT>(wq[i], 0), h = elem<DT>(wp[i], 0);
+#pragma unroll
+    for (int e = 1; e < C::VW; ++e) {
+      g = fmaxf(g, elem<DT>(wq[i], e));
+      h = fmaxf(h, elem<DT>(wp[i], e));
+    }
+    const int k = c0 + (i * 64 + ((int)threadIdx.x & 63)) * C::VW;
+    if (g > nq) a.kq = k;
+    if (h > np) a.kp = k;
+    nq = fmaxf(nq, g);
+    np = fmaxf(np, h);
+  }
+  seq_fence<C>(wq, wp);
+  const float rq = nq == kNegInf ? 0.0f : nq * sp.c_hi, rp = np == kNegInf ? 0.0f : np * sp.c_hi;
+  float tq = 0.0f, tp = 0.0f, hq = 0.0f, hp = 0.0f, x = 0.0f;
+#pragma unroll
+  for (int i = 0; i < C::U; ++i)
+#pragma unroll
+    for (int e = 0; e < C::VW; ++e) {
+      const float zq = elem<DT>(wq[i], e), zp = elem<DT>(wp[i], e);
+      const float aq = fmaf(zq, sp.c_lo, fmaf(zq, sp.c_hi, -rq));
+      const float ap = fmaf(zp, sp.c_lo, fmaf(zp, sp.c_hi, -rp));
+      const float eq = exp2_hw(aq), ep = exp2_hw(ap);
+      tq += eq;
+      tp += ep;
+      if constexpr (MOM) {
+        hq = fmaf(eq, eq > 0.0f ? aq : 0.0f, hq);
+        x = fmaf(eq, eq > 0.0f ? ap : 0.0f, x);
+        hp = fmaf(ep, ep > 0.0f ? ap : 0.0f, hp);
+      }
+      if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+  // the earlier chunks' sums move to the new references
+  const double gq = a.mq == kNegInf ? 0.0 : (double)(a.mq * sp.c_hi) - (double)rq;
+  const double gp = a.mp == kNegInf ? 0.0 : (double)(a.mp * sp.c_hi) - (double)rp;
+  const double fq = (double)exp2_hw((float)gq), fp = (double)exp2_hw((float)gp);
+  if constexpr (MOM) {
+    a.hq = mom_move(a.hq, a.sq, fq, gq) + (double)hq;
+    a.hp = mom_move(a.hp, a.sp, fp, gp) + (double)hp;
+    a.x = mom_move(a.x, a.sq, fq, gp) + (double)x;
+  }
+  a.sq = a.sq * fq + (double)tq;
+  a.sp = a.sp * fp + (double)tp;
+  a.mq = nq;
+  a.mp = np;
+}
+
+// Wave: fn(entries of q, entries of p, first entry) over chunks wi, wi + wpr,
+// .. of a row.
+template <int DT, class C, class F>
+__device__ __forceinline__ void seq_chunks(const char* qrow, const char* prow, int V, int wi,
+                                           int wpr, const void* safe, F&& fn) {
+#pragma unroll 1
+  for (int c0 = wi * C::N; c0 < V; c0 += wpr * C::N) {  // wave-uniform
+    ChunkRegs<C> q, p;
+    load_tiles<DT, C::U, false, 64>(qrow, prow, c0, V, q, p, threadIdx.x & 63, safe);
+    fn(q, p, c0);
+  }
+}
+
+// Wave: the sub-chunk (of K masses m in LDS) where u W falls and the target
+// mass left at its start, as find_part; returns W.
+__device__ __forceinline__ double seq_find(const double* m, int K, float u, int* ks_out,
+                                           double* rem_out) {
+  const int lane = threadIdx.x & 63;
+  double W = 0.0;
+  for (int k0 = 0; k0 < K; k0 += 64) W += wave_sum(k0 + lane < K ? m[k0 + lane] : 0.0);
+  const double target = (double)u * W;
+  double carry = 0.0, rem = 0.0;
+  int ks = -1, klast = -1;
+  for (int k0 = 0; k0 < K && ks < 0; k0 += 64) {
+    const double ml = k0 + lane < K ? m[k0 + lane] : 0.0;
+    const double incl = carry + wave_incl_scan(ml);
+    const unsigned long long pos = __ballot(ml > 0.0);
+    const unsigned long long hit = __ballot(ml > 0.0 && incl > target);
+    if (pos) klast = k0 + 63 - __clzll(pos);
+    if (hit) {
+      const int l = __ffsll(hit) - 1;
+      ks = k0 + l;
+      rem = target - (lane_f64(incl, l) - lane_f64(ml, l));
+    }
+    carry = lane_f64(incl, 63);
+  }
+  if (ks < 0) {  // rounding left u W at or past the end: the last part with mass
+    ks = klast;
+    rem = __builtin_huge_val();
+  }
+  *ks_out = ks;
+  *rem_out = rem;
+  return W;
+}
+
+// Whole block: the draw of sequence b at row j* = f from distribution KIND.
+// Returns false (to every thread) for an empty residual.
+template <int DT, int KIND>
+__device__ __forceinline__ bool seq_draw(const Params& P, int b, int f, const SeqParam& sp, float u,
+                                         SeqShared& sh) {
+  using C = SubC<DT>;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, V = P.V;
+  const int64_t row = (int64_t)b * (P.gamma + 1) + f;
+  const char* qrow = (const char*)P.q + row * V * StatTile<DT>::EB;
+  const char* prow = (const char*)P.p + row * V * StatTile<DT>::EB;
+  const ProbScale ps = prob_scale(sp, sh.rs[f], KIND == kTokRes || KIND == kTokPi);
+  const int ns = (V + C::N - 1) / C::N;
+  ChunkRegs<C> cq = {}, cp = {};
+  for (int sc = wv; sc < ns; sc += kSeqWaves) {
+    load_chunks<DT, C, KIND>(qrow, prow, (int64_t)sc * C::N, V, cq, cp, P.hdr);
+    float t = 0.0f;
+#pragma unroll
+    for (int e = 0; e < C::VW; ++e)
+      t += weight_of<DT, KIND>(elem<DT>(cq[0], e), elem<DT>(cp[0], e), ps);
+    const double m = wave_sum((double)t);
+    if (lane == 0) sh.mass[sc] = m;
+  }
+  __syncthreads();
+  int ks;
+  double rem;
+  const double W = seq_find(sh.mass, ns, u, &ks, &rem);  // every wavefront alike
+  if ((KIND == kResidual || KIND == kTokRes) && !(W > 0.0)) return false;
+  if (threadIdx.x == 0) {
+    if (P.out_norm) P.out_norm[b] = (float)W;
+    if (ks < 0) P.out_token[b] = -1;
+  }
+  // the wavefront that summed the sub-chunk draws in it, its entries still
+  // loaded when it was its last one
+  if (ks >= 0 && wv == ks % kSeqWaves) {
+    if (ks + kSeqWaves < ns)
+      load_chunks<DT, C, KIND>(qrow, prow, (int64_t)ks * C::N, V, cq, cp, P.hdr);
+    pick_from<DT, C, KIND>(P, b, (int64_t)ks * C::N, rem, ps, cq, cp);
+  }
+  return true;
+}
+
+// Sub-chunks of a row, and the wavefronts that read it: one per four
+// sub-chunks, at most 16 / (gamma + 1).
+__host__ __device__ constexpr int seq_subs(int V, int sub) { return (V + sub - 1) / sub; }
+__host__ __device__ constexpr int seq_wpr(int g1, int ns) {
+  const int most = g1 >= kSeqWaves ? 1 : kSeqWaves / g1, want = (ns + 3) / 4;
+  return want < most ? want : most;
+}
+
+template <int DT, int MS, int U>
+__global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
+  __shared__ SeqShared sh;
+  using C = Chunk<DT, U>;
+  constexpr int EB = StatTile<DT>::EB;
+  const int b = blockIdx.x, gamma = P.gamma, g1 = gamma + 1, V = P.V;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int wpr = seq_wpr(g1, seq_subs(V, SubC<DT>::N));  // wavefronts per row
+  const int rpp = kSeqWaves / wpr;                        // rows at a time
+  const int slot = wv / wpr, wi = wv % wpr;
+  const int jend = slot < rpp ? g1 : 0;
+  const SeqParam sp = seq_param(P, b);
+  const int64_t r0 = (int64_t)b * g1;
+  const int mrule = (MS != 0 && needs_mom(sp)) ? sp.rule : 0;
+  const bool tok = is_token(sp.rule);
+  // The decision's inputs of this wavefront's first row: its draft token and
+  // uniform are requested before the row's entries, the token's logits after
+  // them, so that neither costs a round trip of its own.
+  const bool dec0 = wi == 0 && slot < jend && sp.valid && !sp.greedy;
+  DraftIn pre{-1, 0.0f, 0.0f, 0.0f};
+  if (dec0) {
+    pre.x = draft_token(P, b, slot);
+    pre.u = P.uniforms[r0 + slot];
+  }
+  // 1. the wavefronts' shares of every row
+  for (int j = slot; j < jend; j += rpp) {
+    const char* qrow = (const char*)P.q + (r0 + j) * V * EB;
+    const char* prow = (const char*)P.p + (r0 + j) * V * EB;
+    SeqAcc a;
+    seq_chunks<DT, C>(qrow, prow, V, wi, wpr, P.hdr,
+                      [&](ChunkRegs<C>& q, ChunkRegs<C>& p, int c0) {
+                        if (MS != 0 && mrule) seq_sum<DT, C, true>(q, p, c0, sp, a);
+                        else seq_sum<DT, C, false>(q, p, c0, sp, a);
+                      });
+    if (dec0 && j == slot && pre.x >= 0 && pre.x < V) {
+      pre.zqx = load_logit<DT>(P.q, r0 + j, V, pre.x);
+      pre.zpx = load_logit<DT>(P.p, r0 + j, V, pre.x);
+    }
+    const float Mq = wave_max(a.mq), Mp = wave_max(a.mp);
+    const double gq = a.mq == kNegInf ? 0.0 : (double)(a.mq * sp.c_hi) - (double)(Mq * sp.c_hi);
+    const double gp = a.mp == kNegInf ? 0.0 : (double)(a.mp * sp.c_hi) - (double)(Mp * sp.c_hi);
+    const double fq = (double)exp2_hw((float)gq), fp = (double)exp2_hw((float)gp);
+    SeqPart t;
+    t.mq = Mq;
+    t.mp = Mp;
+    t.sq = wave_sum(a.mq == kNegInf ? 0.0 : a.sq * fq);
+    t.sp = wave_sum(a.mp == kNegInf ? 0.0 : a.sp * fp);
+    t.hq = t.hp = t.x = 0.0;
+    if (MS != 0 && mrule) {
+      t.hq = wave_sum(a.mq == kNegInf ? 0.0 : mom_move(a.hq, a.sq, fq, gq));
+      t.hp = wave_sum(a.mp == kNegInf ? 0.0 : mom_move(a.hp, a.sp, fp, gp));
+      t.x = wave_sum(a.mq == kNegInf ? 0.0 : mom_move(a.x, a.sq, fq, gp));
+    }
+    t.kq = t.kp = 0;
+    if (sp.greedy) {  // uniform
+      t.kq = wave_min(a.mq == Mq ? a.kq : 0x7fffffff);
+      t.kp = wave_min(a.mp == Mp ? a.kp : 0x7fffffff);
+    }
+    if (lane == 0) sh.part[j * wpr + wi] = t;
+  }
+  if (wpr > 1) __syncthreads();
+  else __builtin_amdgcn_wave_barrier();  // a row's share is its own wavefront's
+  const auto inputs = [&](int j) {
+    return j == slot ? pre
+                     : draft_in<DT>(P, (int)r0 + j, sp.valid ? draft_token(P, b, j) : -1, sp);
+  };
+  // 2. the row's statistics; rows that need no second look are decided
+  bool any2 = false;
+  for (int j = slot; j < jend && wi == 0; j += rpp) {
+    DraftIn in = inputs(j);
+    if (sp.greedy && sp.valid) in.x = draft_token(P, b, j);
+    const SeqPart* t = sh.part + j * wpr;
+    float Mq = kNegInf, Mp = kNegInf;
+    for (int w = 0; w < wpr; ++w) {
+      Mq = fmaxf(Mq, t[w].mq);
+      Mp = fmaxf(Mp, t[w].mp);
+    }
+    const double Rq = (double)(Mq * sp.c_hi), Rp = (double)(Mp * sp.c_hi);
+    double Sq = 0.0, Sp = 0.0, Hq = 0.0, Hp = 0.0, X = 0.0;
+    int kq = 0x7fffffff, kp = 0x7fffffff;
+    for (int w = 0; w < wpr; ++w) {
+      if (t[w].mq == Mq) kq = min(kq, t[w].kq);
+      if (t[w].mp == Mp) kp = min(kp, t[w].kp);
+      const bool iq = t[w].mq != kNegInf, ip = t[w].mp != kNegInf;
+      const double gq = iq ? (double)(t[w].mq * sp.c_hi) - Rq : 0.0;
+      const double gp = ip ? (double)(t[w].mp * sp.c_hi) - Rp : 0.0;
+      const double fq = (double)exp2_hw((float)gq), fp = (double)exp2_hw((float)gp);
+      if (iq) Sq += t[w].sq * fq;
+      if (ip) Sp += t[w].sp * fp;
+      if (MS != 0 && mrule) {
+        if (iq) mom_add(Hq, t[w].hq, t[w].sq, fq, gq);
+        if (ip) mom_add(Hp, t[w].hp, t[w].sp, fp, gp);
+        if (iq) mom_add(X, t[w].x, t[w].sq, fq, ip ? gp : -__builtin_huge_val());
+      }
+    }
+    RowStat rs{};
+    const double lq2 = log2_acc(Sq), lp2 = log2_acc(Sp);
+    rs.lz_q = (Mq == kNegInf ? (double)kNegInf : Rq) + lq2;
+    rs.lz_p = (Mp == kNegInf ? (double)kNegInf : Rp) + lp2;
+    rs.slog = (MS != 0 && mrule) ? log_stat(mrule, lq2, lp2, Sq, Sp, Hq, Hp, X) : 0.0;
+    rs.zmax_q = Mq;
+    rs.zmax_p = Mp;
+    rs.amax_q = rs.amax_p = -1;
+    bool need = false;
+    float zpx = in.zpx;
+    if (sp.valid && sp.greedy) {
+      rs.amax_q = kq;
+      rs.amax_p = kp;
+      arg_rows_w<DT>(P, (int)r0 + j, rs);
+      if (((tok && sp.rule != SPC_RULE_TOKEN_V1) || sp.rule == SPC_RULE_BILD) && rs.amax_q < V)
+        zpx = load_logit<DT>(P.p, r0 + j, V, rs.amax_q);
+    } else if (sp.valid && tok) {
+      need = true;
+    } else if (sp.valid && has_tv_parts(sp.rule)) {
+      need = P.out_stats || tv_free_decision(sp, rs, 0.0) < 0;
+      if (!need) rs.tv = 1.0;  // any D_TV decides it alike
+    }
+    any2 |= need;
+    RowDecision d{};
+    if (sp.valid && !need) d = decide_row(sp, rs, j, gamma, V, in.x, in.zqx, zpx, in.u);
+    if (lane == 0) {
+      sh.rs[j] = rs;
+      sh.pass2[j] = need;
+      if (!need) {
+        row_outputs(P, (int)r0 + j, sp, d);
+        sh.dec[j] = sp.valid ? d.keep | (d.delta << 1) : 0;
+      }
+    }
+  }
+  // 3. rows that need a second look at their entries: D_TV or eta
+  if (__syncthreads_or(any2)) {
+    for (int j = slot; j < jend; j += rpp) {
+      if (!sh.pass2[j]) continue;  // wave-uniform
+      const char* qrow = (const char*)P.q + (r0 + j) * V * EB;
+      const char* prow = (const char*)P.p + (r0 + j) * V * EB;
+      const ProbScale ps = prob_scale(sp, sh.rs[j], tok);
+      double acc = 0.0;
+      seq_chunks<DT, C>(qrow, prow, V, wi, wpr, P.hdr,
+                        [&](ChunkRegs<C>& q, ChunkRegs<C>& p, int) {
+                          acc += tok ? pass2_sum<DT, U, true>(q, p, ps)
+                                     : pass2_sum<DT, U, false>(q, p, ps);
+                        });
+      acc = wave_sum(acc);
+      if (lane == 0) sh.tv[j * wpr + wi] = acc;
+    }
+    __syncthreads();
+    for (int j = slot; j < jend && wi == 0; j += rpp) {
+      if (!sh.pass2[j]) continue;  // wave-uniform
+      const DraftIn in = inputs(j);
+      RowStat rs = sh.rs[j];
+      rs.tv = 0.0;
+      for (int w = 0; w < wpr; ++w) rs.tv += sh.tv[j * wpr + w];
+      const RowDecision d = decide_row(sp, rs, j, gamma, V, in.x, in.zqx, in.zpx, in.u);
+      if (lane == 0) {
+        sh.rs[j].tv = rs.tv;
+        row_outputs(P, (int)r0 + j, sp, d);
+        sh.dec[j] = d.keep | (d.delta << 1);
+      }
+    }
+    __syncthreads();
+  }
+  // 4. the first rejection (row gamma rejects), the same in every wavefront
+  const int dec = lane < g1 ? sh.dec[lane] : 1;
+  const uint64_t rej = __ballot(!(dec & 1));
+  const int f = __builtin_ctzll(rej);
+  const int delta = (lane_i32(dec, f) >> 1) & 1;
+  if (threadIdx.x == 0) {
+    P.out_accept[b] = sp.valid ? f : -1;
+    if (!sp.valid || sp.greedy) {
+      const RowStat rs = sh.rs[f];
+      P.out_token[b] =
+          !sp.valid ? -1 : (delta || sp.rule == SPC_RULE_LOSSY) ? rs.amax_p : rs.amax_q;
+      if (P.out_norm) P.out_norm[b] = sp.valid ? 1.0f : 0.0f;
+    }
+  }
+  if (!sp.valid || sp.greedy) return;  // block-uniform
+  // 5. the draw from row j*
+  const int kind = sample_kind(sp, f, gamma, delta);
+  const float us = P.uniforms[r0 + gamma];
+  bool done;
+  if (kind == kResidual) done = seq_draw<DT, kResidual>(P, b, f, sp, us, sh);
+  else if (kind == kTokRes) done = seq_draw<DT, kTokRes>(P, b, f, sp, us, sh);
+  else if (kind == kQ) done = seq_draw<DT, kQ>(P, b, f, sp, us, sh);
+  else if (kind == kTokPi) done = seq_draw<DT, kTokPi>(P, b, f, sp, us, sh);
+  else done = false;
+  if (done) return;
+  // p: the extra token's distribution, or the stand-in for an empty residual
+  // (possible only through rounding)
+  __syncthreads();
+  (void)seq_draw<DT, kP>(P, b, f, sp, us, sh);
+}
+
+template <int DT>
+hipError_t launch_seq_t(const Params& P, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end) {
+  if (ev_begin) {
+    const hipError_t e = hipEventRecord(ev_begin, st);
+    if (e != hipSuccess) return e;
+  }
+  const dim3 grid((unsigned)P.B), block(kSeqThreads);
+  // lane loads a wavefront takes at a time: those of its share of a row, up
+  // to four (one with first moments, whose sums take the registers)
+  const int ns = seq_subs(P.V, SubC<DT>::N), wpr = seq_wpr(P.gamma + 1, ns);
+  const int own = (ns + wpr - 1) / wpr;
+  if (P.mom_set) hipLaunchKernelGGL((k_seq<DT, 7, 1>), grid, block, 0, st, P);
+  else if (own == 1) hipLaunchKernelGGL((k_seq<DT, 0, 1>), grid, block, 0, st, P);
+  else if (own == 2) hipLaunchKernelGGL((k_seq<DT, 0, 2>), grid, block, 0, st, P);
+  else hipLaunchKernelGGL((k_seq<DT, 0, 4>), grid, block, 0, st, P);
+  hipError_t err = hipGetLastError();
+  if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, st);
+  return err;
+}
+
 // ================================================================ small problems
 // k_small: one launch for a batch whose rows fit in one workgroup's registers
 // (V up to kSmallThreads * kSmallU lane loads of VW entries).  grid (R),
@@ -3124,6 +3545,15 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st) {
   const unsigned groups = (unsigned)std::min<size_t>((n + 255) / 256, 1024);
   hipLaunchKernelGGL(k_fill_zero, dim3(groups), dim3(256), 0, st, static_cast<uint32_t*>(ptr), n);
   return hipGetLastError();
+}
+
+int seq_row_elems(int dtype) {
+  return kSeqSubs * (dtype == 1 ? SubC<1>::N : SubC<0>::N);
+}
+hipError_t launch_seq(const Params& P, int dtype, hipEvent_t ev_begin, hipEvent_t ev_end,
+                      hipStream_t st) {
+  return dtype == 1 ? launch_seq_t<1>(P, st, ev_begin, ev_end)
+                    : launch_seq_t<0>(P, st, ev_begin, ev_end);
 }
 
 int small_row_elems(int dtype) {

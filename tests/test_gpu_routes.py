@@ -51,3 +51,33 @@ def test_rows_do_not_depend_on_their_alignment(dtype, V):
     _, tok, _ = spc.spc_verify_ex(q, p, draft, u, W.OPT, 0.1, 1.0, out_row_stats=st)
     assert torch.equal(st, st[:1, :1].expand(B, g1, 8))
     assert torch.equal(tok, tok[:1].expand(B))
+
+
+# A workgroup per sequence: one to sixteen wavefronts a row, more rows than
+# wavefronts, one to four lane loads at a time, rows that end inside a lane
+# load, and the longest sequences it takes (few rows: 8192 entries, 4096 with
+# a second pass; many: 40960, 20480).
+@pytest.mark.parametrize("dtype,B,gamma,V", [
+    ("bf16", 3, 1, 2), ("f32", 3, 1, 3), ("bf16", 5, 15, 255), ("f32", 4, 16, 239),
+    ("bf16", 2, 63, 64), ("f32", 3, 2, 1365), ("bf16", 7, 7, 513), ("bf16", 3, 1, 4096),
+    ("f32", 3, 1, 2047), ("bf16", 300, 4, 1025), ("f32", 140, 4, 4095), ("bf16", 65, 7, 2559),
+    ("f32", 129, 1, 10239)])
+@pytest.mark.parametrize("rule", [W.DIFF, W.OPT, W.TOKEN_V2, W.LOSSY, W.BILD, W.OPTLOG])
+@pytest.mark.parametrize("greedy", [False, True])
+def test_short_sequences(dtype, B, gamma, V, rule, greedy):
+    wl = W.WORKLOADS[3].with_(B=B, gamma=gamma, V=V, dtype=dtype, rule=rule, alpha=0.1,
+                              temperature=0.0 if greedy else 0.7)
+    parity.parity_workload(wl, 1, step0=57, stats=V % 2 == 0, report_name=f"seq.{dtype}.{V}")
+
+
+@pytest.mark.parametrize("dtype,B,gamma,V", [("bf16", 12, 4, 800), ("f32", 90, 3, 5000)])
+def test_short_sequences_mixed(dtype, B, gamma, V):
+    """Per-sequence rules and temperatures, and an out-of-range draft."""
+    wl = W.WORKLOADS[5].with_(B=B, gamma=gamma, V=V, dtype=dtype)
+    inp = W.generate(wl, 3, DEV)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    inp["rule"] = torch.randint(0, 13, (B,), generator=g, device=DEV, dtype=torch.int32)
+    inp["draft"][1] = V + 3
+    a = parity.run_gpu(inp, per_seq=True)
+    h = parity.host_inputs(inp)
+    parity.compare(a, parity.run_oracle(h), h, dtype)
