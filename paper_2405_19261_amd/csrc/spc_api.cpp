@@ -327,12 +327,19 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
   const bool tok_rows = may_sample && (rules & kTok);
   const bool full = b_launch * g1 > (int64_t)cus;
   const int64_t seq_most = !full ? (tv_rows || tok_rows ? 4096 : 8192)
-                           : tv_rows || need_mom || !may_sample ? 20480 : 40960;
+                           : tv_rows || need_mom || !may_sample ? 20480
+                                                                : 40960;
   const bool seq = V <= spc::seq_row_elems(dtype) && g1 * V <= seq_most && B <= 2 * (int64_t)cus;
   // Other small problems (rows that fit one workgroup's registers, at most two
   // rows per compute unit, no first moments): one launch, a workgroup per row.
+  // Without a second pass, rows of more than 24576 entries are faster as
+  // statistics tiles and a draw pass when their tiles fit the chip at once
+  // (bfloat16 B=8 gamma=4: V=32128 20.7 as rows, 17.5 as tiles, V=24001 17.5
+  // and 18.4, V=20000 17.0 and 17.8).
   const bool small = !seq && !need_mom && V <= spc::small_row_elems(dtype) &&
-                     b_launch * g1 <= 2 * (int64_t)cus;
+                     b_launch * g1 <= 2 * (int64_t)cus &&
+                     (V <= 24576 || tv_rows || tok_rows || !may_sample ||
+                      b_launch * g1 * stat_tiles(dtype, V) > 4 * (int64_t)cus);
   const int64_t nt = stat_tiles(dtype, V);
   const int64_t eb = dtype == SPC_BF16 ? 2 : 4;
 

@@ -101,23 +101,44 @@ struct LaneVec<1> {  // bfloat16
   typedef u32x4 type __attribute__((aligned(2)));
 };
 
-// The first `n` < VW entries of a lane load at `a`, the others -inf: the lane
-// load that holds a row's last entries where the vocabulary is no multiple
-// of VW.  Read entry by entry, so nothing past the row is touched.
+// The lane load that a row ends in, where the vocabulary is no multiple of
+// VW: its n entries (0 < n < VW), the others -inf.  x holds the row's last VW
+// entries (nothing past the row is read); they move down by VW - n places.  A
+// row of fewer than VW entries is read entry by entry from `row`.
 template <int DT>
-__device__ __forceinline__ void load_partial(const char* a, int n, uint32_t (&x)[4]) {
-  if constexpr (DT == 1) {
-    const uint16_t* s = reinterpret_cast<const uint16_t*>(a);
+__device__ __forceinline__ void lane_tail(const char* row, int V, int n, uint32_t (&x)[4]) {
+  constexpr int VW = Tile<DT, 1>::VW;
+  if (V >= VW) {  // uniform, as n
+    constexpr uint32_t kPad = DT == 1 ? 0xff80ff80u : 0xff800000u;
+    const int shift = (VW - n) * Tile<DT, 1>::EB;  // bytes
+    if (shift & 8) {
+      x[0] = x[2];
+      x[1] = x[3];
+      x[2] = x[3] = kPad;
+    }
+    if (shift & 4) {
+      x[0] = x[1];
+      x[1] = x[2];
+      x[2] = x[3];
+      x[3] = kPad;
+    }
+    if (shift & 2) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t lo = 2 * j < n ? (uint32_t)s[2 * j] : 0xff80u;
-      const uint32_t hi = 2 * j + 1 < n ? (uint32_t)s[2 * j + 1] : 0xff80u;
-      x[j] = lo | (hi << 16);
+      for (int j = 0; j < 4; ++j)
+        x[j] = __builtin_amdgcn_alignbyte(j < 3 ? x[j + 1] : kPad, x[j], 2);
     }
   } else {
-    const uint32_t* s = reinterpret_cast<const uint32_t*>(a);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) x[j] = j < n ? s[j] : 0xff800000u;
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (DT == 1) {
+        const uint16_t* s = reinterpret_cast<const uint16_t*>(row);
+        const uint32_t lo = 2 * j < n ? (uint32_t)s[2 * j] : 0xff80u;
+        const uint32_t hi = 2 * j + 1 < n ? (uint32_t)s[2 * j + 1] : 0xff80u;
+        x[j] = lo | (hi << 16);
+      } else {
+        x[j] = j < n ? reinterpret_cast<const uint32_t*>(row)[j] : 0xff800000u;
+      }
+    }
   }
 }
 
@@ -126,11 +147,10 @@ __device__ __forceinline__ void load_partial(const char* a, int n, uint32_t (&x)
 // e = t0 + (i*GT + t) * VW .. + VW - 1 (interleaved, so each load
 // instruction of a wavefront reads one contiguous 1 KiB).  Addresses are a
 // uniform base plus a 32-bit lane offset.  Only issues the loads: a lane
-// whose lane load is not wholly before `end` reads other entries (the tile's
-// first ones; the row's first ones where the tile holds no whole lane load;
-// `safe`, any 16 readable bytes, where the row holds none), which mask_tile
-// replaces.  The two are apart so that a caller issues every load of both
-// tensors before anything branches or waits on their values.
+// whose lane load is not wholly before `end` reads the last VW entries before
+// it (`safe`, any 16 readable bytes, where the row has fewer), which mask_tile
+// then puts right.  The two are apart so that a caller issues every load of
+// both tensors before anything branches or waits on their values.
 template <int DT, int U, bool NT, int GT = kThreads>
 __device__ __forceinline__ void load_tile(const char* row, int64_t t0, int64_t end,
                                           uint32_t (&w)[U][Tile<DT, U>::NW], int tid,
@@ -139,13 +159,13 @@ __device__ __forceinline__ void load_tile(const char* row, int64_t t0, int64_t e
   using LV = typename LaneVec<DT>::type;
   constexpr int kSpan = GT * U * T::VW;  // entries of a whole tile
   const int left = (int)(end - t0 < (int64_t)kSpan ? end - t0 : (int64_t)kSpan);
-  const char* base = left >= T::VW ? row + t0 * T::EB
-                     : end >= T::VW ? row : static_cast<const char*>(safe);
+  const bool some = t0 + left >= T::VW;
+  const char* base = some ? row + t0 * T::EB : static_cast<const char*>(safe);
+  const int last = some ? left - T::VW : 0;
 #pragma unroll
   for (int i = 0; i < U; ++i) {
     const int e = (i * GT + tid) * T::VW;
-    const LV* src =
-        reinterpret_cast<const LV*>(base + (uint32_t)((e + T::VW <= left ? e : 0) * T::EB));
+    const LV* src = reinterpret_cast<const LV*>(base + min(e, last) * T::EB);
     const u32x4 v = NT ? __builtin_nontemporal_load(src) : *src;
     w[i][0] = v.x;
     w[i][1] = v.y;
@@ -155,8 +175,7 @@ __device__ __forceinline__ void load_tile(const char* row, int64_t t0, int64_t e
 }
 
 // After load_tile: entries at or past `end` become -inf.  Whole tiles take
-// one uniform branch.  Where the row ends inside a lane load, that load's
-// lane reads it entry by entry.
+// one uniform branch.
 template <int DT, int U, int GT = kThreads>
 __device__ __forceinline__ void mask_tile(const char* row, int64_t t0, int64_t end,
                                           uint32_t (&w)[U][Tile<DT, U>::NW], int tid) {
@@ -165,23 +184,22 @@ __device__ __forceinline__ void mask_tile(const char* row, int64_t t0, int64_t e
   constexpr int kSpan = GT * U * T::VW;
   if (end - t0 >= (int64_t)kSpan) return;
   const int left = (int)(end - t0);
+  const int n = left % T::VW, slot = left / T::VW;
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+    if (n != 0 && i == slot / GT) {  // uniform: the lane load the row ends in
+      uint32_t x[4];
+#pragma unroll
+      for (int j = 0; j < T::NW; ++j) x[j] = w[i][j];
+      lane_tail<DT>(row, end < T::VW ? (int)end : T::VW, n, x);
+#pragma unroll
+      for (int j = 0; j < T::NW; ++j) w[i][j] = tid == slot % GT ? x[j] : w[i][j];
+    }
 #pragma unroll
   for (int i = 0; i < U; ++i) {
-    const bool ok = (i * GT + tid) * T::VW + T::VW <= left;
+    const bool ok = (i * GT + tid) * T::VW < left;
 #pragma unroll
     for (int j = 0; j < T::NW; ++j) w[i][j] = ok ? w[i][j] : kPad;
-  }
-  if (left % T::VW != 0) {  // uniform
-    const int slot = left / T::VW;
-    if (tid == slot % GT) {
-      uint32_t x[4];
-      load_partial<DT>(row + (t0 + slot * T::VW) * T::EB, left % T::VW, x);
-#pragma unroll
-      for (int i = 0; i < U; ++i)
-        if (i == slot / GT)
-#pragma unroll
-          for (int j = 0; j < T::NW; ++j) w[i][j] = x[j];
-    }
   }
 }
 
@@ -2643,11 +2661,15 @@ __device__ __forceinline__ bool seq_draw(const Params& P, int b, int f, const Se
   return true;
 }
 
-// Sub-chunks of a row, and the wavefronts that read it: one per four
-// sub-chunks, at most 16 / (gamma + 1).
+// Sub-chunks of a row, the most of them a wavefront takes at a time, and the wavefronts that read a row: one per
+// that many, at most 16 / (gamma + 1).
 __host__ __device__ constexpr int seq_subs(int V, int sub) { return (V + sub - 1) / sub; }
+template <int DT>
+constexpr int kSeqU = 4;
+template <int DT>
 __host__ __device__ constexpr int seq_wpr(int g1, int ns) {
-  const int most = g1 >= kSeqWaves ? 1 : kSeqWaves / g1, want = (ns + 3) / 4;
+  const int most = g1 >= kSeqWaves ? 1 : kSeqWaves / g1;
+  const int want = (ns + kSeqU<DT> - 1) / kSeqU<DT>;
   return want < most ? want : most;
 }
 
@@ -2658,8 +2680,8 @@ __global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
   constexpr int EB = StatTile<DT>::EB;
   const int b = blockIdx.x, gamma = P.gamma, g1 = gamma + 1, V = P.V;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wpr = seq_wpr(g1, seq_subs(V, SubC<DT>::N));  // wavefronts per row
-  const int rpp = kSeqWaves / wpr;                        // rows at a time
+  const int wpr = seq_wpr<DT>(g1, seq_subs(V, SubC<DT>::N));  // wavefronts per row
+  const int rpp = kSeqWaves / wpr;                            // rows at a time
   const int slot = wv / wpr, wi = wv % wpr;
   const int jend = slot < rpp ? g1 : 0;
   const SeqParam sp = seq_param(P, b);
@@ -2788,11 +2810,14 @@ __global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
       const char* prow = (const char*)P.p + (r0 + j) * V * EB;
       const ProbScale ps = prob_scale(sp, sh.rs[j], tok);
       double acc = 0.0;
-      seq_chunks<DT, C>(qrow, prow, V, wi, wpr, P.hdr,
-                        [&](ChunkRegs<C>& q, ChunkRegs<C>& p, int) {
-                          acc += tok ? pass2_sum<DT, U, true>(q, p, ps)
-                                     : pass2_sum<DT, U, false>(q, p, ps);
-                        });
+      // (two lane loads at a time: four spill beside the rest of the step)
+      constexpr int U2 = U < 2 ? U : 2;
+      using C2 = Chunk<DT, U2>;
+      seq_chunks<DT, C2>(qrow, prow, V, wi, wpr, P.hdr,
+                         [&](ChunkRegs<C2>& q, ChunkRegs<C2>& p, int) {
+                           acc += tok ? pass2_sum<DT, U2, true>(q, p, ps)
+                                      : pass2_sum<DT, U2, false>(q, p, ps);
+                         });
       acc = wave_sum(acc);
       if (lane == 0) sh.tv[j * wpr + wi] = acc;
     }
@@ -2851,13 +2876,17 @@ hipError_t launch_seq_t(const Params& P, hipStream_t st, hipEvent_t ev_begin, hi
   }
   const dim3 grid((unsigned)P.B), block(kSeqThreads);
   // lane loads a wavefront takes at a time: those of its share of a row, up
-  // to four (one with first moments, whose sums take the registers)
-  const int ns = seq_subs(P.V, SubC<DT>::N), wpr = seq_wpr(P.gamma + 1, ns);
+  // to kSeqU (one with first moments, whose sums take the registers)
+  const int ns = seq_subs(P.V, SubC<DT>::N), wpr = seq_wpr<DT>(P.gamma + 1, ns);
   const int own = (ns + wpr - 1) / wpr;
-  if (P.mom_set) hipLaunchKernelGGL((k_seq<DT, 7, 1>), grid, block, 0, st, P);
-  else if (own == 1) hipLaunchKernelGGL((k_seq<DT, 0, 1>), grid, block, 0, st, P);
-  else if (own == 2) hipLaunchKernelGGL((k_seq<DT, 0, 2>), grid, block, 0, st, P);
-  else hipLaunchKernelGGL((k_seq<DT, 0, 4>), grid, block, 0, st, P);
+  if (P.mom_set)
+    hipLaunchKernelGGL((k_seq<DT, 7, 1>), grid, block, 0, st, P);
+  else if (own == 1)
+    hipLaunchKernelGGL((k_seq<DT, 0, 1>), grid, block, 0, st, P);
+  else if (own == 2)
+    hipLaunchKernelGGL((k_seq<DT, 0, 2>), grid, block, 0, st, P);
+  else
+    hipLaunchKernelGGL((k_seq<DT, 0, kSeqU<DT>>), grid, block, 0, st, P);
   hipError_t err = hipGetLastError();
   if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, st);
   return err;
@@ -2926,22 +2955,23 @@ template <int DT>
 using SmallRegs = uint32_t[kSmallU][Tile<DT, kSmallU>::NW];
 
 // Thread t's lane load i of a row (entries (i * 1024 + t) * VW ..), raw: a
-// lane load not wholly inside the row reads the row's first entries instead
-// (`safe`, 16 readable bytes, where the row holds no whole lane load).  The
-// passes read a lane load wholly past the row as -inf through small_elem;
-// small_tail fills the one the row ends in.  Keeping the raw words, rather
-// than selecting the padding once, spares the registers of a second copy.
+// lane load not wholly inside the row reads the row's last VW entries instead
+// (`safe`, 16 readable bytes, where the row has fewer).  The passes read a
+// lane load wholly past the row as -inf through small_elem; small_tail puts
+// the one the row ends in right.  Keeping the raw words, rather than
+// selecting the padding once, spares the registers of a second copy.
 template <int DT>
 __device__ __forceinline__ void small_load(const char* row, int V, SmallRegs<DT>& w,
                                            const void* safe) {
   using T = Tile<DT, kSmallU>;
   using LV = typename LaneVec<DT>::type;
   const char* base = V >= T::VW ? row : static_cast<const char*>(safe);
+  const int last = V >= T::VW ? V - T::VW : 0;
 #pragma unroll
   for (int i = 0; i < kSmallU; ++i) {
     const int e = (i * kSmallThreads + (int)threadIdx.x) * T::VW;
     const u32x4 v = __builtin_nontemporal_load(
-        reinterpret_cast<const LV*>(base + (uint32_t)((e + T::VW <= V ? e : 0) * T::EB)));
+        reinterpret_cast<const LV*>(base + (uint32_t)(min(e, last) * T::EB)));
     w[i][0] = v.x;
     w[i][1] = v.y;
     w[i][2] = v.z;
@@ -2954,13 +2984,16 @@ __device__ __forceinline__ void small_tail(const char* row, int V, SmallRegs<DT>
   if (V % T::VW == 0) return;  // uniform
   const int slot = V / T::VW;
   if ((int)threadIdx.x == slot % kSmallThreads) {
-    uint32_t x[4];
-    load_partial<DT>(row + (uint32_t)(slot * T::VW * T::EB), V % T::VW, x);
+    uint32_t x[4] = {};
 #pragma unroll
     for (int i = 0; i < kSmallU; ++i)
-      if (i == slot / kSmallThreads)
 #pragma unroll
-        for (int j = 0; j < T::NW; ++j) w[i][j] = x[j];
+      for (int j = 0; j < T::NW; ++j) x[j] = i == slot / kSmallThreads ? w[i][j] : x[j];
+    lane_tail<DT>(row, V, V % T::VW, x);
+#pragma unroll
+    for (int i = 0; i < kSmallU; ++i)
+#pragma unroll
+      for (int j = 0; j < T::NW; ++j) w[i][j] = i == slot / kSmallThreads ? x[j] : w[i][j];
   }
 }
 

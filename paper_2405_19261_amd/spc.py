@@ -98,14 +98,30 @@ def _dtype_code(t):
     raise TypeError(f"logits must be float32 or bfloat16, not {t.dtype}")
 
 
+# A call's host side is a few microseconds, as long as the kernel of a small
+# step, so it takes addresses as plain integers (the declared argument types
+# convert them), names C functions once, and reads the current stream's handle
+# without building a Stream object: torch.cuda.current_stream() alone took
+# 2.6 us of a 9.1 us call (B = 1, gamma = 4, V = 1000), which takes HOSTUS now.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = None  # the current stream's handle, once torch has been asked for a stream
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream()
+    handle = torch.cuda.current_stream().cuda_stream  # (initialises torch's HIP state)
+    device, current = (getattr(torch._C, n, None)
+                       for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
+    if device is not None and current is not None:
+        _raw_stream = lambda: current(device())  # noqa: E731
+    return handle
 
 
 def _check(status):
@@ -113,25 +129,24 @@ def _check(status):
         raise SpcError(status, lib().spc_last_error().decode())
 
 
-def _outputs(q, B, gamma, out):
-    if out is not None:
-        return out
-    dev = q.device
+def _outputs(dev, B, gamma):
     return (torch.empty(B, dtype=torch.int32, device=dev),
             torch.empty(B, dtype=torch.int32, device=dev),
             torch.empty((B, gamma + 1), dtype=torch.uint8, device=dev))
 
 
 def _shape(q, p, draft):
-    if q.dim() != 3 or q.shape != p.shape or q.dtype != p.dtype:
+    qs = q.shape
+    if len(qs) != 3 or qs != p.shape or q.dtype != p.dtype:
         raise ValueError("q and p must both be [B, gamma+1, V] of one dtype")
     if not (q.is_contiguous() and p.is_contiguous()):
         raise ValueError("inputs must be contiguous")
-    if p.device != q.device:
+    dev = q.device
+    if p.device != dev:
         raise ValueError("q and p must be on one device")
-    B, g1, V = q.shape
-    _check_arg("draft", draft, torch.int32, q.device, (B, g1 - 1))
-    return B, g1 - 1, V
+    B, g1, V = qs
+    _check_arg("draft", draft, torch.int32, dev, (B, g1 - 1))
+    return B, g1 - 1, V, dev
 
 
 def _check_arg(name, t, dtype, device, shape=None):
@@ -144,15 +159,15 @@ def _check_arg(name, t, dtype, device, shape=None):
         raise ValueError(f"{name} must be on {device}, not {t.device}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, not {tuple(t.shape)}")
 
 
 def spc_verify(q, p, draft, uniforms, rule, alpha, temperature, out=None, stream=None):
     """One verify step; returns (accept_len [B], next_token [B], defer_mask [B, gamma+1])."""
-    B, gamma, V = _shape(q, p, draft)
-    _check_arg("uniforms", uniforms, torch.float32, q.device, (B, gamma + 1))
-    acc, tok, dm = _outputs(q, B, gamma, out)
+    B, gamma, V, dev = _shape(q, p, draft)
+    _check_arg("uniforms", uniforms, torch.float32, dev, (B, gamma + 1))
+    acc, tok, dm = out if out is not None else _outputs(dev, B, gamma)
     _check(lib().spc_verify(_ptr(q), _ptr(p), _dtype_code(q), _ptr(draft), _ptr(uniforms), B,
                             gamma, V, int(rule), float(alpha), float(temperature), _ptr(acc),
                             _ptr(tok), _ptr(dm), _stream(stream)))
@@ -161,8 +176,8 @@ def spc_verify(q, p, draft, uniforms, rule, alpha, temperature, out=None, stream
 
 def spc_greedy_verify(q, p, draft, rule, alpha, out=None, stream=None):
     """The temperature-0 step; returns (accept_len, next_token, defer_mask)."""
-    B, gamma, V = _shape(q, p, draft)
-    acc, tok, dm = _outputs(q, B, gamma, out)
+    B, gamma, V, dev = _shape(q, p, draft)
+    acc, tok, dm = out if out is not None else _outputs(dev, B, gamma)
     _check(lib().spc_greedy_verify(_ptr(q), _ptr(p), _dtype_code(q), _ptr(draft), B, gamma, V,
                                    int(rule), float(alpha), _ptr(acc), _ptr(tok), _ptr(dm),
                                    _stream(stream)))
@@ -177,8 +192,7 @@ def _verify_ex(entry, q, p, draft, uniforms, rule, alpha, temperature, rule_per_
     rules_present: bitmask of the rule ids rule_per_seq may hold (0 = any).
     ev_tiles: for profiling, a pair of raw hipEvent_t handles (integers)
     recorded around the statistics kernel of the call's first launch."""
-    B, gamma, V = _shape(q, p, draft)
-    dev = q.device
+    B, gamma, V, dev = _shape(q, p, draft)
     _check_arg("uniforms", uniforms, torch.float32, dev, (B, gamma + 1))
     _check_arg("rule_per_seq", rule_per_seq, torch.int32, dev, (B,))
     _check_arg("alpha_per_seq", alpha_per_seq, torch.float32, dev, (B,))
@@ -186,20 +200,13 @@ def _verify_ex(entry, q, p, draft, uniforms, rule, alpha, temperature, rule_per_
     _check_arg("out_row_stats", out_row_stats, torch.float32, dev, (B, gamma + 1, 8))
     _check_arg("out_argmax", out_argmax, torch.int32, dev, (B, gamma + 1, 2))
     _check_arg("out_sample_norm", out_sample_norm, torch.float32, dev, (B,))
-    acc, tok, dm = _outputs(q, B, gamma, out)
-    ex = ExArgs()
-    ex.rule_per_seq = _ptr(rule_per_seq)
-    ex.alpha_per_seq = _ptr(alpha_per_seq)
-    ex.temp_per_seq = _ptr(temp_per_seq)
-    ex.out_row_stats = _ptr(out_row_stats)
-    ex.out_argmax = _ptr(out_argmax)
-    ex.out_sample_norm = _ptr(out_sample_norm)
-    if workspace is not None:
-        if workspace.device != dev or not workspace.is_contiguous():
-            raise ValueError("workspace must be a contiguous tensor on the logits' device")
-        ex.workspace = _ptr(workspace)
-        ex.workspace_bytes = workspace.numel() * workspace.element_size()
-    ex.rules_present = int(rules_present)
+    acc, tok, dm = out if out is not None else _outputs(dev, B, gamma)
+    if workspace is not None and (workspace.device != dev or not workspace.is_contiguous()):
+        raise ValueError("workspace must be a contiguous tensor on the logits' device")
+    ex = ExArgs(_ptr(rule_per_seq), _ptr(alpha_per_seq), _ptr(temp_per_seq), _ptr(out_row_stats),
+                _ptr(out_argmax), _ptr(out_sample_norm), _ptr(workspace),
+                0 if workspace is None else workspace.numel() * workspace.element_size(),
+                int(rules_present))
     if ev_tiles is not None:
         ex.ev_tiles_begin, ex.ev_tiles_end = int(ev_tiles[0]), int(ev_tiles[1])
     _check(getattr(lib(), entry)(_ptr(q), _ptr(p), _dtype_code(q), _ptr(draft), _ptr(uniforms), B,
