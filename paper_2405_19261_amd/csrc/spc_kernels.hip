@@ -2542,24 +2542,37 @@ __device__ __forceinline__ void seq_sum(ChunkRegs<C>& wq, ChunkRegs<C>& wp, int 
   }
   seq_fence<C>(wq, wp);
   const float rq = nq == kNegInf ? 0.0f : nq * sp.c_hi, rp = np == kNegInf ? 0.0f : np * sp.c_hi;
-  float tq = 0.0f, tp = 0.0f, hq = 0.0f, hp = 0.0f, x = 0.0f;
+  // (float pairwise within a lane load, fp64 across them)
+  double tq = 0.0, tp = 0.0;
+  float hq = 0.0f, hp = 0.0f, x = 0.0f;
 #pragma unroll
-  for (int i = 0; i < C::U; ++i)
+  for (int i = 0; i < C::U; ++i) {
+    float eq[C::VW], ep[C::VW];
 #pragma unroll
     for (int e = 0; e < C::VW; ++e) {
       const float zq = elem<DT>(wq[i], e), zp = elem<DT>(wp[i], e);
       const float aq = fmaf(zq, sp.c_lo, fmaf(zq, sp.c_hi, -rq));
       const float ap = fmaf(zp, sp.c_lo, fmaf(zp, sp.c_hi, -rp));
-      const float eq = exp2_hw(aq), ep = exp2_hw(ap);
-      tq += eq;
-      tp += ep;
+      eq[e] = exp2_hw(aq);
+      ep[e] = exp2_hw(ap);
       if constexpr (MOM) {
-        hq = fmaf(eq, eq > 0.0f ? aq : 0.0f, hq);
-        x = fmaf(eq, eq > 0.0f ? ap : 0.0f, x);
-        hp = fmaf(ep, ep > 0.0f ? ap : 0.0f, hp);
+        hq = fmaf(eq[e], eq[e] > 0.0f ? aq : 0.0f, hq);
+        x = fmaf(eq[e], eq[e] > 0.0f ? ap : 0.0f, x);
+        hp = fmaf(ep[e], ep[e] > 0.0f ? ap : 0.0f, hp);
       }
       if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int h = 1; h < C::VW; h <<= 1)
+#pragma unroll
+      for (int e = 0; e + h < C::VW; e += 2 * h) {
+        eq[e] += eq[e + h];
+        ep[e] += ep[e + h];
+      }
+    tq += (double)eq[0];
+    tp += (double)ep[0];
+    __builtin_amdgcn_sched_barrier(0);
+  }
   // the earlier chunks' sums move to the new references
   const double gq = a.mq == kNegInf ? 0.0 : (double)(a.mq * sp.c_hi) - (double)rq;
   const double gp = a.mp == kNegInf ? 0.0 : (double)(a.mp * sp.c_hi) - (double)rp;
@@ -2569,8 +2582,8 @@ __device__ __forceinline__ void seq_sum(ChunkRegs<C>& wq, ChunkRegs<C>& wp, int 
     a.hp = mom_move(a.hp, a.sp, fp, gp) + (double)hp;
     a.x = mom_move(a.x, a.sq, fq, gp) + (double)x;
   }
-  a.sq = a.sq * fq + (double)tq;
-  a.sp = a.sp * fp + (double)tp;
+  a.sq = a.sq * fq + tq;
+  a.sp = a.sp * fp + tp;
   a.mq = nq;
   a.mp = np;
 }
@@ -3404,9 +3417,11 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
   __shared__ Shared sh;
   __shared__ RowStat srow;
   __shared__ PickState pks;
+  __shared__ TilePart only;
   const int k = blockIdx.x, b = blockIdx.y;
   const SeqParam sp = seq_param(P, b);
-  const int V = P.V;
+  const int V = P.V, nt = P.nt;
+  const float u = sp.valid && !sp.greedy ? P.uniforms[b] : 0.0f;
   const char* row = (const char*)P.q + (int64_t)b * V * T::EB;
   const int64_t t0 = (int64_t)k * T::N;
   uint32_t w[T::U][T::NW];
@@ -3478,24 +3493,32 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
     }
     TilePart t{tot, 0.0, (M == kNegInf) ? kNegInf : R, kNegInf, M, kNegInf,
                ARGMAX ? am : -1, -1};
-    st_tile(P.tiles + (int64_t)b * P.nt + k, t);
+    if (nt == 1) only = t;  // the row's only tile: no one else reads it
+    else st_tile(P.tiles + (int64_t)b * nt + k, t);
   }
-  if (!arrive_last(P.samp_cnt + (int64_t)b * kDraftCntStride, (uint32_t)P.nt, sh)) return;
-  // the last tile of row b: merge the row (wave 0, a tile per lane)
+  if (nt == 1) __syncthreads();  // block-uniform
+  else if (!arrive_last(P.samp_cnt + (int64_t)b * kDraftCntStride, (uint32_t)nt, sh)) return;
+  // the last tile of row b: merge the row (wave 0, lane l tiles l, l + 64, ..;
+  // each lane's first tile is read once, for the merge and the draw)
+  TilePart h0{0.0, 0.0, kNegInf, kNegInf, kNegInf, kNegInf, 0x7fffffff, 0x7fffffff};
   if (threadIdx.x < 64) {
-    TilePart h{0.0, 0.0, kNegInf, kNegInf, kNegInf, kNegInf, 0x7fffffff, 0x7fffffff};
-    float zq = kNegInf, rq = kNegInf;
-    for (int kk = lane; kk < P.nt; kk += 64) {
-      const TilePart tk = ld_tile(P.tiles + (int64_t)b * P.nt + kk);
+    if (nt == 1) {
+      if (lane == 0) h0 = only;
+    } else if (lane < nt) {
+      h0 = ld_tile(P.tiles + (int64_t)b * nt + lane);
+    }
+    float zq = h0.zmax_q, rq = h0.r_q;
+    for (int kk = lane + 64; kk < nt; kk += 64) {
+      const TilePart tk = ld_tile(P.tiles + (int64_t)b * nt + kk);
       zq = fmaxf(zq, tk.zmax_q);
       rq = fmaxf(rq, tk.r_q);
     }
     zq = wave_max(zq);
     rq = wave_max(rq);
-    double sq = 0.0;
-    int aq = 0x7fffffff;
-    for (int kk = lane; kk < P.nt; kk += 64) {
-      h = ld_tile(P.tiles + (int64_t)b * P.nt + kk);
+    double sq = h0.s_q * exp2_acc((double)h0.r_q - (double)rq);
+    int aq = ARGMAX && lane < nt && h0.zmax_q == zq ? h0.amax_q : 0x7fffffff;
+    for (int kk = lane + 64; kk < nt; kk += 64) {
+      const TilePart h = ld_tile(P.tiles + (int64_t)b * nt + kk);
       sq += h.s_q * exp2_acc((double)h.r_q - (double)rq);
       if (ARGMAX && h.zmax_q == zq) aq = min(aq, h.amax_q);
     }
@@ -3518,7 +3541,17 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
   if (threadIdx.x < 64) {
     int ks;
     double rem;
-    find_part<kSrcDraft>(P, b, b, P.nt, rs, P.uniforms[b], &ks, &rem);
+    if (nt <= 64) {
+      // one tile per lane, already read: find_part's search
+      const double m = lane < nt ? h0.s_q * exp2_acc((double)h0.r_q - rs.lz_q) : 0.0;
+      const double target = (double)u * wave_sum(m);
+      const double incl = wave_incl_scan(m);
+      const unsigned long long pos = __ballot(m > 0.0), hit = __ballot(m > 0.0 && incl > target);
+      ks = hit ? __ffsll(hit) - 1 : pos ? 63 - __clzll(pos) : -1;
+      rem = hit ? target - (lane_f64(incl, ks) - lane_f64(m, ks)) : __builtin_huge_val();
+    } else {
+      find_part<kSrcDraft>(P, b, b, nt, rs, u, &ks, &rem);
+    }
     if (threadIdx.x == 0) {
       pks = PickState{ks, kQ, kSrcDraft, rem};
       if (ks < 0) P.out_token[b] = -1;

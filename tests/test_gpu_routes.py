@@ -1,8 +1,10 @@
 """The kernels' routes at the sizes where each can go wrong, against the fp64
 oracle (needs an MI355X)."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import parity
 from paper_2405_19261_amd import spc
 from paper_2405_19261_amd import workloads as W
@@ -81,3 +83,18 @@ def test_short_sequences_mixed(dtype, B, gamma, V):
     a = parity.run_gpu(inp, per_seq=True)
     h = parity.host_inputs(inp)
     parity.compare(a, parity.run_oracle(h), h, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [3, 4096, 4097, 8192, 8193, 64 * 8192 + 5, 65 * 4096])
+@pytest.mark.parametrize("T", [1.0, 0.0])
+def test_drafter_rows_of_one_tile_and_of_many(dtype, V, T):
+    """One tile (nothing published), two, and either side of a tile per lane."""
+    wl = W.WORKLOADS[3].with_(B=9, V=V, dtype=dtype)
+    z = W.generate(wl, 6, DEV)["q"][:, 0].contiguous()
+    u = torch.rand(9, generator=torch.Generator(device=DEV).manual_seed(2), device=DEV)
+    tok = spc.spc_draft_sample(z, T, uniforms=u).cpu().numpy()
+    o_tok, o_margin = oracle.draft_sample(parity.host_logits(z), np.full(9, T, np.float32),
+                                          u.cpu().numpy())
+    for g, o, m in zip(tok, o_tok, o_margin):
+        assert g == o or m < parity.NEAR, (g, o, m)
