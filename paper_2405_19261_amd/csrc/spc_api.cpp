@@ -83,9 +83,8 @@ WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype) {
   L.rowline = o;
   o = align_up(o + 4 * (size_t)(kMaxRows * kLineWords), 256);
   L.zero_end = o;
-  // the job pass's list: at most R nt TV tiles handed back by their
-  // workgroups or R nt 4 TV or eta slices (a row has one kind), and 2 R + B
-  // spare
+  // the job pass's list: at most R nt 4 TV or eta slices (a row has one
+  // kind), and 2 R + B spare
   L.jobs = o; o = align_up(o + 8 * (size_t)(2 * R + B + R * nt * kSlices), 256);
   L.tiles = o; o = align_up(o + sizeof(TilePart) * R * nt, 256);
   L.tvpart = o; o = align_up(o + sizeof(double) * R * nt * kSlices, 256);
@@ -109,7 +108,7 @@ namespace {
 // Bound of a statistics workgroup's wait for a TV row's merge, in ticks of
 // the 100 MHz real-time clock: 4000 (40 us).  SPC_TV_WAIT_TICKS overrides it
 // (read at every call); a test sets 0 so that every wait gives up at once
-// and the job pass takes the tiles.
+// and the rows' merges take the tiles.
 uint32_t tv_wait_ticks() {
   const char* e = getenv("SPC_TV_WAIT_TICKS");
   if (!e || !*e) return 4000u;
@@ -377,19 +376,18 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     // kernel (k_tvpass) when the rule is batch-wide, so that most rows may
     // need it; with per-sequence rules (a few TV rows among others) their
     // slices are job-pass items (tv_jobs).
-    P.tv_self = (tv_rows && R * nt <= 2 * (int64_t)cus) ? 1 : 0;
+    P.tv_self = (tv_rows && R * nt <= 2 * (int64_t)cus && nt <= spc::kTvTiles) ? 1 : 0;
     // batches of at least 64 statistics tiles per compute unit stream two
     // tiles per workgroup (without first moments): B = 32 at the Gemma
     // vocabulary (32 per CU) is faster with one, B = 128 and 256 with two
     P.pair = (!P.tv_self && mom_set == 0 && R * nt >= 64 * (int64_t)cus) ? 1 : 0;
     P.tv_jobs = (tv_rows && !P.tv_self && per_rule) ? 1 : 0;
     const bool tv_pass = tv_rows && !P.tv_self && !P.tv_jobs;
-    // the job pass: eta slices, TV slices (tv_jobs), and the TV tiles whose wait for their row's merge timed out (tv_self)
-    const bool job_pass = (may_sample && (rules & kTok)) || P.tv_self || P.tv_jobs;
+    // the job pass: eta slices, and TV slices (tv_jobs)
+    const bool job_pass = (may_sample && (rules & kTok)) || P.tv_jobs;
     P.may_greedy = (force_greedy || per_temp) ? 1 : 0;
     P.wait_ticks = tv_wait_ticks();
-    // jobs: TV tiles whose wait timed out or TV slices, the
-    // slices of the tiles a token row lists for eta (a row has one kind)
+    // jobs: TV slices, or the slices of the tiles a token row lists for eta (a row has one kind)
     P.single_slots = 2 * R + bl + R * nt * spc::kSlices;
     P.nsub = (int32_t)(nt * spc::tile_subchunks(dtype));
     // workgroups of the job pass: a wavefront per item of its largest

@@ -124,7 +124,12 @@ constexpr int kHdrLines = kHdrExit + kExitLeaves + 1;
 // draw pass's arrivals for the sequence, the drafter kernel's per-row
 // arrivals, and the sequence's outcome for the draw pass.
 constexpr int kRowArrive = 0, kSeqMask = 2, kRowReady = 5, kRowTvArrive = 6, kSeqResArrive = 7,
-              kDraftArrive = 8, kSeqInfo = 9;
+              kDraftArrive = 8, kSeqInfo = 9, kRowGate = 10;
+// A TV row's gate where its own tiles wait for its merge (64 bits): merged
+// (take the TV pass), decided without one, and in the low bits the tiles whose
+// workgroups gave up waiting, so at most kTvTiles tiles a row.
+constexpr int kTvTiles = 62;
+constexpr uint64_t kTvReady = 1ull << 63, kTvSkip = 1ull << 62, kTvLost = kTvSkip - 1;
 // A sequence's outcome word (kSeqInfo): kSeqInfoSet | sample kind << 8 | j*.
 constexpr uint32_t kSeqInfoSet = 0x80000000u;
 

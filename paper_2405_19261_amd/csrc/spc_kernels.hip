@@ -1631,7 +1631,7 @@ __device__ __forceinline__ void tv_slice_regs_w(
 // eta second pass over a row and the residual masses of row j* of a sequence
 // are "row jobs" of nt chunks (one per tile); the two halves of a greedy
 // row's argmax and the draws from statistics partials are single chunks.
-enum JobKind : int { kJobTv = 1, kJobEta = 2, kJobTvTile = 6, kJobTvSlice = 7 };
+enum JobKind : int { kJobEta = 2, kJobTvSlice = 7 };
 
 // A job entry: kind (bits 60..63), an extra field (bits 32..59: the argmax
 // tensor, or a draw's sample kind and j*) and the row or sequence it belongs
@@ -1659,6 +1659,9 @@ __device__ __forceinline__ uint32_t* row_word(const Params& P, int64_t r, int w)
 }
 __device__ __forceinline__ uint64_t* seq_mask(const Params& P, int64_t b) {
   return reinterpret_cast<uint64_t*>(row_word(P, b, kSeqMask));
+}
+__device__ __forceinline__ uint64_t* row_gate(const Params& P, int64_t r) {
+  return reinterpret_cast<uint64_t*>(row_word(P, r, kRowGate));
 }
 __device__ __forceinline__ uint64_t lane_u64(uint64_t v, int l) {
   return ((uint64_t)(uint32_t)lane_i32((int)(v >> 32), l) << 32) |
@@ -1873,6 +1876,67 @@ __device__ __forceinline__ int row_decide_w(const Params& P, int r, int b, int j
   return f >= p_old ? f : -1;
 }
 
+// Wave: the row's decision once its TV, eta or argmax is known; when it
+// settles j*, the sequence's finish publishes to the next job pass.
+template <int DT>
+__device__ __forceinline__ void row_job_decide(const Params& P, int r) {
+  const int g1 = P.gamma + 1, np = P.nt * kSlices;
+  const int b = r / g1, j = r - b * g1;
+  RowStat rs = ld_rowstat(P.rowstat + r);
+  // the TV or eta partials of every slice, in slice order
+  double s = 0.0;
+  for (int k = threadIdx.x & 63; k < np; k += 64)
+    s += ld_dev_f64(P.tvpart + (int64_t)r * np + k);
+  rs.tv = wave_sum(s);
+  const SeqParam sp = seq_param(P, b);
+  int rec = 0;
+  const int f = row_decide_w<DT>(P, r, b, j, sp, rs, nullptr, &rec);
+  if (f >= 0) seq_finish_w<DT>(P, b, f, sp, rec);
+}
+
+// How the statistics tiles serve the TV pass (OPT / OPTLOG rows at T > 0):
+// not at all (the TV pass kernel takes it, or there is no TV row), or, in a
+// grid resident at once, on their own row from registers (tv_self).
+enum TvMode : int { kTvNone = 0, kTvSelf = 2 };
+
+// Wave: the last of the 4 nt slices of TV row rv arrived: its decision (and
+// the sequence's finish), then the row's flags are cleared for the next call.
+template <int DT>
+__device__ __forceinline__ void tv_row_done(const Params& P, int rv) {
+  row_job_decide<DT>(P, rv);
+  if ((threadIdx.x & 63) == 0) {
+    if (P.tv_self) st_u64(row_gate(P, rv), 0ull);
+    else st_u32(row_word(P, rv, kRowReady), 0u);
+  }
+}
+
+// Wave: n tiles of TV row rv arrive without a TV pass, the row having been
+// decided without one; the last arrival clears the gate for the next call.
+__device__ __forceinline__ void tv_skip_arrive_w(const Params& P, int rv, uint32_t n) {
+  if (arrive_last_w(row_word(P, rv, kRowTvArrive), (uint32_t)(kSlices * P.nt), kSlices * n) &&
+      (threadIdx.x & 63) == 0)
+    st_u64(row_gate(P, rv), 0ull);
+}
+
+// Wave (the row's merge): the TV pass of the tiles whose workgroups gave up
+// waiting, their entries read again.
+template <int DT>
+__device__ __forceinline__ void tv_take_over_w(const Params& P, int r, uint64_t lost, bool skip,
+                                               const SeqParam& sp) {
+  const uint32_t n = (uint32_t)__popcll(lost);
+  if (skip) {
+    tv_skip_arrive_w(P, r, n);
+    return;
+  }
+#pragma unroll 1
+  for (uint64_t m = lost; m; m &= m - 1)
+#pragma unroll 1
+    for (int w = 0; w < kSlices; ++w)
+      pass2_slice_w<DT, false>(P, r, __builtin_ctzll(m), w, sp);
+  if (arrive_last_w(row_word(P, r, kRowTvArrive), (uint32_t)(kSlices * P.nt), kSlices * n))
+    tv_row_done<DT>(P, r);
+}
+
 // Wave: the lowest indices of greedy row r's two maxima, from the starts of
 // the lane loads that hold them (rs.amax_q / amax_p), read again entry by
 // entry: lanes 0 .. 31 q's, lanes 32 .. 63 p's, one round trip.
@@ -1896,7 +1960,7 @@ __device__ __forceinline__ void arg_rows_w(const Params& P, int r, RowStat& rs) 
 // publish its second pass (TV, or eta for the tiles its statistics leave
 // open) or its argmax to the job pass, or decide it and, when that settles
 // j*, finish the sequence.
-template <int DT, int MS, bool GR>
+template <int DT, int MS, int TVM, bool GR>
 __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int j,
                                              const SeqParam& sp, int x) {
   const int lane = threadIdx.x & 63;
@@ -1920,13 +1984,20 @@ __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int 
       st_rowstat(P.rowstat + r, rs);
       if (!P.tv_jobs) {
         vmem_drain();
-        st_u32(row_word(P, r, kRowReady), 1u);
+        if (!P.tv_self) st_u32(row_word(P, r, kRowReady), 1u);
       }
     }
     // (with tv_jobs the row's TV slices are jobs of the job pass)
     if (!free && P.tv_jobs)
       publish_singles_w(P, kJobTvSlice, (uint32_t)r, (uint32_t)(nt * kSlices));
-    if (lane == 0 && free && P.tv_self) st_u32(row_word(P, r, kRowReady), 2u);
+    if constexpr (TVM == kTvSelf) {
+      // release the row's waiting workgroups; the tiles of those that gave up
+      // before are this wavefront's
+      uint64_t old = 0;
+      if (lane == 0) old = or_u64(row_gate(P, r), free ? kTvSkip : kTvReady);
+      const uint64_t lost = lane_u64(old, 0) & kTvLost;
+      if (lost) tv_take_over_w<DT>(P, r, lost, free, sp);
+    }
     if (!free) return;
     rs.tv = 1.0;  // any D_TV in [lo, 1] decides it alike
   }
@@ -1974,65 +2045,29 @@ __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int 
   if (f >= 0) seq_finish_w<DT>(P, b, f, sp, rec);
 }
 
-// Wave: the row's decision once its TV, eta or argmax is known; when it
-// settles j*, the sequence's finish publishes to the next job pass.
-template <int DT>
-__device__ __forceinline__ void row_job_decide(const Params& P, int r) {
-  const int g1 = P.gamma + 1, np = P.nt * kSlices;
-  const int b = r / g1, j = r - b * g1;
-  RowStat rs = ld_rowstat(P.rowstat + r);
-  // the TV or eta partials of every slice, in slice order
-  double s = 0.0;
-  for (int k = threadIdx.x & 63; k < np; k += 64)
-    s += ld_dev_f64(P.tvpart + (int64_t)r * np + k);
-  rs.tv = wave_sum(s);
-  const SeqParam sp = seq_param(P, b);
-  int rec = 0;
-  const int f = row_decide_w<DT>(P, r, b, j, sp, rs, nullptr, &rec);
-  if (f >= 0) seq_finish_w<DT>(P, b, f, sp, rec);
-}
-
-// The wait of a workgroup for a TV row's merge is bounded by P.wait_ticks of
-// the 100 MHz real-time clock (by default 4000: 40 us, far beyond the usual
-// wait); past it the tile goes to the job pass.
-
-// Wave: the last of the 4 nt slices of TV row rv arrived: its decision (and
-// the sequence's finish), then the row's ready
-// flag is cleared for the next call.
-template <int DT>
-__device__ __forceinline__ void tv_row_done(const Params& P, int rv) {
-  row_job_decide<DT>(P, rv);
-  if ((threadIdx.x & 63) == 0) st_u32(row_word(P, rv, kRowReady), 0u);
-}
-
-// Wait (bounded, thread 0) for the ready flag of TV row rv; block-uniform
-// result: 1 (merged, take the TV pass), 2 (decided without one) or 0 (timed
-// out: the job pass takes tile k of the row's TV pass).
+// Wait (bounded, thread 0) for the merge of TV row rv; block-uniform result: 1
+// (merged, take the TV pass), 2 (decided without one) or 0.  The wait is
+// bounded by P.wait_ticks of the 100 MHz real-time clock (by default 4000: 40
+// us, far beyond the usual wait); past it the workgroup marks its tile k in
+// the row's gate and leaves, and the wavefront that merges the row finds the
+// mark when it sets the outcome and takes the tile.  So nothing depends on
+// which workgroups are resident together.
 __device__ __forceinline__ uint32_t tv_wait_ready(const Params& P, int rv, int k, Shared& sh) {
   if (threadIdx.x == 0) {
-    const uint32_t* flag = row_word(P, rv, kRowReady);
-    uint32_t f = ld_u32(flag);
+    uint64_t* gate = row_gate(P, rv);
+    uint64_t f = ld_u64(gate);
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    while (f == 0u && __builtin_amdgcn_s_memrealtime() - t0 < (uint64_t)P.wait_ticks) {
+    while (!(f & (kTvReady | kTvSkip)) &&
+           __builtin_amdgcn_s_memrealtime() - t0 < (uint64_t)P.wait_ticks) {
       __builtin_amdgcn_s_sleep(4);
-      f = ld_u32(flag);
+      f = ld_u64(gate);
     }
-    sh.flag = (int)f;
-    if (f == 0u) publish_single(P, kJobTvTile, (uint32_t)k, (uint32_t)rv);
+    if (!(f & (kTvReady | kTvSkip))) f = or_u64(gate, 1ull << k);  // (set in between: taken)
+    sh.flag = (f & kTvReady) ? 1 : (f & kTvSkip) ? 2 : 0;
   }
   __syncthreads();
   return (uint32_t)sh.flag;
 }
-
-// Wave 0: a tile of TV row rv arrives (weight kSlices) without a TV pass,
-// the row having been decided without one (flag 2); the last arrival
-// clears the flag for the next call.
-__device__ __forceinline__ void tv_skip_arrive_w(const Params& P, int rv) {
-  if (arrive_last_w(row_word(P, rv, kRowTvArrive), (uint32_t)(kSlices * P.nt), kSlices) &&
-      (threadIdx.x & 63) == 0)
-    st_u32(row_word(P, rv, kRowReady), 0u);
-}
-
 
 // Whole block: the TV pass over tile k of the block's own row r from the
 // registers that hold the tile (small batches: every tile of the grid is
@@ -2047,7 +2082,7 @@ __device__ __forceinline__ void tv_self(
   const uint32_t f = tv_wait_ready(P, r, k, sh);  // block-uniform
   if (f == 0u) return;
   if (f == 2u) {
-    if (threadIdx.x < 64) tv_skip_arrive_w(P, r);
+    if (threadIdx.x < 64) tv_skip_arrive_w(P, r, 1u);
     return;
   }
   tv_slice_regs_w<DT>(P, r, k, threadIdx.x >> 6, sp, wq, wp);
@@ -2167,11 +2202,6 @@ __device__ __forceinline__ void draw_stats(const Params& P, int b, int64_t row, 
   else draw_tile<DT, kTokPi>(P, b, row, ks, rem, ps, dv);
 }
 
-// How the statistics tiles serve the TV pass (OPT / OPTLOG rows at T > 0):
-// not at all (the TV pass kernel takes it, or there is no TV row), or, in a
-// grid resident at once, on their own row from registers (tv_self).
-enum TvMode : int { kTvNone = 0, kTvSelf = 2 };
-
 // The statistics tiles.  grid (nt, R): tile k of row r, its logits read
 // non-temporally; with PAIR, grid (ceil(nt / 2), R) and tiles 2x and 2x + 1,
 // both loaded at once (large batches: half the arrivals, twice the bytes in
@@ -2235,7 +2265,7 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
     }
     if ((uint32_t)lane_i32((int)prev, 0) + n == (uint32_t)nt) {
       vmem_drain();
-      row_merged_w<DT, MS, GR>(P, r, b, j, sp, x);
+      row_merged_w<DT, MS, TVM, GR>(P, r, b, j, sp, x);
     }
   }
   if constexpr (TVM == kTvSelf) {
@@ -2358,9 +2388,8 @@ __device__ __forceinline__ void exit_tree(const Params& P) {
 }
 
 // The job pass: a static walk over the jobs the statistics kernel of this
-// call published: a slice of a TV row (batches of mixed rules), a slice of
-// a tile a token row listed for eta, a TV tile whose wait timed out, an
-// Wavefront w of the grid takes
+// call published: a slice of a TV row (batches of mixed rules), or a slice of
+// a tile a token row listed for eta.  Wavefront w of the grid takes
 // items w, w + W, ...  The item that completes a job decides its row; a
 // sequence that decision finishes is drawn by the draw pass that follows.
 // Held to 128 VGPRs: two workgroups per compute unit.
@@ -2397,20 +2426,7 @@ __global__ __launch_bounds__(kJobThreads) __attribute__((amdgpu_waves_per_eu(4))
       const uint64_t e = lane_u64(mine, i);
       const int kind = job_kind(e);
       const int id = (int)job_id(e);
-      if (kind == kJobTvTile) {
-        // a tile whose wait for its row's merge timed out: its four slices,
-        // unless the row was decided without a TV pass
-        if (ld_u32(row_word(P, id, kRowReady)) == 2u) {  // wave-uniform
-          tv_skip_arrive_w(P, id);
-          continue;
-        }
-        const SeqParam spt = seq_param(P, id / g1);
-#pragma unroll 1
-        for (int w = 0; w < kSlices; ++w)
-          pass2_slice_w<DT, false>(P, id, (int)job_extra(e), w, spt);
-        if (arrive_last_w(row_word(P, id, kRowTvArrive), (uint32_t)(kSlices * nt), kSlices))
-          tv_row_done<DT>(P, id);
-      } else if (kind == kJobTvSlice) {
+      if (kind == kJobTvSlice) {
         // slice x % 4 of tile x / 4 of TV row id
         const int x = (int)job_extra(e);
         pass2_slice_w<DT, false>(P, id, x / kSlices, x % kSlices, seq_param(P, id / g1));
