@@ -391,9 +391,6 @@ __device__ __forceinline__ uint32_t add_u32(uint32_t* p, uint32_t v) {
 __device__ __forceinline__ uint32_t xchg_u32(uint32_t* p, uint32_t v) {
   return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void max_u32(uint32_t* p, uint32_t v) {
-  (void)__hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ uint64_t or_u64(uint64_t* p, uint64_t v) {
   return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -434,19 +431,6 @@ __device__ __forceinline__ double lane_f64(double v, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                           __builtin_amdgcn_readlane(__double2loint(v), l));
 }
-__device__ __forceinline__ RowStat lane_rowstat(const RowStat& x, int l) {
-  RowStat y;
-  y.lz_q = lane_f64(x.lz_q, l);
-  y.lz_p = lane_f64(x.lz_p, l);
-  y.tv = lane_f64(x.tv, l);
-  y.slog = lane_f64(x.slog, l);
-  y.zmax_q = lane_f32(x.zmax_q, l);
-  y.zmax_p = lane_f32(x.zmax_p, l);
-  y.amax_q = lane_i32(x.amax_q, l);
-  y.amax_p = lane_i32(x.amax_p, l);
-  return y;
-}
-
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, dpp_f32<kDppXor1>(v));
   v = fmaxf(v, dpp_f32<kDppXor2>(v));
@@ -509,25 +493,6 @@ struct PickState {
   int src;     // MassSrc of the part masses
   double rem;  // target mass remaining at the start of that part
 };
-
-// Block sums: per-wave results combined in wave order (a fixed order, so
-// every thread and every run gets the same value); valid in every thread.
-template <int NWV>
-__device__ __forceinline__ void block_sum2(double& a, double& b, SharedT<NWV>& sh) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  a = wave_sum(a);
-  b = wave_sum(b);
-  __syncthreads();
-  if (lane == 0) { sh.d[wv][0] = a; sh.d[wv][1] = b; }
-  __syncthreads();
-  a = sh.d[0][0];
-  b = sh.d[0][1];
-#pragma unroll
-  for (int w = 1; w < NWV; ++w) {
-    a += sh.d[w][0];
-    b += sh.d[w][1];
-  }
-}
 
 // "Am I the last of `n` arrivals?" for the whole block.  Thread 0 wrote the
 // data it shares with st_dev_* before the call; on true, the counter is reset
@@ -601,12 +566,6 @@ __device__ __forceinline__ bool is_log(int rule) {
 // Rules whose deferral reads D_TV (Lemma 3), which the second pass sums.
 __device__ __forceinline__ bool has_tv_parts(int rule) {
   return rule == SPC_RULE_OPT || rule == SPC_RULE_OPTLOG;
-}
-
-// Sequences whose rows need the second pass: OPT and OPTLOG (D_TV of
-// Lemma 3) and the token rules (eta of Alg. 6) at temperature > 0.
-__device__ __forceinline__ bool needs_pass2(const SeqParam& s) {
-  return s.valid && !s.greedy && (has_tv_parts(s.rule) || is_token(s.rule));
 }
 
 // Sequences whose statistics tiles also take first moments: the entropies of
@@ -1213,16 +1172,6 @@ __device__ __forceinline__ void subchunk_masses(const Params& P, int64_t row, in
   __syncthreads();
 }
 
-// Wave 0: the total of a tile's sub-chunk masses (after subchunk_masses),
-// summed by the same scan the in-tile draw runs, so a draw whose target falls
-// in this tile by the tile masses finds it among the sub-chunks.
-template <int DT, int NWV, int TN = StatTile<DT>::N>
-__device__ __forceinline__ double tile_mass(const SharedT<NWV>& sh) {
-  constexpr int NS = TN / SubChunk<DT, NWV, TN>::N;
-  const int lane = threadIdx.x & 63;
-  return lane_f64(wave_incl_scan(lane < NS ? sh.dv[lane] : 0.0), NS - 1);
-}
-
 // Whole block: the draw inside the tile at entry t0.  Wave 0 scans the
 // sub-chunk masses for the sub-chunk where rem is crossed and draws inside it.
 template <int DT, int KIND, int NWV, int TN = StatTile<DT>::N>
@@ -1513,8 +1462,6 @@ __device__ __forceinline__ bool eta_from_stats(const TokenRule& tr, const TilePa
 // arithmetic, so a row's result does not depend on which did it.
 static_assert(kSlices == kWaves, "a tile has one slice per wavefront of its workgroup");
 template <int DT>
-using PartC = Chunk<DT, 2 * StatTile<DT>::U>;  // half a tile, wave-contiguous
-template <int DT>
 using SubC = Chunk<DT, 1>;
 
 // Wave: "am I the last of n arrivals on cnt?" after this wavefront's item
@@ -1627,15 +1574,12 @@ __device__ __forceinline__ void tv_slice_regs_w(
 }
 
 // ================================================================ the step
-// Jobs a row or a sequence publishes for the job pass that follows: a TV or
-// eta second pass over a row and the residual masses of row j* of a sequence
-// are "row jobs" of nt chunks (one per tile); the two halves of a greedy
-// row's argmax and the draws from statistics partials are single chunks.
+// Jobs a row publishes for the job pass that follows: a slice of its TV pass,
+// or a slice of a tile it listed for eta.
 enum JobKind : int { kJobEta = 2, kJobTvSlice = 7 };
 
-// A job entry: kind (bits 60..63), an extra field (bits 32..59: the argmax
-// tensor, or a draw's sample kind and j*) and the row or sequence it belongs
-// to (bits 0..31).
+// A job entry: kind (bits 60..63), the slice (bits 32..59) and the row it
+// belongs to (bits 0..31).
 __device__ __forceinline__ uint64_t job_entry(int kind, uint32_t extra, uint32_t id) {
   return ((uint64_t)kind << 60) | ((uint64_t)(extra & 0x0fffffffu) << 32) | (uint64_t)id;
 }
@@ -1668,15 +1612,9 @@ __device__ __forceinline__ uint64_t lane_u64(uint64_t v, int l) {
          (uint64_t)(uint32_t)lane_i32((int)(uint32_t)v, l);
 }
 
-// Publish a job (whose inputs are stored) for the job pass, a later launch.
+// Publish jobs (whose inputs are stored) for the job pass, a later launch.
 // The pass never holds more jobs than its list has slots; the bound only
 // keeps a broken count from writing past it.
-__device__ __forceinline__ void publish_single(const Params& P, int kind, uint32_t extra,
-                                               uint32_t id) {
-  const uint32_t s = add_u32(hdr_word(P, kHdrJobs), 1u);
-  if ((int64_t)s >= P.single_slots) return;
-  st_u64(job_list(P) + s, job_entry(kind, extra, id));
-}
 // Wave: n jobs (kind, extra = 0 .. n-1, id), one reservation.
 __device__ __forceinline__ void publish_singles_w(const Params& P, int kind, uint32_t id,
                                                   uint32_t n) {
@@ -1690,14 +1628,6 @@ __device__ __forceinline__ void publish_singles_w(const Params& P, int kind, uin
     st_u64(job_list(P) + s0 + x, job_entry(kind, x, id));
   }
 }
-
-// Shared state of a job workgroup.
-struct StepShared {
-  Shared sh;
-  RowStat rs;
-  PickState pk;
-  int a[4];  // values thread 0 or wave 0 hands to the block
-};
 
 // What a sampled sequence with first rejection f (delta there) draws from.
 __device__ __forceinline__ int sample_kind(const SeqParam& sp, int f, int gamma, int delta) {
@@ -1876,8 +1806,8 @@ __device__ __forceinline__ int row_decide_w(const Params& P, int r, int b, int j
   return f >= p_old ? f : -1;
 }
 
-// Wave: the row's decision once its TV, eta or argmax is known; when it
-// settles j*, the sequence's finish publishes to the next job pass.
+// Wave: the row's decision once its TV or eta is known, and the sequence's
+// finish when that settles j*.
 template <int DT>
 __device__ __forceinline__ void row_job_decide(const Params& P, int r) {
   const int g1 = P.gamma + 1, np = P.nt * kSlices;
@@ -1957,9 +1887,8 @@ __device__ __forceinline__ void arg_rows_w(const Params& P, int r, RowStat& rs) 
 }
 
 // Wave, after the last tile of row r = (b, j) arrived: merge the row, then
-// publish its second pass (TV, or eta for the tiles its statistics leave
-// open) or its argmax to the job pass, or decide it and, when that settles
-// j*, finish the sequence.
+// open its second pass (TV, or eta for the tiles its statistics leave open),
+// or decide it and, when that settles j*, finish the sequence.
 template <int DT, int MS, int TVM, bool GR>
 __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int j,
                                              const SeqParam& sp, int x) {
