@@ -228,6 +228,88 @@ T* offset(T* p, int64_t n) {
   return p ? p + n : p;
 }
 
+// Rules by what they need of a row besides its maxima and normalisers.
+constexpr uint32_t kAllRules = (1u << (SPC_RULE_OPTLOG + 1)) - 1u;
+constexpr uint32_t kTvRules = (1u << SPC_RULE_OPT) | (1u << SPC_RULE_OPTLOG);
+constexpr uint32_t kLogRules = (1u << SPC_RULE_BILD) | (1u << SPC_RULE_CHOWLOG) |
+                               (1u << SPC_RULE_DIFFLOG) | (1u << SPC_RULE_OPTLOG);
+constexpr uint32_t kTokRules = (1u << SPC_RULE_TOKEN_V1) | (1u << SPC_RULE_TOKEN_V2) |
+                               (1u << SPC_RULE_TOKEN_V3);
+
+struct Route {
+  bool seq = false, small = false;  // the one-launch paths; neither: statistics tiles
+  bool tv_self = false, tv_pass = false, tv_jobs = false, job_pass = false, pair = false;
+  int mom_set = 0;  // first moments the statistics sum (kMom* bits)
+};
+
+// Which kernels one launch of a verify call runs, from its sizes and from the
+// rules its sequences may hold (`rules`, a bitmask; `per_rule`: per-sequence
+// rules).  B: sequences of the call, b_launch: the most of them in a launch,
+// R: rows of this launch.  sampled: some sequence may be at temperature > 0,
+// greedy: the batch is at temperature 0.
+Route choose_route(int64_t B, int64_t b_launch, int64_t R, int64_t g1, int64_t V, int dtype,
+                   uint32_t rules, bool per_rule, bool sampled, bool greedy, int64_t cus) {
+  Route t;
+  // first moments of the log-loss rules (BiLD* at temperature 0 reads one
+  // logit instead): x for BiLD*, H(q) for ChowLog, H(q) and H(p) otherwise
+  const bool need_mom = (rules & kLogRules) && !(rules == (1u << SPC_RULE_BILD) && greedy);
+  t.mom_set = !need_mom ? 0
+                        : ((rules & (1u << SPC_RULE_BILD)) ? spc::kMomX : 0) |
+                              ((rules & (1u << SPC_RULE_CHOWLOG)) ? spc::kMomHQ : 0) |
+                              ((rules & ((1u << SPC_RULE_DIFFLOG) | (1u << SPC_RULE_OPTLOG)))
+                                   ? spc::kMomHQ | spc::kMomHP
+                                   : 0);
+  // Rows of OPT / OPTLOG at T > 0 are decided after their TV pass, rows of
+  // a token rule after their eta pass (the job pass, for the tiles their
+  // statistics leave open), every other row by its last statistics tile.
+  const bool tv_rows = sampled && (rules & kTvRules);
+  const bool tok_rows = sampled && (rules & kTokRules);
+  // Batches of short sequences take the one-launch path with a workgroup per
+  // sequence: up to a length that depends on how the rows fill the chip
+  // otherwise.  us per step, that path / the next best, bfloat16 unless said:
+  //   rows within the compute units: Diff V=1000 gamma=4 B=1 f32 9.4 / 10.4,
+  //   V=4000 gamma=1 9.6 / 10.5, V=4000 gamma=4 13.0 / 11.1; OPT f32 V=1000
+  //   gamma=1 9.9 / 10.7, gamma=7 13.5 / 11.3, TokenV2 V=2000 gamma=7 17.5 / 16.1;
+  //   more rows: Diff B=256 gamma=7 V=4000 16.9 / 26.9, B=64 gamma=4 V=8000
+  //   f32 17.4 / 21.9, gamma=7 V=16000 29.4 / 28.1; OPT B=64 gamma=4 V=4000
+  //   f32 19.9 / 21.2, gamma=7 23.9 / 22.2; TokenV2 B=256 gamma=7 V=4000
+  //   27.0 / 68.3; DiffLog B=64 gamma=4 V=4000 f32 19.5 / 20.2; greedy B=256
+  //   gamma=4 V=8000 19.0 / 15.1.
+  const bool full = b_launch * g1 > cus;
+  const int64_t seq_most = !full ? (tv_rows || tok_rows ? 4096 : 8192)
+                           : tv_rows || need_mom || !sampled ? 20480
+                                                             : 40960;
+  t.seq = V <= spc::seq_row_elems(dtype) && g1 * V <= seq_most && B <= 2 * cus;
+  if (t.seq) return t;
+  // Other small problems (rows that fit one workgroup's registers, at most two
+  // rows per compute unit, no first moments): one launch, a workgroup per row.
+  // Without a second pass, rows of more than 24576 entries are faster as
+  // statistics tiles and a draw pass when their tiles fit the chip at once
+  // (bfloat16 B=8 gamma=4: V=32128 20.7 as rows, 17.5 as tiles, V=24001 17.5
+  // and 18.4, V=20000 17.0 and 17.8).
+  const int64_t nt = stat_tiles(dtype, V);
+  t.small = !need_mom && V <= spc::small_row_elems(dtype) && b_launch * g1 <= 2 * cus &&
+            (V <= 24576 || tv_rows || tok_rows || !sampled || b_launch * g1 * nt > 4 * cus);
+  if (t.small) return t;
+  // Where TV rows get their TV pass.  In a grid that is resident at once
+  // (at most two workgroups per compute unit) each TV row takes it from
+  // its own tiles' registers once the row is merged (tv_self).  Otherwise
+  // a kernel of its own reads the TV rows again after the statistics
+  // kernel (k_tvpass) when the rule is batch-wide, so that most rows may
+  // need it; with per-sequence rules (a few TV rows among others) their
+  // slices are job-pass items (tv_jobs).
+  t.tv_self = tv_rows && R * nt <= 2 * cus && nt <= spc::kTvTiles;
+  // batches of at least 64 statistics tiles per compute unit stream two
+  // tiles per workgroup (without first moments): B = 32 at the Gemma
+  // vocabulary (32 per CU) is faster with one, B = 128 and 256 with two
+  t.pair = !t.tv_self && !need_mom && R * nt >= 64 * cus;
+  t.tv_jobs = tv_rows && !t.tv_self && per_rule;
+  t.tv_pass = tv_rows && !t.tv_self && !t.tv_jobs;
+  // the job pass: eta slices, and TV slices (tv_jobs)
+  t.job_pass = tok_rows || t.tv_jobs;
+  return t;
+}
+
 spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_t* draft,
                        const float* uniforms, int32_t B, int32_t gamma, int32_t V, int32_t rule,
                        float alpha, float temperature, bool force_greedy, int32_t* out_accept,
@@ -290,55 +372,9 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
   }
 
   // The rules the batch may hold decide what each launch computes.
-  constexpr uint32_t kAll = (1u << (SPC_RULE_OPTLOG + 1)) - 1u;
-  constexpr uint32_t kTv = (1u << SPC_RULE_OPT) | (1u << SPC_RULE_OPTLOG);
-  constexpr uint32_t kLog = (1u << SPC_RULE_BILD) | (1u << SPC_RULE_CHOWLOG) |
-                            (1u << SPC_RULE_DIFFLOG) | (1u << SPC_RULE_OPTLOG);
-  const uint32_t mask = ex ? ex->rules_present & kAll : 0u;
-  const uint32_t rules = per_rule ? (mask ? mask : kAll) : (1u << rule);
+  const uint32_t mask = ex ? ex->rules_present & kAllRules : 0u;
+  const uint32_t rules = per_rule ? (mask ? mask : kAllRules) : (1u << rule);
   const bool may_sample = !force_greedy && (per_temp || temperature > 0.0f);
-  // first moments of the log-loss rules (BiLD* at temperature 0 reads one
-  // logit instead): x for BiLD*, H(q) for ChowLog, H(q) and H(p) otherwise
-  const bool need_mom = (rules & kLog) && !(rules == (1u << SPC_RULE_BILD) && force_greedy);
-  const int mom_set = !need_mom ? 0
-                                : ((rules & (1u << SPC_RULE_BILD)) ? spc::kMomX : 0) |
-                                      ((rules & (1u << SPC_RULE_CHOWLOG)) ? spc::kMomHQ : 0) |
-                                      ((rules & ((1u << SPC_RULE_DIFFLOG) | (1u << SPC_RULE_OPTLOG)))
-                                           ? spc::kMomHQ | spc::kMomHP
-                                           : 0);
-  // Rows of OPT / OPTLOG at T > 0 are decided after their TV pass, rows of
-  // a token rule after their eta pass (the job pass, for the tiles their
-  // statistics leave open), every other row by its last statistics tile.
-  constexpr uint32_t kTok = (1u << SPC_RULE_TOKEN_V1) | (1u << SPC_RULE_TOKEN_V2) |
-                            (1u << SPC_RULE_TOKEN_V3);
-  const bool tv_rows = may_sample && (rules & kTv);
-  // Batches of short sequences take the one-launch path with a workgroup per
-  // sequence: up to a length that depends on how the rows fill the chip
-  // otherwise.  us per step, that path / the next best, bfloat16 unless said:
-  //   rows within the compute units: Diff V=1000 gamma=4 B=1 f32 9.4 / 10.4,
-  //   V=4000 gamma=1 9.6 / 10.5, V=4000 gamma=4 13.0 / 11.1; OPT f32 V=1000
-  //   gamma=1 9.9 / 10.7, gamma=7 13.5 / 11.3, TokenV2 V=2000 gamma=7 17.5 / 16.1;
-  //   more rows: Diff B=256 gamma=7 V=4000 16.9 / 26.9, B=64 gamma=4 V=8000
-  //   f32 17.4 / 21.9, gamma=7 V=16000 29.4 / 28.1; OPT B=64 gamma=4 V=4000
-  //   f32 19.9 / 21.2, gamma=7 23.9 / 22.2; TokenV2 B=256 gamma=7 V=4000
-  //   27.0 / 68.3; DiffLog B=64 gamma=4 V=4000 f32 19.5 / 20.2; greedy B=256
-  //   gamma=4 V=8000 19.0 / 15.1.
-  const bool tok_rows = may_sample && (rules & kTok);
-  const bool full = b_launch * g1 > (int64_t)cus;
-  const int64_t seq_most = !full ? (tv_rows || tok_rows ? 4096 : 8192)
-                           : tv_rows || need_mom || !may_sample ? 20480
-                                                                : 40960;
-  const bool seq = V <= spc::seq_row_elems(dtype) && g1 * V <= seq_most && B <= 2 * (int64_t)cus;
-  // Other small problems (rows that fit one workgroup's registers, at most two
-  // rows per compute unit, no first moments): one launch, a workgroup per row.
-  // Without a second pass, rows of more than 24576 entries are faster as
-  // statistics tiles and a draw pass when their tiles fit the chip at once
-  // (bfloat16 B=8 gamma=4: V=32128 20.7 as rows, 17.5 as tiles, V=24001 17.5
-  // and 18.4, V=20000 17.0 and 17.8).
-  const bool small = !seq && !need_mom && V <= spc::small_row_elems(dtype) &&
-                     b_launch * g1 <= 2 * (int64_t)cus &&
-                     (V <= 24576 || tv_rows || tok_rows || !may_sample ||
-                      b_launch * g1 * stat_tiles(dtype, V) > 4 * (int64_t)cus);
   const int64_t nt = stat_tiles(dtype, V);
   const int64_t eb = dtype == SPC_BF16 ? 2 : 4;
 
@@ -359,7 +395,6 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     P.temp = force_greedy ? 0.0f : temperature;
     P.force_greedy = force_greedy ? 1 : 0;
     P.rule_mask = per_rule ? mask : 0u;
-    P.mom_set = mom_set;
     P.rule_ps = per_rule ? ex->rule_per_seq + b0 : nullptr;
     P.alpha_ps = per_alpha ? ex->alpha_per_seq + b0 : nullptr;
     P.temp_ps = (per_temp && !force_greedy) ? ex->temp_per_seq + b0 : nullptr;
@@ -369,22 +404,12 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     P.out_stats = ex ? offset(ex->out_row_stats, b0 * g1 * 8) : nullptr;
     P.out_argmax = ex ? offset(ex->out_argmax, b0 * g1 * 2) : nullptr;
     P.out_norm = ex ? offset(ex->out_sample_norm, b0) : nullptr;
-    // Where TV rows get their TV pass.  In a grid that is resident at once
-    // (at most two workgroups per compute unit) each TV row takes it from
-    // its own tiles' registers once the row is merged (tv_self).  Otherwise
-    // a kernel of its own reads the TV rows again after the statistics
-    // kernel (k_tvpass) when the rule is batch-wide, so that most rows may
-    // need it; with per-sequence rules (a few TV rows among others) their
-    // slices are job-pass items (tv_jobs).
-    P.tv_self = (tv_rows && R * nt <= 2 * (int64_t)cus && nt <= spc::kTvTiles) ? 1 : 0;
-    // batches of at least 64 statistics tiles per compute unit stream two
-    // tiles per workgroup (without first moments): B = 32 at the Gemma
-    // vocabulary (32 per CU) is faster with one, B = 128 and 256 with two
-    P.pair = (!P.tv_self && mom_set == 0 && R * nt >= 64 * (int64_t)cus) ? 1 : 0;
-    P.tv_jobs = (tv_rows && !P.tv_self && per_rule) ? 1 : 0;
-    const bool tv_pass = tv_rows && !P.tv_self && !P.tv_jobs;
-    // the job pass: eta slices, and TV slices (tv_jobs)
-    const bool job_pass = (may_sample && (rules & kTok)) || P.tv_jobs;
+    const Route route = choose_route(B, b_launch, R, g1, V, dtype, rules, per_rule, may_sample,
+                                     force_greedy, cus);
+    P.mom_set = route.mom_set;
+    P.tv_self = route.tv_self ? 1 : 0;
+    P.pair = route.pair ? 1 : 0;
+    P.tv_jobs = route.tv_jobs ? 1 : 0;
     P.may_greedy = (force_greedy || per_temp) ? 1 : 0;
     P.wait_ticks = tv_wait_ticks();
     // jobs: TV slices, or the slices of the tiles a token row lists for eta (a row has one kind)
@@ -393,7 +418,7 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     // workgroups of the job pass: a wavefront per item of its largest
     // expected list (eta or TV slices of every tile), at most two workgroups per compute unit
     const int64_t np = nt * spc::kSlices;
-    const int64_t items1 = np * (((rules & kTok) || P.tv_jobs) ? R : 0);
+    const int64_t items1 = np * (route.job_pass ? R : 0);
     constexpr int64_t kW = spc::kJobThreads / 64;
     const int job_groups = (int)std::max<int64_t>(
         1, std::min<int64_t>((items1 + kW - 1) / kW, 2 * (int64_t)cus));
@@ -411,16 +436,17 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     const bool first = b0 == 0;
     hipEvent_t ev0 = first && ex ? ex->ev_tiles_begin : nullptr;
     hipEvent_t ev1 = first && ex ? ex->ev_tiles_end : nullptr;
-    if (seq) {
+    if (route.seq) {
       e = spc::launch_seq(P, dtype, ev0, ev1, stream);
-    } else if (small) {
+    } else if (route.small) {
       // one launch: a workgroup per row holding the row in registers
       P.nsub = spc::kSmallSub;
       e = spc::launch_small(P, dtype, ev0, ev1, stream);
     } else {
       // sequences with a draw are drawn by the draw pass, the last kernel
       // (greedy ones write their token directly)
-      e = spc::launch_step(P, dtype, may_sample, tv_pass, job_pass, job_groups, ev0, ev1, stream);
+      e = spc::launch_step(P, dtype, may_sample, route.tv_pass, route.job_pass, job_groups, ev0, ev1,
+                           stream);
     }
     if (e != hipSuccess) return fail(SPC_E_HIP, "kernel launch: %s", hipGetErrorString(e));
   }
@@ -580,6 +606,19 @@ void spc_release(void) {
   }
   g_ws.clear();
   (void)hipSetDevice(cur);
+}
+
+int32_t spc_debug_route(int32_t B, int32_t gamma, int32_t V, int32_t dtype, uint32_t rules,
+                        int32_t per_rule, int32_t greedy, int32_t cus) {
+  if (check_shape(B, gamma, V) != SPC_OK || (dtype != SPC_F32 && dtype != SPC_BF16) || cus < 1)
+    return 0;
+  const int64_t g1 = (int64_t)gamma + 1, bl = seqs_per_launch(B, gamma);
+  const Route t = choose_route(B, bl, bl * g1, g1, V, dtype, rules & kAllRules, per_rule != 0,
+                               greedy == 0, greedy != 0, cus);
+  return (t.seq ? spc::kRouteSeq : t.small ? spc::kRouteSmall : spc::kRouteTiles) |
+         (t.tv_self ? spc::kRouteTvSelf : 0) | (t.tv_pass ? spc::kRouteTvPass : 0) |
+         (t.tv_jobs ? spc::kRouteTvJobs : 0) | (t.job_pass ? spc::kRouteJobs : 0) |
+         (t.pair ? spc::kRoutePair : 0);
 }
 
 const char* spc_version(void) { return "libspeccascade 0.2 (gfx950)"; }

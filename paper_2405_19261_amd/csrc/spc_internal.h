@@ -177,4 +177,21 @@ hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass,
 // 4-byte aligned): a fill a graph capture may record.
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream);
 
+// The kernels a verify call runs, for tests of the dispatch: the first launch
+// of a call of these sizes whose sequences may hold `rules` (a bitmask), on a
+// device of `cus` compute units; 0 for sizes no call takes.
+enum RouteBit : int32_t {
+  kRouteSeq = 1,      // k_seq
+  kRouteSmall = 2,    // k_small
+  kRouteTiles = 4,    // k_tiles (and k_res)
+  kRouteTvSelf = 8,   // TV passes from the row's own tiles
+  kRouteTvPass = 16,  // k_tvpass
+  kRouteTvJobs = 32,  // TV slices in the job pass
+  kRouteJobs = 64,    // k_jobs
+  kRoutePair = 128    // two tiles per workgroup
+};
+
 }  // namespace spc
+
+extern "C" int32_t spc_debug_route(int32_t B, int32_t gamma, int32_t V, int32_t dtype,
+                                   uint32_t rules, int32_t per_rule, int32_t greedy, int32_t cus);

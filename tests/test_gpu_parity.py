@@ -89,13 +89,13 @@ def test_tv_rules_without_row_statistics(rule, alpha, cfg, B):
 
 
 @pytest.mark.parametrize("cfg", [2, 3])
-def test_tv_wait_timeout_takes_the_job_pass(cfg, monkeypatch):
+def test_tv_wait_timeout_leaves_the_tile_to_the_merge(cfg, monkeypatch):
     """A statistics workgroup's wait for a TV row's merge is bounded; with the
     bound at 0 ticks every wait that does not find the row merged gives up at
-    once and the job pass takes the tile.  The T5 shape (a resident grid)
-    takes its TV passes from the rows' own tiles and so waits; the Gemma
-    shape takes them in the TV pass kernel and never waits.  Both must match
-    the oracle."""
+    once and the row's merge takes the tile.  The T5 shape (a
+    resident grid) takes its TV passes from the rows' own tiles and so waits;
+    the Gemma shape takes them in the TV pass kernel and never waits.  Both
+    must match the oracle."""
     monkeypatch.setenv("SPC_TV_WAIT_TICKS", "0")
     wl = W.WORKLOADS[cfg].with_(B=8, rule=W.OPT, alpha=0.1, temperature=1.0)
     _flush(f"[parity] tv wait 0: cfg{cfg} OPT B=8")
@@ -647,7 +647,7 @@ def test_argmax_ties_lowest_index(dtype, V):
 
 @pytest.mark.parametrize("dtype,V,rule,alpha", [
     ("bf16", 600000, W.DIFF, 0.05),      # 74 tiles per row
-    ("bf16", 600001, W.OPT, 0.1),        # unaligned rows: 293 tiles, 3 groups of part loads
+    ("bf16", 600001, W.OPT, 0.1),        # rows at any alignment, 74 tiles
     ("f32", 1100000, W.TOKEN_V3, 0.3),   # 269 tiles
     ("bf16", 600000, W.DIFFLOG, 0.5),    # moments merged over 74 tiles
 ])

@@ -21,44 +21,90 @@ def _gpu():
     torch.cuda.synchronize()
 
 
+# Bits of spc_debug_route.
+SEQ, SMALL, TILES, TV_SELF, TV_PASS, TV_JOBS, JOBS, PAIR = (1 << i for i in range(8))
+
+
+def route(B, gamma, V, dtype, rule, greedy=False, per_seq=False):
+    """The kernels a call of these sizes runs on this device."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return spc.lib().spc_debug_route(B, gamma, V, spc.SPC_BF16 if dtype == "bf16" else
+                                     spc.SPC_F32, 1 << rule, int(per_seq), int(greedy), cus)
+
+
+def check(inp, dtype, greedy=False, stats=True, per_seq=False):
+    """One call against the oracle; returns the GPU's outputs."""
+    g = parity.run_gpu(inp, greedy=greedy, stats=stats, per_seq=per_seq)
+    h = parity.host_inputs(inp)
+    parity.compare(g, parity.run_oracle(h, greedy=greedy), h, dtype, greedy=greedy)
+    return g
+
+
 # Rows that start inside a 16-byte vector and end inside a lane load: fewer
 # entries than one vector, one entry either side of a vector, of a
 # wavefront's lane load and of a tile (8192 bfloat16 / 4096 float32), on the
-# statistics-tile path (more rows than the one-launch paths take).
-@pytest.mark.parametrize("dtype,V,B,rule", [
-    ("bf16", 2, 300, W.DIFF), ("bf16", 7, 300, W.OPT), ("bf16", 9, 300, W.TOKEN_V2),
-    ("bf16", 511, 300, W.LOSSY), ("bf16", 513, 300, W.OPT), ("bf16", 8191, 280, W.DIFF),
-    ("bf16", 8193, 280, W.TOKEN_V1), ("bf16", 40001, 5, W.OPT), ("bf16", 65543, 70, W.DIFF),
-    ("f32", 3, 300, W.DIFF), ("f32", 5, 300, W.OPT), ("f32", 4095, 280, W.BILD),
-    ("f32", 4097, 280, W.DIFFLOG), ("f32", 33333, 6, W.OPTLOG)])
+# statistics-tile path (more sequences than the one-launch paths take, or
+# rows longer than theirs) with each of its second passes.
+@pytest.mark.parametrize("dtype,V,B,rule,want", [
+    ("bf16", 2, 600, W.DIFF, 0), ("bf16", 7, 600, W.OPT, TV_PASS),
+    ("bf16", 9, 600, W.TOKEN_V2, JOBS), ("bf16", 511, 600, W.LOSSY, 0),
+    ("bf16", 513, 600, W.OPT, TV_PASS), ("bf16", 513, 600, W.DIFFLOG, 0),
+    ("bf16", 8191, 560, W.DIFF, 0), ("bf16", 8193, 560, W.TOKEN_V1, JOBS),
+    ("bf16", 40001, 5, W.OPT, TV_SELF), ("bf16", 40001, 5, W.TOKEN_V2, JOBS),
+    ("bf16", 65543, 70, W.DIFF, 0), ("bf16", 65543, 40, W.OPT, TV_PASS),
+    ("f32", 3, 600, W.DIFF, 0), ("f32", 5, 600, W.OPT, TV_PASS), ("f32", 5, 600, W.TOKEN_V3, JOBS),
+    ("f32", 4095, 560, W.BILD, 0), ("f32", 4097, 560, W.DIFFLOG, 0),
+    ("f32", 33333, 6, W.OPTLOG, TV_SELF), ("f32", 33333, 40, W.OPTLOG, TV_PASS)])
 @pytest.mark.parametrize("greedy", [False, True])
-def test_rows_at_any_alignment(dtype, V, B, rule, greedy):
+def test_rows_at_any_alignment(dtype, V, B, rule, want, greedy):
+    passes = TV_SELF | TV_PASS | TV_JOBS | JOBS
+    r = route(B, 1, V, dtype, rule, greedy)
+    assert r & TILES and (greedy or r & passes == want), r
     wl = W.WORKLOADS[3].with_(B=B, gamma=1, V=V, dtype=dtype, rule=rule, alpha=0.1,
                               temperature=0.0 if greedy else 1.0)
     parity.parity_workload(wl, 1, step0=31, report_name=f"anyalign.{dtype}.{V}")
 
 
-@pytest.mark.parametrize("dtype,V", [("bf16", 20003), ("f32", 9999)])
-def test_rows_do_not_depend_on_their_alignment(dtype, V):
+@pytest.mark.parametrize("dtype,V,B,rule", [("bf16", 8193, 560, W.OPT), ("bf16", 40001, 70, W.OPT),
+                                            ("f32", 33333, 70, W.OPTLOG)])
+def test_tv_jobs_at_any_alignment(dtype, V, B, rule):
+    """TV slices as job-pass items: per-sequence rules."""
+    assert route(B, 1, V, dtype, rule, per_seq=True) & TV_JOBS
+    wl = W.WORKLOADS[3].with_(B=B, gamma=1, V=V, dtype=dtype, rule=rule, alpha=0.1)
+    check(W.generate(wl, 33, DEV), dtype, per_seq=True)
+
+
+@pytest.mark.parametrize("rule", [W.OPT, W.TOKEN_V2, W.DIFFLOG])
+@pytest.mark.parametrize("dtype,V,path", [
+    ("bf16", 1001, SEQ), ("f32", 1001, SEQ), ("bf16", 20003, SMALL), ("f32", 9999, SMALL),
+    ("bf16", 40003, TILES), ("f32", 20001, TILES)])
+def test_rows_do_not_depend_on_their_alignment(dtype, V, path, rule):
     """The same row at every position of the batch, so at every alignment,
-    gives bitwise the same statistics."""
+    gives bitwise the same statistics and the same draw."""
+    if rule == W.DIFFLOG and path == SMALL:
+        path = TILES  # first moments
+    B, g1 = 16, 3
+    assert route(B, g1 - 1, V, dtype, rule) & path
     g = torch.Generator(device=DEV).manual_seed(3)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
-    B, g1 = 16, 3
     row = torch.randn(2, V, generator=g, device=DEV).to(dt)
     q, p = (row[i].expand(B, g1, V).contiguous() for i in range(2))
     draft = torch.zeros(B, g1 - 1, dtype=torch.int32, device=DEV)
     st = torch.empty(B, g1, 8, device=DEV)
+    norm = torch.empty(B, device=DEV)
     u = torch.full((B, g1), 0.5, device=DEV)
-    _, tok, _ = spc.spc_verify_ex(q, p, draft, u, W.OPT, 0.1, 1.0, out_row_stats=st)
+    _, tok, _ = spc.spc_verify_ex(q, p, draft, u, rule, 0.1, 1.0, out_row_stats=st,
+                                  out_sample_norm=norm)
+    # (a token rule's row reports r at its own draft; the draft is the same)
     assert torch.equal(st, st[:1, :1].expand(B, g1, 8))
     assert torch.equal(tok, tok[:1].expand(B))
+    assert torch.equal(norm, norm[:1].expand(B))
 
 
 # A workgroup per sequence: one to sixteen wavefronts a row, more rows than
-# wavefronts, one to four lane loads at a time, rows that end inside a lane
-# load, and the longest sequences it takes (few rows: 8192 entries, 4096 with
-# a second pass; many: 40960, 20480).
+# wavefronts, one to four lane loads at a time, and rows that end inside a
+# lane load.  (A shape whose rule makes it longer than this path takes runs
+# on the next one.)
 @pytest.mark.parametrize("dtype,B,gamma,V", [
     ("bf16", 3, 1, 2), ("f32", 3, 1, 3), ("bf16", 5, 15, 255), ("f32", 4, 16, 239),
     ("bf16", 2, 63, 64), ("f32", 3, 2, 1365), ("bf16", 7, 7, 513), ("bf16", 3, 1, 4096),
@@ -69,7 +115,113 @@ def test_rows_do_not_depend_on_their_alignment(dtype, V):
 def test_short_sequences(dtype, B, gamma, V, rule, greedy):
     wl = W.WORKLOADS[3].with_(B=B, gamma=gamma, V=V, dtype=dtype, rule=rule, alpha=0.1,
                               temperature=0.0 if greedy else 0.7)
-    parity.parity_workload(wl, 1, step0=57, stats=V % 2 == 0, report_name=f"seq.{dtype}.{V}")
+    inp = W.generate(wl, 57, DEV)
+    with_stats = check(inp, dtype, greedy)
+    plain = check(inp, dtype, greedy, stats=False)
+    for k in ("accept_len", "next_token", "defer"):
+        np.testing.assert_array_equal(plain[k], with_stats[k])
+
+
+# The longest sequences that path takes.
+@pytest.mark.parametrize("dtype,B,gamma,V,rule", [
+    ("bf16", 3, 1, 4095, W.DIFF), ("f32", 3, 3, 2047, W.LOSSY), ("bf16", 3, 1, 2047, W.OPT),
+    ("f32", 2, 3, 1023, W.TOKEN_V1), ("bf16", 4, 3, 1021, W.TOKEN_V3),
+    ("bf16", 129, 1, 20479, W.DIFF), ("f32", 129, 1, 20479, W.LOSSY),
+    ("f32", 60, 4, 8191, W.TOKEN_V2), ("bf16", 129, 1, 20477, W.TOKEN_V1),
+    ("bf16", 129, 1, 10239, W.OPT), ("f32", 60, 4, 4095, W.OPT)])
+def test_longest_short_sequences(dtype, B, gamma, V, rule):
+    assert route(B, gamma, V, dtype, rule) & SEQ
+    wl = W.WORKLOADS[3].with_(B=B, gamma=gamma, V=V, dtype=dtype, rule=rule, alpha=0.1)
+    inp = W.generate(wl, 58, DEV)
+    check(inp, dtype)
+    check(inp, dtype, stats=False)
+
+
+@pytest.mark.parametrize("dtype,gamma,V", [("bf16", 2, 1201), ("f32", 4, 810), ("bf16", 3, 1000)])
+@pytest.mark.parametrize("rule,alpha", [(W.OPT, 0.1), (W.TOKEN_V2, 0.05), (W.BILD, 6.0),
+                                        (W.OPTLOG, 1.0), (W.LOSSY, 0.3)])
+def test_short_sequences_masked(dtype, gamma, V, rule, alpha):
+    """-inf entries in both tensors, whole lane loads and wavefronts among them."""
+    B = 8
+    assert route(B, gamma, V, dtype, rule) & SEQ
+    wl = W.WORKLOADS[3].with_(B=B, gamma=gamma, V=V, dtype=dtype, rule=rule, alpha=alpha)
+    inp = W.generate(wl, 2, DEV)
+    g0 = torch.Generator(device=DEV).manual_seed(99)
+    for k in ("q", "p"):
+        m = torch.rand(inp[k].shape, generator=g0, device=DEV) < 0.3
+        m[1::3, :, 128:700] = True
+        m[..., 0] = False  # at least one finite entry per row
+        if k == "p" and rule == W.BILD:
+            m[::2] = False  # half the sequences keep a finite cross-entropy
+        inp[k][m] = float("-inf")
+    inp["draft"] = W.draw_drafts(inp["q"], inp["temperature"], g0)
+    check(inp, dtype)
+
+
+@pytest.mark.parametrize("dtype,gamma,V", [("bf16", 2, 1201), ("f32", 4, 1203), ("bf16", 1, 3000)])
+def test_short_sequences_argmax_ties(dtype, gamma, V):
+    """Ties within a lane load, across lanes, lane loads and wavefronts: the
+    lowest index, batch-wide and per sequence."""
+    B = 8
+    assert route(B, gamma, V, dtype, W.OPT, greedy=True) & SEQ
+    wl = W.WORKLOADS[4].with_(B=B, gamma=gamma, V=V, dtype=dtype)
+    inp = W.generate(wl, 9, DEV)
+    rng = np.random.default_rng(4)
+    low = {}
+    for k in ("q", "p"):
+        x = inp[k].float().cpu().numpy()
+        low[k] = np.empty(x.shape[:2], np.int64)
+        for i in np.ndindex(*x.shape[:2]):
+            n = int(rng.integers(0, V - 530))
+            pos = ([V - 1, V - 2, 0], [n + 3, n + 1], [n + 512, n + 9, n + 64],
+                   list(rng.choice(V, 9, replace=False)), [V - 1, V - 3])[int(rng.integers(0, 5))]
+            x[i][pos] = float(np.ceil(x[i].max())) + 1.0
+            low[k][i] = min(pos)
+        inp[k].copy_(torch.from_numpy(x).to(inp[k].dtype))
+    g = check(inp, dtype, greedy=True)
+    for c, k in enumerate(("q", "p")):
+        np.testing.assert_array_equal(g["argmax"][..., c], low[k])
+    check(inp, dtype, greedy=True, per_seq=True)
+
+
+@pytest.mark.parametrize("dtype,gamma,V", [("bf16", 3, 1001), ("f32", 4, 800), ("bf16", 6, 1170)])
+def test_short_sequences_identical_models(dtype, gamma, V):
+    """p = q: every draft is kept, D_TV and H(q) - H(p) are exactly 0."""
+    wl = W.WORKLOADS[3].with_(B=9, gamma=gamma, V=V, dtype=dtype)
+    same = W.generate(wl, 3, DEV)
+    same["p"] = same["q"].clone()
+    for rule, alpha in ((W.LOSSY, 0.3), (W.DIFFLOG, 0.0), (W.OPTLOG, 0.5), (W.DIFF, 0.0),
+                        (W.OPT, 0.1)):
+        same["rule"][:] = rule
+        same["alpha"][:] = alpha
+        g = check(same, dtype)
+        assert (g["accept_len"] == gamma).all() and (g["defer"] == 0).all()
+        if rule in (W.OPT, W.OPTLOG):
+            assert (g["row_stats"][..., 6] == 0).all()
+        if rule in (W.DIFFLOG, W.OPTLOG):
+            assert (g["row_stats"][..., 7] == 0).all()
+
+
+# TV passes from the rows' own tiles, either side of the most tiles a row's
+# gate holds (62 of 4096 float32 entries), with the wait as it is and at 0
+# ticks (every workgroup that does not find its row merged leaves its tile to
+# the merge), with row statistics (every row takes its TV pass) and without
+# (rows D_TV cannot change are decided at their merge and skip theirs).
+@pytest.mark.parametrize("ticks", [None, "0"])
+@pytest.mark.parametrize("dtype,B,gamma,V,rule,want", [
+    ("f32", 1, 2, 253952, W.OPT, TV_SELF), ("f32", 1, 2, 253953, W.OPT, TV_PASS),
+    ("f32", 1, 1, 253952, W.OPTLOG, TV_SELF), ("f32", 8, 5, 32128, W.OPT, TV_SELF),
+    ("bf16", 4, 2, 100003, W.OPT, TV_SELF), ("bf16", 4, 2, 100003, W.OPTLOG, TV_SELF)])
+def test_tv_pass_from_resident_tiles(dtype, B, gamma, V, rule, want, ticks, monkeypatch):
+    if ticks is not None:
+        monkeypatch.setenv("SPC_TV_WAIT_TICKS", ticks)
+    assert route(B, gamma, V, dtype, rule) & want
+    wl = W.WORKLOADS[3].with_(B=B, gamma=gamma, V=V, dtype=dtype, rule=rule,
+                              alpha=0.1 if rule == W.OPT else 0.5)
+    for step in (21, 22, 23):
+        inp = W.generate(wl, step, DEV)
+        check(inp, dtype)
+        check(inp, dtype, stats=False)
 
 
 @pytest.mark.parametrize("dtype,B,gamma,V", [("bf16", 12, 4, 800), ("f32", 90, 3, 5000)])
