@@ -2698,8 +2698,15 @@ __global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
     }
     if (lane == 0) sh.part[j * wpr + wi] = t;
   }
-  if (wpr > 1) __syncthreads();
-  else __builtin_amdgcn_wave_barrier();  // a row's share is its own wavefront's
+  if (wpr > 1) {
+    __syncthreads();
+  } else {
+    // a row's share is its own wavefront's: lane 0's store before every
+    // lane's load (a wave barrier alone orders no memory for the compiler)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
   const auto inputs = [&](int j) {
     return j == slot ? pre
                      : draft_in<DT>(P, (int)r0 + j, sp.valid ? draft_token(P, b, j) : -1, sp);
