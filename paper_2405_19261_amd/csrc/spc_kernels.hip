@@ -242,6 +242,21 @@ __device__ __forceinline__ int first_max_index(const uint32_t (&w)[U][Tile<DT, U
   return m == kNegInf ? 0x7fffffff : base + gi * GT * T::VW + ei;
 }
 
+// Sum of N weights w(0) .. w(N - 1) in float32, pairwise (a weight meets
+// log2 N roundings rather than up to N), two at a time: the barrier keeps the
+// temporaries of the weights few.
+template <int N, class W>
+__device__ __forceinline__ float pair_sum(W&& w, int e0 = 0) {
+  if constexpr (N == 2) {
+    const float t = w(e0) + w(e0 + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    return t;
+  } else {
+    const float a = pair_sum<N / 2>(w, e0);
+    return a + pair_sum<N / 2>(w, e0 + N / 2);
+  }
+}
+
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float log2_hw(float x) { return __builtin_amdgcn_logf(x); }
 
@@ -253,6 +268,41 @@ __device__ __forceinline__ double exp2_acc(double d) {
   const double n = floor(d);
   return ldexp((double)exp2_hw((float)(d - n)), (int)n);
 }
+
+// 2^d in fp64 for a factor between two references (d <= 0, finite): the
+// hardware 2^x at d rounded to float32, put right to first order for what the
+// rounding dropped, so that only the hardware's own error (about one float32
+// ulp) is left.  Without the correction a factor carries |d| / 2 of them.
+// Arguments below -126 give 0.
+__device__ __forceinline__ double exp2_fac(double d) {
+  const float h = fmaxf((float)d, -1000.0f);
+  const double e = (double)exp2_hw(h);
+  return fma(e * kLn2, d - (double)h, e);
+}
+
+// The factor and the type of a thread's sum in the kernels that stream tiles.
+// EX: exp2_fac, and float64 across a thread's lane loads; else the hardware's
+// 2^x and float32.  Rows at any alignment take EX.  Mean errors of a row's
+// largest probability, before / after: bfloat16 3.2e-8 / 2.0e-8, float32
+// 2.4e-8 / 1.6e-8 (entry-by-entry loads into tiles of 2048 entries, which
+// these rows once had, 2.2e-8); of H(q) - H(p) 1.5e-7 / 7.3e-8.  Aligned rows
+// keep the cheaper form: EX costs them 1% (640 greedy rows of V = 256 000
+// bfloat16, 121.3 and 122.6 us) and 10% with first moments.
+template <bool EX>
+__device__ __forceinline__ double ref_fac(double d) {
+  if constexpr (EX) return exp2_fac(d);
+  else return (double)exp2_hw((float)d);
+}
+template <bool EX>
+struct ThreadSumT {
+  typedef float type;
+};
+template <>
+struct ThreadSumT<true> {
+  typedef double type;
+};
+template <bool EX>
+using ThreadSum = typename ThreadSumT<EX>::type;
 
 // log2 of a positive finite fp64 value: S = m 2^e with m in [1/sqrt(2),
 // sqrt(2)), m = head + tail with a float32 head, log2(m) = log2(head) +
@@ -1157,13 +1207,9 @@ __device__ __forceinline__ void subchunk_masses(const Params& P, int64_t row, in
     double m = 0.0;
 #pragma unroll
     for (int i = 0; i < C::U; ++i) {
-      float t = 0.0f;
-#pragma unroll
-      for (int e = 0; e < C::VW; ++e) {
-        t += weight_of<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps);
-        // two entries at a time keep the weights' temporaries few
-        if (e & 1) __builtin_amdgcn_sched_barrier(0);
-      }
+      const float t = pair_sum<C::VW>([&](int e) {
+        return weight_of<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps);
+      });
       m += (double)t;
     }
     m = wave_sum(m);
@@ -1205,16 +1251,19 @@ __device__ __forceinline__ void pick_tile(const Params& P, int b, int64_t row, i
 // x = sum 2^a_q a_p (entries of zero weight contribute nothing, so -inf
 // logits never meet an infinite factor; a finite-weight q entry facing a -inf
 // p logit makes x = -inf).  Moments outside the set stay 0.
-template <int DT, int MOM>
+template <int DT, int MOM, bool EX>
 __device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
                                           const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW],
-                                          const SeqParam& sp, float rq, float rp, float& sq,
-                                          float& spp, float& hq, float& hp, float& xq) {
+                                          const SeqParam& sp, float rq, float rp,
+                                          ThreadSum<EX>& sq, ThreadSum<EX>& spp, float& hq,
+                                          float& hp, float& xq) {
+  typedef ThreadSum<EX> S;
   using T = StatTile<DT>;
   if constexpr (MOM) {
     // one running sum per quantity: the moments' extra values stay short-lived
 #pragma unroll
-    for (int i = 0; i < T::U; ++i)
+    for (int i = 0; i < T::U; ++i) {
+      float lq = EX ? 0.0f : (float)sq, lp = EX ? 0.0f : (float)spp;
 #pragma unroll
       for (int e = 0; e < T::VW; ++e) {
         const float zq = elem<DT>(wq[i], e), zp = elem<DT>(wp[i], e);
@@ -1222,14 +1271,17 @@ __device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT>::U][
         const float ap = fmaf(zp, sp.c_lo, fmaf(zp, sp.c_hi, -rp));
         const float tq = exp2_hw(aq), tp = exp2_hw(ap);
         const bool wq_pos = tq > 0.0f;
-        sq += tq;
-        spp += tp;
+        lq += tq;
+        lp += tp;
         if constexpr ((MOM & kMomHQ) != 0) hq = fmaf(tq, wq_pos ? aq : 0.0f, hq);
         if constexpr ((MOM & kMomX) != 0) xq = fmaf(tq, wq_pos ? ap : 0.0f, xq);
         if constexpr ((MOM & kMomHP) != 0) hp = fmaf(tp, tp > 0.0f ? ap : 0.0f, hp);
         // keep the scheduler from hoisting every exponential of the tile
         if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
+      sq = EX ? sq + (S)lq : (S)lq;
+      spp = EX ? spp + (S)lp : (S)lp;
+    }
   } else {
 #pragma unroll
     for (int i = 0; i < T::U; ++i) {
@@ -1247,8 +1299,8 @@ __device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT>::U][
           tq[e] += tq[e + h];
           tp[e] += tp[e + h];
         }
-      sq += tq[0];
-      spp += tp[0];
+      sq += (S)tq[0];
+      spp += (S)tp[0];
     }
   }
 }
@@ -1256,7 +1308,7 @@ __device__ __forceinline__ void tile_sums(const uint32_t (&wq)[StatTile<DT>::U][
 // The partial of statistics tile k of row r from its loaded entries (wq, wp),
 // written by thread 0 through agent-scope stores, for readers in the same
 // launch.
-template <int DT, int MOM, bool GR>
+template <int DT, int MOM, bool GR, bool EX>
 __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, const SeqParam& sp,
                                              const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
                                              const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW],
@@ -1295,9 +1347,10 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
   }
   const float rq = (mq == kNegInf) ? 0.0f : mq * sp.c_hi;
   const float rp = (mp == kNegInf) ? 0.0f : mp * sp.c_hi;
-  float sq = 0.0f, spp = 0.0f, hq = 0.0f, hp = 0.0f, xq = 0.0f;
+  ThreadSum<EX> sq = 0, spp = 0;
+  float hq = 0.0f, hp = 0.0f, xq = 0.0f;
   constexpr bool mom = MOM;
-  tile_sums<DT, MOM>(wq, wp, sp, rq, rp, sq, spp, hq, hp, xq);
+  tile_sums<DT, MOM, EX>(wq, wp, sp, rq, rp, sq, spp, hq, hp, xq);
   // the moments are complete here: left free, the compiler sinks their
   // accumulation into the conditional combine below and keeps every
   // exponential of the tile live until then
@@ -1308,7 +1361,7 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const float Wq = wave_max(mq), Wp = wave_max(mp);
   const double eq = (double)rq - (double)(Wq * sp.c_hi), ep = (double)rp - (double)(Wp * sp.c_hi);
-  const double fq = (double)exp2_hw((float)eq), fp = (double)exp2_hw((float)ep);
+  const double fq = ref_fac<EX>(eq), fp = ref_fac<EX>(ep);
   double dq = (mq == kNegInf) ? 0.0 : (double)sq * fq;
   double dp = (mp == kNegInf) ? 0.0 : (double)spp * fp;
   dq = wave_sum(dq);
@@ -1352,9 +1405,9 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
     for (int w = 0; w < kWaves; ++w) {
       const float wq_ = sh.m[w][0], wp_ = sh.m[w][1];
       if (wq_ != kNegInf)
-        tq += sh.d[w][0] * (double)exp2_hw((float)((double)(wq_ * sp.c_hi) - (double)Rq));
+        tq += sh.d[w][0] * ref_fac<EX>((double)(wq_ * sp.c_hi) - (double)Rq);
       if (wp_ != kNegInf)
-        tp += sh.d[w][1] * (double)exp2_hw((float)((double)(wp_ * sp.c_hi) - (double)Rp));
+        tp += sh.d[w][1] * ref_fac<EX>((double)(wp_ * sp.c_hi) - (double)Rp);
     }
     TilePart t;
     t.s_q = tq;
@@ -1384,7 +1437,7 @@ __device__ __forceinline__ void tile_partial(const Params& P, int r, int k, cons
         const float wq_ = sh.m[w][0], wp_ = sh.m[w][1];
         const double gq = (wq_ == kNegInf) ? 0.0 : (double)(wq_ * sp.c_hi) - (double)Rq;
         const double gp = (wp_ == kNegInf) ? 0.0 : (double)(wp_ * sp.c_hi) - (double)Rp;
-        const double fq_ = (double)exp2_hw((float)gq), fp_ = (double)exp2_hw((float)gp);
+        const double fq_ = ref_fac<EX>(gq), fp_ = ref_fac<EX>(gp);
         // a wave's sums d_w are against the wave max, as its moments are
         if (wq_ != kNegInf) mom_add(m.hq, sh.h[w][0], sh.d[w][0], fq_, gq);
         if (wp_ != kNegInf) mom_add(m.hp, sh.h[w][1], sh.d[w][1], fp_, gp);
@@ -1408,22 +1461,15 @@ __device__ __forceinline__ double pass2_sum(const uint32_t (&wq)[U][Tile<DT, U>:
   double acc = 0.0;
 #pragma unroll
   for (int i = 0; i < T::U; ++i) {
-    float t = 0.0f;
-#pragma unroll
-    for (int e = 0; e < T::VW; ++e) {
+    const float t = pair_sum<T::VW>([&](int e) {
       const float zq = elem<DT>(wq[i], e), zp = elem<DT>(wp[i], e);
-      if constexpr (TOK) {
-        t += token_r(ps.tok, zq, zp) ? prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo) : 0.0f;
-      } else {
-        // D_TV for the deferral decision, where an absolute error of about
-        // 1e-7 is far inside the decision margin (the replacement draw sums
-        // the same difference: residual_weight)
-        const float pq = prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo);
-        const float pp = prob(zp, ps.c_hi, ps.c_lo, ps.p_hi, ps.p_lo);
-        t += fmaxf(pp - pq, 0.0f);
-      }
-      if (e & 1) __builtin_amdgcn_sched_barrier(0);
-    }
+      if constexpr (TOK)
+        return token_r(ps.tok, zq, zp) ? prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo) : 0.0f;
+      // D_TV for the deferral decision, where an absolute error of about
+      // 1e-7 is far inside the decision margin (the replacement draw sums
+      // the same difference: residual_weight)
+      return residual_weight<DT>(zq, zp, ps);
+    });
     acc += (double)t;
     // one lane load at a time: with the whole tile already in registers the
     // scheduler would otherwise start every entry's exponentials at once
@@ -1491,12 +1537,9 @@ __device__ __forceinline__ double slice_masses_of(const uint32_t (&cq)[StatTile<
   double mine = 0.0;
 #pragma unroll
   for (int i = 0; i < T::U; ++i) {
-    float t = 0.0f;
-#pragma unroll
-    for (int e = 0; e < T::VW; ++e) {
-      t += weight_k<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps, kind);
-      if (e & 1) __builtin_amdgcn_sched_barrier(0);
-    }
+    const float t = pair_sum<T::VW>([&](int e) {
+      return weight_k<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps, kind);
+    });
     const double s = wave_sum((double)t);
     if (lane == i) mine = s;
     __builtin_amdgcn_sched_barrier(0);
@@ -2149,7 +2192,7 @@ __device__ __forceinline__ void draw_stats(const Params& P, int b, int64_t row, 
 // With first moments the block is held to 96 VGPRs (five workgroups per
 // SIMD); the two-tile form keeps its registers (capped, it spills in the
 // streaming loop).
-template <int DT, int MS, int TVM, bool PAIR = false, bool GR = true>
+template <int DT, int MS, int TVM, bool EX, bool PAIR = false, bool GR = true>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
   static_assert(!PAIR || TVM == kTvNone, "a pair of tiles takes no TV pass");
@@ -2177,17 +2220,17 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
   mask_tile<DT, T::U>(qrow, t0, V, wq, threadIdx.x);
   mask_tile<DT, T::U>(prow, t0, V, wp, threadIdx.x);
   if (MS != 0 && needs_mom(sp))
-    tile_partial<DT, MS, GR>(P, r, k, sp, wq, wp, sh);
+    tile_partial<DT, MS, GR, EX>(P, r, k, sp, wq, wp, sh);
   else
-    tile_partial<DT, 0, GR>(P, r, k, sp, wq, wp, sh);
+    tile_partial<DT, 0, GR, EX>(P, r, k, sp, wq, wp, sh);
   if constexpr (PAIR) {
     if (two) {
       mask_tile<DT, T::U>(qrow, t0 + T::N, V, vq, threadIdx.x);
       mask_tile<DT, T::U>(prow, t0 + T::N, V, vp, threadIdx.x);
       if (MS != 0 && needs_mom(sp))
-        tile_partial<DT, MS, GR>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
+        tile_partial<DT, MS, GR, EX>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
       else
-        tile_partial<DT, 0, GR>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
+        tile_partial<DT, 0, GR, EX>(P, r, k + 1, sp, vq, vp, shs[PAIR ? 1 : 0]);
     }
   }
   const uint32_t n = two ? 2u : 1u;  // tiles this block adds to its row
@@ -2378,7 +2421,7 @@ __global__ __launch_bounds__(kJobThreads) __attribute__((amdgpu_waves_per_eu(4))
   }
 }
 
-template <int DT>
+template <int DT, bool EX>
 hipError_t launch_step_t(const Params& P, hipStream_t st, bool draw_pass, bool tv_pass,
                          bool job_pass, int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end) {
   const dim3 grid((unsigned)P.nt, (unsigned)(P.B * (P.gamma + 1))), block(kThreads);
@@ -2390,25 +2433,25 @@ hipError_t launch_step_t(const Params& P, hipStream_t st, bool draw_pass, bool t
   if (!P.tv_self && P.pair && P.mom_set == 0) {
     const dim3 grid2((unsigned)((P.nt + 1) / 2), (unsigned)(P.B * (P.gamma + 1)));
     if (P.may_greedy)
-      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, true>), grid2, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, EX, true>), grid2, block, 0, st, P);
     else
-      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, true, false>), grid2, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, EX, true, false>), grid2, block, 0, st, P);
   } else if (!P.tv_self) {
     if (P.mom_set == 0 && P.may_greedy)
-      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, EX>), grid, block, 0, st, P);
     else if (P.mom_set == 0)
-      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, false, false>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvNone, EX, false, false>), grid, block, 0, st, P);
     else if (P.mom_set == kMomX)
-      hipLaunchKernelGGL((k_tiles<DT, kMomX, kTvNone>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, kMomX, kTvNone, EX>), grid, block, 0, st, P);
     else if (P.mom_set == kMomHQ)
-      hipLaunchKernelGGL((k_tiles<DT, kMomHQ, kTvNone>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, kMomHQ, kTvNone, EX>), grid, block, 0, st, P);
     else
-      hipLaunchKernelGGL((k_tiles<DT, kAll, kTvNone>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, kAll, kTvNone, EX>), grid, block, 0, st, P);
   } else {
     if (P.mom_set == 0)
-      hipLaunchKernelGGL((k_tiles<DT, 0, kTvSelf>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, 0, kTvSelf, EX>), grid, block, 0, st, P);
     else
-      hipLaunchKernelGGL((k_tiles<DT, kAll, kTvSelf>), grid, block, 0, st, P);
+      hipLaunchKernelGGL((k_tiles<DT, kAll, kTvSelf, EX>), grid, block, 0, st, P);
   }
   hipError_t err = hipGetLastError();
   if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, st);
@@ -2475,7 +2518,7 @@ struct SeqAcc {
 };
 template <int DT, class C, bool MOM>
 __device__ __forceinline__ void seq_sum(ChunkRegs<C>& wq, ChunkRegs<C>& wp, int c0,
-                                        const SeqParam& sp, SeqAcc& a) {
+                                        bool first, const SeqParam& sp, SeqAcc& a) {
 #pragma clang fp contract(off)
   float nq = a.mq, np = a.mp;
 #pragma unroll
@@ -2525,17 +2568,27 @@ __device__ __forceinline__ void seq_sum(ChunkRegs<C>& wq, ChunkRegs<C>& wp, int 
     tp += (double)ep[0];
     __builtin_amdgcn_sched_barrier(0);
   }
-  // the earlier chunks' sums move to the new references
-  const double gq = a.mq == kNegInf ? 0.0 : (double)(a.mq * sp.c_hi) - (double)rq;
-  const double gp = a.mp == kNegInf ? 0.0 : (double)(a.mp * sp.c_hi) - (double)rp;
-  const double fq = (double)exp2_hw((float)gq), fp = (double)exp2_hw((float)gp);
-  if constexpr (MOM) {
-    a.hq = mom_move(a.hq, a.sq, fq, gq) + (double)hq;
-    a.hp = mom_move(a.hp, a.sp, fp, gp) + (double)hp;
-    a.x = mom_move(a.x, a.sq, fq, gp) + (double)x;
+  if (first) {  // wave-uniform
+    a.sq = tq;
+    a.sp = tp;
+    if constexpr (MOM) {
+      a.hq = (double)hq;
+      a.hp = (double)hp;
+      a.x = (double)x;
+    }
+  } else {
+    // the earlier chunks' sums move to the new references
+    const double gq = a.mq == kNegInf ? 0.0 : (double)(a.mq * sp.c_hi) - (double)rq;
+    const double gp = a.mp == kNegInf ? 0.0 : (double)(a.mp * sp.c_hi) - (double)rp;
+    const double fq = exp2_fac(gq), fp = exp2_fac(gp);
+    if constexpr (MOM) {
+      a.hq = mom_move(a.hq, a.sq, fq, gq) + (double)hq;
+      a.hp = mom_move(a.hp, a.sp, fp, gp) + (double)hp;
+      a.x = mom_move(a.x, a.sq, fq, gp) + (double)x;
+    }
+    a.sq = a.sq * fq + tq;
+    a.sp = a.sp * fp + tp;
   }
-  a.sq = a.sq * fq + tq;
-  a.sp = a.sp * fp + tp;
   a.mq = nq;
   a.mp = np;
 }
@@ -2600,10 +2653,9 @@ __device__ __forceinline__ bool seq_draw(const Params& P, int b, int f, const Se
   ChunkRegs<C> cq = {}, cp = {};
   for (int sc = wv; sc < ns; sc += kSeqWaves) {
     load_chunks<DT, C, KIND>(qrow, prow, (int64_t)sc * C::N, V, cq, cp, P.hdr);
-    float t = 0.0f;
-#pragma unroll
-    for (int e = 0; e < C::VW; ++e)
-      t += weight_of<DT, KIND>(elem<DT>(cq[0], e), elem<DT>(cp[0], e), ps);
+    const float t = pair_sum<C::VW>([&](int e) {
+      return weight_of<DT, KIND>(elem<DT>(cq[0], e), elem<DT>(cp[0], e), ps);
+    });
     const double m = wave_sum((double)t);
     if (lane == 0) sh.mass[sc] = m;
   }
@@ -2669,8 +2721,8 @@ __global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
     SeqAcc a;
     seq_chunks<DT, C>(qrow, prow, V, wi, wpr, P.hdr,
                       [&](ChunkRegs<C>& q, ChunkRegs<C>& p, int c0) {
-                        if (MS != 0 && mrule) seq_sum<DT, C, true>(q, p, c0, sp, a);
-                        else seq_sum<DT, C, false>(q, p, c0, sp, a);
+                        if (MS != 0 && mrule) seq_sum<DT, C, true>(q, p, c0, c0 == wi * C::N, sp, a);
+                        else seq_sum<DT, C, false>(q, p, c0, c0 == wi * C::N, sp, a);
                       });
     if (dec0 && j == slot && pre.x >= 0 && pre.x < V) {
       pre.zqx = load_logit<DT>(P.q, r0 + j, V, pre.x);
@@ -2679,7 +2731,7 @@ __global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
     const float Mq = wave_max(a.mq), Mp = wave_max(a.mp);
     const double gq = a.mq == kNegInf ? 0.0 : (double)(a.mq * sp.c_hi) - (double)(Mq * sp.c_hi);
     const double gp = a.mp == kNegInf ? 0.0 : (double)(a.mp * sp.c_hi) - (double)(Mp * sp.c_hi);
-    const double fq = (double)exp2_hw((float)gq), fp = (double)exp2_hw((float)gp);
+    const double fq = exp2_fac(gq), fp = exp2_fac(gp);
     SeqPart t;
     t.mq = Mq;
     t.mp = Mp;
@@ -2716,28 +2768,33 @@ __global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
   for (int j = slot; j < jend && wi == 0; j += rpp) {
     DraftIn in = inputs(j);
     if (sp.greedy && sp.valid) in.x = draft_token(P, b, j);
+    // (one share, of a row read by one wavefront, is the row's)
     const SeqPart* t = sh.part + j * wpr;
-    float Mq = kNegInf, Mp = kNegInf;
-    for (int w = 0; w < wpr; ++w) {
+    float Mq = t[0].mq, Mp = t[0].mp;
+    for (int w = 1; w < wpr; ++w) {
       Mq = fmaxf(Mq, t[w].mq);
       Mp = fmaxf(Mp, t[w].mp);
     }
     const double Rq = (double)(Mq * sp.c_hi), Rp = (double)(Mp * sp.c_hi);
-    double Sq = 0.0, Sp = 0.0, Hq = 0.0, Hp = 0.0, X = 0.0;
-    int kq = 0x7fffffff, kp = 0x7fffffff;
-    for (int w = 0; w < wpr; ++w) {
-      if (t[w].mq == Mq) kq = min(kq, t[w].kq);
-      if (t[w].mp == Mp) kp = min(kp, t[w].kp);
-      const bool iq = t[w].mq != kNegInf, ip = t[w].mp != kNegInf;
-      const double gq = iq ? (double)(t[w].mq * sp.c_hi) - Rq : 0.0;
-      const double gp = ip ? (double)(t[w].mp * sp.c_hi) - Rp : 0.0;
-      const double fq = (double)exp2_hw((float)gq), fp = (double)exp2_hw((float)gp);
-      if (iq) Sq += t[w].sq * fq;
-      if (ip) Sp += t[w].sp * fp;
-      if (MS != 0 && mrule) {
-        if (iq) mom_add(Hq, t[w].hq, t[w].sq, fq, gq);
-        if (ip) mom_add(Hp, t[w].hp, t[w].sp, fp, gp);
-        if (iq) mom_add(X, t[w].x, t[w].sq, fq, ip ? gp : -__builtin_huge_val());
+    double Sq = t[0].sq, Sp = t[0].sp, Hq = t[0].hq, Hp = t[0].hp, X = t[0].x;
+    int kq = t[0].kq, kp = t[0].kp;
+    if (wpr > 1) {  // uniform
+      Sq = Sp = Hq = Hp = X = 0.0;
+      kq = kp = 0x7fffffff;
+      for (int w = 0; w < wpr; ++w) {
+        if (t[w].mq == Mq) kq = min(kq, t[w].kq);
+        if (t[w].mp == Mp) kp = min(kp, t[w].kp);
+        const bool iq = t[w].mq != kNegInf, ip = t[w].mp != kNegInf;
+        const double gq = iq ? (double)(t[w].mq * sp.c_hi) - Rq : 0.0;
+        const double gp = ip ? (double)(t[w].mp * sp.c_hi) - Rp : 0.0;
+        const double fq = exp2_fac(gq), fp = exp2_fac(gp);
+        if (iq) Sq += t[w].sq * fq;
+        if (ip) Sp += t[w].sp * fp;
+        if (MS != 0 && mrule) {
+          if (iq) mom_add(Hq, t[w].hq, t[w].sq, fq, gq);
+          if (ip) mom_add(Hp, t[w].hp, t[w].sp, fp, gp);
+          if (iq) mom_add(X, t[w].x, t[w].sq, fq, ip ? gp : -__builtin_huge_val());
+        }
       }
     }
     RowStat rs{};
@@ -3024,34 +3081,38 @@ __device__ __forceinline__ RowStat small_stats(SmallRegs<DT>& wq, SmallRegs<DT>&
   }
   const float rq = (mq == kNegInf) ? 0.0f : mq * sp.c_hi;
   const float rp = (mp == kNegInf) ? 0.0f : mp * sp.c_hi;
-  float sq = 0.0f, spp = 0.0f, hq = 0.0f, hp = 0.0f, xq = 0.0f;
+  double sq = 0.0, spp = 0.0;
+  float hq = 0.0f, hp = 0.0f, xq = 0.0f;
 #pragma unroll
   for (int i = 0; i < kSmallU; ++i) {
     if (!small_live<DT>(i, V)) continue;  // wavefront-uniform
     const bool ok = small_ok<DT>(i, V);
-#pragma unroll
-    for (int e = 0; e < T::VW; ++e) {
-      const float zq = small_elem<DT>(wq[i], e, ok), zp = small_elem<DT>(wp[i], e, ok);
-      const float aq = fmaf(zq, sp.c_lo, fmaf(zq, sp.c_hi, -rq));
-      const float ap = fmaf(zp, sp.c_lo, fmaf(zp, sp.c_hi, -rp));
-      const float tq = exp2_hw(aq), tp = exp2_hw(ap);
-      sq += tq;
-      spp += tp;
+    const auto arg = [&](const uint32_t* w, int e, float r) {
+      const float z = small_elem<DT>(w, e, ok);
+      return fmaf(z, sp.c_lo, fmaf(z, sp.c_hi, -r));
+    };
+    // float32 pairwise within a lane load, float64 across them
+    sq += (double)pair_sum<T::VW>([&](int e) {
+      const float aq = arg(wq[i], e, rq), tq = exp2_hw(aq);
       if constexpr (MOM) {
         hq = fmaf(tq, tq > 0.0f ? aq : 0.0f, hq);
-        xq = fmaf(tq, tq > 0.0f ? ap : 0.0f, xq);
-        hp = fmaf(tp, tp > 0.0f ? ap : 0.0f, hp);
+        xq = fmaf(tq, tq > 0.0f ? arg(wp[i], e, rp) : 0.0f, xq);
       }
-      if (e & 1) __builtin_amdgcn_sched_barrier(0);
-    }
+      return tq;
+    });
+    spp += (double)pair_sum<T::VW>([&](int e) {
+      const float ap = arg(wp[i], e, rp), tp = exp2_hw(ap);
+      if constexpr (MOM) hp = fmaf(tp, tp > 0.0f ? ap : 0.0f, hp);
+      return tp;
+    });
   }
   small_fence(wq, wp);
   // waves against the wave max, then the block against the row max (fp64)
   const float Wq = wave_max(mq), Wp = wave_max(mp);
   const double eq = (double)rq - (double)(Wq * sp.c_hi), ep = (double)rp - (double)(Wp * sp.c_hi);
-  const double fq = exp2_acc(eq), fp = exp2_acc(ep);
-  const double dq = wave_sum(mq == kNegInf ? 0.0 : (double)sq * fq);
-  const double dp = wave_sum(mp == kNegInf ? 0.0 : (double)spp * fp);
+  const double fq = exp2_fac(eq), fp = exp2_fac(ep);
+  const double dq = wave_sum(mq == kNegInf ? 0.0 : sq * fq);
+  const double dp = wave_sum(mp == kNegInf ? 0.0 : spp * fp);
   double mhq = 0.0, mhp = 0.0, mx = 0.0;
   if constexpr (MOM) {
     mhq = wave_sum(mq == kNegInf ? 0.0 : mom_move(hq, sq, fq, eq));
@@ -3118,13 +3179,9 @@ template <int DT, int KIND>
 __device__ __forceinline__ float small_weight_row(const uint32_t (&wq)[Tile<DT, kSmallU>::NW],
                                                   const uint32_t (&wp)[Tile<DT, kSmallU>::NW],
                                                   bool ok, const ProbScale& ps, int kind) {
-  float t = 0.0f;
-#pragma unroll
-  for (int e = 0; e < Tile<DT, kSmallU>::VW; ++e) {
-    t += weight_k<DT, KIND>(small_elem<DT>(wq, e, ok), small_elem<DT>(wp, e, ok), ps, kind);
-    if (e & 1) __builtin_amdgcn_sched_barrier(0);
-  }
-  return t;
+  return pair_sum<Tile<DT, kSmallU>::VW>([&](int e) {
+    return weight_k<DT, KIND>(small_elem<DT>(wq, e, ok), small_elem<DT>(wp, e, ok), ps, kind);
+  });
 }
 
 // Whole block: the masses of the row's sub-chunks under KIND (sub-chunk
@@ -3258,20 +3315,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
     for (int i = 0; i < kSmallU; ++i) {
       if (!small_live<DT>(i, V)) continue;  // wavefront-uniform
       const bool ok = small_ok<DT>(i, V);
-      float t = 0.0f;
-#pragma unroll
-      for (int e = 0; e < T::VW; ++e) {
+      acc += (double)pair_sum<T::VW>([&](int e) {
         const float zq = small_elem<DT>(wq[i], e, ok), zp = small_elem<DT>(wp[i], e, ok);
-        if (eta) {
-          t += token_r(ps.tok, zq, zp) ? prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo) : 0.0f;
-        } else {
-          const float pq = prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo);
-          const float pp = prob(zp, ps.c_hi, ps.c_lo, ps.p_hi, ps.p_lo);
-          t += fmaxf(pp - pq, 0.0f);
-        }
-        if (e & 1) __builtin_amdgcn_sched_barrier(0);
-      }
-      acc += (double)t;
+        if (eta)
+          return token_r(ps.tok, zq, zp) ? prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo) : 0.0f;
+        return residual_weight<DT>(zq, zp, ps);
+      });
     }
     rs.tv = small_sum(acc, sh);
     small_fence(wq, wp);
@@ -3370,7 +3419,7 @@ hipError_t launch_small_t(const Params& P, hipStream_t st, hipEvent_t ev_begin,
 // masses give the tile where u W falls, then the tile's sub-chunks and
 // lanes are scanned in vocabulary order.  A greedy row (temperature 0)
 // takes the lowest index attaining its max instead.
-template <int DT, bool ARGMAX, int TM>
+template <int DT, bool ARGMAX, int TM, bool EX>
 __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
   using T = DraftTile<DT, TM>;
   __shared__ Shared sh;
@@ -3408,7 +3457,7 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
       for (int j = 0; j < T::NW; ++j) asm volatile("" : "+v"(w[i][j]));
   }
   const float r = (m == kNegInf) ? 0.0f : m * sp.c_hi;
-  float s = 0.0f;
+  ThreadSum<EX> s = 0;
 #pragma unroll
   for (int i = 0; i < T::U; ++i) {
     float t[T::VW];
@@ -3421,13 +3470,12 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
     for (int h = 1; h < T::VW; h <<= 1)
 #pragma unroll
       for (int e = 0; e + h < T::VW; e += 2 * h) t[e] += t[e + h];
-    s += t[0];
+    s += (ThreadSum<EX>)t[0];
   }
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const float Wm = wave_max(m);
-  double d = (m == kNegInf)
-                 ? 0.0
-                 : (double)s * (double)exp2_hw((float)((double)r - (double)(Wm * sp.c_hi)));
+  const double fd = ref_fac<EX>((double)r - (double)(Wm * sp.c_hi));
+  double d = (m == kNegInf) ? 0.0 : (double)s * fd;
   d = wave_sum(d);
   if constexpr (ARGMAX) im = wave_min((m == Wm) ? im : 0x7fffffff);
   if (lane == 0) {
@@ -3447,7 +3495,7 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
     for (int x = 0; x < kWaves; ++x) {
       const float wm = sh.m[x][0];
       if (wm != kNegInf)
-        tot += sh.d[x][0] * (double)exp2_hw((float)((double)(wm * sp.c_hi) - (double)R));
+        tot += sh.d[x][0] * ref_fac<EX>((double)(wm * sp.c_hi) - (double)R);
       if (ARGMAX && wm == M) am = min(am, sh.i[x][0]);
     }
     TilePart t{tot, 0.0, (M == kNegInf) ? kNegInf : R, kNegInf, M, kNegInf,
@@ -3523,13 +3571,13 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
                                        sh);
 }
 
-template <int DT, int TM>
+template <int DT, int TM, bool EX>
 hipError_t launch_draft_t(const Params& P, bool argmax, hipStream_t st) {
   const dim3 grid(P.nt, P.B);
   if (argmax)
-    hipLaunchKernelGGL((k_draft<DT, true, TM>), grid, dim3(kThreads), 0, st, P);
+    hipLaunchKernelGGL((k_draft<DT, true, TM, EX>), grid, dim3(kThreads), 0, st, P);
   else
-    hipLaunchKernelGGL((k_draft<DT, false, TM>), grid, dim3(kThreads), 0, st, P);
+    hipLaunchKernelGGL((k_draft<DT, false, TM, EX>), grid, dim3(kThreads), 0, st, P);
   return hipGetLastError();
 }
 
@@ -3551,9 +3599,13 @@ int draft_tile_elems(int dtype, bool long_tiles) {
 
 hipError_t launch_draft(const Params& P, int dtype, bool argmax, bool long_tiles,
                         hipStream_t st) {
-  if (long_tiles)
-    return dtype == 1 ? launch_draft_t<1, 2>(P, argmax, st) : launch_draft_t<0, 2>(P, argmax, st);
-  return dtype == 1 ? launch_draft_t<1, 1>(P, argmax, st) : launch_draft_t<0, 1>(P, argmax, st);
+  const bool ex = P.V % (dtype == 1 ? StatTile<1>::VW : StatTile<0>::VW) != 0;  // as launch_step
+  const auto launch =
+      dtype == 1 ? (long_tiles ? (ex ? launch_draft_t<1, 2, true> : launch_draft_t<1, 2, false>)
+                               : (ex ? launch_draft_t<1, 1, true> : launch_draft_t<1, 1, false>))
+                 : (long_tiles ? (ex ? launch_draft_t<0, 2, true> : launch_draft_t<0, 2, false>)
+                               : (ex ? launch_draft_t<0, 1, true> : launch_draft_t<0, 1, false>));
+  return launch(P, argmax, st);
 }
 
 namespace {
@@ -3594,9 +3646,11 @@ hipError_t launch_small(const Params& P, int dtype, hipEvent_t ev_begin,
 hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass, bool job_pass,
                        int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end,
                        hipStream_t st) {
-  if (dtype == 1)
-    return launch_step_t<1>(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin, ev_end);
-  return launch_step_t<0>(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin, ev_end);
+  // rows that start inside a vector take the EX sums (ref_fac)
+  const bool ex = P.V % (dtype == 1 ? StatTile<1>::VW : StatTile<0>::VW) != 0;
+  const auto launch = dtype == 1 ? (ex ? launch_step_t<1, true> : launch_step_t<1, false>)
+                                 : (ex ? launch_step_t<0, true> : launch_step_t<0, false>);
+  return launch(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin, ev_end);
 }
 
 }  // namespace spc
