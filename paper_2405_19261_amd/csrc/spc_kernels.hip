@@ -2190,11 +2190,12 @@ __device__ __forceinline__ void draw_stats(const Params& P, int b, int64_t row, 
 // own row's TV pass; otherwise waves 1-3 leave after the partials.
 // GR: some row may be at temperature 0 (its tiles track their argmax).
 // With first moments the block is held to 96 VGPRs (five workgroups per
-// SIMD); the two-tile form keeps its registers (capped, it spills in the
-// streaming loop).
+// SIMD), with EX to 128, where it spills nothing (bfloat16 DiffLog B = 24
+// gamma = 5 V = 100 003: 42.2 us at five, 36.8 at four); the two-tile form
+// keeps its registers (capped, it spills in the streaming loop).
 template <int DT, int MS, int TVM, bool EX, bool PAIR = false, bool GR = true>
 __global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(MS != 0 ? 5 : 1))) void k_tiles(Params P) {
+__attribute__((amdgpu_waves_per_eu(MS != 0 ? (EX ? 4 : 5) : 1))) void k_tiles(Params P) {
   static_assert(!PAIR || TVM == kTvNone, "a pair of tiles takes no TV pass");
   constexpr bool NT = true;
   using T = StatTile<DT>;
