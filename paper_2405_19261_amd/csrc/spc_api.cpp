@@ -293,7 +293,11 @@ Route choose_route(int64_t B, int64_t b_launch, int64_t R, int64_t g1, int64_t V
   if (t.small) return t;
   // Where TV rows get their TV pass.  In a grid that is resident at once
   // (at most two workgroups per compute unit) each TV row takes it from
-  // its own tiles' registers once the row is merged (tv_self).  Otherwise
+  // its own tiles' registers once the row is merged (tv_self), up to the 62
+  // tiles a row's gate holds.  (With more the second read is no slower: at 63,
+  // float32 V = 256 000, rows that wait for 62 others, against k_tvpass:
+  // gamma = 1 OPT 21.8 / 22.0 us, OPTLog 21.1 / 20.0; gamma = 7 OPT 26.9 /
+  // 26.7, OPTLog 26.3 / 23.7.)  Otherwise
   // a kernel of its own reads the TV rows again after the statistics
   // kernel (k_tvpass) when the rule is batch-wide, so that most rows may
   // need it; with per-sequence rules (a few TV rows among others) their

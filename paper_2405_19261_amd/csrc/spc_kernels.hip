@@ -1883,33 +1883,6 @@ __device__ __forceinline__ void tv_row_done(const Params& P, int rv) {
   }
 }
 
-// Wave: n tiles of TV row rv arrive without a TV pass, the row having been
-// decided without one; the last arrival clears the gate for the next call.
-__device__ __forceinline__ void tv_skip_arrive_w(const Params& P, int rv, uint32_t n) {
-  if (arrive_last_w(row_word(P, rv, kRowTvArrive), (uint32_t)(kSlices * P.nt), kSlices * n) &&
-      (threadIdx.x & 63) == 0)
-    st_u64(row_gate(P, rv), 0ull);
-}
-
-// Wave (the row's merge): the TV pass of the tiles whose workgroups gave up
-// waiting, their entries read again.
-template <int DT>
-__device__ __forceinline__ void tv_take_over_w(const Params& P, int r, uint64_t lost, bool skip,
-                                               const SeqParam& sp) {
-  const uint32_t n = (uint32_t)__popcll(lost);
-  if (skip) {
-    tv_skip_arrive_w(P, r, n);
-    return;
-  }
-#pragma unroll 1
-  for (uint64_t m = lost; m; m &= m - 1)
-#pragma unroll 1
-    for (int w = 0; w < kSlices; ++w)
-      pass2_slice_w<DT, false>(P, r, __builtin_ctzll(m), w, sp);
-  if (arrive_last_w(row_word(P, r, kRowTvArrive), (uint32_t)(kSlices * P.nt), kSlices * n))
-    tv_row_done<DT>(P, r);
-}
-
 // Wave: the lowest indices of greedy row r's two maxima, from the starts of
 // the lane loads that hold them (rs.amax_q / amax_p), read again entry by
 // entry: lanes 0 .. 31 q's, lanes 32 .. 63 p's, one round trip.
@@ -1932,9 +1905,10 @@ __device__ __forceinline__ void arg_rows_w(const Params& P, int r, RowStat& rs) 
 // Wave, after the last tile of row r = (b, j) arrived: merge the row, then
 // open its second pass (TV, or eta for the tiles its statistics leave open),
 // or decide it and, when that settles j*, finish the sequence.
+// lost (LDS, kTvSelf): the tiles of a TV row left to this workgroup.
 template <int DT, int MS, int TVM, bool GR>
 __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int j,
-                                             const SeqParam& sp, int x) {
+                                             const SeqParam& sp, int x, uint64_t* lost) {
   const int lane = threadIdx.x & 63;
   const int nt = P.nt;
   // the decision's draft inputs, requested together with the tile partials
@@ -1945,9 +1919,9 @@ __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int 
   if (GR && sp.valid && sp.greedy) arg_rows_w<DT>(P, r, rs);
   if (sp.valid && !sp.greedy && has_tv_parts(sp.rule)) {
     // Without row statistics to report, a row whose decision D_TV cannot
-    // change is decided now and takes no TV pass: its ready flag says 2 to
-    // its own waiting workgroups (tv_self) and stays 0 for the TV pass
-    // kernel.  Every other row is published as merged (flag 1).
+    // change is decided now and takes no TV pass: its gate says so to its own
+    // waiting workgroups (tv_self), its ready flag stays 0 for the TV pass
+    // kernel.  Every other row is published as merged.
     // (the tile-mass bound, lowered by 1e-5 relative and 1e-6 absolute: the
     // computed D_TV, whose error is ~1e-7 of the mass summed, stays above it)
     const double lo = fmax(0.0, tv_low * (1.0 - 1e-5) - 1e-6);
@@ -1964,11 +1938,8 @@ __device__ __forceinline__ void row_merged_w(const Params& P, int r, int b, int 
       publish_singles_w(P, kJobTvSlice, (uint32_t)r, (uint32_t)(nt * kSlices));
     if constexpr (TVM == kTvSelf) {
       // release the row's waiting workgroups; the tiles of those that gave up
-      // before are this wavefront's
-      uint64_t old = 0;
-      if (lane == 0) old = or_u64(row_gate(P, r), free ? kTvSkip : kTvReady);
-      const uint64_t lost = lane_u64(old, 0) & kTvLost;
-      if (lost) tv_take_over_w<DT>(P, r, lost, free, sp);
+      // before are this workgroup's (tv_self)
+      if (lane == 0) *lost = or_u64(row_gate(P, r), free ? kTvSkip : kTvReady) & kTvLost;
     }
     if (!free) return;
     rs.tv = 1.0;  // any D_TV in [lo, 1] decides it alike
@@ -2044,25 +2015,32 @@ __device__ __forceinline__ uint32_t tv_wait_ready(const Params& P, int rv, int k
 // Whole block: the TV pass over tile k of the block's own row r from the
 // registers that hold the tile (small batches: every tile of the grid is
 // resident at once, so the row's last tile arrives while the others wait).
-// Once the row's merge has set its ready flag each wavefront sums its slice;
-// the last of the row's slices decides the row.
+// Once the row's merge has set its gate each wavefront sums its slice; the
+// last of the row's slices decides the row.  The merging workgroup then takes
+// the tiles left to it (lost, zero elsewhere), reading them again, and
+// arrives for them too.  (In the merge itself, with the own tile's registers
+// live, the same code raised the kernel from 113 to 140 VGPRs.)
 template <int DT>
 __device__ __forceinline__ void tv_self(
-    const Params& P, int r, int k, const SeqParam& sp, Shared& sh,
+    const Params& P, int r, int k, const SeqParam& sp, Shared& sh, const uint64_t* lost,
     const uint32_t (&wq)[StatTile<DT>::U][StatTile<DT>::NW],
     const uint32_t (&wp)[StatTile<DT>::U][StatTile<DT>::NW]) {
   const uint32_t f = tv_wait_ready(P, r, k, sh);  // block-uniform
   if (f == 0u) return;
-  if (f == 2u) {
-    if (threadIdx.x < 64) tv_skip_arrive_w(P, r, 1u);
-    return;
+  if (f == 1u) tv_slice_regs_w<DT>(P, r, k, threadIdx.x >> 6, sp, wq, wp);
+  const uint64_t mine = *lost;
+  if (f == 1u) {  // (decided without a TV pass: nothing to read)
+#pragma unroll 1
+    for (uint64_t m = mine; m; m &= m - 1)
+      pass2_slice_w<DT, false>(P, r, __builtin_ctzll(m), threadIdx.x >> 6, sp);
   }
-  tv_slice_regs_w<DT>(P, r, k, threadIdx.x >> 6, sp, wq, wp);
   vmem_drain();
   __syncthreads();  // all four slices are stored
-  if (threadIdx.x < 64 &&
-      arrive_last_w(row_word(P, r, kRowTvArrive), (uint32_t)(kSlices * P.nt), kSlices))
-    tv_row_done<DT>(P, r);
+  if (threadIdx.x < 64 && arrive_last_w(row_word(P, r, kRowTvArrive), (uint32_t)(kSlices * P.nt),
+                                        kSlices * (1u + (uint32_t)__popcll(mine)))) {
+    if (f == 1u) tv_row_done<DT>(P, r);
+    else if (threadIdx.x == 0) st_u64(row_gate(P, r), 0ull);
+  }
 }
 
 // ---------------------------------------------------------------- draws
@@ -2192,15 +2170,18 @@ __device__ __forceinline__ void draw_stats(const Params& P, int b, int64_t row, 
 // With first moments the block is held to 96 VGPRs (five workgroups per
 // SIMD), with EX to 128, where it spills nothing (bfloat16 DiffLog B = 24
 // gamma = 5 V = 100 003: 42.2 us at five, 36.8 at four); the two-tile form
-// keeps its registers (capped, it spills in the streaming loop).
+// keeps its registers (capped, it spills in the streaming loop), and so does
+// kTvSelf, whose grids put at most two workgroups on a compute unit.
 template <int DT, int MS, int TVM, bool EX, bool PAIR = false, bool GR = true>
 __global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(MS != 0 ? (EX ? 4 : 5) : 1))) void k_tiles(Params P) {
+__attribute__((amdgpu_waves_per_eu(MS != 0 && TVM == kTvNone ? (EX ? 4 : 5) : 1))) void k_tiles(
+    Params P) {
   static_assert(!PAIR || TVM == kTvNone, "a pair of tiles takes no TV pass");
   constexpr bool NT = true;
   using T = StatTile<DT>;
   __shared__ Shared shs[PAIR ? 2 : 1];
   Shared& sh = shs[0];
+  __shared__ uint64_t lost;
   const int k = PAIR ? 2 * (int)blockIdx.x : (int)blockIdx.x, r = blockIdx.y;
   const int nt = P.nt, g1 = P.gamma + 1, V = P.V;
   const int b = r / g1, j = r - b * g1;
@@ -2236,6 +2217,7 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? (EX ? 4 : 5) : 1))) void k_tiles(Pa
   }
   const uint32_t n = two ? 2u : 1u;  // tiles this block adds to its row
   if (threadIdx.x < 64) {
+    if (TVM == kTvSelf && threadIdx.x == 0) lost = 0ull;
     // wave 0: thread 0 stored the partials; arrive on the row's counter
     uint32_t prev = 0;
     if (threadIdx.x == 0) {
@@ -2245,11 +2227,11 @@ __attribute__((amdgpu_waves_per_eu(MS != 0 ? (EX ? 4 : 5) : 1))) void k_tiles(Pa
     }
     if ((uint32_t)lane_i32((int)prev, 0) + n == (uint32_t)nt) {
       vmem_drain();
-      row_merged_w<DT, MS, TVM, GR>(P, r, b, j, sp, x);
+      row_merged_w<DT, MS, TVM, GR>(P, r, b, j, sp, x, &lost);
     }
   }
   if constexpr (TVM == kTvSelf) {
-    if (sp.valid && !sp.greedy && has_tv_parts(sp.rule)) tv_self<DT>(P, r, k, sp, sh, wq, wp);
+    if (sp.valid && !sp.greedy && has_tv_parts(sp.rule)) tv_self<DT>(P, r, k, sp, sh, &lost, wq, wp);
   }
 }
 

@@ -28,6 +28,9 @@ def route(B, gamma, V, dtype, rules, per_seq=False, greedy=False):
     ((8, 4, 20000, "bf16", [W.DIFFLOG]), TILES),  # no first moments in rows held by a workgroup
     # a resident grid with per-sequence rules takes its TV passes itself
     ((4, 4, 100000, "bf16", [W.DIFF, W.OPT], True), TILES | TV_SELF),
+    # more tiles a row than its gate holds
+    ((1, 1, 253952, "f32", [W.OPT]), TILES | TV_SELF),
+    ((1, 1, 256000, "f32", [W.OPT]), TILES | TV_PASS),
     # sizes no call takes
     ((0, 4, 1000, "bf16", [W.DIFF]), 0), ((1, 64, 1000, "bf16", [W.DIFF]), 0),
     ((1, 4, 1, "bf16", [W.DIFF]), 0)])

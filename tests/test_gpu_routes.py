@@ -210,7 +210,7 @@ def test_short_sequences_identical_models(dtype, gamma, V):
 @pytest.mark.parametrize("ticks", [None, "0"])
 @pytest.mark.parametrize("dtype,B,gamma,V,rule,want", [
     ("f32", 1, 2, 253952, W.OPT, TV_SELF), ("f32", 1, 2, 253953, W.OPT, TV_PASS),
-    ("f32", 1, 1, 253952, W.OPTLOG, TV_SELF), ("f32", 8, 5, 32128, W.OPT, TV_SELF),
+    ("f32", 1, 1, 253952, W.OPTLOG, TV_SELF), ("f32", 1, 1, 256000, W.OPTLOG, TV_PASS), ("f32", 8, 5, 32128, W.OPT, TV_SELF),
     ("bf16", 4, 2, 100003, W.OPT, TV_SELF), ("bf16", 4, 2, 100003, W.OPTLOG, TV_SELF)])
 def test_tv_pass_from_resident_tiles(dtype, B, gamma, V, rule, want, ticks, monkeypatch):
     if ticks is not None:
