@@ -279,7 +279,7 @@ Route choose_route(int64_t B, int64_t b_launch, int64_t R, int64_t g1, int64_t V
   const int64_t seq_most = !full ? (tv_rows || tok_rows ? 4096 : 8192)
                            : tv_rows || need_mom || !sampled ? 20480
                                                              : 40960;
-  t.seq = V <= spc::seq_row_elems(dtype) && g1 * V <= seq_most && B <= 2 * cus;
+  t.seq = V <= spc::kSeqSubs * spc::seq_sub_elems(dtype) && g1 * V <= seq_most && B <= 2 * cus;
   if (t.seq) return t;
   // Other small problems (rows that fit one workgroup's registers, at most two
   // rows per compute unit, no first moments): one launch, a workgroup per row.

@@ -153,8 +153,10 @@ hipError_t launch_draft(const Params& P, int dtype, bool argmax, bool long_tiles
                         hipStream_t stream);
 
 // The short-sequence path (k_seq): a workgroup per sequence, rows of at most
-// seq_row_elems entries.  It uses no workspace but 16 readable bytes (hdr).
-int seq_row_elems(int dtype);
+// kSeqSubs sub-chunks of seq_sub_elems entries (a wavefront's lane load).  It
+// uses no workspace but 16 readable bytes (hdr).
+constexpr int kSeqSubs = 256;
+int seq_sub_elems(int dtype);
 hipError_t launch_seq(const Params& P, int dtype, hipEvent_t ev_begin, hipEvent_t ev_end,
                       hipStream_t stream);
 

@@ -203,6 +203,34 @@ __device__ __forceinline__ void mask_tile(const char* row, int64_t t0, int64_t e
   }
 }
 
+// Lane loads at any 2-byte address.  A row of an odd bfloat16 vocabulary may
+// start 2 bytes past a multiple of 4, and 16-byte loads there are slow; its
+// lane loads are made 2 bytes earlier (inside the tensor, whose first row is
+// aligned), with the 2 bytes that then lie past them, and shifted.
+struct HalfLoad {
+  u32x4 v;
+  uint32_t h, m;  // the last two bytes, and the shift (0 or 2 bytes)
+};
+template <bool NT>
+__device__ __forceinline__ HalfLoad half_load(const char* a) {
+  HalfLoad x;
+  x.m = (uint32_t)reinterpret_cast<uintptr_t>(a) & 2u;
+  const auto* src = reinterpret_cast<const typename LaneVec<0>::type*>(a - x.m);
+  x.v = NT ? __builtin_nontemporal_load(src) : *src;
+  x.h = *reinterpret_cast<const uint16_t*>(a + 14);
+  return x;
+}
+__device__ __forceinline__ void half_shift(const HalfLoad& x, uint32_t (&w)[4]) {
+  w[0] = __builtin_amdgcn_alignbyte(x.v.y, x.v.x, x.m);
+  w[1] = __builtin_amdgcn_alignbyte(x.v.z, x.v.y, x.m);
+  w[2] = __builtin_amdgcn_alignbyte(x.v.w, x.v.z, x.m);
+  w[3] = __builtin_amdgcn_alignbyte(x.h, x.v.w, x.m);
+}
+template <int DT>
+__device__ __forceinline__ bool half_row(const char* row) {  // uniform
+  return DT == 1 && (reinterpret_cast<uintptr_t>(row) & 2u);
+}
+
 // Both tensors' lane loads of the tile at entry t0 of a row, masked.  TQ /
 // TP: which of them to read (the other's words are left alone).
 template <int DT, int U, bool NT, int GT = kThreads, bool TQ = true, bool TP = true>
@@ -212,6 +240,64 @@ __device__ __forceinline__ void load_tiles(const char* qrow, const char* prow, i
                                            const void* safe) {
   if (TQ) load_tile<DT, U, NT, GT>(qrow, t0, end, wq, tid, safe);
   if (TP) load_tile<DT, U, NT, GT>(prow, t0, end, wp, tid, safe);
+  if (TQ) mask_tile<DT, U, GT>(qrow, t0, end, wq, tid);
+  if (TP) mask_tile<DT, U, GT>(prow, t0, end, wp, tid);
+}
+
+// The same for short calls, which are bound by the latency of these loads:
+// lane loads that a wavefront holds nothing of are not made, lanes past the row
+// read the tile's first lane load, whose address is as the row's, and rows at
+// odd 2-byte addresses are read by half_load.
+template <int DT, int U, bool NT, int GT = kThreads, bool TQ = true, bool TP = true>
+__device__ __forceinline__ void load_short(const char* qrow, const char* prow, int64_t t0,
+                                           int64_t end, uint32_t (&wq)[U][Tile<DT, U>::NW],
+                                           uint32_t (&wp)[U][Tile<DT, U>::NW], int tid,
+                                           const void* safe) {
+  using T = Tile<DT, U>;
+  using LV = typename LaneVec<DT>::type;
+  constexpr int kSpan = GT * U * T::VW;
+  const int left = (int)(end - t0 < (int64_t)kSpan ? end - t0 : (int64_t)kSpan);
+  const bool some = t0 + left >= T::VW;
+  const char* qb = some ? qrow + t0 * T::EB : static_cast<const char*>(safe);
+  const char* pb = some ? prow + t0 * T::EB : static_cast<const char*>(safe);
+  const int last = some ? left - T::VW : 0;
+  const auto live = [&](int i) { return (i * GT + (tid & ~63)) * T::VW < left; };
+  const auto off = [&](int i) {
+    const int e = (i * GT + tid) * T::VW;
+    return (e <= last ? e : e < left ? last : min(last, 0)) * T::EB;
+  };
+  const auto put = [&](uint32_t (&w)[T::NW], const u32x4& v) {
+    w[0] = v.x;
+    w[1] = v.y;
+    w[2] = v.z;
+    w[3] = v.w;
+  };
+  const auto plain = [&](const char* a) {
+    const LV* src = reinterpret_cast<const LV*>(a);
+    return (u32x4)(NT ? __builtin_nontemporal_load(src) : *src);
+  };
+  if (half_row<DT>(qb)) {  // (q and p rows have the same alignment)
+    HalfLoad hq[U], hp[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      if (!live(i)) continue;  // wavefront-uniform
+      if (TQ) hq[i] = half_load<NT>(qb + off(i));
+      if (TP) hp[i] = half_load<NT>(pb + off(i));
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      if (!live(i)) continue;
+      if (TQ) half_shift(hq[i], wq[i]);
+      if (TP) half_shift(hp[i], wp[i]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      if (!live(i)) continue;
+      if (TQ) put(wq[i], plain(qb + off(i)));
+      if (TP) put(wp[i], plain(pb + off(i)));
+    }
+  }
   if (TQ) mask_tile<DT, U, GT>(qrow, t0, end, wq, tid);
   if (TP) mask_tile<DT, U, GT>(prow, t0, end, wp, tid);
 }
@@ -1005,13 +1091,14 @@ using ChunkRegs = uint32_t[C::U][C::NW];
 // Both tensors' lane loads of the chunk starting at entry c0 of a row (V
 // entries), as the distribution KIND needs them; a chunk past the row is all
 // -inf.
-template <int DT, class C, int KIND>
+template <int DT, class C, int KIND, bool SHORT = false>
 __device__ __forceinline__ void load_chunks(const char* qrow, const char* prow, int64_t c0, int V,
                                             ChunkRegs<C>& wq, ChunkRegs<C>& wp,
                                             const void* safe) {
   const bool live = c0 < V;  // wave-uniform
-  load_tiles<DT, C::U, false, 64, KIND != kP, KIND != kQ>(qrow, prow, live ? c0 : 0, live ? V : 0,
-                                                          wq, wp, threadIdx.x & 63, safe);
+  const auto load = SHORT ? load_short<DT, C::U, false, 64, KIND != kP, KIND != kQ>
+                          : load_tiles<DT, C::U, false, 64, KIND != kP, KIND != kQ>;
+  load(qrow, prow, live ? c0 : 0, live ? V : 0, wq, wp, threadIdx.x & 63, safe);
 }
 
 // Sources of the part masses of the sampled distribution: the statistics
@@ -2466,7 +2553,6 @@ hipError_t launch_step_t(const Params& P, hipStream_t st, bool draw_pass, bool t
 // many of them as it has chunks.
 constexpr int kSeqThreads = 1024;
 constexpr int kSeqWaves = kSeqThreads / 64;
-constexpr int kSeqSubs = 256;  // sub-chunks (64 lane loads) a row may have
 
 struct SeqPart {  // one wavefront's share of a row
   double sq, sp, hq, hp, x;
@@ -2584,7 +2670,7 @@ __device__ __forceinline__ void seq_chunks(const char* qrow, const char* prow, i
 #pragma unroll 1
   for (int c0 = wi * C::N; c0 < V; c0 += wpr * C::N) {  // wave-uniform
     ChunkRegs<C> q, p;
-    load_tiles<DT, C::U, false, 64>(qrow, prow, c0, V, q, p, threadIdx.x & 63, safe);
+    load_short<DT, C::U, false, 64>(qrow, prow, c0, V, q, p, threadIdx.x & 63, safe);
     fn(q, p, c0);
   }
 }
@@ -2635,7 +2721,7 @@ __device__ __forceinline__ bool seq_draw(const Params& P, int b, int f, const Se
   const int ns = (V + C::N - 1) / C::N;
   ChunkRegs<C> cq = {}, cp = {};
   for (int sc = wv; sc < ns; sc += kSeqWaves) {
-    load_chunks<DT, C, KIND>(qrow, prow, (int64_t)sc * C::N, V, cq, cp, P.hdr);
+    load_chunks<DT, C, KIND, true>(qrow, prow, (int64_t)sc * C::N, V, cq, cp, P.hdr);
     const float t = pair_sum<C::VW>([&](int e) {
       return weight_of<DT, KIND>(elem<DT>(cq[0], e), elem<DT>(cp[0], e), ps);
     });
@@ -2655,23 +2741,23 @@ __device__ __forceinline__ bool seq_draw(const Params& P, int b, int f, const Se
   // loaded when it was its last one
   if (ks >= 0 && wv == ks % kSeqWaves) {
     if (ks + kSeqWaves < ns)
-      load_chunks<DT, C, KIND>(qrow, prow, (int64_t)ks * C::N, V, cq, cp, P.hdr);
+      load_chunks<DT, C, KIND, true>(qrow, prow, (int64_t)ks * C::N, V, cq, cp, P.hdr);
     pick_from<DT, C, KIND>(P, b, (int64_t)ks * C::N, rem, ps, cq, cp);
   }
   return true;
 }
 
-// Sub-chunks of a row, the most of them a wavefront takes at a time, and the wavefronts that read a row: one per
-// that many, at most 16 / (gamma + 1).
-__host__ __device__ constexpr int seq_subs(int V, int sub) { return (V + sub - 1) / sub; }
-template <int DT>
-constexpr int kSeqU = 4;
-template <int DT>
+// The wavefronts that read a row of ns sub-chunks: one per four, at most
+// 16 / (gamma + 1) (with one per two, float32 steps take 4% longer).
 __host__ __device__ constexpr int seq_wpr(int g1, int ns) {
   const int most = g1 >= kSeqWaves ? 1 : kSeqWaves / g1;
-  const int want = (ns + kSeqU<DT> - 1) / kSeqU<DT>;
+  const int want = (ns + 3) / 4;
   return want < most ? want : most;
 }
+// Lane loads a wavefront takes at a time, at most.  bfloat16: with four, a
+// workgroup's 128 VGPRs spill 30 and Diff steps take 5 to 12% longer.
+template <int DT>
+constexpr int kSeqU = DT == SPC_BF16 ? 2 : 4;
 
 template <int DT, int MS, int U>
 __global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
@@ -2680,7 +2766,7 @@ __global__ __launch_bounds__(kSeqThreads) void k_seq(Params P) {
   constexpr int EB = StatTile<DT>::EB;
   const int b = blockIdx.x, gamma = P.gamma, g1 = gamma + 1, V = P.V;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wpr = seq_wpr<DT>(g1, seq_subs(V, SubC<DT>::N));  // wavefronts per row
+  const int wpr = seq_wpr(g1, (V + SubC<DT>::N - 1) / SubC<DT>::N);  // wavefronts per row
   const int rpp = kSeqWaves / wpr;                            // rows at a time
   const int slot = wv / wpr, wi = wv % wpr;
   const int jend = slot < rpp ? g1 : 0;
@@ -2889,13 +2975,13 @@ hipError_t launch_seq_t(const Params& P, hipStream_t st, hipEvent_t ev_begin, hi
   const dim3 grid((unsigned)P.B), block(kSeqThreads);
   // lane loads a wavefront takes at a time: those of its share of a row, up
   // to kSeqU (one with first moments, whose sums take the registers)
-  const int ns = seq_subs(P.V, SubC<DT>::N), wpr = seq_wpr<DT>(P.gamma + 1, ns);
+  const int ns = (P.V + SubC<DT>::N - 1) / SubC<DT>::N, wpr = seq_wpr(P.gamma + 1, ns);
   const int own = (ns + wpr - 1) / wpr;
   if (P.mom_set)
     hipLaunchKernelGGL((k_seq<DT, 7, 1>), grid, block, 0, st, P);
   else if (own == 1)
     hipLaunchKernelGGL((k_seq<DT, 0, 1>), grid, block, 0, st, P);
-  else if (own == 2)
+  else if (own == 2 || kSeqU<DT> == 2)
     hipLaunchKernelGGL((k_seq<DT, 0, 2>), grid, block, 0, st, P);
   else
     hipLaunchKernelGGL((k_seq<DT, 0, kSeqU<DT>>), grid, block, 0, st, P);
@@ -2966,28 +3052,58 @@ __device__ __forceinline__ double small_sum(double v, SmallShared& sh) {
 template <int DT>
 using SmallRegs = uint32_t[kSmallU][Tile<DT, kSmallU>::NW];
 
-// Thread t's lane load i of a row (entries (i * 1024 + t) * VW ..), raw: a
-// lane load not wholly inside the row reads the row's last VW entries instead
-// (`safe`, 16 readable bytes, where the row has fewer).  The passes read a
-// lane load wholly past the row as -inf through small_elem; small_tail puts
-// the one the row ends in right.  Keeping the raw words, rather than
-// selecting the padding once, spares the registers of a second copy.
+// Whether any lane of this wavefront holds entries of lane load i
+// (wavefront-uniform): lane loads wholly past the row are skipped.
 template <int DT>
-__device__ __forceinline__ void small_load(const char* row, int V, SmallRegs<DT>& w,
+__device__ __forceinline__ bool small_live(int i, int V) {
+  return (i * kSmallThreads + (int)(threadIdx.x & ~63)) * Tile<DT, kSmallU>::VW < V;
+}
+
+// Thread t's lane load i of a row of both tensors (entries (i * 1024 + t) * VW
+// ..), raw, as load_short makes them.  The passes read a lane load wholly past
+// the row as -inf through small_elem; small_tail puts the one the row ends in
+// right.  Keeping the raw words, rather than selecting the padding once, spares
+// the registers of a second copy.
+template <int DT>
+__device__ __forceinline__ void small_load(const char* qrow, const char* prow, int V,
+                                           SmallRegs<DT>& wq, SmallRegs<DT>& wp,
                                            const void* safe) {
   using T = Tile<DT, kSmallU>;
   using LV = typename LaneVec<DT>::type;
-  const char* base = V >= T::VW ? row : static_cast<const char*>(safe);
-  const int last = V >= T::VW ? V - T::VW : 0;
-#pragma unroll
-  for (int i = 0; i < kSmallU; ++i) {
+  const bool some = V >= T::VW;
+  const char* qb = some ? qrow : static_cast<const char*>(safe);
+  const char* pb = some ? prow : static_cast<const char*>(safe);
+  const int last = some ? V - T::VW : 0;
+  const auto off = [&](int i) {
     const int e = (i * kSmallThreads + (int)threadIdx.x) * T::VW;
-    const u32x4 v = __builtin_nontemporal_load(
-        reinterpret_cast<const LV*>(base + (uint32_t)(min(e, last) * T::EB)));
-    w[i][0] = v.x;
-    w[i][1] = v.y;
-    w[i][2] = v.z;
-    w[i][3] = v.w;
+    return (uint32_t)((e <= last ? e : e < V ? last : 0) * T::EB);
+  };
+  if (half_row<DT>(qb)) {
+    HalfLoad hq[kSmallU], hp[kSmallU];
+#pragma unroll
+    for (int i = 0; i < kSmallU; ++i) {
+      if (!small_live<DT>(i, V)) continue;  // wavefront-uniform
+      hq[i] = half_load<true>(qb + off(i));
+      hp[i] = half_load<true>(pb + off(i));
+    }
+#pragma unroll
+    for (int i = 0; i < kSmallU; ++i) {
+      if (!small_live<DT>(i, V)) continue;
+      half_shift(hq[i], wq[i]);
+      half_shift(hp[i], wp[i]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kSmallU; ++i) {
+      if (!small_live<DT>(i, V)) continue;
+      const u32x4 q = __builtin_nontemporal_load(reinterpret_cast<const LV*>(qb + off(i)));
+      const u32x4 p = __builtin_nontemporal_load(reinterpret_cast<const LV*>(pb + off(i)));
+#pragma unroll
+      for (int j = 0; j < T::NW; ++j) {
+        wq[i][j] = q[j];
+        wp[i][j] = p[j];
+      }
+    }
   }
 }
 template <int DT>
@@ -3012,13 +3128,6 @@ __device__ __forceinline__ void small_tail(const char* row, int V, SmallRegs<DT>
 template <int DT>
 __device__ __forceinline__ bool small_ok(int i, int V) {
   return (i * kSmallThreads + (int)threadIdx.x) * Tile<DT, kSmallU>::VW < V;
-}
-
-// Whether any lane of this wavefront holds entries of lane load i
-// (wavefront-uniform): lane loads wholly past the row are skipped.
-template <int DT>
-__device__ __forceinline__ bool small_live(int i, int V) {
-  return (i * kSmallThreads + (int)(threadIdx.x & ~63)) * Tile<DT, kSmallU>::VW < V;
 }
 
 template <int DT>
@@ -3245,8 +3354,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
   uint32_t wq[kSmallU][T::NW], wp[kSmallU][T::NW];
   const char* qrow = (const char*)P.q + (int64_t)r * V * T::EB;
   const char* prow = (const char*)P.p + (int64_t)r * V * T::EB;
-  small_load<DT>(qrow, V, wq, P.hdr);
-  small_load<DT>(prow, V, wp, P.hdr);
+  small_load<DT>(qrow, prow, V, wq, wp, P.hdr);
   small_tail<DT>(qrow, V, wq);
   small_tail<DT>(prow, V, wp);
   const int mrule = (MS != 0 && needs_mom(sp)) ? sp.rule : 0;
@@ -3607,9 +3715,7 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-int seq_row_elems(int dtype) {
-  return kSeqSubs * (dtype == 1 ? SubC<1>::N : SubC<0>::N);
-}
+int seq_sub_elems(int dtype) { return dtype == 1 ? SubC<1>::N : SubC<0>::N; }
 hipError_t launch_seq(const Params& P, int dtype, hipEvent_t ev_begin, hipEvent_t ev_end,
                       hipStream_t st) {
   return dtype == 1 ? launch_seq_t<1>(P, st, ev_begin, ev_end)
