@@ -142,6 +142,16 @@ __device__ __forceinline__ void lane_tail(const char* row, int V, int n, uint32_
   }
 }
 
+template <int DT, bool NT>
+__device__ __forceinline__ void lane_load(const char* a, uint32_t (&w)[4]) {
+  const auto* src = reinterpret_cast<const typename LaneVec<DT>::type*>(a);
+  const u32x4 v = NT ? __builtin_nontemporal_load(src) : *src;
+  w[0] = v.x;
+  w[1] = v.y;
+  w[2] = v.z;
+  w[3] = v.w;
+}
+
 // Lane loads of one tile of one row into w[U][NW] by the GT threads of a
 // group, tid the thread's index in it.  Thread t's lane load i covers entries
 // e = t0 + (i*GT + t) * VW .. + VW - 1 (interleaved, so each load
@@ -156,7 +166,6 @@ __device__ __forceinline__ void load_tile(const char* row, int64_t t0, int64_t e
                                           uint32_t (&w)[U][Tile<DT, U>::NW], int tid,
                                           const void* safe) {
   using T = Tile<DT, U>;
-  using LV = typename LaneVec<DT>::type;
   constexpr int kSpan = GT * U * T::VW;  // entries of a whole tile
   const int left = (int)(end - t0 < (int64_t)kSpan ? end - t0 : (int64_t)kSpan);
   const bool some = t0 + left >= T::VW;
@@ -165,12 +174,7 @@ __device__ __forceinline__ void load_tile(const char* row, int64_t t0, int64_t e
 #pragma unroll
   for (int i = 0; i < U; ++i) {
     const int e = (i * GT + tid) * T::VW;
-    const LV* src = reinterpret_cast<const LV*>(base + min(e, last) * T::EB);
-    const u32x4 v = NT ? __builtin_nontemporal_load(src) : *src;
-    w[i][0] = v.x;
-    w[i][1] = v.y;
-    w[i][2] = v.z;
-    w[i][3] = v.w;
+    lane_load<DT, NT>(base + min(e, last) * T::EB, w[i]);
   }
 }
 
@@ -244,17 +248,17 @@ __device__ __forceinline__ void load_tiles(const char* qrow, const char* prow, i
   if (TP) mask_tile<DT, U, GT>(prow, t0, end, wp, tid);
 }
 
-// The same for short calls, which are bound by the latency of these loads:
-// lane loads that a wavefront holds nothing of are not made, lanes past the row
-// read the tile's first lane load, whose address is as the row's, and rows at
-// odd 2-byte addresses are read by half_load.
-template <int DT, int U, bool NT, int GT = kThreads, bool TQ = true, bool TP = true>
+// The same for a short sequence's rows of an odd bfloat16 vocabulary, whose
+// time is the latency of these loads: lanes past the row read the tile's first
+// lane load, whose address is as the row's, and rows at odd 2-byte addresses
+// are read by half_load, without the lane loads that a wavefront holds nothing
+// of.
+template <int DT, int U, bool NT, int GT>
 __device__ __forceinline__ void load_short(const char* qrow, const char* prow, int64_t t0,
                                            int64_t end, uint32_t (&wq)[U][Tile<DT, U>::NW],
                                            uint32_t (&wp)[U][Tile<DT, U>::NW], int tid,
                                            const void* safe) {
   using T = Tile<DT, U>;
-  using LV = typename LaneVec<DT>::type;
   constexpr int kSpan = GT * U * T::VW;
   const int left = (int)(end - t0 < (int64_t)kSpan ? end - t0 : (int64_t)kSpan);
   const bool some = t0 + left >= T::VW;
@@ -266,40 +270,29 @@ __device__ __forceinline__ void load_short(const char* qrow, const char* prow, i
     const int e = (i * GT + tid) * T::VW;
     return (e <= last ? e : e < left ? last : min(last, 0)) * T::EB;
   };
-  const auto put = [&](uint32_t (&w)[T::NW], const u32x4& v) {
-    w[0] = v.x;
-    w[1] = v.y;
-    w[2] = v.z;
-    w[3] = v.w;
-  };
-  const auto plain = [&](const char* a) {
-    const LV* src = reinterpret_cast<const LV*>(a);
-    return (u32x4)(NT ? __builtin_nontemporal_load(src) : *src);
-  };
   if (half_row<DT>(qb)) {  // (q and p rows have the same alignment)
     HalfLoad hq[U], hp[U];
 #pragma unroll
     for (int i = 0; i < U; ++i) {
       if (!live(i)) continue;  // wavefront-uniform
-      if (TQ) hq[i] = half_load<NT>(qb + off(i));
-      if (TP) hp[i] = half_load<NT>(pb + off(i));
+      hq[i] = half_load<NT>(qb + off(i));
+      hp[i] = half_load<NT>(pb + off(i));
     }
 #pragma unroll
     for (int i = 0; i < U; ++i) {
       if (!live(i)) continue;
-      if (TQ) half_shift(hq[i], wq[i]);
-      if (TP) half_shift(hp[i], wp[i]);
+      half_shift(hq[i], wq[i]);
+      half_shift(hp[i], wp[i]);
     }
   } else {
 #pragma unroll
     for (int i = 0; i < U; ++i) {
-      if (!live(i)) continue;
-      if (TQ) put(wq[i], plain(qb + off(i)));
-      if (TP) put(wp[i], plain(pb + off(i)));
+      lane_load<DT, NT>(qb + off(i), wq[i]);
+      lane_load<DT, NT>(pb + off(i), wp[i]);
     }
   }
-  if (TQ) mask_tile<DT, U, GT>(qrow, t0, end, wq, tid);
-  if (TP) mask_tile<DT, U, GT>(prow, t0, end, wp, tid);
+  mask_tile<DT, U, GT>(qrow, t0, end, wq, tid);
+  mask_tile<DT, U, GT>(prow, t0, end, wp, tid);
 }
 
 // The lowest entry attaining m among a thread's U lane loads w (lane load i
@@ -366,14 +359,14 @@ __device__ __forceinline__ double exp2_fac(double d) {
   return fma(e * kLn2, d - (double)h, e);
 }
 
-// The factor and the type of a thread's sum in the kernels that stream tiles.
-// EX: exp2_fac, and float64 across a thread's lane loads; else the hardware's
-// 2^x and float32.  Rows at any alignment take EX.  Mean errors of a row's
-// largest probability, before / after: bfloat16 3.2e-8 / 2.0e-8, float32
-// 2.4e-8 / 1.6e-8 (entry-by-entry loads into tiles of 2048 entries, which
-// these rows once had, 2.2e-8); of H(q) - H(p) 1.5e-7 / 7.3e-8.  Aligned rows
-// keep the cheaper form: EX costs them 1% (640 greedy rows of V = 256 000
-// bfloat16, 121.3 and 122.6 us) and 10% with first moments.
+// The factor and the type of a thread's sum, in the kernels that stream tiles
+// or hold rows.  EX: exp2_fac, and float64 across a thread's lane loads; else
+// the hardware's 2^x and float32.  Rows at any alignment take EX.  Mean errors
+// of a row's largest probability, before / after: bfloat16 3.2e-8 / 1.7e-8,
+// float32 2.4e-8 / 1.4e-8 (entry-by-entry loads, which these rows once had,
+// 2.2e-8); of H(q) - H(p) 1.5e-7 / 7.3e-8.  Aligned rows keep the cheaper form:
+// EX costs them 1% (640 greedy rows of V = 256 000 bfloat16, 121.3 and 122.6
+// us; 40 held rows of V = 16 000, 15.3 and 15.6) and 10% with first moments.
 template <bool EX>
 __device__ __forceinline__ double ref_fac(double d) {
   if constexpr (EX) return exp2_fac(d);
@@ -1091,14 +1084,13 @@ using ChunkRegs = uint32_t[C::U][C::NW];
 // Both tensors' lane loads of the chunk starting at entry c0 of a row (V
 // entries), as the distribution KIND needs them; a chunk past the row is all
 // -inf.
-template <int DT, class C, int KIND, bool SHORT = false>
+template <int DT, class C, int KIND>
 __device__ __forceinline__ void load_chunks(const char* qrow, const char* prow, int64_t c0, int V,
                                             ChunkRegs<C>& wq, ChunkRegs<C>& wp,
                                             const void* safe) {
   const bool live = c0 < V;  // wave-uniform
-  const auto load = SHORT ? load_short<DT, C::U, false, 64, KIND != kP, KIND != kQ>
-                          : load_tiles<DT, C::U, false, 64, KIND != kP, KIND != kQ>;
-  load(qrow, prow, live ? c0 : 0, live ? V : 0, wq, wp, threadIdx.x & 63, safe);
+  load_tiles<DT, C::U, false, 64, KIND != kP, KIND != kQ>(qrow, prow, live ? c0 : 0, live ? V : 0,
+                                                          wq, wp, threadIdx.x & 63, safe);
 }
 
 // Sources of the part masses of the sampled distribution: the statistics
@@ -2670,7 +2662,10 @@ __device__ __forceinline__ void seq_chunks(const char* qrow, const char* prow, i
 #pragma unroll 1
   for (int c0 = wi * C::N; c0 < V; c0 += wpr * C::N) {  // wave-uniform
     ChunkRegs<C> q, p;
-    load_short<DT, C::U, false, 64>(qrow, prow, c0, V, q, p, threadIdx.x & 63, safe);
+    if (DT == SPC_BF16 && (V & 1))
+      load_short<DT, C::U, false, 64>(qrow, prow, c0, V, q, p, threadIdx.x & 63, safe);
+    else
+      load_tiles<DT, C::U, false, 64>(qrow, prow, c0, V, q, p, threadIdx.x & 63, safe);
     fn(q, p, c0);
   }
 }
@@ -2721,7 +2716,7 @@ __device__ __forceinline__ bool seq_draw(const Params& P, int b, int f, const Se
   const int ns = (V + C::N - 1) / C::N;
   ChunkRegs<C> cq = {}, cp = {};
   for (int sc = wv; sc < ns; sc += kSeqWaves) {
-    load_chunks<DT, C, KIND, true>(qrow, prow, (int64_t)sc * C::N, V, cq, cp, P.hdr);
+    load_chunks<DT, C, KIND>(qrow, prow, (int64_t)sc * C::N, V, cq, cp, P.hdr);
     const float t = pair_sum<C::VW>([&](int e) {
       return weight_of<DT, KIND>(elem<DT>(cq[0], e), elem<DT>(cp[0], e), ps);
     });
@@ -2741,7 +2736,7 @@ __device__ __forceinline__ bool seq_draw(const Params& P, int b, int f, const Se
   // loaded when it was its last one
   if (ks >= 0 && wv == ks % kSeqWaves) {
     if (ks + kSeqWaves < ns)
-      load_chunks<DT, C, KIND, true>(qrow, prow, (int64_t)ks * C::N, V, cq, cp, P.hdr);
+      load_chunks<DT, C, KIND>(qrow, prow, (int64_t)ks * C::N, V, cq, cp, P.hdr);
     pick_from<DT, C, KIND>(P, b, (int64_t)ks * C::N, rem, ps, cq, cp);
   }
   return true;
@@ -3060,16 +3055,15 @@ __device__ __forceinline__ bool small_live(int i, int V) {
 }
 
 // Thread t's lane load i of a row of both tensors (entries (i * 1024 + t) * VW
-// ..), raw, as load_short makes them.  The passes read a lane load wholly past
-// the row as -inf through small_elem; small_tail puts the one the row ends in
-// right.  Keeping the raw words, rather than selecting the padding once, spares
-// the registers of a second copy.
-template <int DT>
+// ..), raw, loaded as load_short does.  The passes read a lane load wholly past
+// the row as -inf through small_elem; small_tail puts the one that an EX row
+// ends in right.  Keeping the raw words, rather than selecting the padding
+// once, spares the registers of a second copy.
+template <int DT, bool EX>
 __device__ __forceinline__ void small_load(const char* qrow, const char* prow, int V,
                                            SmallRegs<DT>& wq, SmallRegs<DT>& wp,
                                            const void* safe) {
   using T = Tile<DT, kSmallU>;
-  using LV = typename LaneVec<DT>::type;
   const bool some = V >= T::VW;
   const char* qb = some ? qrow : static_cast<const char*>(safe);
   const char* pb = some ? prow : static_cast<const char*>(safe);
@@ -3078,7 +3072,7 @@ __device__ __forceinline__ void small_load(const char* qrow, const char* prow, i
     const int e = (i * kSmallThreads + (int)threadIdx.x) * T::VW;
     return (uint32_t)((e <= last ? e : e < V ? last : 0) * T::EB);
   };
-  if (half_row<DT>(qb)) {
+  if (EX && half_row<DT>(qb)) {
     HalfLoad hq[kSmallU], hp[kSmallU];
 #pragma unroll
     for (int i = 0; i < kSmallU; ++i) {
@@ -3094,22 +3088,14 @@ __device__ __forceinline__ void small_load(const char* qrow, const char* prow, i
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < kSmallU; ++i) {
-      if (!small_live<DT>(i, V)) continue;
-      const u32x4 q = __builtin_nontemporal_load(reinterpret_cast<const LV*>(qb + off(i)));
-      const u32x4 p = __builtin_nontemporal_load(reinterpret_cast<const LV*>(pb + off(i)));
+    for (int i = 0; i < kSmallU; ++i) lane_load<DT, true>(qb + off(i), wq[i]);
 #pragma unroll
-      for (int j = 0; j < T::NW; ++j) {
-        wq[i][j] = q[j];
-        wp[i][j] = p[j];
-      }
-    }
+    for (int i = 0; i < kSmallU; ++i) lane_load<DT, true>(pb + off(i), wp[i]);
   }
 }
 template <int DT>
 __device__ __forceinline__ void small_tail(const char* row, int V, SmallRegs<DT>& w) {
   using T = Tile<DT, kSmallU>;
-  if (V % T::VW == 0) return;  // uniform
   const int slot = V / T::VW;
   if ((int)threadIdx.x == slot % kSmallThreads) {
     uint32_t x[4] = {};
@@ -3135,7 +3121,7 @@ __device__ __forceinline__ float small_elem(const uint32_t* w, int e, bool ok) {
   return ok ? elem<DT>(w, e) : kNegInf;
 }
 
-template <int DT, int MOM, bool ARG>
+template <int DT, int MOM, bool ARG, bool EX>
 __device__ __forceinline__ RowStat small_stats(SmallRegs<DT>& wq, SmallRegs<DT>& wp,
                                                int V, const SeqParam& sp, int mrule,
                                                SmallShared& sh) {
@@ -3173,7 +3159,8 @@ __device__ __forceinline__ RowStat small_stats(SmallRegs<DT>& wq, SmallRegs<DT>&
   }
   const float rq = (mq == kNegInf) ? 0.0f : mq * sp.c_hi;
   const float rp = (mp == kNegInf) ? 0.0f : mp * sp.c_hi;
-  double sq = 0.0, spp = 0.0;
+  typedef ThreadSum<EX> S;
+  S sq = 0, spp = 0;
   float hq = 0.0f, hp = 0.0f, xq = 0.0f;
 #pragma unroll
   for (int i = 0; i < kSmallU; ++i) {
@@ -3183,28 +3170,38 @@ __device__ __forceinline__ RowStat small_stats(SmallRegs<DT>& wq, SmallRegs<DT>&
       const float z = small_elem<DT>(w, e, ok);
       return fmaf(z, sp.c_lo, fmaf(z, sp.c_hi, -r));
     };
-    // float32 pairwise within a lane load, float64 across them
-    sq += (double)pair_sum<T::VW>([&](int e) {
+    const auto add_q = [&](int e) {
       const float aq = arg(wq[i], e, rq), tq = exp2_hw(aq);
       if constexpr (MOM) {
         hq = fmaf(tq, tq > 0.0f ? aq : 0.0f, hq);
         xq = fmaf(tq, tq > 0.0f ? arg(wp[i], e, rp) : 0.0f, xq);
       }
       return tq;
-    });
-    spp += (double)pair_sum<T::VW>([&](int e) {
+    };
+    const auto add_p = [&](int e) {
       const float ap = arg(wp[i], e, rp), tp = exp2_hw(ap);
       if constexpr (MOM) hp = fmaf(tp, tp > 0.0f ? ap : 0.0f, hp);
       return tp;
-    });
+    };
+    if constexpr (EX) {
+      sq += (S)pair_sum<T::VW>(add_q);
+      spp += (S)pair_sum<T::VW>(add_p);
+    } else {
+#pragma unroll
+      for (int e = 0; e < T::VW; ++e) {
+        sq += add_q(e);
+        spp += add_p(e);
+        if (e & 1) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   }
   small_fence(wq, wp);
   // waves against the wave max, then the block against the row max (fp64)
   const float Wq = wave_max(mq), Wp = wave_max(mp);
   const double eq = (double)rq - (double)(Wq * sp.c_hi), ep = (double)rp - (double)(Wp * sp.c_hi);
   const double fq = exp2_fac(eq), fp = exp2_fac(ep);
-  const double dq = wave_sum(mq == kNegInf ? 0.0 : sq * fq);
-  const double dp = wave_sum(mp == kNegInf ? 0.0 : spp * fp);
+  const double dq = wave_sum(mq == kNegInf ? 0.0 : (double)sq * fq);
+  const double dp = wave_sum(mp == kNegInf ? 0.0 : (double)spp * fp);
   double mhq = 0.0, mhp = 0.0, mx = 0.0;
   if constexpr (MOM) {
     mhq = wave_sum(mq == kNegInf ? 0.0 : mom_move(hq, sq, fq, eq));
@@ -3341,7 +3338,7 @@ __device__ __forceinline__ void small_draw_w(const Params& P, int b, int f, int 
   else pick_wave<DT, SubC<DT>, kTokPi>(P, b, row, c0, rem, ps);
 }
 
-template <int DT, int MS>
+template <int DT, int MS, bool EX>
 __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
   using T = Tile<DT, kSmallU>;
   __shared__ SmallShared sh;
@@ -3354,17 +3351,19 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
   uint32_t wq[kSmallU][T::NW], wp[kSmallU][T::NW];
   const char* qrow = (const char*)P.q + (int64_t)r * V * T::EB;
   const char* prow = (const char*)P.p + (int64_t)r * V * T::EB;
-  small_load<DT>(qrow, prow, V, wq, wp, P.hdr);
-  small_tail<DT>(qrow, V, wq);
-  small_tail<DT>(prow, V, wp);
+  small_load<DT, EX>(qrow, prow, V, wq, wp, P.hdr);
+  if constexpr (EX) {
+    small_tail<DT>(qrow, V, wq);
+    small_tail<DT>(prow, V, wp);
+  }
   const int mrule = (MS != 0 && needs_mom(sp)) ? sp.rule : 0;
   RowStat rs;
   if (sp.greedy)  // block-uniform
-    rs = (MS != 0 && mrule) ? small_stats<DT, 1, true>(wq, wp, V, sp, mrule, sh)
-                            : small_stats<DT, 0, true>(wq, wp, V, sp, 0, sh);
+    rs = (MS != 0 && mrule) ? small_stats<DT, 1, true, EX>(wq, wp, V, sp, mrule, sh)
+                            : small_stats<DT, 0, true, EX>(wq, wp, V, sp, 0, sh);
   else
-    rs = (MS != 0 && mrule) ? small_stats<DT, 1, false>(wq, wp, V, sp, mrule, sh)
-                            : small_stats<DT, 0, false>(wq, wp, V, sp, 0, sh);
+    rs = (MS != 0 && mrule) ? small_stats<DT, 1, false, EX>(wq, wp, V, sp, mrule, sh)
+                            : small_stats<DT, 0, false, EX>(wq, wp, V, sp, 0, sh);
   // the logits the decision reads, from the thread holding them: the draft
   // token's, or (greedy TokenV2/V3, BiLD*) p's at the drafter's argmax
   int xi = x;
@@ -3486,18 +3485,18 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
   small_draw_w<DT>(P, b, f, (recf >> 4) & 0xf, (recf >> 8) & 1, sp);
 }
 
-template <int DT>
+template <int DT, bool EX>
 hipError_t launch_small_t(const Params& P, hipStream_t st, hipEvent_t ev_begin,
                           hipEvent_t ev_end) {
   if (ev_begin) {
     const hipError_t e = hipEventRecord(ev_begin, st);
     if (e != hipSuccess) return e;
   }
-  // batches with first moments take the tile path (their registers would not
-  // fit beside the row)
-  if (P.mom_set != 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(P.B * (P.gamma + 1))), block(kSmallThreads);
-  hipLaunchKernelGGL((k_small<DT, 0>), grid, block, 0, st, P);
+  if (P.mom_set)
+    hipLaunchKernelGGL((k_small<DT, 7, EX>), grid, block, 0, st, P);
+  else
+    hipLaunchKernelGGL((k_small<DT, 0, EX>), grid, block, 0, st, P);
   hipError_t err = hipGetLastError();
   if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, st);
   return err;
@@ -3688,9 +3687,16 @@ int draft_tile_elems(int dtype, bool long_tiles) {
   return dtype == 1 ? DraftTile<1, 1>::N : DraftTile<0, 1>::N;
 }
 
+namespace {
+// Rows that start inside a vector take the EX sums (ref_fac).
+bool ex_sums(const Params& P, int dtype) {
+  return P.V % (dtype == 1 ? StatTile<1>::VW : StatTile<0>::VW) != 0;
+}
+}  // namespace
+
 hipError_t launch_draft(const Params& P, int dtype, bool argmax, bool long_tiles,
                         hipStream_t st) {
-  const bool ex = P.V % (dtype == 1 ? StatTile<1>::VW : StatTile<0>::VW) != 0;  // as launch_step
+  const bool ex = ex_sums(P, dtype);
   const auto launch =
       dtype == 1 ? (long_tiles ? (ex ? launch_draft_t<1, 2, true> : launch_draft_t<1, 2, false>)
                                : (ex ? launch_draft_t<1, 1, true> : launch_draft_t<1, 1, false>))
@@ -3728,15 +3734,16 @@ int small_row_elems(int dtype) {
 
 hipError_t launch_small(const Params& P, int dtype, hipEvent_t ev_begin,
                         hipEvent_t ev_end, hipStream_t st) {
-  return dtype == 1 ? launch_small_t<1>(P, st, ev_begin, ev_end)
-                    : launch_small_t<0>(P, st, ev_begin, ev_end);
+  const bool ex = ex_sums(P, dtype);
+  const auto launch = dtype == 1 ? (ex ? launch_small_t<1, true> : launch_small_t<1, false>)
+                                 : (ex ? launch_small_t<0, true> : launch_small_t<0, false>);
+  return launch(P, st, ev_begin, ev_end);
 }
 
 hipError_t launch_step(const Params& P, int dtype, bool draw_pass, bool tv_pass, bool job_pass,
                        int job_groups, hipEvent_t ev_begin, hipEvent_t ev_end,
                        hipStream_t st) {
-  // rows that start inside a vector take the EX sums (ref_fac)
-  const bool ex = P.V % (dtype == 1 ? StatTile<1>::VW : StatTile<0>::VW) != 0;
+  const bool ex = ex_sums(P, dtype);
   const auto launch = dtype == 1 ? (ex ? launch_step_t<1, true> : launch_step_t<1, false>)
                                  : (ex ? launch_step_t<0, true> : launch_step_t<0, false>);
   return launch(P, st, draw_pass, tv_pass, job_pass, job_groups, ev_begin, ev_end);
