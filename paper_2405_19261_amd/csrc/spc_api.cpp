@@ -242,6 +242,93 @@ struct Route {
   int mom_set = 0;  // first moments the statistics sum (kMom* bits)
 };
 
+// What a batch may ask of its rows.
+struct Work {
+  bool tv, tok, mom;  // D_TV, eta, first moments
+  bool greedy;        // temperature 0 throughout
+  bool mixed;         // rules per sequence: only some rows ask for it
+};
+
+// Whether a launch of B sequences takes the one-launch path with a workgroup
+// per sequence (k_seq).  Its time grows with a sequence's gamma + 1 rows of ns
+// sub-chunks (one compute unit reads them) and with the rounds of workgroups;
+// the other paths' with the rows of the batch.  us per step, that path / the
+// next best one (rows held by a workgroup, or statistics tiles), on 256
+// compute units:
+//   rows within the compute units, gamma = 4:
+//     Diff bf16 V=2000 10.9 / 10.9, V=2560 12.9 / 10.8; f32 V=1000 9.6 / 10.5,
+//     V=1501 11.5 / 10.2; greedy bf16 V=1001 7.7 / 8.3, V=1501 8.8 / 8.3; OPT
+//     bf16 V=500 11.7 / 11.7, V=1501 14.9 / 11.7; TokenV2 bf16 V=1000 14.9 /
+//     15.0, V=1501 17.1 / 15.6; CHOW, Diff and OPT mixed bf16 V=813 gamma=3
+//     11.1 / 13.0; DiffLog bf16 gamma=1 V=1192 11.4 / 12.9, gamma=5 V=1800
+//     13.9 / 12.2; OPTLog bf16 gamma=1 V=1600 13.6 / 13.2
+//   one round, more rows: Diff bf16 B=256 gamma=7 V=4000 22 / 33; OPT bf16 B=40
+//     gamma=7 V=2000 14.2 / 17.3, V=2560 19.9 / 17.6; greedy f32 B=64 gamma=4
+//     V=1001 8.6 / 10.8, V=2560 10.8 / 9.9, gamma=3 V=3001 9.4 / 10.2, B=125
+//     V=4024 12.1 / 10.4 (bf16 10.1 / 10.7)
+//   two rounds (B = 400): Diff f32 gamma=4 V=2000 22.9 / 24.8, V=4000 33 / 28;
+//     DiffLog f32 gamma=1 V=2000 21.5 / 22.6, V=4000 28.5 / 23.4
+//   four (B = 1024): Diff bf16 gamma=7 V=1001 39 / 65, V=2560 66 / 65; gamma=1
+//     V=1501 29 / 27; TokenV2 bf16 gamma=7 V=4000 195 / 385
+bool short_sequences(int64_t B, int64_t g1, int64_t V, int dtype, const Work& w, int64_t cus) {
+  const bool bf16 = dtype == SPC_BF16;
+  const int64_t sub = spc::seq_sub_elems(dtype), ns = (V + sub - 1) / sub;
+  if (ns > spc::kSeqSubs) return false;
+  const int64_t n = g1 * V, rows = B * g1, rounds = (B + cus - 1) / cus;
+  const bool four = ns <= 4;
+  if (rows <= cus) {
+    if (w.mom) return n <= (w.tv ? 3072 : w.greedy ? 4096 : bf16 ? 6144 : 4608);
+    if (w.greedy) return n <= 4096 || (V <= 1024 && n <= 8192);
+    if (w.tok || (w.tv && w.mixed)) return n <= 4096;
+    if (w.tv) return g1 * ns <= 4;
+    return g1 * ns <= 16 || (four && g1 * ns <= 32);
+  }
+  if (rounds == 1) {
+    if (w.mom) return n <= (bf16 ? 32768 : rows > 2 * cus ? 20480 : 16384);
+    if (w.greedy)
+      return n <= 20480 && (four || g1 <= 2 || (g1 <= 4 && n <= (bf16 ? 16384 : 12288)) ||
+                            rows > 4 * cus || (rows > 2 * cus && n <= 10240));
+    if (w.tok) return n <= 40960;
+    if (w.tv) return n <= 20480 && (g1 <= 5 || rows > 2 * cus || n <= (bf16 ? 16384 : 10240));
+    return n <= 40960;
+  }
+  if (rounds == 2) {
+    if (w.mom) return ns <= 8 && n <= 32768;
+    if (w.greedy) return four && n <= 20480 && (g1 >= 4 || ns <= 2);
+    if (w.tok) return n <= 40960;
+    if (w.tv) return ns <= 12 && n <= 20480;
+    return ns <= 8 && n <= 40960;
+  }
+  if (w.mom) return n <= 32768 && four && (g1 >= 4 || (bf16 && ns <= 3));
+  if (w.greedy) return n <= 20480 && four && g1 >= 4;
+  if (w.tok) return n <= 40960 && V <= 6400;
+  return n <= 40960 && four && (g1 >= 4 || (bf16 && ns <= 2));
+}
+
+// Whether a launch of other sizes takes the one-launch path with a workgroup
+// per row (k_small), whose rows fit a workgroup's registers, rather than
+// statistics tiles and the passes after them: up to two rows per compute unit.
+// us per step, as rows / as tiles:
+//   rows within the compute units: Diff bf16 V=18565 17.6 / 18.4, V=22992 18.9 /
+//     17.3 (8 to 27 rows), V=22695 19.7 / 21.7 (234 rows); OPT bf16 V=22176
+//     21.4 / 22.9, V=28624 24.0 / 22.7, V=30824 25.7 / 31.0 (135 rows); TokenV2
+//     V=30957 29.4 / 32.2; greedy V=8472 9.4 / 9.1, V=17848 11.6 / 9.6; DiffLog
+//     bf16 V=8191 12.6 / 20.6, V=20003 19.3 / 20.7; OPTLog V=24001 22.0 / 26.5
+//   more rows: Diff bf16 V=3929 19.3 / 19.9, V=5995 21.3 / 20.0, V=21355 32.7 /
+//     23.2; f32 V=2584 17.9 / 17.0; OPT bf16 V=9721 28.0 / 35.3, V=16832 33.2 /
+//     31.3; TokenV2 V=11264 35.5 / 42.8, V=29312 50.7 / 42.1; greedy V=1479
+//     14.4 / 11.4; DiffLog V=2000 23.5 / 21.2
+bool held_rows(int64_t rows, int64_t V, int64_t nt, int dtype, const Work& w, int64_t cus) {
+  if (V > spc::small_row_elems(dtype) || rows > 2 * cus) return false;
+  if (rows > cus) {
+    if (w.greedy || w.mom) return false;
+    return V <= (w.tok ? 16384 : w.tv ? 12288 : dtype == SPC_BF16 ? 4096 : 2048);
+  }
+  if (w.greedy) return V <= 8192;
+  if (w.tok && !w.mom) return true;
+  return V <= (w.tv ? 24576 : w.mom ? 16384 : 20480) || (!w.mom && rows * nt > 2 * cus);
+}
+
 // Which kernels one launch of a verify call runs, from its sizes and from the
 // rules its sequences may hold (`rules`, a bitmask; `per_rule`: per-sequence
 // rules).  B: sequences of the call, b_launch: the most of them in a launch,
@@ -264,32 +351,11 @@ Route choose_route(int64_t B, int64_t b_launch, int64_t R, int64_t g1, int64_t V
   // statistics leave open), every other row by its last statistics tile.
   const bool tv_rows = sampled && (rules & kTvRules);
   const bool tok_rows = sampled && (rules & kTokRules);
-  // Batches of short sequences take the one-launch path with a workgroup per
-  // sequence: up to a length that depends on how the rows fill the chip
-  // otherwise.  us per step, that path / the next best, bfloat16 unless said:
-  //   rows within the compute units: Diff V=1000 gamma=4 B=1 f32 9.4 / 10.4,
-  //   V=4000 gamma=1 9.6 / 10.5, V=4000 gamma=4 13.0 / 11.1; OPT f32 V=1000
-  //   gamma=1 9.9 / 10.7, gamma=7 13.5 / 11.3, TokenV2 V=2000 gamma=7 17.5 / 16.1;
-  //   more rows: Diff B=256 gamma=7 V=4000 16.9 / 26.9, B=64 gamma=4 V=8000
-  //   f32 17.4 / 21.9, gamma=7 V=16000 29.4 / 28.1; OPT B=64 gamma=4 V=4000
-  //   f32 19.9 / 21.2, gamma=7 23.9 / 22.2; TokenV2 B=256 gamma=7 V=4000
-  //   27.0 / 68.3; DiffLog B=64 gamma=4 V=4000 f32 19.5 / 20.2; greedy B=256
-  //   gamma=4 V=8000 19.0 / 15.1.
-  const bool full = b_launch * g1 > cus;
-  const int64_t seq_most = !full ? (tv_rows || tok_rows ? 4096 : 8192)
-                           : tv_rows || need_mom || !sampled ? 20480
-                                                             : 40960;
-  t.seq = V <= spc::kSeqSubs * spc::seq_sub_elems(dtype) && g1 * V <= seq_most && B <= 2 * cus;
+  const Work work{tv_rows, tok_rows, need_mom, !sampled, per_rule};
+  t.seq = short_sequences(b_launch, g1, V, dtype, work, cus);
   if (t.seq) return t;
-  // Other small problems (rows that fit one workgroup's registers, at most two
-  // rows per compute unit, no first moments): one launch, a workgroup per row.
-  // Without a second pass, rows of more than 24576 entries are faster as
-  // statistics tiles and a draw pass when their tiles fit the chip at once
-  // (bfloat16 B=8 gamma=4: V=32128 20.7 as rows, 17.5 as tiles, V=24001 17.5
-  // and 18.4, V=20000 17.0 and 17.8).
   const int64_t nt = stat_tiles(dtype, V);
-  t.small = !need_mom && V <= spc::small_row_elems(dtype) && b_launch * g1 <= 2 * cus &&
-            (V <= 24576 || tv_rows || tok_rows || !sampled || b_launch * g1 * nt > 4 * cus);
+  t.small = held_rows(b_launch * g1, V, nt, dtype, work, cus);
   if (t.small) return t;
   // Where TV rows get their TV pass.  In a grid that is resident at once
   // (at most two workgroups per compute unit) each TV row takes it from

@@ -25,7 +25,21 @@ def route(B, gamma, V, dtype, rules, per_seq=False, greedy=False):
     ((16, 7, 256000, "bf16", [W.OPT]), TILES | TV_PASS),
     ((32, 7, 256000, "bf16", [W.TOKEN_V2]), TILES | JOBS),
     ((8, 4, 20000, "bf16", [W.TOKEN_V2]), SMALL),
-    ((8, 4, 20000, "bf16", [W.DIFFLOG]), TILES),  # no first moments in rows held by a workgroup
+    # short sequences: one round of workgroups, and more
+    ((8, 4, 2000, "bf16", [W.DIFF]), SEQ), ((8, 4, 2000, "bf16", [W.OPT]), SMALL),
+    ((64, 7, 2000, "bf16", [W.OPT]), SEQ), ((64, 7, 3000, "bf16", [W.OPT]), SMALL),
+    ((1024, 7, 1001, "bf16", [W.DIFF]), SEQ), ((1024, 7, 4097, "bf16", [W.DIFF]), TILES),
+    ((600, 1, 2001, "f32", [W.TOKEN_V1]), SEQ), ((600, 1, 6401, "f32", [W.TOKEN_V1]), TILES | JOBS),
+    ((8, 4, 1025, "bf16", [W.DIFF], False, True), SMALL),
+    ((8, 4, 1024, "bf16", [W.DIFF], False, True), SEQ),
+    # rows held by a workgroup: with first moments, and up to two rows a compute unit
+    ((8, 4, 16384, "bf16", [W.DIFFLOG]), SMALL), ((8, 4, 16385, "bf16", [W.DIFFLOG]), TILES),
+    ((8, 4, 24000, "bf16", [W.OPTLOG]), SMALL), ((8, 4, 24584, "bf16", [W.OPTLOG]), TILES | TV_SELF),
+    ((8, 4, 8192, "bf16", [W.DIFF], False, True), SMALL),
+    ((8, 4, 8193, "bf16", [W.DIFF], False, True), TILES),
+    ((8, 4, 20480, "bf16", [W.DIFF]), SMALL), ((8, 4, 20481, "bf16", [W.DIFF]), TILES),
+    ((50, 4, 20481, "bf16", [W.DIFF]), SMALL),
+    ((100, 4, 12288, "bf16", [W.OPT]), SMALL), ((100, 4, 12289, "bf16", [W.OPT]), TILES | TV_PASS),
     # a resident grid with per-sequence rules takes its TV passes itself
     ((4, 4, 100000, "bf16", [W.DIFF, W.OPT], True), TILES | TV_SELF),
     # more tiles a row than its gate holds
@@ -56,3 +70,5 @@ def test_every_size_has_one_route(dtype, rule, greedy):
                 if not r & TILES:
                     assert r in (SEQ, SMALL)
                     assert V <= (32768 if r == SEQ or dtype == "bf16" else 16384)
+                    # (and no more rows than a launch's two a compute unit)
+                    assert r == SEQ or B * (gamma + 1) <= 2 * CUS

@@ -44,20 +44,25 @@ def check(inp, dtype, greedy=False, stats=True, per_seq=False):
 # entries than one vector, one entry either side of a vector, of a
 # wavefront's lane load and of a tile (8192 bfloat16 / 4096 float32), on the
 # statistics-tile path (more sequences than the one-launch paths take, or
-# rows longer than theirs) with each of its second passes.
+# rows longer than theirs) with each of its second passes; sampled rows that
+# another path takes are greedy here.
 @pytest.mark.parametrize("dtype,V,B,rule,want", [
-    ("bf16", 2, 600, W.DIFF, 0), ("bf16", 7, 600, W.OPT, TV_PASS),
-    ("bf16", 9, 600, W.TOKEN_V2, JOBS), ("bf16", 511, 600, W.LOSSY, 0),
-    ("bf16", 513, 600, W.OPT, TV_PASS), ("bf16", 513, 600, W.DIFFLOG, 0),
+    ("bf16", 2, 600, W.DIFF, None), ("bf16", 7, 600, W.OPT, None),
+    ("bf16", 9, 600, W.TOKEN_V2, None), ("bf16", 511, 600, W.LOSSY, None),
+    ("bf16", 513, 600, W.OPT, None), ("bf16", 2049, 600, W.OPT, TV_PASS),
+    ("bf16", 2049, 600, W.DIFFLOG, 0), ("bf16", 3601, 600, W.OPTLOG, TV_PASS),
     ("bf16", 8191, 560, W.DIFF, 0), ("bf16", 8193, 560, W.TOKEN_V1, JOBS),
     ("bf16", 40001, 5, W.OPT, TV_SELF), ("bf16", 40001, 5, W.TOKEN_V2, JOBS),
     ("bf16", 65543, 70, W.DIFF, 0), ("bf16", 65543, 40, W.OPT, TV_PASS),
-    ("f32", 3, 600, W.DIFF, 0), ("f32", 5, 600, W.OPT, TV_PASS), ("f32", 5, 600, W.TOKEN_V3, JOBS),
+    ("f32", 3, 600, W.DIFF, 0), ("f32", 5, 600, W.OPT, TV_PASS), ("f32", 5, 600, W.OPTLOG, TV_PASS),
+    ("f32", 255, 600, W.DIFFLOG, 0), ("f32", 257, 600, W.OPT, TV_PASS),
+    ("f32", 6401, 600, W.TOKEN_V3, JOBS),
     ("f32", 4095, 560, W.BILD, 0), ("f32", 4097, 560, W.DIFFLOG, 0),
     ("f32", 33333, 6, W.OPTLOG, TV_SELF), ("f32", 33333, 40, W.OPTLOG, TV_PASS)])
 @pytest.mark.parametrize("greedy", [False, True])
 def test_rows_at_any_alignment(dtype, V, B, rule, want, greedy):
     passes = TV_SELF | TV_PASS | TV_JOBS | JOBS
+    greedy = greedy or want is None
     r = route(B, 1, V, dtype, rule, greedy)
     assert r & TILES and (greedy or r & passes == want), r
     wl = W.WORKLOADS[3].with_(B=B, gamma=1, V=V, dtype=dtype, rule=rule, alpha=0.1,
@@ -74,16 +79,21 @@ def test_tv_jobs_at_any_alignment(dtype, V, B, rule):
     check(W.generate(wl, 33, DEV), dtype, per_seq=True)
 
 
-@pytest.mark.parametrize("rule", [W.OPT, W.TOKEN_V2, W.DIFFLOG])
-@pytest.mark.parametrize("dtype,V,path", [
-    ("bf16", 1001, SEQ), ("f32", 1001, SEQ), ("bf16", 20003, SMALL), ("f32", 9999, SMALL),
-    ("bf16", 40003, TILES), ("f32", 20001, TILES)])
-def test_rows_do_not_depend_on_their_alignment(dtype, V, path, rule):
+@pytest.mark.parametrize("B,dtype,V,rule,path", [
+    (100, "bf16", 1001, W.OPT, SEQ), (16, "bf16", 1001, W.TOKEN_V2, SEQ),
+    (16, "bf16", 1001, W.DIFFLOG, SEQ), (100, "f32", 1001, W.OPT, SEQ),
+    (16, "f32", 1001, W.TOKEN_V2, SEQ), (16, "f32", 1001, W.DIFFLOG, SEQ),
+    (16, "bf16", 1001, W.OPT, SMALL), (16, "bf16", 20003, W.OPT, SMALL),
+    (16, "bf16", 20003, W.TOKEN_V2, SMALL), (16, "bf16", 9003, W.DIFFLOG, SMALL),
+    (16, "f32", 9999, W.OPT, SMALL), (16, "f32", 9999, W.TOKEN_V2, SMALL),
+    (16, "f32", 9999, W.DIFFLOG, SMALL), (16, "bf16", 40003, W.OPT, TILES),
+    (16, "bf16", 40003, W.TOKEN_V2, TILES), (16, "bf16", 20003, W.DIFFLOG, TILES),
+    (16, "bf16", 40003, W.DIFFLOG, TILES), (16, "f32", 20001, W.OPT, TILES),
+    (16, "f32", 20001, W.TOKEN_V2, TILES), (16, "f32", 20001, W.DIFFLOG, TILES)])
+def test_rows_do_not_depend_on_their_alignment(B, dtype, V, rule, path):
     """The same row at every position of the batch, so at every alignment,
     gives bitwise the same statistics and the same draw."""
-    if rule == W.DIFFLOG and path == SMALL:
-        path = TILES  # first moments
-    B, g1 = 16, 3
+    g1 = 3
     assert route(B, g1 - 1, V, dtype, rule) & path
     g = torch.Generator(device=DEV).manual_seed(3)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
@@ -124,7 +134,10 @@ def test_short_sequences(dtype, B, gamma, V, rule, greedy):
 
 # The longest sequences that path takes.
 @pytest.mark.parametrize("dtype,B,gamma,V,rule", [
-    ("bf16", 3, 1, 4095, W.DIFF), ("f32", 3, 3, 2047, W.LOSSY), ("bf16", 3, 1, 2047, W.OPT),
+    ("bf16", 3, 1, 4095, W.DIFF), ("f32", 3, 3, 1023, W.LOSSY), ("bf16", 3, 1, 1023, W.OPT),
+    ("bf16", 3, 1, 3071, W.DIFFLOG), ("f32", 3, 1, 2303, W.DIFFLOG),
+    ("f32", 129, 1, 8191, W.DIFFLOG), ("bf16", 129, 1, 16383, W.DIFFLOG),
+    ("bf16", 513, 6, 2047, W.DIFF), ("f32", 513, 6, 1023, W.OPT), ("bf16", 513, 5, 6399, W.TOKEN_V2),
     ("f32", 2, 3, 1023, W.TOKEN_V1), ("bf16", 4, 3, 1021, W.TOKEN_V3),
     ("bf16", 129, 1, 20479, W.DIFF), ("f32", 129, 1, 20479, W.LOSSY),
     ("f32", 60, 4, 8191, W.TOKEN_V2), ("bf16", 129, 1, 20477, W.TOKEN_V1),
@@ -137,13 +150,16 @@ def test_longest_short_sequences(dtype, B, gamma, V, rule):
     check(inp, dtype, stats=False)
 
 
-@pytest.mark.parametrize("dtype,gamma,V", [("bf16", 2, 1201), ("f32", 4, 810), ("bf16", 3, 1000)])
+@pytest.mark.parametrize("B,dtype,gamma,V", [
+    (8, "bf16", 2, 1201), (8, "f32", 4, 810), (8, "bf16", 3, 1000), (100, "bf16", 2, 1201),
+    (100, "f32", 4, 810), (100, "bf16", 3, 1000), (8, "bf16", 2, 9001), (8, "f32", 4, 8100)])
 @pytest.mark.parametrize("rule,alpha", [(W.OPT, 0.1), (W.TOKEN_V2, 0.05), (W.BILD, 6.0),
                                         (W.OPTLOG, 1.0), (W.LOSSY, 0.3)])
-def test_short_sequences_masked(dtype, gamma, V, rule, alpha):
-    """-inf entries in both tensors, whole lane loads and wavefronts among them."""
-    B = 8
-    assert route(B, gamma, V, dtype, rule) & SEQ
+def test_short_sequences_masked(B, dtype, gamma, V, rule, alpha):
+    """-inf entries in both tensors, whole lane loads and wavefronts among
+    them: a workgroup per sequence, or (few long rows) per row."""
+    assert route(B, gamma, V, dtype, rule) & (SEQ if B == 100 else SMALL if V > 8000 else
+                                              SEQ | SMALL)
     wl = W.WORKLOADS[3].with_(B=B, gamma=gamma, V=V, dtype=dtype, rule=rule, alpha=alpha)
     inp = W.generate(wl, 2, DEV)
     g0 = torch.Generator(device=DEV).manual_seed(99)
@@ -158,12 +174,14 @@ def test_short_sequences_masked(dtype, gamma, V, rule, alpha):
     check(inp, dtype)
 
 
-@pytest.mark.parametrize("dtype,gamma,V", [("bf16", 2, 1201), ("f32", 4, 1203), ("bf16", 1, 3000)])
-def test_short_sequences_argmax_ties(dtype, gamma, V):
+@pytest.mark.parametrize("B,dtype,gamma,V,path", [
+    (8, "bf16", 2, 1201, SEQ), (8, "f32", 3, 1021, SEQ), (150, "bf16", 1, 3000, SEQ),
+    (70, "f32", 4, 1023, SEQ), (70, "f32", 4, 1203, TILES), (8, "f32", 4, 1203, SMALL), (8, "bf16", 1, 3000, SMALL),
+    (8, "bf16", 4, 8191, SMALL)])
+def test_short_sequences_argmax_ties(B, dtype, gamma, V, path):
     """Ties within a lane load, across lanes, lane loads and wavefronts: the
     lowest index, batch-wide and per sequence."""
-    B = 8
-    assert route(B, gamma, V, dtype, W.OPT, greedy=True) & SEQ
+    assert route(B, gamma, V, dtype, W.OPT, greedy=True) & path
     wl = W.WORKLOADS[4].with_(B=B, gamma=gamma, V=V, dtype=dtype)
     inp = W.generate(wl, 9, DEV)
     rng = np.random.default_rng(4)
@@ -184,7 +202,29 @@ def test_short_sequences_argmax_ties(dtype, gamma, V):
     check(inp, dtype, greedy=True, per_seq=True)
 
 
-@pytest.mark.parametrize("dtype,gamma,V", [("bf16", 3, 1001), ("f32", 4, 800), ("bf16", 6, 1170)])
+# Rows held by a workgroup, with and without first moments: the shortest and
+# longest of their range, a whole number of lane loads and an entry either side.
+@pytest.mark.parametrize("dtype,B,gamma,V", [
+    ("bf16", 6, 7, 1999), ("bf16", 6, 7, 2048), ("bf16", 6, 7, 8191), ("bf16", 6, 7, 8193),
+    ("bf16", 5, 3, 16383), ("bf16", 5, 3, 16384), ("f32", 6, 7, 1021), ("f32", 6, 7, 4095),
+    ("f32", 6, 7, 4096), ("f32", 6, 7, 4097), ("f32", 5, 3, 16383), ("f32", 5, 3, 16384)])
+@pytest.mark.parametrize("rule,alpha,greedy", [
+    (W.OPT, 0.1, False), (W.DIFFLOG, 0.5, False), (W.OPTLOG, 0.5, False), (W.BILD, 1.0, False),
+    (W.TOKEN_V1, 0.1, False), (W.DIFFLOG, 0.5, True), (W.OPT, 0.1, True)])
+def test_rows_held_by_a_workgroup(dtype, B, gamma, V, rule, alpha, greedy):
+    assert route(B, gamma, V, dtype, rule, greedy) & SMALL or (
+        greedy and (V > 8192 or rule == W.OPT))
+    wl = W.WORKLOADS[3].with_(B=B, gamma=gamma, V=V, dtype=dtype, rule=rule, alpha=alpha,
+                              temperature=0.0 if greedy else 0.8)
+    inp = W.generate(wl, 59, DEV)
+    with_stats = check(inp, dtype, greedy)
+    plain = check(inp, dtype, greedy, stats=False)
+    for k in ("accept_len", "next_token", "defer"):
+        np.testing.assert_array_equal(plain[k], with_stats[k])
+
+
+@pytest.mark.parametrize("dtype,gamma,V", [("bf16", 3, 1001), ("f32", 4, 800), ("bf16", 6, 1170),
+                                           ("bf16", 1, 16001), ("f32", 2, 12000)])
 def test_short_sequences_identical_models(dtype, gamma, V):
     """p = q: every draft is kept, D_TV and H(q) - H(p) are exactly 0."""
     wl = W.WORKLOADS[3].with_(B=9, gamma=gamma, V=V, dtype=dtype)
@@ -224,7 +264,8 @@ def test_tv_pass_from_resident_tiles(dtype, B, gamma, V, rule, want, ticks, monk
         check(inp, dtype, stats=False)
 
 
-@pytest.mark.parametrize("dtype,B,gamma,V", [("bf16", 12, 4, 800), ("f32", 90, 3, 5000)])
+@pytest.mark.parametrize("dtype,B,gamma,V", [("bf16", 12, 4, 800), ("f32", 90, 3, 4000), ("f32", 12, 3, 5001),
+                                             ("bf16", 12, 3, 12000), ("f32", 90, 3, 5000)])
 def test_short_sequences_mixed(dtype, B, gamma, V):
     """Per-sequence rules and temperatures, and an out-of-range draft."""
     wl = W.WORKLOADS[5].with_(B=B, gamma=gamma, V=V, dtype=dtype)
@@ -261,9 +302,15 @@ def test_drafter_rows_of_one_tile_and_of_many(dtype, V, T):
     ("bf16", 1001, SEQ), ("f32", 1001, SEQ), ("f32", 2001, SMALL), ("bf16", 2083, SMALL),
     ("bf16", 20003, SMALL), ("bf16", 60003, TILES), ("bf16", 100003, TILES),
     ("f32", 60003, TILES)])
-def test_rounding_of_the_largest_probability(dtype, V, path):
+@pytest.mark.parametrize("moments", [False, True])
+def test_rounding_of_the_largest_probability(dtype, V, path, moments):
     B, gamma, T = 24, 7, 0.7
-    rule = W.OPT if path & TILES else W.CHOW
+    if moments:
+        if path == SMALL:
+            V = min(V, 16001)
+        elif path == SEQ:
+            B = 50
+    rule = (W.OPTLOG if path & TILES else W.DIFFLOG) if moments else W.OPT if path & TILES else W.CHOW
     assert route(B, gamma, V, dtype, rule) & path
     d2, n = 0.0, 0
     for step in range(4):
