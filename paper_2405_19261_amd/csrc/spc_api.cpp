@@ -83,9 +83,9 @@ WsLayout ws_layout(int64_t B, int64_t gamma, int64_t V, int dtype) {
   L.rowline = o;
   o = align_up(o + 4 * (size_t)(kMaxRows * kLineWords), 256);
   L.zero_end = o;
-  // the job pass's list: at most R nt 4 TV or eta slices (a row has one
-  // kind), and 2 R + B spare
-  L.jobs = o; o = align_up(o + 8 * (size_t)(2 * R + B + R * nt * kSlices), 256);
+  // the job pass's list: a slice of every tile for TV or eta (a row has one
+  // kind)
+  L.jobs = o; o = align_up(o + 8 * (size_t)(R * nt * kSlices), 256);
   L.tiles = o; o = align_up(o + sizeof(TilePart) * R * nt, 256);
   L.tvpart = o; o = align_up(o + sizeof(double) * R * nt * kSlices, 256);
   // residual sub-chunk masses per sequence, or (small path) two sets per row
@@ -482,8 +482,7 @@ spc_status verify_impl(const void* q, const void* p, int32_t dtype, const int32_
     P.tv_jobs = route.tv_jobs ? 1 : 0;
     P.may_greedy = (force_greedy || per_temp) ? 1 : 0;
     P.wait_ticks = tv_wait_ticks();
-    // jobs: TV slices, or the slices of the tiles a token row lists for eta (a row has one kind)
-    P.single_slots = 2 * R + bl + R * nt * spc::kSlices;
+    P.single_slots = R * nt * spc::kSlices;
     P.nsub = (int32_t)(nt * spc::tile_subchunks(dtype));
     // workgroups of the job pass: a wavefront per item of its largest
     // expected list (eta or TV slices of every tile), at most two workgroups per compute unit

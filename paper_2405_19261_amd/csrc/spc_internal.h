@@ -71,7 +71,7 @@ struct Params {
   int32_t* out_argmax;
   float* out_norm;
   // launch layout
-  int64_t single_slots;    // jobs the job pass may hold: 2 R + B + R nt kSlices
+  int64_t single_slots;    // jobs the job pass may hold: R nt kSlices (as ws_layout)
   int32_t nsub;            // sub-chunks of a row: nt * tile_subchunks
   int32_t tv_self;         // TV rows get their TV pass from their own tiles' registers
   int32_t pair;            // statistics workgroups take two tiles each (large batches)

@@ -617,10 +617,8 @@ struct RowDecision {
 
 // The part of a draw found by wave 0, for the whole workgroup.
 struct PickState {
-  int k;       // part holding the sample (-1: nothing to draw)
-  int kind;    // SampleKind actually sampled
-  int src;     // MassSrc of the part masses
-  double rem;  // target mass remaining at the start of that part
+  int k;       // tile holding the sample (-1: nothing to draw)
+  double rem;  // target mass remaining at its start
 };
 
 // "Am I the last of `n` arrivals?" for the whole block.  Thread 0 wrote the
@@ -820,11 +818,6 @@ __device__ __forceinline__ float weight_of(float zq, float zp, const ProbScale& 
     const float qe = prob(zq, s.c_hi, s.c_lo, s.q_hi, s.q_lo);
     return token_r(s.tok, zq, zp) ? pe : qe + pe;
   }
-}
-
-template <int DT, int KIND>
-__device__ __forceinline__ float weight_k(float zq, float zp, const ProbScale& s, int) {
-  return weight_of<DT, KIND>(zq, zp, s);
 }
 
 template <int DT>
@@ -1200,7 +1193,7 @@ __device__ __forceinline__ double find_part(const Params& P, int64_t row, int b,
 template <int DT, class C, int KIND>
 __device__ __forceinline__ void pick_from(const Params& P, int b, int64_t c0, double rem,
                                           const ProbScale& ps, const ChunkRegs<C>& cq,
-                                          const ChunkRegs<C>& cp, int kind = -1) {
+                                          const ChunkRegs<C>& cp) {
   const int lane = threadIdx.x & 63;
   double carry = 0.0, before = 0.0;
   int hlane = -1, last_pos = -1;
@@ -1212,7 +1205,7 @@ __device__ __forceinline__ void pick_from(const Params& P, int b, int64_t c0, do
     double m = 0.0;
 #pragma unroll
     for (int e = 0; e < C::VW; ++e) {
-      const float w = weight_k<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps, kind);
+      const float w = weight_of<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps);
       m += (double)w;
       if (w > 0.0f) last_pos = max(last_pos, (int)(base + e));
       if (e & 1) __builtin_amdgcn_sched_barrier(0);
@@ -1243,7 +1236,7 @@ __device__ __forceinline__ void pick_from(const Params& P, int b, int64_t c0, do
   int hit = -1, lastw = -1;
 #pragma unroll
   for (int e = 0; e < C::VW; ++e) {
-    const float w = weight_k<DT, KIND>(elem<DT>(sq, e), elem<DT>(sp_, e), ps, kind);
+    const float w = weight_of<DT, KIND>(elem<DT>(sq, e), elem<DT>(sp_, e), ps);
     run += (double)w;
     if (w > 0.0f) lastw = (int)(hbase + e);
     if (hit < 0 && run > rem && w > 0.0f) hit = (int)(hbase + e);
@@ -1255,14 +1248,14 @@ __device__ __forceinline__ void pick_from(const Params& P, int b, int64_t c0, do
 // The same from memory.
 template <int DT, class C, int KIND>
 __device__ __forceinline__ void pick_wave(const Params& P, int b, int64_t row, int64_t c0,
-                                          double rem, const ProbScale& ps, int kind = -1) {
+                                          double rem, const ProbScale& ps) {
   constexpr int EB = StatTile<DT>::EB;
   const int V = P.V;
   const char* qrow = (const char*)P.q + row * V * EB;
   const char* prow = (const char*)P.p + row * V * EB;
   ChunkRegs<C> cq = {}, cp = {};
   load_chunks<DT, C, KIND>(qrow, prow, c0, V, cq, cp, P.hdr);
-  pick_from<DT, C, KIND>(P, b, c0, rem, ps, cq, cp, kind);
+  pick_from<DT, C, KIND>(P, b, c0, rem, ps, cq, cp);
 }
 
 // Whole block: the masses of the sub-chunks of the TN-entry tile at entry t0
@@ -1610,14 +1603,14 @@ __device__ __forceinline__ bool arrive_last_w(uint32_t* cnt, uint32_t n, uint32_
 template <int DT, int KIND>
 __device__ __forceinline__ double slice_masses_of(const uint32_t (&cq)[StatTile<DT>::U][StatTile<DT>::NW],
                                                   const uint32_t (&cp)[StatTile<DT>::U][StatTile<DT>::NW],
-                                                  const ProbScale& ps, int kind) {
+                                                  const ProbScale& ps) {
   using T = StatTile<DT>;
   const int lane = threadIdx.x & 63;
   double mine = 0.0;
 #pragma unroll
   for (int i = 0; i < T::U; ++i) {
     const float t = pair_sum<T::VW>([&](int e) {
-      return weight_k<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps, kind);
+      return weight_of<DT, KIND>(elem<DT>(cq[i], e), elem<DT>(cp[i], e), ps);
     });
     const double s = wave_sum((double)t);
     if (lane == i) mine = s;
@@ -1631,16 +1624,15 @@ __device__ __forceinline__ double slice_masses_of(const uint32_t (&cq)[StatTile<
 // (float sums per lane load, fp64 across lanes), other lanes 0.
 template <int DT, int KIND>
 __device__ __forceinline__ double slice_masses_w(const Params& P, int64_t row, int64_t t0, int w,
-                                                 const ProbScale& ps, int kind = -1) {
+                                                 const ProbScale& ps) {
   using T = StatTile<DT>;
   const int lane = threadIdx.x & 63, V = P.V;
   uint32_t cq[T::U][T::NW] = {}, cp[T::U][T::NW] = {};
   load_tiles<DT, T::U, false, kThreads, KIND != kP, KIND != kQ>(
       (const char*)P.q + row * V * T::EB, (const char*)P.p + row * V * T::EB, t0, V, cq, cp,
       w * 64 + lane, P.hdr);
-  return slice_masses_of<DT, KIND>(cq, cp, ps, kind);
+  return slice_masses_of<DT, KIND>(cq, cp, ps);
 }
-
 
 // Wave: the second-pass partial of slice w of tile k of row r -- the TV
 // weight max(0, p - q), or eta's share (the q mass of the entries the rule
@@ -2161,22 +2153,19 @@ __device__ __forceinline__ void res_slice_w(const Params& P, int b, int k, int w
   if constexpr (KIND != kTokRes) ps = prob_scale(sp, rs);
   mask_tile<DT, T::U>(qrow, t0, V, cq, w * 64 + lane);
   mask_tile<DT, T::U>(prow, t0, V, cp, w * 64 + lane);
-  const double ml = slice_masses_of<DT, KIND>(cq, cp, ps, -1);
+  const double ml = slice_masses_of<DT, KIND>(cq, cp, ps);
   if (lane < T::U)
     st_dev_f64(P.submass + (int64_t)b * P.nsub + (int64_t)k * (T::U * kSlices) +
                    lane * kSlices + w, ml);
 }
 
-// Wave: the draw inside the NSUB sub-chunks starting at entry e0 whose
-// masses lane i < NSUB holds: the first sub-chunk where the running mass
+// Wave: the draw inside the sub-chunks starting at entry e0 whose masses the
+// lanes hold (0 past the last): the first sub-chunk where the running mass
 // exceeds rem (rounding that leaves rem unreached takes the last sub-chunk
 // with mass), then the entry inside it.
 template <int DT, int KIND>
 __device__ __forceinline__ void draw_in_subs_w(const Params& P, int b, int64_t row, int64_t e0,
-                                               double ml, int nsub, double rem,
-                                               const ProbScale& ps, int kind = -1) {
-  const int lane = threadIdx.x & 63;
-  ml = lane < nsub ? ml : 0.0;
+                                               double ml, double rem, const ProbScale& ps) {
   const double incl = wave_incl_scan(ml);
   const unsigned long long hit = __ballot(ml > 0.0 && incl > rem);
   const unsigned long long pos = __ballot(ml > 0.0);
@@ -2189,8 +2178,7 @@ __device__ __forceinline__ void draw_in_subs_w(const Params& P, int b, int64_t r
     c = pos ? 63 - __clzll(pos) : 0;
     r = __builtin_huge_val();
   }
-  pick_wave<DT, SubC<DT>, KIND>(P, b, row, e0 + (int64_t)c * SubC<DT>::N, r, ps,
-                                          kind);
+  pick_wave<DT, SubC<DT>, KIND>(P, b, row, e0 + (int64_t)c * SubC<DT>::N, r, ps);
 }
 
 // Sub-chunks of a statistics tile.
@@ -2211,7 +2199,7 @@ __device__ __forceinline__ void draw_tile(const Params& P, int b, int64_t row, i
   if (lane < T::U) dv[lane * kSlices + w] = ml;
   __syncthreads();
   if (w != 0) return;
-  draw_in_subs_w<DT, KIND>(P, b, row, t0, lane < kDrawSubs ? dv[lane] : 0.0, kDrawSubs, rem, ps);
+  draw_in_subs_w<DT, KIND>(P, b, row, t0, lane < kDrawSubs ? dv[lane] : 0.0, rem, ps);
 }
 
 // Whole block: the draw of sequence b at row `row` from q, p or a token
@@ -2358,12 +2346,8 @@ __device__ __forceinline__ void pass2_item_w(const Params& P, int r, int c) {
 // partials is made by workgroup (0, b).  The last arrival clears the
 // sequence's outcome word for the next call.  Sequences without a draw
 // (greedy or invalid) have no outcome word and are skipped.
-// bfloat16: held to 80 VGPRs, six resident workgroups per SIMD, so that in
-// large batches (256 sequences: 8192 workgroups) one workgroup's loads
-// overlap another's residual weights.
 template <int DT>
-__global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(DT == SPC_BF16 ? 6 : 1))) void k_res(Params P) {
+__global__ __launch_bounds__(kThreads) void k_res(Params P) {
   __shared__ double dv[kDrawSubs];
   __shared__ int empty;
   const int k = blockIdx.x, b = blockIdx.y;
@@ -3267,9 +3251,9 @@ __device__ __forceinline__ RowStat small_stats(SmallRegs<DT>& wq, SmallRegs<DT>&
 template <int DT, int KIND>
 __device__ __forceinline__ float small_weight_row(const uint32_t (&wq)[Tile<DT, kSmallU>::NW],
                                                   const uint32_t (&wp)[Tile<DT, kSmallU>::NW],
-                                                  bool ok, const ProbScale& ps, int kind) {
+                                                  bool ok, const ProbScale& ps) {
   return pair_sum<Tile<DT, kSmallU>::VW>([&](int e) {
-    return weight_k<DT, KIND>(small_elem<DT>(wq, e, ok), small_elem<DT>(wp, e, ok), ps, kind);
+    return weight_of<DT, KIND>(small_elem<DT>(wq, e, ok), small_elem<DT>(wp, e, ok), ps);
   });
 }
 
@@ -3277,7 +3261,7 @@ __device__ __forceinline__ float small_weight_row(const uint32_t (&wq)[Tile<DT, 
 // i * 16 + w is wave w's lane load i), stored as set `set` of the row for
 // the sequence's draw; returns their total.
 template <int DT, int KIND>
-__device__ __forceinline__ double small_masses(const Params& P, int r, int set, int kind,
+__device__ __forceinline__ double small_masses(const Params& P, int r, int set,
                                                const uint32_t (&wq)[kSmallU][Tile<DT, kSmallU>::NW],
                                                const uint32_t (&wp)[kSmallU][Tile<DT, kSmallU>::NW],
                                                const ProbScale& ps, SmallShared& sh) {
@@ -3287,8 +3271,7 @@ __device__ __forceinline__ double small_masses(const Params& P, int r, int set, 
   for (int i = 0; i < kSmallU; ++i) {
     double m = 0.0;
     if (small_live<DT>(i, P.V))  // wavefront-uniform
-      m = wave_sum((double)small_weight_row<DT, KIND>(wq[i], wp[i], small_ok<DT>(i, P.V),
-                                                           ps, kind));
+      m = wave_sum((double)small_weight_row<DT, KIND>(wq[i], wp[i], small_ok<DT>(i, P.V), ps));
     if (lane == 0)
       st_dev_f64(P.submass + ((int64_t)r * 2 + set) * kSmallSub + i * kSmallWaves + wv, m);
     tot += m;
@@ -3302,11 +3285,11 @@ __device__ __forceinline__ double small_masses_kind(const Params& P, int r, int 
                                                     const uint32_t (&wq)[kSmallU][Tile<DT, kSmallU>::NW],
                                                     const uint32_t (&wp)[kSmallU][Tile<DT, kSmallU>::NW],
                                                     const ProbScale& ps, SmallShared& sh) {
-  if (kind == kResidual) return small_masses<DT, kResidual>(P, r, set, kind, wq, wp, ps, sh);
-  if (kind == kTokRes) return small_masses<DT, kTokRes>(P, r, set, kind, wq, wp, ps, sh);
-  if (kind == kQ) return small_masses<DT, kQ>(P, r, set, kind, wq, wp, ps, sh);
-  if (kind == kP) return small_masses<DT, kP>(P, r, set, kind, wq, wp, ps, sh);
-  return small_masses<DT, kTokPi>(P, r, set, kind, wq, wp, ps, sh);
+  if (kind == kResidual) return small_masses<DT, kResidual>(P, r, set, wq, wp, ps, sh);
+  if (kind == kTokRes) return small_masses<DT, kTokRes>(P, r, set, wq, wp, ps, sh);
+  if (kind == kQ) return small_masses<DT, kQ>(P, r, set, wq, wp, ps, sh);
+  if (kind == kP) return small_masses<DT, kP>(P, r, set, wq, wp, ps, sh);
+  return small_masses<DT, kTokPi>(P, r, set, wq, wp, ps, sh);
 }
 
 // Wave: the draw of sequence b at row j* = f from that row's stored
@@ -3650,7 +3633,7 @@ __global__ __launch_bounds__(kThreads) void k_draft(Params P) {
       find_part<kSrcDraft>(P, b, b, nt, rs, u, &ks, &rem);
     }
     if (threadIdx.x == 0) {
-      pks = PickState{ks, kQ, kSrcDraft, rem};
+      pks = PickState{ks, rem};
       if (ks < 0) P.out_token[b] = -1;
     }
   }
@@ -3670,7 +3653,6 @@ hipError_t launch_draft_t(const Params& P, bool argmax, hipStream_t st) {
     hipLaunchKernelGGL((k_draft<DT, false, TM, EX>), grid, dim3(kThreads), 0, st, P);
   return hipGetLastError();
 }
-
 
 }  // namespace
 
