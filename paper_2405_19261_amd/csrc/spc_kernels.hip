@@ -1743,6 +1743,15 @@ __device__ __forceinline__ void publish_singles_w(const Params& P, int kind, uin
   }
 }
 
+// The mass reported for a draw whose summed mass is W.  q, p and a token
+// rule's target sum to 1 by the row's normalisers, which is what the
+// statistics tiles' partials give (within 1e-8); the float32 weights that the
+// one-launch paths sum to find the entry carry the rounding of their
+// exponentials (6e-8).
+__device__ __forceinline__ float draw_norm(int kind, double W) {
+  return kind != kResidual && kind != kTokRes && W > 0.0 ? 1.0f : (float)W;
+}
+
 // What a sampled sequence with first rejection f (delta there) draws from.
 __device__ __forceinline__ int sample_kind(const SeqParam& sp, int f, int gamma, int delta) {
   if (is_token(sp.rule)) return f < gamma ? kTokRes : kTokPi;
@@ -2713,7 +2722,7 @@ __device__ __forceinline__ bool seq_draw(const Params& P, int b, int f, const Se
   const double W = seq_find(sh.mass, ns, u, &ks, &rem);  // every wavefront alike
   if ((KIND == kResidual || KIND == kTokRes) && !(W > 0.0)) return false;
   if (threadIdx.x == 0) {
-    if (P.out_norm) P.out_norm[b] = (float)W;
+    if (P.out_norm) P.out_norm[b] = draw_norm(KIND, W);
     if (ks < 0) P.out_token[b] = -1;
   }
   // the wavefront that summed the sub-chunk draws in it, its entries still
@@ -3309,7 +3318,7 @@ __device__ __forceinline__ void small_draw_w(const Params& P, int b, int f, int 
   const double W = find_part<kSrcPass, kSmallSub / 64>(P, row, (int)(row * 2 + set), kSmallSub,
                                                        rs, u, &ks, &rem);
   if ((threadIdx.x & 63) == 0) {
-    if (P.out_norm) P.out_norm[b] = (float)W;
+    if (P.out_norm) P.out_norm[b] = draw_norm(kind, W);
     if (ks < 0) P.out_token[b] = -1;
   }
   if (ks < 0) return;  // wave-uniform

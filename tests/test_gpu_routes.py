@@ -324,3 +324,31 @@ def test_rounding_of_the_largest_probability(dtype, V, path, moments):
             d = st[..., c].double() - (z.max(-1).values - z.logsumexp(-1)).exp()
             d2, n = d2 + float(d.pow(2).sum()), n + d.numel()
     assert (d2 / n) ** 0.5 < 2.6e-8
+
+
+# The mass reported for a draw from q, p or a token rule's target: these sum to
+# 1 by the row's normalisers, which the value reported must show to a unit in
+# the last place below 1 (summing the float32 weights that the search uses
+# leaves errors of 1.2e-7 to 7e-7).
+@pytest.mark.parametrize("dtype,B,V,path", [
+    ("bf16", 100, 1001, SEQ), ("f32", 100, 1000, SEQ), ("bf16", 40, 3001, SMALL),
+    ("f32", 40, 4096, SMALL), ("bf16", 24, 16001, SMALL), ("bf16", 24, 60003, TILES)])
+@pytest.mark.parametrize("rule", [W.OPT, W.TOKEN_V2, W.DIFFLOG])
+def test_mass_of_an_extra_token_draw(dtype, B, V, path, rule):
+    gamma = 2
+    assert route(B, gamma, V, dtype, rule) & path
+    seen = 0
+    for step in range(4):
+        wl = W.WORKLOADS[3].with_(B=B, gamma=gamma, V=V, dtype=dtype, rule=rule, alpha=0.1)
+        inp = W.generate(wl, 700 + step, DEV)
+        if rule != W.TOKEN_V2:
+            inp["p"] = inp["q"].clone()  # every draft is kept
+        norm = torch.empty(B, device=DEV)
+        acc, _, _ = spc.spc_verify_ex(inp["q"], inp["p"], inp["draft"], inp["uniforms"], rule, 0.1,
+                                      1.0, out_sample_norm=norm)
+        w = norm[acc == gamma]
+        seen += w.numel()
+        # (a token rule's target as tiles: eta's own rounding)
+        bound = 2.5e-7 if path == TILES and rule == W.TOKEN_V2 else 6e-8
+        assert ((w - 1).abs() <= bound).all(), (w - 1).abs().max()
+    assert seen
