@@ -3256,6 +3256,34 @@ __device__ __forceinline__ RowStat small_stats(SmallRegs<DT>& wq, SmallRegs<DT>&
   return sh.rs;
 }
 
+// The q mass of the entries a token rule marks (in) and of the others (out),
+// of VW entries z(e) -> {zq, zp}.
+template <int VW, class Z>
+__device__ __forceinline__ void eta_add(Z&& z, const ProbScale& ps, double& in, double& out) {
+  float w[VW];
+  bool r[VW];
+#pragma unroll
+  for (int e = 0; e < VW; ++e) {
+    const float2 t = z(e);
+    r[e] = token_r(ps.tok, t.x, t.y);
+    w[e] = prob(t.x, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo);
+    if (e & 1) __builtin_amdgcn_sched_barrier(0);
+  }
+  in += (double)pair_sum<VW>([&](int e) { return r[e] ? w[e] : 0.0f; });
+  out += (double)pair_sum<VW>([&](int e) { return r[e] ? 0.0f : w[e]; });
+}
+// eta from the two masses of a whole row, whose sum is 1: from the smaller,
+// whose rounding (of the weights' exponentials, in proportion) is the smaller.
+// Taken by unaligned rows of more than kEtaBoth entries, which were statistics
+// tiles once (there eta comes from the statistics): mean errors of eta for
+// V = 10 007 and 20 003 bfloat16 2.9e-8 as tiles, 5.0e-8 from the marked mass,
+// 2.8e-8 so, for 0.5 us of 19.5 (28.4 as tiles).
+constexpr int kEtaBoth = 4096;
+__device__ __forceinline__ double eta_of(double in, double out) {
+  return in > 0.5 ? 1.0 - out : in;
+}
+
+
 // Thread: sum over its entries of the sampled distribution KIND's weights
 // for lane load i (float, entry order).
 template <int DT, int KIND>
@@ -3393,19 +3421,27 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(Params P) {
   const bool eta = sp.valid && !sp.greedy && is_token(sp.rule);
   if (tv || eta) {  // block-uniform
     const ProbScale ps = prob_scale(sp, rs, eta);
-    double acc = 0.0;
+    const bool both = EX && eta && V > kEtaBoth;
+    double acc = 0.0, out = 0.0;
 #pragma unroll
     for (int i = 0; i < kSmallU; ++i) {
       if (!small_live<DT>(i, V)) continue;  // wavefront-uniform
       const bool ok = small_ok<DT>(i, V);
-      acc += (double)pair_sum<T::VW>([&](int e) {
-        const float zq = small_elem<DT>(wq[i], e, ok), zp = small_elem<DT>(wp[i], e, ok);
-        if (eta)
-          return token_r(ps.tok, zq, zp) ? prob(zq, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo) : 0.0f;
-        return residual_weight<DT>(zq, zp, ps);
-      });
+      const auto z = [&](int e) {
+        return make_float2(small_elem<DT>(wq[i], e, ok), small_elem<DT>(wp[i], e, ok));
+      };
+      if (both)
+        eta_add<T::VW>(z, ps, acc, out);
+      else
+        acc += (double)pair_sum<T::VW>([&](int e) {
+          const float2 t = z(e);
+          if (eta)
+            return token_r(ps.tok, t.x, t.y) ? prob(t.x, ps.c_hi, ps.c_lo, ps.q_hi, ps.q_lo) : 0.0f;
+          return residual_weight<DT>(t.x, t.y, ps);
+        });
     }
     rs.tv = small_sum(acc, sh);
+    if (both) rs.tv = eta_of(rs.tv, small_sum(out, sh));  // block-uniform
     small_fence(wq, wp);
   }
   // The distributions this row may be drawn from if it is the sequence's
